@@ -377,10 +377,20 @@ template <typename T>
 int launch_linear(int B, int D, RowBlocks rb, const T* A, const T* Wt, const T* bias, T* Y, hipStream_t st,
                   const T* rowadd = nullptr);
 
+// The products of host_train.h (matrix instructions for any shape, fp32 and bf16).
+int launch_gemm_f32(const GemmDesc& d, const float* A, const float* Bm, const float* bias, float* C, hipStream_t st,
+                    int split = 1, long split_stride = 0);
+int linear_as_gemm(int B, int D, RowBlocks rb, const float* X, const float* W, const float* bias, float* Y, hipStream_t st,
+                   const float* rowadd);
+int linear_as_gemm(int B, int D, RowBlocks rb, const bf16* X, const bf16* W, const bf16* bias, bf16* Y, hipStream_t st,
+                   const bf16* rowadd);
+int token_scores(int B, int Cin, int N, int D, int heads, int g, const float* z, const float* Mf, float* S, hipStream_t st);
+int token_scores(int B, int Cin, int N, int D, int heads, int g, const bf16* z, const float* Mf, float* S, hipStream_t st);
+
 template <>
 int launch_linear<float>(int B, int D, RowBlocks rb, const float* A, const float* Wt, const float* bias,
                          float* Y, hipStream_t st, const float* rowadd) {
-  return launch_linear_generic<float>(B, D, rb, A, Wt, bias, Y, st, rowadd);
+  return linear_as_gemm(B, D, rb, A, Wt, bias, Y, st, rowadd);
 }
 
 template <>
@@ -395,6 +405,7 @@ int launch_linear<bf16>(int B, int D, RowBlocks rb, const bf16* A, const bf16* W
       default: return launch_linear_mfma_cfg<256, 256, 2, 2, 0>(B, D, rb, A, Wt, bias, Y, st, rowadd);
     }
   }
+  if (!force_generic()) return linear_as_gemm(B, D, rb, A, Wt, bias, Y, st, rowadd);
   return launch_linear_generic<bf16>(B, D, rb, A, Wt, bias, Y, st, rowadd);
 }
 
@@ -427,10 +438,7 @@ int run_level(dchag_dtype dt, int B, int Cin, int N, int D, int heads, const dch
   }
   {
     StageTimer tm(DCHAG_STAGE_SCORES, st);
-    const long T_total = (long)B * Cin * N;
-    k_scores_generic<T, 8><<<dim3((unsigned)((T_total + 3) / 4)), 256, 0, st>>>(T_total, Cin, N, D, heads, g, zin,
-                                                                               Mf, S);
-    if ((rc = launch_status())) return rc;
+    if ((rc = token_scores(B, Cin, N, D, heads, g, zin, Mf, S, st))) return rc;
   }
   {
     StageTimer tm(DCHAG_STAGE_VPROJ, st);
@@ -562,8 +570,8 @@ int fast_scores(int B, int Cin, int N, int D, int heads, const dchag_level* lv, 
     while (D % DQ) DQ >>= 1;
     const size_t clds = (size_t)DQ * (pp * 2 + heads * 4 + 4) + (size_t)3 * TPL * 64 * 20 * 4;
     auto compose = TPL == 1 ? k_compose_score_weights<1> : (TPL == 2 ? k_compose_score_weights<2> : k_compose_score_weights<4>);
-    if (ensure_dynamic_lds(reinterpret_cast<const void*>(compose), (int)clds)) return DCHAG_ERR_LAUNCH;
     if (!compose_mfma && phase != 2) {
+      if (ensure_dynamic_lds(reinterpret_cast<const void*>(compose), (int)clds)) return DCHAG_ERR_LAUNCH;
       compose<<<dim3(Cin), 256, clds, st>>>(D, heads, pp, g, DQ, px->MfT, px->We, px->be, px->ce, px->Ms, px->Msb, px->cs);
       if ((rc = launch_status())) return rc;
     }

@@ -163,31 +163,58 @@ int launch_gemm(const GemmDesc& d, const TA* A, const TB* Bm, const TB* bias, TC
   return launch_status();
 }
 
-// bf16 products go to the MFMA kernel when it tiles them: K a multiple of 64 and not ragged, each operand with
-// one unit stride, every other stride and offset a multiple of 8 elements (16-byte rows).
+// Single-precision products.  split > 1: see k_gemm_f32 (the caller adds the partial results up).
+inline int launch_gemm_f32(const GemmDesc& d, const float* A, const float* Bm, const float* bias, float* C, hipStream_t st,
+                           int split, long split_stride) {
+  const long batch = (long)(d.reduce_b ? 1 : d.nb) * d.nk * d.na;
+  const long mt = (d.M + 63) / 64;
+  if (batch * split > 65535 || mt > 65535 || d.M < 1 || d.N < 1) return DCHAG_ERR_SHAPE;
+  const bool at = d.A.s1 != 1, bt = d.Bm.s0 != 1;
+  if ((at && d.A.s0 != 1) || (bt && d.Bm.s1 != 1)) return DCHAG_ERR_SHAPE;
+  auto vec_ok = [](const GemmOperand& o, long row, const float* p) {
+    return !((o.sb | o.sk | o.sa | row) & 3) && !(reinterpret_cast<uintptr_t>(p) & 15);
+  };
+  const int va = vec_ok(d.A, at ? d.A.s1 : d.A.s0, A), vb = vec_ok(d.Bm, bt ? d.Bm.s0 : d.Bm.s1, Bm);
+  auto kern = at ? (bt ? k_gemm_f32<true, true> : k_gemm_f32<true, false>)
+                 : (bt ? k_gemm_f32<false, true> : k_gemm_f32<false, false>);
+  kern<<<dim3((d.N + 63) / 64, (unsigned)mt, (unsigned)(batch * split)), 256, 0, st>>>(d, va, vb, split, split_stride, A, Bm,
+                                                                                     bias, C);
+  return launch_status();
+}
+
+// bf16 products go to the MFMA kernel when it tiles them: K not ragged, a multiple of 8 where it is an operand's unit
+// stride; each operand with one unit stride, every other stride and offset a multiple of 8 elements (16-byte rows).
 inline bool mult8(long v) { return (v & 7) == 0; }
 inline bool gemm_mfma_ok(const GemmDesc& d) {
-  if (d.K % 64 || d.ragged == 2 || dbg(SW_GEMM_GENERIC)) return false;
+  if (d.ragged == 2 || dbg(SW_GEMM_GENERIC)) return false;
   const bool at = d.A.s1 != 1, bt = d.Bm.s0 != 1;
+  if ((!at || !bt) && d.K % 8) return false;
   if (at && (d.A.s0 != 1 || d.M % 8 || d.M < 8 || d.ragged)) return false;
   if (bt && (d.Bm.s1 != 1 || d.N % 8 || d.N < 8)) return false;
   return mult8(d.A.sb) && mult8(d.A.sk) && mult8(d.A.sa) && mult8(at ? d.A.s1 : d.A.s0) && mult8(d.Bm.sb) &&
          mult8(d.Bm.sk) && mult8(d.Bm.sa) && mult8(bt ? d.Bm.s0 : d.Bm.s1);
 }
 
-template <int BM, int BN, int WM, int WN, typename TC>
-int launch_gemm_mfma_tile(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias, TC* C, TC* rowsum,
+template <int BM, int BN, int WM, int WN, bool EXTRA, typename TC>
+int launch_gemm_mfma_form(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias, TC* C, TC* rowsum,
                           hipStream_t st) {
   const long batch = (long)(d.reduce_b ? 1 : d.nb) * d.nk * d.na;
   const long mt = (d.M + BM - 1) / BM;
   if (batch > 65535 || mt > 65535 || d.M < 1 || d.N < 1) return DCHAG_ERR_SHAPE;
   const bool at = d.A.s1 != 1, bt = d.Bm.s0 != 1;
-  auto kern = at ? (bt ? k_gemm_mfma<BM, BN, WM, WN, true, true, TC> : k_gemm_mfma<BM, BN, WM, WN, true, false, TC>)
-                 : (bt ? k_gemm_mfma<BM, BN, WM, WN, false, true, TC> : k_gemm_mfma<BM, BN, WM, WN, false, false, TC>);
+  auto kern = at ? (bt ? k_gemm_mfma<BM, BN, WM, WN, true, true, EXTRA, TC> : k_gemm_mfma<BM, BN, WM, WN, true, false, EXTRA, TC>)
+                 : (bt ? k_gemm_mfma<BM, BN, WM, WN, false, true, EXTRA, TC> : k_gemm_mfma<BM, BN, WM, WN, false, false, EXTRA, TC>);
   constexpr int lds = 2 * (BM + BN) * 128;
   if (ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds)) return DCHAG_ERR_LAUNCH;
   kern<<<dim3((d.N + BN - 1) / BN, (unsigned)mt, (unsigned)batch), 256, lds, st>>>(d, A, Bm, bias, C, rowsum);
   return launch_status();
+}
+
+template <int BM, int BN, int WM, int WN, typename TC>
+int launch_gemm_mfma_tile(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias, TC* C, TC* rowsum,
+                          hipStream_t st) {
+  return d.K % 64 || d.rowadd ? launch_gemm_mfma_form<BM, BN, WM, WN, true, TC>(d, A, Bm, bias, C, rowsum, st)
+                              : launch_gemm_mfma_form<BM, BN, WM, WN, false, TC>(d, A, Bm, bias, C, rowsum, st);
 }
 
 // Tile shape by the extent of the output: a narrow N (one head, one patch of pixels) or a short M (the rows
@@ -211,9 +238,49 @@ int launch_gemm_bf16(const GemmDesc& d0, const bf16* A, const bf16* Bm, const bf
 // True when launch_gemm_bf16 will deliver the row sums of A along with the product.
 inline bool gemm_rowsum_ok(const GemmDesc& d) { return gemm_mfma_ok(d) && d.A.s1 != 1 && !dbg(SW_COLSUM); }
 
+// Y[r][o] = sum_j X[r][j] W[k][o][j] + bias[k][o] (+ rowadd[r][o]) over row blocks, as a product of the kernels above.
+inline GemmDesc linear_desc(int B, int D, RowBlocks rb, const void* rowadd) {
+  GemmDesc d{};
+  d.M = rb.rows_per_group; d.N = D; d.K = D; d.nb = B; d.nk = rb.G; d.na = 1;
+  d.ragged = 1; d.ragged_total = rb.rows_per_b; d.ragged_nominal = rb.rows_per_group;
+  d.A = {(long)rb.rows_per_b * D, (long)rb.rows_per_group * D, 0, (long)D, 1};
+  d.Bm = {0, (long)D * D, 0, 1, (long)D};
+  d.C = d.A;
+  d.bias_sk = D;
+  d.scale = 1.f;
+  d.rowadd = rowadd;
+  return d;
+}
+inline int linear_as_gemm(int B, int D, RowBlocks rb, const float* X, const float* W, const float* bias, float* Y,
+                          hipStream_t st, const float* rowadd) {
+  return launch_gemm_f32(linear_desc(B, D, rb, rowadd), X, W, bias, Y, st);
+}
+inline int linear_as_gemm(int B, int D, RowBlocks rb, const bf16* X, const bf16* W, const bf16* bias, bf16* Y,
+                          hipStream_t st, const bf16* rowadd) {
+  return launch_gemm_bf16<bf16>(linear_desc(B, D, rb, rowadd), X, W, bias, Y, st);
+}
+// Raw scores S[b,c,n,a] = z[b,c,n,:] . M[k][a][:] of the shape-generic path.
+inline int token_scores(int B, int Cin, int N, int D, int heads, int g, const float* z, const float* Mf, float* S,
+                        hipStream_t st) {
+  GemmDesc d{};
+  d.M = g * N; d.N = heads; d.K = D; d.nb = B; d.nk = groups_of(Cin, g); d.na = 1;
+  d.ragged = 1; d.ragged_total = Cin * N; d.ragged_nominal = g * N;
+  d.A = {(long)Cin * N * D, (long)g * N * D, 0, (long)D, 1};
+  d.Bm = {0, (long)heads * D, 0, 1, (long)D};
+  d.C = {(long)Cin * N * heads, (long)g * N * heads, 0, (long)heads, 1};
+  d.scale = 1.f;
+  return launch_gemm_f32(d, z, Mf, nullptr, S, st);
+}
+inline int token_scores(int B, int Cin, int N, int D, int heads, int g, const bf16* z, const float* Mf, float* S,
+                        hipStream_t st) {
+  const long T_total = (long)B * Cin * N;
+  k_scores_generic<bf16, 8><<<dim3((unsigned)((T_total + 3) / 4)), 256, 0, st>>>(T_total, Cin, N, D, heads, g, z, Mf, S);
+  return launch_status();
+}
+
 // Same-type products of the level kernels: MFMA for bf16 where it tiles, the fp32-FMA kernel otherwise.
 inline int gemm_tt(const GemmDesc& d, const float* A, const float* Bm, const float* bias, float* C, hipStream_t st) {
-  return launch_gemm<float, float, float>(d, A, Bm, bias, C, st);
+  return launch_gemm_f32(d, A, Bm, bias, C, st);
 }
 inline int gemm_tt(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias, bf16* C, hipStream_t st) {
   return launch_gemm_bf16<bf16>(d, A, Bm, bias, C, st);
@@ -229,7 +296,7 @@ inline int gemm_with_bias_grad(GemmDesc d, int B, int D, RowBlocks rb, const flo
     k_colsum<float, float><<<dim3((D + 63) / 64, rb.G), 1024, 0, st>>>(B, D, rb, X, db);
     if ((rc = launch_status())) return rc;
   }
-  return dW ? launch_gemm<float, float, float>(d, X, Y, nullptr, dW, st) : DCHAG_OK;
+  return dW ? launch_gemm_f32(d, X, Y, nullptr, dW, st) : DCHAG_OK;
 }
 inline int gemm_with_bias_grad(GemmDesc d, int B, int D, RowBlocks rb, const bf16* X, const bf16* Y, bf16* dW, bf16* db,
                                hipStream_t st) {
@@ -279,10 +346,7 @@ int generic_alpha(int B, int Cin, int N, int D, int heads, const dchag_level* lv
     if ((rc = launch_status())) return rc;
   }
   StageTimer tm(DCHAG_STAGE_SCORES, st);
-  const long T_total = (long)B * Cin * N;
-  k_scores_generic<T, 8><<<dim3((unsigned)((T_total + 3) / 4)), 256, 0, st>>>(T_total, Cin, N, D, heads, g, zin, lb.Mf,
-                                                                             lb.alpha);
-  if ((rc = launch_status())) return rc;
+  if ((rc = token_scores(B, Cin, N, D, heads, g, zin, lb.Mf, lb.alpha, st))) return rc;
   const long total = (long)B * G * N * heads;
   k_softmax_group<<<dim3((unsigned)((total + 255) / 256)), 256, 0, st>>>(Cin, N, heads, g, G, total, lb.alpha);
   return launch_status();
@@ -748,7 +812,8 @@ inline int tokens_backward_fused(int B, int Cin, int N, int D, int heads, int g,
 // dz (value and key path) and r[k][a][:] = sum over the group's tokens of ds[., a] z[., :].
 template <typename T>
 int tokens_backward_generic(int B, int Cin, int N, int D, int heads, int g, const T* zin, const T* w, const float* alpha,
-                            const float* ds, const float* Mf, T* dz, float* r, bool want_r, hipStream_t st) {
+                            const float* ds, const float* Mf, T* dz, float* r, float* rpart, bool want_r,
+                            hipStream_t st) {
   const int G = groups_of(Cin, g);
   int rc;
   {
@@ -765,13 +830,27 @@ int tokens_backward_generic(int B, int Cin, int N, int D, int heads, int g, cons
   d.Bm = {(long)Cin * N * D, (long)g * N * D, 0, (long)D, 1};
   d.C = {0, (long)heads * D, 0, (long)D, 1};
   d.scale = 1.f;
-  return launch_gemm<float, T, float>(d, ds, zin, nullptr, r, st);
+  if constexpr (std::is_same<T, float>::value) {
+    // few rows (heads) against a contraction over all tokens of a group: dealt to enough blocks to fill the chip, at least
+    // four slices of 32 tokens each and no more partial sums than the tiles the buffer is sized for
+    const int pt = dz_patches(B, G, N, D, g), n_tiles = (N + pt - 1) / pt;
+    const long blocks = (long)((D + 63) / 64) * ((heads + 63) / 64) * B * G;
+    int S = 1;
+    while (blocks * S < 4L * compute_units() && 2 * S <= n_tiles && (long)g * N / 32 >= 8L * S && B * G * 2L * S <= 65535) S *= 2;
+    const long per = (long)heads * D;
+    d.reduce_b = 0;
+    d.C = {(long)G * S * per, (long)S * per, 0, (long)D, 1};
+    if ((rc = launch_gemm_f32(d, ds, zin, nullptr, rpart, st, S, per))) return rc;
+    return sum_key_path_partials(B, G, S, heads, D, rpart, r, st);
+  } else {
+    return launch_gemm<float, T, float>(d, ds, zin, nullptr, r, st);
+  }
 }
 
 inline int tokens_backward(int B, int Cin, int N, int D, int heads, int g, const float* zin, const float* w,
                            const float* alpha, const float* ds, const float* Mf, const bf16*, float* dz, float* r,
-                           float*, bool want_r, hipStream_t st) {
-  return tokens_backward_generic<float>(B, Cin, N, D, heads, g, zin, w, alpha, ds, Mf, dz, r, want_r, st);
+                           float* rpart, bool want_r, hipStream_t st) {
+  return tokens_backward_generic<float>(B, Cin, N, D, heads, g, zin, w, alpha, ds, Mf, dz, r, rpart, want_r, st);
 }
 inline int tokens_backward(int B, int Cin, int N, int D, int heads, int g, const bf16* zin, const bf16* w,
                            const float* alpha, const float* ds, const float* Mf, const bf16* Mb, bf16* dz, float* r,
@@ -781,7 +860,7 @@ inline int tokens_backward(int B, int Cin, int N, int D, int heads, int g, const
   const size_t lds = (size_t)2 * pt * g * 16 * 4;
   const bool mfma = D % 256 == 0 && heads <= 32 && !dbg(SW_DZ_VALU);
   if ((!mfma && heads > 16) || D % 4 || lds > 128 * 1024 || dbg(SW_GENERIC_LEVEL))
-    return tokens_backward_generic<bf16>(B, Cin, N, D, heads, g, zin, w, alpha, ds, Mf, dz, r, want_r, st);
+    return tokens_backward_generic<bf16>(B, Cin, N, D, heads, g, zin, w, alpha, ds, Mf, dz, r, rpart, want_r, st);
   const int n_tiles = (N + pt - 1) / pt;
   int rc;
   {

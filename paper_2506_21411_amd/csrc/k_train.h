@@ -36,6 +36,7 @@ struct GemmDesc {
   float scale;
   long rs_sk, rs_sa;   // k_gemm_mfma with a transposed A: optional row sums of A over the contraction, per (k, a)
   int c_vec;           // k_gemm_mfma: C rows are contiguous and 16-byte aligned, N % 8 == 0: store whole 16-byte chunks
+  const void* rowadd;  // optional [M][N] addend of C's type, the same for every batch item (k_gemm_mfma, k_gemm_f32)
 };
 
 template <typename TA, typename TB, typename TC>
@@ -638,7 +639,11 @@ namespace dchag {
 // Strided batched matrix product on bf16 MFMA (32x32x16, fp32 accumulation), BM x BN x 64 tiles,
 // four wavefronts (WM x WN), operands staged through XOR-swizzled LDS rows of 64 contraction elements.
 // Same contract as k_gemm_generic (GemmDesc), restricted to:
-//   K % 64 == 0 (no ragged K), every operand has one unit stride, 16-byte aligned rows.
+//   no ragged K, every operand has one unit stride, 16-byte aligned rows (so K % 8 == 0 where an operand's unit stride
+//   is the contraction index).  A last slice of fewer than 64 steps is filled up with zeros: the contraction over 135
+//   patches of a 384-wide model (a weight gradient, 8 groups) takes 8 us here against 75 us on the fp32-FMA kernel that
+//   used to take every K that is no multiple of 64.  Only EXTRA instances carry that code and the row addend (with both in
+//   every instance a training step of whole slices took 2.93 ms instead of 2.75).
 // An operand whose unit stride is the contraction index is copied chunk by chunk (AT / BT = false);
 // one whose unit stride is its row index m (or n) is read as 8 x 8 blocks (8 contraction steps x 8
 // rows), transposed in registers and written as whole 16-byte LDS chunks (AT / BT = true; threads
@@ -647,7 +652,7 @@ namespace dchag {
 // elements when reduce_b is set): the bias gradients that go with a weight gradient, at no extra pass over A.
 // grid (ceil(N/BN), ceil(M/BM), batch), block 256, dynamic LDS 2 x (BM + BN) x 128 bytes.
 // ---------------------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, bool AT, bool BT, typename TC>
+template <int BM, int BN, int WM, int WN, bool AT, bool BT, bool EXTRA, typename TC>
 __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __restrict__ A, const bf16* __restrict__ Bm,
                                                    const bf16* __restrict__ bias, TC* __restrict__ C,
                                                    TC* __restrict__ rowsum) {
@@ -683,7 +688,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   bf16x8 a_reg[AT ? 8 : A_CH], b_reg[BT ? 8 : B_CH];
-  const int KT = d.K / 64;
+  const int KT = (d.K + 63) / 64;
   const int steps = (b1 - b0) * KT;
   const int tb = tid - (256 - BN);                          // B's transposing threads: tb >= 0
 
@@ -692,10 +697,41 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
   const bool want_rs = AT && rowsum != nullptr && blockIdx.x == 0;
   float rsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
+  auto load_tail = [&](const bf16* Ab, const bf16* Bb, int k0) {
+    const bf16x8 zero = {};
+    if (!AT) {
+#pragma unroll
+      for (int i = 0; i < A_CH; ++i) {
+        const int idx = tid + i * 256, gr = min(m0 + (idx >> 3), M - 1), kk = k0 + (idx & 7) * 8;
+        a_reg[i] = kk < d.K ? *reinterpret_cast<const bf16x8*>(Ab + d.A.s0 * gr + kk) : zero;
+      }
+    } else if (tid < BM) {
+      const int gm = min(m0 + (tid % (BM / 8)) * 8, M - 8), kk = k0 + (tid / (BM / 8)) * 8;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        a_reg[i] = kk + i < d.K ? *reinterpret_cast<const bf16x8*>(Ab + d.A.s1 * (kk + i) + gm) : zero;
+    }
+    if (!BT) {
+#pragma unroll
+      for (int i = 0; i < B_CH; ++i) {
+        const int idx = tid + i * 256, gr = min(n0 + (idx >> 3), d.N - 1), kk = k0 + (idx & 7) * 8;
+        b_reg[i] = kk < d.K ? *reinterpret_cast<const bf16x8*>(Bb + d.Bm.s1 * gr + kk) : zero;
+      }
+    } else if (tb >= 0) {
+      const int gn = min(n0 + (tb % (BN / 8)) * 8, d.N - 8), kk = k0 + (tb / (BN / 8)) * 8;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        b_reg[i] = kk + i < d.K ? *reinterpret_cast<const bf16x8*>(Bb + d.Bm.s0 * (kk + i) + gn) : zero;
+    }
+  };
   auto load = [&](int s) {
     const int b = b0 + s / KT, k0 = (s % KT) * 64;
     const bf16* Ab = A + d.A.sb * b + d.A.sk * k + d.A.sa * a;
     const bf16* Bb = Bm + d.Bm.sb * b + d.Bm.sk * k + d.Bm.sa * a;
+    if (EXTRA && k0 + 64 > d.K) {                            // uniform: the ragged last slice, zeros past the end
+      load_tail(Ab, Bb, k0);
+      return;
+    }
     if (!AT) {
 #pragma unroll
       for (int i = 0; i < A_CH; ++i) {
@@ -808,6 +844,7 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
   // 32x32 accumulator block: lane holds column (lane % 32); register r holds row 8 (r / 4) + 4 (lane / 32) + r % 4
   TC* Cb = C + d.C.sb * b0 + d.C.sk * k + d.C.sa * a;
   const bf16* bs = bias ? bias + d.bias_sk * k + d.bias_sa * a : nullptr;
+  const TC* radd = EXTRA ? static_cast<const TC*>(d.rowadd) : nullptr;
   if (sizeof(TC) == 2 && d.c_vec) {
     // the tile goes through LDS (the stages are no longer read) so that rows leave in 16-byte chunks:
     // a lane's accumulator column is 2 bytes wide, a row of the tile up to 256 bytes
@@ -823,7 +860,9 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int ml = wm * (BM / WM) + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-          tile[ml * PITCH + nl] = (bf16)(acc[i][j][r] * d.scale + bv);
+          float v = acc[i][j][r] * d.scale + bv;
+          if (radd && m0 + ml < M && n0 + nl < d.N) v += to_f32(radd[(size_t)(m0 + ml) * d.N + n0 + nl]);
+          tile[ml * PITCH + nl] = (bf16)v;
         }
     }
     __syncthreads();
@@ -846,8 +885,158 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int m = m0 + wm * (BM / WM) + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-        if (m < M) Cb[d.C.s0 * m + d.C.s1 * n] = from_f32<TC>(acc[i][j][r] * d.scale + bv);
+        if (m < M)
+          Cb[d.C.s0 * m + d.C.s1 * n] =
+              from_f32<TC>(acc[i][j][r] * d.scale + bv + (radd ? to_f32(radd[(size_t)m * d.N + n]) : 0.f));
       }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// The same products in single precision: 64 x 64 tiles on v_mfma_f32_32x32x2_f32 (fp32 operands and accumulation, twice
+// the rate of unpacked vector FMAs), contraction in slices of 32, four wavefronts (2 x 2) of 32 x 32.  Takes the whole
+// GemmDesc contract (ragged M or K, any strides with one unit stride per operand, any alignment) plus a row addend.
+//   Rows of 32 contraction steps lie in LDS with a pitch of 36 floats (16-byte reads of 32 rows hit every bank group
+//   evenly); a lane reads four steps at once, half 0 of the wavefront steps 8 s .. 8 s + 3 and half 1 the next four, and
+//   feeds them to four products (both operands pair the steps the same way, so the contraction is complete).
+//   An operand whose unit stride is the contraction index is copied in 16-byte pieces, one whose unit stride is its row
+//   index is read as 4 x 4 blocks and transposed in registers.  Two slices are in flight in registers ahead of the
+//   one being multiplied: what bounded the FMA kernels it replaces was a load round trip per 16 steps (2 to 3 us each;
+//   24 us for a product over 128 steps).
+//   split > 1: the contraction is dealt to `split` blocks, block t takes slices [t, t + 1) * per of it and writes its own
+//   partial result at offset split_stride * t (per batch item); bias and addend are then not applied.
+// grid (ceil(N/64), ceil(M/64), batch * split), block 256.
+// ---------------------------------------------------------------------------------------
+template <bool AT, bool BT>
+__global__ __launch_bounds__(256) void k_gemm_f32(GemmDesc d, int va, int vb, int split, long split_stride,
+                                                  const float* __restrict__ A, const float* __restrict__ Bm,
+                                                  const float* __restrict__ bias, float* __restrict__ C) {
+  constexpr int PITCH = 36;
+  __shared__ __attribute__((aligned(16))) float As[2][64 * PITCH];
+  __shared__ __attribute__((aligned(16))) float Bs[2][64 * PITCH];
+  int z = blockIdx.z;
+  const int part = z % split;
+  z /= split;
+  const int a = z % d.na;
+  z /= d.na;
+  const int k = z % d.nk;
+  const int b0 = d.reduce_b ? 0 : z / d.nk;
+  const int b1 = d.reduce_b ? d.nb : b0 + 1;
+  int M = d.M, K = d.K;
+  if (d.ragged) {
+    int left = d.ragged_total - k * d.ragged_nominal;
+    left = left < d.ragged_nominal ? left : d.ragged_nominal;
+    if (d.ragged == 1) M = left; else K = left;
+  }
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  if (m0 >= M) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lhi = lane >> 5;
+  const int KT = (K + 31) / 32;
+  const int per = ((b1 - b0) * KT + split - 1) / split;
+  const int s_begin = part * per, s_end = min(s_begin + per, (b1 - b0) * KT);
+
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+
+  // one operand's share of a slice in registers: four 16-byte pieces (row-fast operands: a 4 x 4 block; others: two pieces)
+  auto load_op = [&](bool T, int vec, const float* P, long srow, long sk, int r0, int R, int k0, int t, f32x4 (&reg)[4]) {
+    if (!T) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int idx = tid + i * 256, row = r0 + (idx >> 3), kk = k0 + (idx & 7) * 4;
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        if (row < R) {
+          const float* p = P + srow * row + kk;
+          if (vec && kk + 4 <= K) v = *reinterpret_cast<const f32x4*>(p);
+          else
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (kk + e < K) v[e] = p[e];
+        }
+        reg[i] = v;
+      }
+    } else if (t >= 0 && t < 128) {                         // 16 row blocks x 8 blocks of four steps
+      const int row = r0 + (t & 15) * 4, kb = k0 + (t >> 4) * 4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        if (kb + i < K) {
+          const float* p = P + sk * (kb + i) + row;
+          if (vec && row + 4 <= R) v = *reinterpret_cast<const f32x4*>(p);
+          else
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (row + e < R) v[e] = p[e];
+        }
+        reg[i] = v;
+      }
+    }
+  };
+  auto store_op = [&](bool T, float* S, int t, const f32x4 (&reg)[4]) {
+    if (!T) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int idx = tid + i * 256;
+        *reinterpret_cast<f32x4*>(S + (idx >> 3) * PITCH + (idx & 7) * 4) = reg[i];
+      }
+    } else if (t >= 0 && t < 128) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<f32x4*>(S + ((t & 15) * 4 + e) * PITCH + (t >> 4) * 4) =
+            f32x4{reg[0][e], reg[1][e], reg[2][e], reg[3][e]};
+    }
+  };
+  const int ta = tid, tb = BT && AT ? tid - 128 : tid;
+  f32x4 ar[2][4], br[2][4];                                  // the two slices in flight
+  auto load = [&](int s, f32x4 (&ra)[4], f32x4 (&rb)[4]) {
+    const int b = b0 + s / KT, k0 = (s % KT) * 32;
+    load_op(AT, va, A + d.A.sb * b + d.A.sk * k + d.A.sa * a, d.A.s0, d.A.s1, m0, M, k0, ta, ra);
+    load_op(BT, vb, Bm + d.Bm.sb * b + d.Bm.sk * k + d.Bm.sa * a, d.Bm.s1, d.Bm.s0, n0, d.N, k0, tb, rb);
+  };
+  auto multiply = [&](int buf) {
+    const float* Ap = As[buf] + (wm * 32 + l32) * PITCH + lhi * 4;
+    const float* Bp = Bs[buf] + (wn * 32 + l32) * PITCH + lhi * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 av = *reinterpret_cast<const f32x4*>(Ap + q * 8), bv = *reinterpret_cast<const f32x4*>(Bp + q * 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[e], acc, 0, 0, 0);
+    }
+  };
+  // slice s goes to LDS buffer s & 1 one step before it is multiplied; its registers then take slice s + 2
+  auto step = [&](int s, int buf, f32x4 (&ra)[4], f32x4 (&rb)[4]) {   // ra, rb: slice s + 1's registers
+    if (s + 1 < s_end) {
+      store_op(AT, As[buf ^ 1], ta, ra);
+      store_op(BT, Bs[buf ^ 1], tb, rb);
+      if (s + 3 < s_end) load(s + 3, ra, rb);
+    }
+    multiply(buf);
+    __syncthreads();
+  };
+  if (s_begin < s_end) {
+    load(s_begin, ar[0], br[0]);
+    if (s_begin + 1 < s_end) load(s_begin + 1, ar[1], br[1]);
+    store_op(AT, As[0], ta, ar[0]);
+    store_op(BT, Bs[0], tb, br[0]);
+    if (s_begin + 2 < s_end) load(s_begin + 2, ar[0], br[0]);
+    __syncthreads();
+    for (int s = s_begin; s < s_end; s += 2) {
+      step(s, 0, ar[1], br[1]);
+      if (s + 1 < s_end) step(s + 1, 1, ar[0], br[0]);
+    }
+  }
+  // lane: column l32, register r: row 8 (r / 4) + 4 (lane / 32) + r % 4
+  const int n = n0 + wn * 32 + l32;
+  if (n >= d.N) return;
+  float* Cb = C + d.C.sb * b0 + d.C.sk * k + d.C.sa * a + split_stride * part;
+  const float bv = bias && split == 1 ? bias[d.bias_sk * k + d.bias_sa * a + n] : 0.f;
+  const float* radd = split == 1 ? static_cast<const float*>(d.rowadd) : nullptr;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
+    if (m < M) Cb[d.C.s0 * m + d.C.s1 * n] = acc[r] * d.scale + bv + (radd ? radd[(size_t)m * d.N + n] : 0.f);
   }
 }
 

@@ -1,0 +1,96 @@
+"""GPU parity at the sizes where the matrix products of the library can go wrong: contractions that no slice divides,
+outputs that no tile divides, operands whose rows are not 16-byte aligned, contractions dealt to several blocks.
+Forward (with and without the positional embedding) and every gradient against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2506_21411_amd as dchag
+from workloads import ShapeCfg, make_problem
+
+from .test_gpu_train import ATT, TOL, dev, dev_level, host, rel_err, say
+
+pytestmark = pytest.mark.gpu
+
+
+def check_training_step(cfg, seed=77):
+    pr = make_problem(cfg)
+    d = cfg.dtype
+    args = (dev(pr.x, d), dev(pr.We, d), dev(pr.be, d), dev(pr.ce, d), [dev_level(lv, d) for lv in pr.levels], cfg.p,
+            cfg.heads)
+    gs = [lv.group_size for lv in pr.levels]
+    code = dchag.DCHAG_F32 if d == "f32" else dchag.DCHAG_BF16
+    ws = torch.empty(dchag.dchag_workspace_bytes(code, cfg.B, cfg.C, cfg.H, cfg.W, cfg.p, cfg.D, cfg.heads, gs, 3),
+                     dtype=torch.uint8, device="cuda")
+    out = dchag.dchag_forward_keep(*args, ws)
+    dout = dev(np.random.Generator(np.random.PCG64(seed)).standard_normal((cfg.B, cfg.N, cfg.D)).astype(np.float32), d)
+    dx, dWe, dtb = torch.empty_like(args[0]), torch.empty_like(args[1]), torch.empty_like(args[3])
+    grads = []
+    for lv in args[4]:
+        names = ("Wv", "bv") if lv.kind else ATT
+        grads.append(dchag.LevelGrads(**{"d" + n: torch.empty_like(getattr(lv, n)) for n in names}))
+    dchag.dchag_backward(*args, dout, grads, dx=dx, dWe=dWe, dtok_bias=dtb, workspace=ws, kept=True)
+    torch.cuda.synchronize()
+    want = oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads).reshape(cfg.B, cfg.N, cfg.D)
+    errs = {"out": rel_err(host(out), want)}
+    ref = oracle.backward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads, host(dout).reshape(-1, cfg.D))
+    for name, got in (("dx", dx), ("dWe", dWe), ("dtok_bias", dtb)):
+        want_g = ref[name]
+        if name == "dx":                                  # patch rows [B*N, C, p*p] -> image
+            hp, wp = cfg.H // cfg.p, cfg.W // cfg.p
+            want_g = want_g.reshape(cfg.B, hp, wp, cfg.C, cfg.p, cfg.p).transpose(0, 3, 1, 4, 2, 5).reshape(got.shape)
+        errs[name] = rel_err(host(got), want_g)
+    for i, (g, r) in enumerate(zip(grads, ref["levels"])):
+        for name, got in vars(g).items():
+            if got is None:
+                continue
+            if name == "dbk":
+                assert not host(got).any()
+                continue
+            # a group of one has no gradient on its query path: the oracle's exact zeros leave nothing to divide by
+            if np.abs(r[name]).max() < 1e-12:
+                assert np.abs(host(got)).max() < 1e-6
+                continue
+            errs[f"l{i}.{name}"] = rel_err(host(got), r[name])
+    worst = max(errs, key=errs.get)
+    say(f"  worst {worst} {errs[worst]:.3e}  out {errs['out']:.3e}")
+    assert errs[worst] < TOL[d], errs
+
+
+PRODUCTS = [
+    # bf16, embeddings no 256 divides: 135 patches (contraction of two slices and 7), 384 columns, 77 = 7 x 10 + 7 channels
+    dict(dtype="bf16", B=2, C=21, H=144, W=240, p=16, D=384, heads=6, group_sizes=(10, 3)),
+    # contraction shorter than one slice (9 patches, heads of 32 columns), 160 columns
+    dict(dtype="bf16", B=1, C=5, H=12, W=12, p=4, D=160, heads=5, group_sizes=(3, 2)),
+    # one patch
+    dict(dtype="bf16", B=1, C=4, H=8, W=8, p=8, D=128, heads=2, group_sizes=(4,)),
+    # f32: 136 columns (tiles of 64 and a remainder of 8), 7 patches, 17 columns a head: rows that are no multiple of 4
+    dict(dtype="f32", B=2, C=9, H=2, W=14, p=2, D=136, heads=8, group_sizes=(4, 3)),
+    # 5 heads (rows of 5 floats: no 16-byte loads), 33 patches, 40 columns
+    dict(dtype="f32", B=1, C=11, H=6, W=22, p=2, D=40, heads=5, group_sizes=(11,)),
+    # a contraction over 16 x 200 tokens dealt to several blocks, the last group shorter (13 members)
+    dict(dtype="f32", B=1, C=29, H=40, W=80, p=4, D=64, heads=2, group_sizes=(16, 2)),
+]
+
+
+@pytest.mark.parametrize("kw", PRODUCTS)
+def test_training_step_at_the_edges_of_the_products(kw):
+    say(f"products {kw}")
+    check_training_step(ShapeCfg(name="t", x_kind="gauss_mu_sigma", seed=11, **kw))
+
+
+@pytest.mark.parametrize("kw", [PRODUCTS[0], PRODUCTS[3]])
+def test_positional_embedding_is_added_by_the_products(kw):
+    cfg = ShapeCfg(name="t", x_kind="gauss_mu_sigma", seed=12, **kw)
+    say(f"products, positional embedding {kw}")
+    pr = make_problem(cfg)
+    d = cfg.dtype
+    pos = np.random.Generator(np.random.PCG64(3)).standard_normal((cfg.N, cfg.D)).astype(np.float32)
+    pos_d = dev(pos, d)
+    out = dchag.dchag_forward_pos(dev(pr.x, d), dev(pr.We, d), dev(pr.be, d), dev(pr.ce, d),
+                                  [dev_level(lv, d) for lv in pr.levels], cfg.p, cfg.heads, pos_d)
+    want = oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads).reshape(cfg.B, cfg.N, cfg.D)
+    err = rel_err(host(out), want + host(pos_d)[None])
+    say(f"  err {err:.3e}")
+    assert err < TOL[d]
