@@ -19,6 +19,7 @@
 #include "k_mfma.h"
 #include "k_fused.h"
 #include "k_train.h"
+#include "k_pixel_train.h"
 #include "k_yardstick.h"
 
 using namespace dchag;
@@ -57,6 +58,7 @@ enum Switch {
   SW_TOKENIZE_PER_TILE,
   SW_TOKENS_UNFUSED,
   SW_TOKEN_SCORES,
+  SW_TRAIN_TOKENS,
   SW_VAGG_SPLIT,
   SW_VALUE_UNFOLDED,
   SW_COUNT
@@ -90,6 +92,7 @@ struct SwitchTable {
     "DCHAG_TOKENIZE_PER_TILE",
     "DCHAG_TOKENS_UNFUSED",
     "DCHAG_TOKEN_SCORES",
+    "DCHAG_TRAIN_TOKENS",
     "DCHAG_VAGG_SPLIT",
     "DCHAG_VALUE_UNFOLDED"};
     for (int i = 0; i < SW_COUNT; ++i) {
@@ -938,7 +941,7 @@ size_t dchag_workspace_bytes(dchag_dtype dt, int B, int C, int H, int W, int p, 
   if (which == 1) return forward_ws(dt, B, C, N, p * p, D, heads, n_levels, group_sizes).total;
   if (n_levels > 16) return 0;
   if (which == 2) return folded_ws(dt, B, C, N, p * p, D, heads, n_levels, group_sizes).total;
-  if (which == 3) return backward_ws(dt, B, C, N, p * p, D, heads, n_levels, group_sizes, nullptr).total;
+  if (which == 3) return train_ws_bytes(dt, B, C, N, p, D, heads, n_levels, group_sizes);
   return 0;
 }
 
@@ -1242,9 +1245,10 @@ static int train_call(int which, dchag_dtype dt, int B, int C, int H, int W, int
         if (misaligned(q)) return DCHAG_ERR_ALIGN;
     }
   const int N = (H / p) * (W / p);
-  const BackwardWs w = backward_ws(dt, B, C, N, p * p, D, heads, n_levels, gs, kinds);
+  const bool pixels = pixel_train_ok(dt, B, C, N, p, D, heads, &levels[0], gs[0]);
+  const BackwardWs w = backward_ws(dt, B, C, N, p * p, D, heads, n_levels, gs, kinds, pixels);
   // a keep / reverse pair shares one workspace, so both are held to the size dchag_workspace_bytes reports
-  const size_t need = which == 3 ? w.total : backward_ws(dt, B, C, N, p * p, D, heads, n_levels, gs, nullptr).total;
+  const size_t need = which == 3 ? w.total : train_ws_bytes(dt, B, C, N, p, D, heads, n_levels, gs);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) || w.total == 0 || workspace_bytes < need)
     return DCHAG_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);

@@ -107,17 +107,79 @@ inline int dz_patches(int B, int G, int N, int D, int g) {
   return pt;
 }
 
+// Buffers of an attention first level trained from the pixels (k_pixel_train.h): what the forward sweep leaves for the
+// reverse sweep comes first, from `dot` on they are the reverse sweep's own.
+struct PixelWs {
+  size_t qp, mf, mb, alpha, o, y, fold, wft, wg, ug, ut, wet, dot, dal, er, et, part, fr, ft, wvt, m2, x, ones;
+  int splits;
+};
+
+inline PixelDims pixel_dims(int B, int C, int N, int pp, int D, int heads, int g) {
+  PixelDims d{};
+  d.B = B; d.C = C; d.N = N; d.D = D; d.g = g; d.G = groups_of(C, g); d.heads = heads;
+  d.gpad = round_up(g, 8); d.Np = round_up(N, 32); d.NT = round_up(N, 64);
+  d.gq = pp == 16 ? round_up(g, 4) : g; d.gp = round_up(g, 32);
+  d.RE = d.gq * pp + d.gp; d.KE = d.gq * pp + 2 * d.gp;
+  return d;
+}
+
+// Blocks the contraction over the patches of k_pixel_outer is dealt to, so that the weight-sized product still fills the
+// chip: doubled while there are fewer than two workgroups per compute unit's two slots and eight slices are left for each.
+inline int pixel_outer_splits(const PixelDims& d) {
+  const long tiles = (long)d.G * ((d.RE + 127) / 128) * (d.D / 128);
+  const int slices = d.B * (d.NT / 64);
+  int s = 1;
+  while (tiles * s < 2L * compute_units() && slices >= 16 * s) s *= 2;
+  return s;
+}
+
+inline size_t pixel_ws(const PixelDims& d, int pp, bool keep_y, size_t off, PixelWs* w) {
+  const size_t B = d.B, C = d.C, D = d.D, G = d.G, h = d.heads;
+  auto take = [&](size_t bytes) { const size_t o = off; off += align_up(bytes); return o; };
+  w->qp = take(G * D * 4);
+  w->mf = take(G * h * D * 4);
+  w->mb = take(G * h * D * 2);
+  w->alpha = take(B * G * d.gpad * h * d.Np * 4);
+  w->o = take(B * G * d.N * D * 2);
+  w->y = take(keep_y ? B * G * d.N * D * 2 : 0);
+  w->fold = take(value_fold_bytes(d.C, d.D, pp));                // Wf, then the folded token bias
+  w->wft = take(C * pp * D * 2);
+  w->wg = take(pp == 16 ? G * D * d.gq * 16 * 2 : 0);
+  w->ug = take(pp == 16 ? B * G * d.N * d.gq * 16 * 2 : 0);
+  w->ut = take(B * C * pp * d.NT * 2);
+  w->wet = take(C * pp * D * 2);                                 // forward only
+  w->dot = take(B * G * D * d.NT * 2);
+  w->dal = take(B * G * d.gpad * std::max(h, D / 64) * d.Np * 4);
+  w->er = take(G * D * d.KE * 2);
+  w->et = take(G * d.RE * D * 2);
+  w->splits = pixel_outer_splits(d);
+  w->part = take(w->splits > 1 ? (size_t)w->splits * G * d.RE * D * 4 : 0);
+  w->fr = take(G * 64 * d.KE * 2);
+  w->ft = take(G * d.RE * 64 * 2);
+  w->wvt = take(G * D * D * 2);
+  w->m2 = take(G * D * 64 * 2);
+  w->x = take(G * D * (size_t)((pp == 16 ? d.gq * 16 : 0) + 2 * d.gp) * 2);
+  w->ones = take((size_t)d.NT * 2);
+  return off;
+}
+
 struct BackwardWs {
   size_t tokens, patches, kept[16], dz[2], dalpha, w, d_o, r, dq, rpart, ms, msb, cs, mft, total;
+  bool pixels;                     // the first level is trained from the pixels: px instead of tokens, patches, kept[0]
+  PixelWs px;
 };
 
 inline BackwardWs backward_ws(dchag_dtype dt, int B, int C, int N, int pp, int D, int heads, int n_levels,
-                              const int32_t* group_sizes, const int32_t* kinds) {
+                              const int32_t* group_sizes, const int32_t* kinds, bool pixels = false) {
   BackwardWs w{};
   const size_t es = elem_size(dt);
   size_t off = 0;
-  w.tokens = off; off += align_up((size_t)B * C * N * D * es);
-  w.patches = off; off += align_up((size_t)B * C * N * pp * es);
+  w.pixels = pixels;
+  w.tokens = off;
+  if (!pixels) off += align_up((size_t)B * C * N * D * es);
+  w.patches = off;
+  if (!pixels) off += align_up((size_t)B * C * N * pp * es);
+  if (pixels) off = pixel_ws(pixel_dims(B, C, N, pp, D, heads, group_sizes[0]), pp, n_levels > 1, off, &w.px);
   int c_in = C;
   size_t dal = 0, wv = 0, dov = 0, rv = 0, dqv = 0, dz0 = 0, dz1 = 0, rp = 0;
   for (int l = 0; l < n_levels; ++l) {
@@ -125,6 +187,13 @@ inline BackwardWs backward_ws(dchag_dtype dt, int B, int C, int N, int pp, int D
     if (g < 1) return BackwardWs{};
     const int G = groups_of(c_in, g);
     const bool linear = kinds && kinds[l] == DCHAG_LEVEL_LINEAR;
+    if (l == 0 && pixels) {
+      dov = std::max(dov, align_up((size_t)B * G * N * D * es));
+      rv = std::max(rv, align_up((size_t)G * heads * D * 4));
+      dqv = std::max(dqv, align_up((size_t)G * D * 4));
+      c_in = G;
+      continue;
+    }
     w.kept[l] = off;
     off += kept_level(dt, B, c_in, N, D, heads, g, linear, l + 1 < n_levels).total;
     const size_t dzb = align_up((size_t)B * c_in * N * D * es);
@@ -907,6 +976,62 @@ int outer_rows(int D, int G, int rows_per_vec, float scale, const float* rowv, c
   return launch_status();
 }
 
+// Reverse of a level's output projection: dWo, dbo and d_o, the gradient at its input o [B,G,N,D].
+template <typename T>
+int output_projection_backward(int B, int G, int N, int D, const dchag_level* lv, const dchag_level_grads* gr, const T* dy,
+                               const T* o, T* d_o, hipStream_t st) {
+  const RowBlocks rbo{G, G * N, N};
+  const long sBG = (long)G * N * D, sG = (long)N * D;          // strides of a [B,G,N,D] tensor
+  int rc;
+  StageTimer tm(DCHAG_STAGE_BWD_OPROJ, st);
+  {                                                             // dWo[k][i][j] = sum_{b,n} dy[..,i] o[..,j];  dbo = sum dy
+    GemmDesc d{};
+    d.M = D; d.N = D; d.K = N; d.nb = B; d.nk = G; d.na = 1; d.reduce_b = 1;
+    d.A = {sBG, sG, 0, 1, (long)D};
+    d.Bm = {sBG, sG, 0, (long)D, 1};
+    d.C = {0, (long)D * D, 0, (long)D, 1};
+    d.scale = 1.f;
+    d.rs_sk = D;
+    if ((rc = gemm_with_bias_grad(d, B, D, rbo, dy, o, static_cast<T*>(gr->dWo), static_cast<T*>(gr->dbo), st)))
+      return rc;
+  }
+  GemmDesc d{};                                                 // d_o[.., j] = sum_i dy[.., i] Wo[k][i][j]
+  d.M = N; d.N = D; d.K = D; d.nb = B; d.nk = G; d.na = 1;
+  d.A = {sBG, sG, 0, (long)D, 1};
+  d.Bm = {0, (long)D * D, 0, (long)D, 1};
+  d.C = {sBG, sG, 0, (long)D, 1};
+  d.scale = 1.f;
+  return gemm_tt(d, dy, static_cast<const T*>(lv->Wo), static_cast<const T*>(nullptr), d_o, st);
+}
+
+// Key and query weight gradients of a level from the key-path sums r [G,heads,D].
+template <typename T>
+int key_query_backward(int G, int D, int heads, const dchag_level* lv, const dchag_level_grads* gr, const float* Qp,
+                       const float* r, float* dQ, hipStream_t st) {
+  const int dh = D / heads;
+  int rc;
+  StageTimer tm(DCHAG_STAGE_BWD_KEY_QUERY, st);
+  if (gr->dbk) {
+    const long n = (long)G * D;
+    k_fill_zero<T><<<dim3((unsigned)((n + 255) / 256)), 256, 0, st>>>(n, static_cast<T*>(gr->dbk));
+    if ((rc = launch_status())) return rc;
+  }
+  if (gr->dWk && (rc = outer_rows<float, T>(D, G, dh, 1.f / sqrtf((float)dh), Qp, r, static_cast<T*>(gr->dWk), st)))
+    return rc;
+  if (!gr->dWq && !gr->dbq && !gr->dquery) return DCHAG_OK;
+  k_query_grad<T><<<dim3((D + 3) / 4, G), 256, 0, st>>>(D, heads, static_cast<const T*>(lv->Wk), r, dQ,
+                                                        static_cast<T*>(gr->dbq));
+  if ((rc = launch_status())) return rc;
+  if (gr->dWq && (rc = outer_rows<T, T>(D, G, D, 1.f, dQ, static_cast<const T*>(lv->query), static_cast<T*>(gr->dWq), st)))
+    return rc;
+  if (gr->dquery) {
+    k_query_input_grad<T><<<dim3((D + 63) / 64, G), 1024, 0, st>>>(D, static_cast<const T*>(lv->Wq), dQ,
+                                                                   static_cast<T*>(gr->dquery));
+    if ((rc = launch_status())) return rc;
+  }
+  return DCHAG_OK;
+}
+
 // Reverse of one attention level.  dy is the gradient at the level's output [B,G,N,D]; dz receives the
 // gradient at its input [B,Cin,N,D].
 template <typename T>
@@ -915,32 +1040,11 @@ int attention_level_backward(int B, int Cin, int N, int D, int heads, const dcha
                              float* dalpha, T* w, T* d_o, float* r, float* dQ, float* rpart, hipStream_t st) {
   const int g = lv->group_size, G = groups_of(Cin, g), dh = D / heads;
   const T* Wv = static_cast<const T*>(lv->Wv);
-  const T* Wo = static_cast<const T*>(lv->Wo);
   const RowBlocks rbo{G, G * N, N};
   const long sBG = (long)G * N * D, sG = (long)N * D;          // strides of a [B,G,N,D] tensor
   const long uB = (long)G * N * heads * D, uG = (long)N * heads * D;
   int rc;
-  {
-    StageTimer tm(DCHAG_STAGE_BWD_OPROJ, st);
-    {                                                           // dWo[k][i][j] = sum_{b,n} dy[..,i] o[..,j];  dbo = sum dy
-      GemmDesc d{};
-      d.M = D; d.N = D; d.K = N; d.nb = B; d.nk = G; d.na = 1; d.reduce_b = 1;
-      d.A = {sBG, sG, 0, 1, (long)D};
-      d.Bm = {sBG, sG, 0, (long)D, 1};
-      d.C = {0, (long)D * D, 0, (long)D, 1};
-      d.scale = 1.f;
-      d.rs_sk = D;
-      if ((rc = gemm_with_bias_grad(d, B, D, rbo, dy, lb.o, static_cast<T*>(gr->dWo), static_cast<T*>(gr->dbo), st)))
-        return rc;
-    }
-    GemmDesc d{};                                               // d_o[.., j] = sum_i dy[.., i] Wo[k][i][j]
-    d.M = N; d.N = D; d.K = D; d.nb = B; d.nk = G; d.na = 1;
-    d.A = {sBG, sG, 0, (long)D, 1};
-    d.Bm = {0, (long)D * D, 0, (long)D, 1};
-    d.C = {sBG, sG, 0, (long)D, 1};
-    d.scale = 1.f;
-    if ((rc = gemm_tt(d, dy, Wo, nullptr, d_o, st))) return rc;
-  }
+  if ((rc = output_projection_backward<T>(B, G, N, D, lv, gr, dy, lb.o, d_o, st))) return rc;
   {
     StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
     {                                                           // dWv[k][a*dh+i][j] = sum_{b,n} d_o[.., a*dh+i] u[.., a, j]
@@ -979,27 +1083,9 @@ int attention_level_backward(int B, int Cin, int N, int D, int heads, const dcha
     if ((rc = tokens_backward(B, Cin, N, D, heads, g, zin, w, lb.alpha, dalpha, lb.Mf, lb.Mb, dz, r, rpart, want_r, st)))
       return rc;
   }
-  StageTimer tm(DCHAG_STAGE_BWD_KEY_QUERY, st);
-  if (gr->dbk) {
-    const long n = (long)G * D;
-    k_fill_zero<T><<<dim3((unsigned)((n + 255) / 256)), 256, 0, st>>>(n, static_cast<T*>(gr->dbk));
-    if ((rc = launch_status())) return rc;
-  }
-  if (gr->dWk && (rc = outer_rows<float, T>(D, G, dh, 1.f / sqrtf((float)dh), lb.Qp, r, static_cast<T*>(gr->dWk), st)))
-    return rc;
-  if (!want_q) return DCHAG_OK;
-  k_query_grad<T><<<dim3((D + 3) / 4, G), 256, 0, st>>>(D, heads, static_cast<const T*>(lv->Wk), r, dQ,
-                                                        static_cast<T*>(gr->dbq));
-  if ((rc = launch_status())) return rc;
-  if (gr->dWq && (rc = outer_rows<T, T>(D, G, D, 1.f, dQ, static_cast<const T*>(lv->query), static_cast<T*>(gr->dWq), st)))
-    return rc;
-  if (gr->dquery) {
-    k_query_input_grad<T><<<dim3((D + 63) / 64, G), 1024, 0, st>>>(D, static_cast<const T*>(lv->Wq), dQ,
-                                                                   static_cast<T*>(gr->dquery));
-    if ((rc = launch_status())) return rc;
-  }
-  return DCHAG_OK;
+  return key_query_backward<T>(G, D, heads, lv, gr, lb.Qp, r, dQ, st);
 }
+
 template <typename T>
 int linear_level_backward(int B, int Cin, int N, int D, const dchag_level* lv, const dchag_level_grads* gr,
                           const T* zin, const T* dy, T* dz, hipStream_t st) {
@@ -1167,6 +1253,179 @@ inline int linear_first_backward(int B, int C, int H, int W, int p, int D, const
   return DCHAG_OK;
 }
 
+// ---- attention first level trained from the pixels (k_pixel_train.h) ----
+
+// Taken by the shapes whose first level dchag_forward_folded takes from the pixels, when it is the cheaper route.  The route through
+// the tokens moves about ten times B N C D elements; this one multiplies 6 C D D pp flops whatever B N is: the line
+// B N = D pp / 512 is where the two meet at 4.5 TB/s and 0.75 PFLOP/s.  DCHAG_TRAIN_TOKENS (debugging aid) keeps the tokens.
+inline bool pixel_train_ok(dchag_dtype dt, int B, int C, int N, int p, int D, int heads, const dchag_level* first, int g) {
+  const int pp = p * p;
+  if (!values_from_pixels(dt, p, D, heads, first) || dbg(SW_TRAIN_TOKENS)) return false;
+  if ((long)B * N * 512 < (long)D * pp) return false;
+  const PixelDims d = pixel_dims(B, C, N, pp, D, heads, g);
+  const long tiles_n = (N + 127) / 128, tiles_d = D / 128, tiles_r = (d.RE + 127) / 128;
+  return (long)B * d.G <= 65535 && C <= 65535 && tiles_n * std::max(tiles_d, tiles_r) * B * d.G <= (1L << 30) &&
+         tiles_r * tiles_d * d.G * 64 <= (1L << 30) && (long)d.G * d.gq * (pp / 8) / 32 <= 65534;
+}
+
+// What dchag_workspace_bytes reports for a training step: the kinds of the levels are not known there, so the larger of the
+// routes the first level may take.
+inline size_t train_ws_bytes(dchag_dtype dt, int B, int C, int N, int p, int D, int heads, int n_levels, const int32_t* gs) {
+  dchag_level attention{};
+  size_t total = backward_ws(dt, B, C, N, p * p, D, heads, n_levels, gs, nullptr).total;
+  if (total && pixel_train_ok(dt, B, C, N, p, D, heads, &attention, gs[0]))
+    total = std::max(total, backward_ws(dt, B, C, N, p * p, D, heads, n_levels, gs, nullptr, true).total);
+  return total;
+}
+
+inline TileWork pixel_tiles(int fast, int slow, int nb, int G) {
+  TileWork tw{};
+  tw.n_tiles = fast; tw.m_tiles = slow; tw.nb = nb; tw.total = fast * slow * nb * G;
+  return tw;
+}
+inline unsigned tile_grid(const TileWork& tw) { return (unsigned)((tw.total + kXcds - 1) / kXcds * kXcds); }
+
+inline int transpose_rows(int batch, int R, int RT, int Cc, const bf16* in, bf16* out, hipStream_t st) {
+  k_transpose<<<dim3((unsigned)((RT + 63) / 64), (unsigned)((Cc + 255) / 256), (unsigned)batch), 256, 0, st>>>(R, RT, Cc, in,
+                                                                                                            out);
+  return launch_status();
+}
+
+template <class K>
+int raise_pair_lds(K kern) { return ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kPairLdsBytes); }
+
+// Forward half: folded weights (both layouts), softmax weights from the pixels, o; y is left to the caller.
+template <int PP>
+int pixel_level_forward(int B, int C, int H, int W, int p, int D, int heads, const dchag_level* lv, const bf16* x,
+                        const bf16* We, const bf16* be, const bf16* ce, unsigned char* ws, const BackwardWs& bw, PixelScores px,
+                        hipStream_t st) {
+  const PixelWs& w = bw.px;
+  PixelDims d = pixel_dims(B, C, (H / p) * (W / p), PP, D, heads, lv->group_size);
+  d.H = H; d.W = W;
+  auto at = [&](size_t off) { return reinterpret_cast<bf16*>(ws + off); };
+  bf16 *Wf = at(w.fold), *fb = at(w.fold + align_up((size_t)C * D * PP * 2));
+  const bf16* Wv = static_cast<const bf16*>(lv->Wv);
+  float* alpha = reinterpret_cast<float*>(ws + w.alpha);
+  int rc;
+  if ((rc = fast_scores(B, C, d.N, D, heads, lv, nullptr, reinterpret_cast<float*>(ws + w.qp),
+                        reinterpret_cast<float*>(ws + w.mf), at(w.mb), alpha, st, &px, nullptr, nullptr, 3)))
+    return rc;
+  {
+    StageTimer tm(DCHAG_STAGE_FOLD_VALUE, st);
+    if ((rc = transpose_rows(C, D, D, PP, We, at(w.wet), st))) return rc;
+    const TileWork tw = pixel_tiles((d.gq * PP + 127) / 128, D / 128, 1, d.G);
+    if ((rc = raise_pair_lds(k_pixel_fold<PP>))) return rc;
+    k_pixel_fold<PP><<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, at(w.wet), Wv, Wf, at(w.wft), at(w.wg));
+    if ((rc = launch_status())) return rc;
+    if (be || ce) {
+      k_fold_token_bias<<<dim3(D / 32, d.G), 256, 0, st>>>(C, D, d.g, Wv, be, ce, fb);
+      if ((rc = launch_status())) return rc;
+    }
+  }
+  {
+    StageTimer tm(DCHAG_STAGE_BWD_TOKENIZE, st);
+    k_pixel_rows<(PP == 64 ? 8 : 4)><<<dim3((unsigned)(d.NT / 64), (unsigned)((d.G * d.gq * (PP / 8) + 31) / 32), (unsigned)B),
+                                       256, 0, st>>>(d, x, at(w.ut), at(w.ug));
+    if ((rc = launch_status())) return rc;
+  }
+  // what the reverse sweep will use as scratch takes the partial sums of few tiles
+  return attend_pixels_forward(B, C, H, W, p, D, heads, lv, x, be || ce, alpha, ws + w.fold, ws + w.dot, w.m2 - w.dot, at(w.o),
+                               st);
+}
+
+// Reverse half, given dy = d L / d (level output) [B,G,N,D].
+template <int PP>
+int pixel_level_backward(int B, int C, int H, int W, int p, int D, int heads, const dchag_level* lv,
+                         const dchag_level_grads* gr, const bf16* x, const bf16* We, const bf16* be, const bf16* ce,
+                         const bf16* dy, bf16* dx, bf16* dWe, bf16* dtok_bias, unsigned char* ws, const BackwardWs& bw,
+                         hipStream_t st) {
+  const PixelWs& w = bw.px;
+  PixelDims d = pixel_dims(B, C, (H / p) * (W / p), PP, D, heads, lv->group_size);
+  d.H = H; d.W = W;
+  const int N = d.N, G = d.G, dh = D / heads;
+  const bool h32 = dh == 32;
+  const int ppc = h32 ? 1 : dh / 64;                       // pieces of a head's columns in the d alpha buffer
+  auto at = [&](size_t off) { return reinterpret_cast<bf16*>(ws + off); };
+  auto atf = [&](size_t off) { return reinterpret_cast<float*>(ws + off); };
+  bf16 *Wf = at(w.fold), *fb = (be || ce) ? at(w.fold + align_up((size_t)C * D * PP * 2)) : nullptr;
+  const bf16* Wv = static_cast<const bf16*>(lv->Wv);
+  bf16* d_o = at(bw.d_o);
+  float *alpha = atf(w.alpha), *dal = atf(w.dal), *r = atf(bw.r);
+  const bool want_r = gr->dWk || gr->dWq || gr->dbq || gr->dquery;
+  const bool want_te = dWe || dtok_bias;
+  int rc;
+  if ((rc = output_projection_backward<bf16>(B, G, N, D, lv, gr, dy, at(w.o), d_o, st))) return rc;
+  if (gr->dbv && (rc = colsum<bf16>(B, D, RowBlocks{G, G * N, N}, d_o, static_cast<bf16*>(gr->dbv), st))) return rc;
+  if (want_r || want_te || dx) {
+    StageTimer tm(DCHAG_STAGE_BWD_SOFTMAX, st);
+    const TileWork tw = pixel_tiles(D / 128, (N + 127) / 128, B, G);
+    auto kern = h32 ? k_pixel_dalpha<PP, true> : k_pixel_dalpha<PP, false>;
+    if ((rc = raise_pair_lds(kern))) return rc;
+    kern<<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, PP == 64 ? x : at(w.ug), PP == 64 ? Wf : at(w.wg), fb, d_o,
+                                                          dal);
+    if ((rc = launch_status())) return rc;
+    k_pixel_jacobian<<<dim3((unsigned)((d.Np + 63) / 64), (unsigned)((heads + 3) / 4), (unsigned)(B * G)), 256, 0, st>>>(
+        d, ppc, alpha, dal);
+    if ((rc = launch_status())) return rc;
+  }
+  if (dx) {
+    StageTimer tm(DCHAG_STAGE_BWD_TOKENS, st);
+    const TileWork tw = pixel_tiles((std::min(d.g, C) * PP + 127) / 128, (N + 127) / 128, B, G);
+    auto kern = h32 ? k_pixel_dx<PP, true> : k_pixel_dx<PP, false>;
+    if ((rc = raise_pair_lds(kern))) return rc;
+    kern<<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, ppc, at(w.wft), d_o, alpha, dal, at(bw.msb), dx);
+    if ((rc = launch_status())) return rc;
+  }
+  if (gr->dWv || want_te) {
+    StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
+    if ((rc = transpose_rows(B * G, N, d.NT, D, d_o, at(w.dot), st))) return rc;
+  }
+  if (want_r || gr->dWv || want_te) {
+    StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
+    const long row = 64 + (PP == 16 ? d.gq * 16 : 0) + 2 * d.gp;
+    k_pixel_prep<PP><<<dim3((unsigned)(((long)D * row + 255) / 256), (unsigned)G), 256, 0, st>>>(
+        d, atf(w.mf), We, be, ce, at(w.m2), at(w.x), at(w.ones));
+    if ((rc = launch_status())) return rc;
+  }
+  if (gr->dWv || want_te) {
+    StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
+    const TileWork tw = pixel_tiles((d.RE + 127) / 128, D / 128, w.splits, G);
+    auto kern = h32 ? k_pixel_outer<PP, true> : k_pixel_outer<PP, false>;
+    if ((rc = raise_pair_lds(kern))) return rc;
+    kern<<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, w.splits, at(w.ut), at(w.ones), at(w.dot), alpha, at(w.er),
+                                                          at(w.et), atf(w.part));
+    if ((rc = launch_status())) return rc;
+    if (w.splits > 1) {
+      k_pixel_outer_merge<PP><<<dim3((unsigned)(D / 64), (unsigned)((d.RE + 15) / 16), (unsigned)G), 256, 0, st>>>(
+          d, w.splits, atf(w.part), at(w.er), at(w.et));
+      if ((rc = launch_status())) return rc;
+    }
+  }
+  if (want_r || want_te) {
+    StageTimer tm(DCHAG_STAGE_BWD_KEY_QUERY, st);
+    k_pixel_key_sums<PP><<<dim3((unsigned)d.gp, (unsigned)G), 256, 0, st>>>(d, ppc, dal, at(w.ut), at(w.fr), at(w.ft));
+    if ((rc = launch_status())) return rc;
+  }
+  if (want_te) {
+    StageTimer tm(DCHAG_STAGE_BWD_TOKENIZE, st);
+    if ((rc = transpose_rows(G, D, D, D, Wv, at(w.wvt), st))) return rc;
+    const TileWork tw = pixel_tiles((d.RE + 127) / 128, D / 128, 1, G);
+    if ((rc = raise_pair_lds(k_pixel_dwe<PP>))) return rc;
+    k_pixel_dwe<PP><<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, at(w.et), at(w.ft), at(w.wvt), at(w.m2), dWe,
+                                                                     dtok_bias);
+    if ((rc = launch_status())) return rc;
+  }
+  if (gr->dWv || want_r) {
+    StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
+    const TileWork tw = pixel_tiles(D / 128, D / 128 + 1, 1, G);
+    if ((rc = raise_pair_lds(k_pixel_dwv<PP>))) return rc;
+    k_pixel_dwv<PP><<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, at(w.er), at(w.fr), We, at(w.x),
+                                                                     static_cast<bf16*>(gr->dWv), want_r ? r : nullptr);
+    if ((rc = launch_status())) return rc;
+  }
+  return key_query_backward<bf16>(G, D, heads, lv, gr, atf(w.qp), r, atf(bw.dq), st);
+}
+
 // The two halves of a training step.  keep_forward fills the workspace with what the reverse sweep reads
 // (tokens, and per level: inputs, folded keys, softmax weights, per-head token averages, pre-projection outputs)
 // and, if asked, writes the path's output; reverse_sweep walks the levels backwards over that workspace.
@@ -1191,7 +1450,7 @@ int keep_forward(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int h
       first = 1;
     }
   }
-  if (!first && (rc = dchag_tokenize(dt, B, C, H, W, p, D, x, We, be, ce, ws + w.tokens, st))) return rc;
+  if (!first && !w.pixels && (rc = dchag_tokenize(dt, B, C, H, W, p, D, x, We, be, ce, ws + w.tokens, st))) return rc;
   const PixelScores px = pixel_scores_of<T>(x, We, be, ce, H, W, p, ws, w.ms, w.msb, w.cs, w.mft);
   const bool use_px = dt == DCHAG_BF16 && train_fast(dt, D, heads) && pixel_scores_ok(p, heads);
   // every attention level's weight-only prep in ONE launch, straight into the level's kept buffers
@@ -1204,8 +1463,13 @@ int keep_forward(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int h
         const bool linear = levels[l].kind == DCHAG_LEVEL_LINEAR;
         const int G = groups_of(cl, gs[l]);
         if (!linear) {
-          const LevelBufs<bf16> lb = level_bufs<bf16>(ws + w.kept[l], kept_level(dt, B, cl, N, D, heads, gs[l], false,
-                                                                                 l + 1 < n_levels));
+          LevelBufs<bf16> lb = level_bufs<bf16>(ws + w.kept[l], kept_level(dt, B, cl, N, D, heads, gs[l], false,
+                                                                           l + 1 < n_levels));
+          if (l == 0 && w.pixels) {
+            lb.Qp = reinterpret_cast<float*>(ws + w.px.qp);
+            lb.Mf = reinterpret_cast<float*>(ws + w.px.mf);
+            lb.Mb = reinterpret_cast<bf16*>(ws + w.px.mb);
+          }
           jobs[nj++] = KeyPrepJob{&levels[l], G, PrepBufs{lb.Qp, lb.Mf, lb.Mb}, (l == 0 && use_px) ? px.MfT : nullptr};
         }
         cl = G;
@@ -1213,6 +1477,26 @@ int keep_forward(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int h
       set_level(0);
       if (nj && (rc = launch_query_keys(D, heads, jobs, nj, st))) return rc;
       if (nj) phase = 3;
+    }
+  }
+  if constexpr (std::is_same<T, bf16>::value) {
+    if (w.pixels) {
+      set_level(1);
+      const bf16 *xb = static_cast<const bf16*>(x), *Wb = static_cast<const bf16*>(We), *bb = static_cast<const bf16*>(be),
+                 *cb = static_cast<const bf16*>(ce);
+      rc = p == 8 ? pixel_level_forward<64>(B, C, H, W, p, D, heads, &levels[0], xb, Wb, bb, cb, ws, w, px, st)
+                  : pixel_level_forward<16>(B, C, H, W, p, D, heads, &levels[0], xb, Wb, bb, cb, ws, w, px, st);
+      if (rc) return rc;
+      c_in = groups_of(C, gs[0]);
+      bf16* y = n_levels == 1 ? static_cast<bf16*>(out) : reinterpret_cast<bf16*>(ws + w.px.y);
+      if (y) {                                                                // out may be NULL: see below
+        StageTimer tm(DCHAG_STAGE_OPROJ, st);
+        if ((rc = oproj(B, D, RowBlocks{c_in, c_in * N, N}, reinterpret_cast<const bf16*>(ws + w.px.o),
+                        static_cast<const bf16*>(levels[0].Wo), static_cast<const bf16*>(levels[0].bo), y, st)))
+          return rc;
+      }
+      zin = y;
+      first = 1;
     }
   }
   for (int l = first; l < n_levels; ++l) {
@@ -1249,7 +1533,8 @@ int reverse_sweep(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int 
     const bool linear = levels[l].kind == DCHAG_LEVEL_LINEAR, last = l + 1 == n_levels;
     kl[l] = kept_level(dt, B, cins[l], N, D, heads, gs[l], linear, !last);
     cins[l + 1] = groups_of(cins[l], gs[l]);
-    zins[l + 1] = last ? nullptr : reinterpret_cast<const T*>(ws + w.kept[l] + kl[l].y);
+    zins[l + 1] = last ? nullptr
+                       : reinterpret_cast<const T*>(ws + (l == 0 && w.pixels ? w.px.y : w.kept[l] + kl[l].y));
   }
   int rc;
   const T* dy = static_cast<const T*>(dout);
@@ -1260,6 +1545,17 @@ int reverse_sweep(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int 
     unsigned char* lw = ws + w.kept[l];
     T* dz = reinterpret_cast<T*>(ws + w.dz[l & 1]);
     if constexpr (std::is_same<T, bf16>::value) {
+      if (l == 0 && w.pixels) {
+        const bf16 *xb = static_cast<const bf16*>(x), *Wb = static_cast<const bf16*>(We), *bb = static_cast<const bf16*>(be),
+                   *cb = static_cast<const bf16*>(ce);
+        bf16 *gx = static_cast<bf16*>(dx), *gw = static_cast<bf16*>(dWe), *gt = static_cast<bf16*>(dtok_bias);
+        rc = p == 8 ? pixel_level_backward<64>(B, C, H, W, p, D, heads, &levels[0], &grads[0], xb, Wb, bb, cb, dy, gx, gw, gt,
+                                               ws, w, st)
+                    : pixel_level_backward<16>(B, C, H, W, p, D, heads, &levels[0], &grads[0], xb, Wb, bb, cb, dy, gx, gw, gt,
+                                               ws, w, st);
+        set_level(0);
+        return rc;
+      }
       if (l == 0 && no_tokens) {
         rc = linear_first_backward(B, C, H, W, p, D, &levels[0], &grads[0], static_cast<const bf16*>(x),
                                    static_cast<const bf16*>(We), static_cast<const bf16*>(be),

@@ -14,8 +14,8 @@ from .test_gpu_train import ATT, TOL, dev, dev_level, host, rel_err, say
 pytestmark = pytest.mark.gpu
 
 
-def check_training_step(cfg, seed=77):
-    pr = make_problem(cfg)
+def check_training_step(cfg, seed=77, biases=True):
+    pr = make_problem(cfg, biases=biases)
     d = cfg.dtype
     args = (dev(pr.x, d), dev(pr.We, d), dev(pr.be, d), dev(pr.ce, d), [dev_level(lv, d) for lv in pr.levels], cfg.p,
             cfg.heads)
@@ -28,7 +28,7 @@ def check_training_step(cfg, seed=77):
     dx, dWe, dtb = torch.empty_like(args[0]), torch.empty_like(args[1]), torch.empty_like(args[3])
     grads = []
     for lv in args[4]:
-        names = ("Wv", "bv") if lv.kind else ATT
+        names = [n for n in (("Wv", "bv") if lv.kind else ATT) if getattr(lv, n) is not None]
         grads.append(dchag.LevelGrads(**{"d" + n: torch.empty_like(getattr(lv, n)) for n in names}))
     dchag.dchag_backward(*args, dout, grads, dx=dx, dWe=dWe, dtok_bias=dtb, workspace=ws, kept=True)
     torch.cuda.synchronize()
