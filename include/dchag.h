@@ -275,13 +275,15 @@ int dchag_backward(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int
 /*
  * A training step without the recomputation: dchag_forward_keep is dchag_forward_folded that leaves, in a
  * workspace of dchag_backward's size and layout (which = 3), everything the reverse sweep reads (tokens; per
- * level its inputs, folded keys, softmax weights, per-head token averages, pre-projection outputs), and
+ * level its inputs, folded keys, softmax weights, per-head token averages, pre-projection outputs; or what takes their place
+ * at a first level taken from the pixels), and
  * dchag_backward_kept is the reverse sweep alone.  dchag_backward_kept must be given the same arguments and the
  * workspace of the dchag_forward_keep call, untouched in between (the library cannot check that); any number of
  * dchag_backward_kept calls (different dout) may follow one dchag_forward_keep.  The gradients equal those of
- * dchag_backward bit for bit; the output equals dchag_forward_folded's bit for bit wherever that call takes the
- * u_a route at the first level, and up to rounding where it folds the projection into the tokenizer (the kept
- * forward always forms tokens and u_a: the reverse sweep reads them).  For callers that keep activations between the two passes,
+ * dchag_backward bit for bit; the output equals dchag_forward_folded's, bit for bit wherever both take the same route at the
+ * first level (tokens and u_a, or the pixels), and up to rounding otherwise.  A training step takes an attention first level
+ * from the pixels where that is cheaper (large bf16 problems of the shapes dchag_forward_folded takes from the pixels): then
+ * neither its tokens nor their gradients are formed in either pass.  For callers that keep activations between the two passes,
  * as training loops do; the paper describes the two passes of its module (Section 3.3), not how they share state.
  */
 int dchag_forward_keep(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int heads,

@@ -58,7 +58,7 @@ enum Switch {
   SW_TOKENIZE_PER_TILE,
   SW_TOKENS_UNFUSED,
   SW_TOKEN_SCORES,
-  SW_TRAIN_TOKENS,
+  SW_TRAIN_ROUTE,
   SW_VAGG_SPLIT,
   SW_VALUE_UNFOLDED,
   SW_COUNT
@@ -92,7 +92,7 @@ struct SwitchTable {
     "DCHAG_TOKENIZE_PER_TILE",
     "DCHAG_TOKENS_UNFUSED",
     "DCHAG_TOKEN_SCORES",
-    "DCHAG_TRAIN_TOKENS",
+    "DCHAG_TRAIN_ROUTE",
     "DCHAG_VAGG_SPLIT",
     "DCHAG_VALUE_UNFOLDED"};
     for (int i = 0; i < SW_COUNT; ++i) {

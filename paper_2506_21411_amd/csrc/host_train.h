@@ -110,8 +110,8 @@ inline int dz_patches(int B, int G, int N, int D, int g) {
 // Buffers of an attention first level trained from the pixels (k_pixel_train.h): what the forward sweep leaves for the
 // reverse sweep comes first, from `dot` on they are the reverse sweep's own.
 struct PixelWs {
-  size_t qp, mf, mb, alpha, o, y, fold, wft, wg, ug, ut, wet, dot, dal, er, et, part, fr, ft, wvt, m2, x, ones;
-  int splits;
+  size_t qp, mf, mb, alpha, o, y, fold, wft, wg, ug, ut, wet, dot, dal, er, et, part, fr, ft, wvt, m2, x, rk;
+  int splits, key_splits;
 };
 
 inline PixelDims pixel_dims(int B, int C, int N, int pp, int D, int heads, int g) {
@@ -124,12 +124,18 @@ inline PixelDims pixel_dims(int B, int C, int N, int pp, int D, int heads, int g
 }
 
 // Blocks the contraction over the patches of k_pixel_outer is dealt to, so that the weight-sized product still fills the
-// chip: doubled while there are fewer than two workgroups per compute unit's two slots and eight slices are left for each.
-inline int pixel_outer_splits(const PixelDims& d) {
-  const long tiles = (long)d.G * ((d.RE + 127) / 128) * (d.D / 128);
+// chip: doubled while there is less than one per compute unit and eight slices are left for each.
+inline int pixel_outer_splits(const PixelDims& d, int pp) {
+  const long tiles = (long)d.G * ((d.gq * pp + 127) / 128) * (d.D / 256);
   const int slices = d.B * (d.NT / 64);
   int s = 1;
-  while (tiles * s < 2L * compute_units() && slices >= 16 * s) s *= 2;
+  while (tiles * s < compute_units() && slices >= 16 * s) s *= 2;
+  return s;
+}
+// The same for the key-path sums (64 rows): at most 16, at least two slices each.
+inline int pixel_key_splits(const PixelDims& d) {
+  int s = 1;
+  while ((long)d.G * (d.D / 256) * s < compute_units() && d.KE / 64 >= 4 * s && s < 16) s *= 2;
   return s;
 }
 
@@ -147,19 +153,20 @@ inline size_t pixel_ws(const PixelDims& d, int pp, bool keep_y, size_t off, Pixe
   w->wg = take(pp == 16 ? G * D * d.gq * 16 * 2 : 0);
   w->ug = take(pp == 16 ? B * G * d.N * d.gq * 16 * 2 : 0);
   w->ut = take(B * C * pp * d.NT * 2);
-  w->wet = take(C * pp * D * 2);                                 // forward only
+  w->wet = take(pp == 16 ? C * pp * D * 2 : 0);                  // forward only
   w->dot = take(B * G * D * d.NT * 2);
   w->dal = take(B * G * d.gpad * std::max(h, D / 64) * d.Np * 4);
   w->er = take(G * D * d.KE * 2);
   w->et = take(G * d.RE * D * 2);
-  w->splits = pixel_outer_splits(d);
-  w->part = take(w->splits > 1 ? (size_t)w->splits * G * d.RE * D * 4 : 0);
+  w->splits = pixel_outer_splits(d, pp);
+  w->part = take(w->splits > 1 ? (size_t)w->splits * G * d.gq * pp * D * 4 : 0);
   w->fr = take(G * 64 * d.KE * 2);
   w->ft = take(G * d.RE * 64 * 2);
   w->wvt = take(G * D * D * 2);
   w->m2 = take(G * D * 64 * 2);
   w->x = take(G * D * (size_t)((pp == 16 ? d.gq * 16 : 0) + 2 * d.gp) * 2);
-  w->ones = take((size_t)d.NT * 2);
+  w->key_splits = pixel_key_splits(d);
+  w->rk = take((size_t)w->key_splits * G * h * D * 4);
   return off;
 }
 
@@ -1255,13 +1262,21 @@ inline int linear_first_backward(int B, int C, int H, int W, int p, int D, const
 
 // ---- attention first level trained from the pixels (k_pixel_train.h) ----
 
-// Taken by the shapes whose first level dchag_forward_folded takes from the pixels, when it is the cheaper route.  The route through
-// the tokens moves about ten times B N C D elements; this one multiplies 6 C D D pp flops whatever B N is: the line
-// B N = D pp / 512 is where the two meet at 4.5 TB/s and 0.75 PFLOP/s.  DCHAG_TRAIN_TOKENS (debugging aid) keeps the tokens.
+// Taken by the shapes whose first level dchag_forward_folded takes from the pixels, when it is the cheaper route.  The route
+// through the tokens streams tokens and per-head averages, Q = B N C D (1 + heads / g) elements; this one multiplies weight-sized
+// products, C D D pp, whatever B N is, and is a few launches longer.  Fitted to twelve shapes: 2.46 us per million of Q against
+// 8.8 us per 10^9 of C D D pp and 85 us.  Training steps, tokens / pixels: 512 bands x 4 x 256 patches, D 1024: 2.75 / 1.49 ms;
+// 512 x 2 x 256, D 2048: 5.31 / 3.87 ms; 512 x 1 x 256, D 2048: 3.38 / 3.27 ms; 256 x 1 x 256, D 1024: 652 / 679 us; 4 x 4 patches:
+// 64 x 1 x 512, D 512: 367 / 362 us; 40 x 2 x 256, D 512: 330 / 353 us.  DCHAG_TRAIN_ROUTE (debugging aid) = tokens / pixels
+// overrides the rule, never the shape limits.
 inline bool pixel_train_ok(dchag_dtype dt, int B, int C, int N, int p, int D, int heads, const dchag_level* first, int g) {
   const int pp = p * p;
-  if (!values_from_pixels(dt, p, D, heads, first) || dbg(SW_TRAIN_TOKENS)) return false;
-  if ((long)B * N * 512 < (long)D * pp) return false;
+  if (!values_from_pixels(dt, p, D, heads, first)) return false;
+  if (const char* e = dbg(SW_TRAIN_ROUTE)) {
+    if (e[0] == 't') return false;
+  } else if ((double)B * N * C * D * (1. + (double)heads / std::min(g, C)) < (double)C * D * D * pp / 280. + 33.5e6) {
+    return false;
+  }
   const PixelDims d = pixel_dims(B, C, N, pp, D, heads, g);
   const long tiles_n = (N + 127) / 128, tiles_d = D / 128, tiles_r = (d.RE + 127) / 128;
   return (long)B * d.G <= 65535 && C <= 65535 && tiles_n * std::max(tiles_d, tiles_r) * B * d.G <= (1L << 30) &&
@@ -1312,14 +1327,19 @@ int pixel_level_forward(int B, int C, int H, int W, int p, int D, int heads, con
     return rc;
   {
     StageTimer tm(DCHAG_STAGE_FOLD_VALUE, st);
-    if ((rc = transpose_rows(C, D, D, PP, We, at(w.wet), st))) return rc;
-    const TileWork tw = pixel_tiles((d.gq * PP + 127) / 128, D / 128, 1, d.G);
-    if ((rc = raise_pair_lds(k_pixel_fold<PP>))) return rc;
-    k_pixel_fold<PP><<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, at(w.wet), Wv, Wf, at(w.wft), at(w.wg));
-    if ((rc = launch_status())) return rc;
-    if (be || ce) {
-      k_fold_token_bias<<<dim3(D / 32, d.G), 256, 0, st>>>(C, D, d.g, Wv, be, ce, fb);
+    if (PP == 64) {
+      if ((rc = fold_value_weights(C, p, D, lv, We, be, ce, ws + w.fold, st))) return rc;
+      if ((rc = transpose_rows(C, D, D, PP, Wf, at(w.wft), st))) return rc;
+    } else {
+      if ((rc = transpose_rows(C, D, D, PP, We, at(w.wet), st))) return rc;
+      const TileWork tw = pixel_tiles((d.gq * PP + 127) / 128, D / 256, 1, d.G);
+      if ((rc = raise_pair_lds(k_pixel_fold))) return rc;
+      k_pixel_fold<<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, at(w.wet), Wv, Wf, at(w.wft), at(w.wg));
       if ((rc = launch_status())) return rc;
+      if (be || ce) {
+        k_fold_token_bias<<<dim3(D / 32, d.G), 256, 0, st>>>(C, D, d.g, Wv, be, ce, fb);
+        if ((rc = launch_status())) return rc;
+      }
     }
   }
   {
@@ -1358,10 +1378,10 @@ int pixel_level_backward(int B, int C, int H, int W, int p, int D, int heads, co
   if (gr->dbv && (rc = colsum<bf16>(B, D, RowBlocks{G, G * N, N}, d_o, static_cast<bf16*>(gr->dbv), st))) return rc;
   if (want_r || want_te || dx) {
     StageTimer tm(DCHAG_STAGE_BWD_SOFTMAX, st);
-    const TileWork tw = pixel_tiles(D / 128, (N + 127) / 128, B, G);
+    const TileWork tw = pixel_tiles(D / 256, (N + 127) / 128, B, G);
     auto kern = h32 ? k_pixel_dalpha<PP, true> : k_pixel_dalpha<PP, false>;
     if ((rc = raise_pair_lds(kern))) return rc;
-    kern<<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, PP == 64 ? x : at(w.ug), PP == 64 ? Wf : at(w.wg), fb, d_o,
+    kern<<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, PP == 64 ? x : at(w.ug), PP == 64 ? Wf : at(w.wg), fb, d_o,
                                                           dal);
     if ((rc = launch_status())) return rc;
     k_pixel_jacobian<<<dim3((unsigned)((d.Np + 63) / 64), (unsigned)((heads + 3) / 4), (unsigned)(B * G)), 256, 0, st>>>(
@@ -1370,10 +1390,13 @@ int pixel_level_backward(int B, int C, int H, int W, int p, int D, int heads, co
   }
   if (dx) {
     StageTimer tm(DCHAG_STAGE_BWD_TOKENS, st);
-    const TileWork tw = pixel_tiles((std::min(d.g, C) * PP + 127) / 128, (N + 127) / 128, B, G);
-    auto kern = h32 ? k_pixel_dx<PP, true> : k_pixel_dx<PP, false>;
+    const int rows = std::min(d.g, C) * PP;
+    const bool tall = rows > 128;                          // 256 rows x 128 patches, or 128 x 256
+    const TileWork tw = tall ? pixel_tiles((rows + 255) / 256, (N + 127) / 128, B, G) : pixel_tiles(1, (N + 255) / 256, B, G);
+    auto kern = h32 ? (tall ? k_pixel_dx<PP, true, 4> : k_pixel_dx<PP, true, 2>)
+                    : (tall ? k_pixel_dx<PP, false, 4> : k_pixel_dx<PP, false, 2>);
     if ((rc = raise_pair_lds(kern))) return rc;
-    kern<<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, ppc, at(w.wft), d_o, alpha, dal, at(bw.msb), dx);
+    kern<<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, ppc, at(w.wft), d_o, alpha, dal, at(bw.msb), dx);
     if ((rc = launch_status())) return rc;
   }
   if (gr->dWv || want_te) {
@@ -1384,44 +1407,58 @@ int pixel_level_backward(int B, int C, int H, int W, int p, int D, int heads, co
     StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
     const long row = 64 + (PP == 16 ? d.gq * 16 : 0) + 2 * d.gp;
     k_pixel_prep<PP><<<dim3((unsigned)(((long)D * row + 255) / 256), (unsigned)G), 256, 0, st>>>(
-        d, atf(w.mf), We, be, ce, at(w.m2), at(w.x), at(w.ones));
+        d, atf(w.mf), We, be, ce, at(w.m2), at(w.x));
     if ((rc = launch_status())) return rc;
   }
   if (gr->dWv || want_te) {
     StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
-    const TileWork tw = pixel_tiles((d.RE + 127) / 128, D / 128, w.splits, G);
+    const TileWork tw = pixel_tiles((d.gq * PP + 127) / 128, D / 256, w.splits, G);
     auto kern = h32 ? k_pixel_outer<PP, true> : k_pixel_outer<PP, false>;
     if ((rc = raise_pair_lds(kern))) return rc;
-    kern<<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, w.splits, at(w.ut), at(w.ones), at(w.dot), alpha, at(w.er),
-                                                          at(w.et), atf(w.part));
+    kern<<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, w.splits, at(w.ut), at(w.dot), alpha, at(w.er), at(w.et),
+                                                          atf(w.part));
+    if ((rc = launch_status())) return rc;
+    k_pixel_member_sums<PP><<<dim3((unsigned)(D / 32), (unsigned)(d.gp / 32), (unsigned)G), 512, 0, st>>>(
+        d, alpha, at(w.dot), at(w.er), at(w.et));
     if ((rc = launch_status())) return rc;
     if (w.splits > 1) {
-      k_pixel_outer_merge<PP><<<dim3((unsigned)(D / 64), (unsigned)((d.RE + 15) / 16), (unsigned)G), 256, 0, st>>>(
+      k_pixel_outer_merge<PP><<<dim3((unsigned)(D / 64), (unsigned)((d.gq * PP + 15) / 16), (unsigned)G), 256, 0, st>>>(
           d, w.splits, atf(w.part), at(w.er), at(w.et));
       if ((rc = launch_status())) return rc;
     }
   }
   if (want_r || want_te) {
     StageTimer tm(DCHAG_STAGE_BWD_KEY_QUERY, st);
-    k_pixel_key_sums<PP><<<dim3((unsigned)d.gp, (unsigned)G), 256, 0, st>>>(d, ppc, dal, at(w.ut), at(w.fr), at(w.ft));
+    const int lds = 8 * ((PP == 64 ? 2 : 1) * 4096 + 256);
+    if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_pixel_key_sums<PP>), lds)) return DCHAG_ERR_LAUNCH;
+    k_pixel_key_sums<PP><<<dim3((unsigned)d.gp, (unsigned)G), 512, lds, st>>>(d, ppc, dal, at(w.ut), at(w.fr), at(w.ft));
     if ((rc = launch_status())) return rc;
   }
   if (want_te) {
     StageTimer tm(DCHAG_STAGE_BWD_TOKENIZE, st);
     if ((rc = transpose_rows(G, D, D, D, Wv, at(w.wvt), st))) return rc;
-    const TileWork tw = pixel_tiles((d.RE + 127) / 128, D / 128, 1, G);
+    const TileWork tw = pixel_tiles((d.RE + 127) / 128, D / 256, 1, G);
     if ((rc = raise_pair_lds(k_pixel_dwe<PP>))) return rc;
-    k_pixel_dwe<PP><<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, at(w.et), at(w.ft), at(w.wvt), at(w.m2), dWe,
+    k_pixel_dwe<PP><<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, at(w.et), at(w.ft), at(w.wvt), at(w.m2), dWe,
                                                                      dtok_bias);
     if ((rc = launch_status())) return rc;
   }
-  if (gr->dWv || want_r) {
+  if (gr->dWv) {
     StageTimer tm(DCHAG_STAGE_BWD_VALUE, st);
-    const TileWork tw = pixel_tiles(D / 128, D / 128 + 1, 1, G);
-    if ((rc = raise_pair_lds(k_pixel_dwv<PP>))) return rc;
-    k_pixel_dwv<PP><<<dim3(tile_grid(tw)), 256, kPairLdsBytes, st>>>(d, tw, at(w.er), at(w.fr), We, at(w.x),
-                                                                     static_cast<bf16*>(gr->dWv), want_r ? r : nullptr);
+    const TileWork tw = pixel_tiles(D / 256, D / 128, 1, G);
+    if ((rc = raise_pair_lds(k_pixel_dwv<PP, false>))) return rc;
+    k_pixel_dwv<PP, false><<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, 1, at(w.er), at(w.fr), We, at(w.x),
+                                                                           static_cast<bf16*>(gr->dWv), nullptr);
     if ((rc = launch_status())) return rc;
+  }
+  if (want_r) {
+    StageTimer tm(DCHAG_STAGE_BWD_KEY_QUERY, st);
+    const TileWork tw = pixel_tiles(D / 256, 1, w.key_splits, G);
+    if ((rc = raise_pair_lds(k_pixel_dwv<PP, true>))) return rc;
+    k_pixel_dwv<PP, true><<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, w.key_splits, at(w.er), at(w.fr), We,
+                                                                          at(w.x), nullptr, atf(w.rk));
+    if ((rc = launch_status())) return rc;
+    if ((rc = sum_key_path_partials(1, G, w.key_splits, heads, D, atf(w.rk), r, st))) return rc;
   }
   return key_query_backward<bf16>(G, D, heads, lv, gr, atf(w.qp), r, atf(bw.dq), st);
 }

@@ -16,16 +16,20 @@
 // operands: 4 products of the tokenizer's size and 3 of the value fold's, where the route through the tokens streams
 // tokens, averages, their gradients and the token gradients (about ten passes over B C N D elements).
 //
-// All products run on one loop: tiles of 128 x 128 x 64, four wavefronts (2 x 2) of 64 x 64, two 32-KiB stages filled by
-// direct-to-LDS loads one slice ahead, two workgroups per compute unit (the shape whose ring kernel measured within 3 % of
-// the larger ones at a third of the code), so one workgroup's load round trip hides under the other's products.
+// All products run on one loop (pair_loop): tiles of 128 x 256 or 256 x 128 outputs, eight wavefronts of 64 x 64, contraction in
+// slices of 64 through three 48-KiB stages that are filled by direct-to-LDS loads two slices ahead.  The barrier sits behind a
+// slice's third k-step, when all its fragments are in registers: it frees the slice's stage and hands the next slice over, whose
+// first fragments are read under the last products.  (128 x 128 tiles with two stages and two workgroups per compute unit
+// waited for each slice's loads: the value-weight gradient of 512 bands took 262 us, 3.5 us a slice.)
 #pragma once
 #include "k_fused.h"
 #include "k_train.h"
 
 namespace dchag {
 
-constexpr int kPairStageBytes = 256 * 128, kPairLdsBytes = 2 * kPairStageBytes;
+constexpr int kPairTileBytes = 384 * 128;                 // rows of both operands, 128 bytes each
+constexpr int kPairExtraBytes = 4096;                     // k_pixel_outer: softmax weights of a slice
+constexpr int kPairStageBytes = kPairTileBytes + kPairExtraBytes, kPairLdsBytes = 3 * kPairStageBytes;
 
 // Sizes of a pixel-route first level.  Np: alpha / ds pitch (N to 32); NT: pitch of n-contiguous operands (N to 64);
 // gq: members a contraction over (member, pixel) runs over (g, or g to a multiple of 4 for 16 pixels); gp: g to 32;
@@ -34,23 +38,27 @@ struct PixelDims {
   int B, C, N, D, g, G, heads, gpad, Np, NT, gq, gp, RE, KE, H, W;
 };
 
+template <int WM>   // wavefronts along the tile's rows: 2 (128 x 256) or 4 (256 x 128)
 struct PairLane {
+  static constexpr int WN = 8 / WM, ROWS = 64 * WM, COLS = 64 * WN;
+  static constexpr int AL = ROWS / 64, BL = COLS / 64;      // loads per wavefront and slice
   int lane, wave, wm, wn, l32, lhi, a_base, b_base;
   int ck[4];
   __device__ __forceinline__ void init() {
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    wm = wave >> 1;
-    wn = wave & 1;
+    wm = wave / WN;
+    wn = wave % WN;
     l32 = lane & 31;
     lhi = lane >> 5;
     a_base = (wm * 64 + l32) * 128;
-    b_base = 128 * 128 + (wn * 64 + l32) * 128;
+    b_base = ROWS * 128 + (wn * 64 + l32) * 128;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) ck[kk] = ((kk * 2 + lhi) ^ swz_chunk(l32)) * 16;
   }
-  // load i of this wavefront fills tile row 32 wave + 8 i + lane / 8 with its chunk chunk(row)
-  __device__ __forceinline__ int row(int i) const { return wave * 32 + i * 8 + (lane >> 3); }
+  // load i of this wavefront fills row (A: 8 AL wave + 8 i + lane / 8; B likewise) with its chunk chunk(row)
+  __device__ __forceinline__ int row_a(int i) const { return wave * (8 * AL) + i * 8 + (lane >> 3); }
+  __device__ __forceinline__ int row_b(int i) const { return wave * (8 * BL) + i * 8 + (lane >> 3); }
   __device__ __forceinline__ int chunk(int row) const { return (lane & 7) ^ swz_chunk(row); }
   __device__ __forceinline__ void read(const unsigned char* st, int kk, bf16x8 (&a)[2], bf16x8 (&b)[2]) const {
 #pragma unroll
@@ -59,26 +67,56 @@ struct PairLane {
       b[i] = *reinterpret_cast<const bf16x8*>(st + b_base + i * 4096 + ck[kk]);
     }
   }
-  __device__ __forceinline__ void fill(const bf16* const (&a)[4], const bf16* const (&b)[4], unsigned char* st) const {
+  __device__ __forceinline__ void fill(const bf16* const (&a)[AL], const bf16* const (&b)[BL], unsigned char* st) const {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load16_to_lds(a[i], st + wave * 4096 + i * 1024);
+    for (int i = 0; i < AL; ++i) load16_to_lds(a[i], st + (wave * AL + i) * 1024);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load16_to_lds(b[i], st + 128 * 128 + wave * 4096 + i * 1024);
+    for (int i = 0; i < BL; ++i) load16_to_lds(b[i], st + ROWS * 128 + (wave * BL + i) * 1024);
   }
 };
 
-// issue(s, stage) starts the loads of slice s, compute(s, stage) multiplies it.
-template <class Issue, class Compute>
-__device__ __forceinline__ void pair_loop(unsigned char* smem, int begin, int end, Issue issue, Compute compute) {
+// issue(s, stage) starts the loads of slice s, step(s, kk, a, b, stage) takes the fragments of its k-step kk (stage: where the
+// slice lies; not to be read by step 3, which runs after the stage has been handed back), post(s) runs behind them.
+template <int WM, class Issue, class Step, class Post>
+__device__ __forceinline__ void pair_loop(unsigned char* smem, int begin, int end, const PairLane<WM>& L, Issue issue,
+                                          Step step, Post post) {
+  constexpr int LD = PairLane<WM>::AL + PairLane<WM>::BL;  // a wavefront with further loads waits for a few more
   if (begin >= end) return;
   issue(begin, smem);
+  if (begin + 1 < end) {
+    issue(begin + 1, smem + kPairStageBytes);
+    wait_vmcnt<LD>();
+  } else {
+    wait_vmcnt<0>();
+  }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  if (begin + 2 < end) issue(begin + 2, smem + 2 * kPairStageBytes);
+  bf16x8 a0[2], b0[2], a1[2], b1[2];
+  L.read(smem, 0, a0, b0);
+  int sc = 0;
   for (int s = begin; s < end; ++s) {
-    wait_vmcnt<0>();                                       // slice s has landed (this wavefront's share) ...
+    const unsigned char* st = smem + sc * kPairStageBytes;
+    L.read(st, 1, a1, b1);
+    step(s, 0, a0, b0, st);
+    L.read(st, 2, a0, b0);
+    step(s, 1, a1, b1, st);
+    L.read(st, 3, a1, b1);
+    step(s, 2, a0, b0, st);
+    // slice s + 1 has landed (this wavefront's share; the loads of slice s + 2 may stay in flight) and this slice's reads are
+    // in registers
+    if (s + 2 < end) wait_vmcnt<LD>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_waitcnt((7 << 4) | (63 & 15) | ((63 >> 4) << 14));       // lgkmcnt(0), vmcnt untouched
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();                          // ... and for everyone; slice s - 1's stage is free
+    __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (s + 1 < end) issue(s + 1, smem + ((s + 1 - begin) & 1) * kPairStageBytes);
-    compute(s, smem + ((s - begin) & 1) * kPairStageBytes);
+    if (s + 3 < end) issue(s + 3, smem + sc * kPairStageBytes);                 // the stage just released
+    sc = sc == 2 ? 0 : sc + 1;
+    L.read(smem + sc * kPairStageBytes, 0, a0, b0);        // past the last slice: a stale stage, read and not used
+    step(s, 3, a1, b1, st);
+    post(s);
   }
 }
 
@@ -90,17 +128,11 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[2][2]) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 }
-__device__ __forceinline__ void pair_products(f32x16 (&acc)[2][2], const unsigned char* st, const PairLane& L) {
-  bf16x8 a[4][2], b[4][2];
+__device__ __forceinline__ void pair_products(f32x16 (&acc)[2][2], const bf16x8 (&a)[2], const bf16x8 (&b)[2]) {
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) L.read(st, kk, a[kk], b[kk]);
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][i], b[kk][j], acc[i][j], 0, 0, 0);
+    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -184,18 +216,15 @@ __global__ __launch_bounds__(256) void k_pixel_rows(PixelDims d, const bf16* __r
 //   M2[k][j][64]: the folded keys of column j, heads 0 .. 31 (zeros past `heads`), twice (they meet F's hi and lo parts)
 //   X[k][j][XE]:  for 4 x 4 patches the tokenizer rows We[c][j][:] of the group's members (pitch 16, zeros for missing ones),
 //                 then be[c][j] of the members (gp entries, zeros past the group) and ce[c][j] likewise; XE = (16 gq) + 2 gp
-//   ones[n]:      1 for n < N, 0 up to NT
 // grid (ceil(D (64 + XE) / 256), G), block 256.
 // ---------------------------------------------------------------------------------------
 template <int PP>
 __global__ __launch_bounds__(256) void k_pixel_prep(PixelDims d, const float* __restrict__ Mf, const bf16* __restrict__ We,
                                                     const bf16* __restrict__ be, const bf16* __restrict__ ce,
-                                                    bf16* __restrict__ M2, bf16* __restrict__ X, bf16* __restrict__ ones) {
+                                                    bf16* __restrict__ M2, bf16* __restrict__ X) {
   const int XW = PP == 16 ? d.gq * 16 : 0, XE = XW + 2 * d.gp, row = 64 + XE;
   const int k = blockIdx.y, gk = min(d.g, d.C - k * d.g);
   const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (k == 0)
-    for (long i = idx; i < d.NT; i += (long)gridDim.x * 256) ones[i] = (bf16)(i < d.N ? 1.f : 0.f);
   if (idx >= (long)d.D * row) return;
   const int j = (int)(idx / row), t = (int)(idx % row);
   if (t < 64) {
@@ -216,40 +245,48 @@ __global__ __launch_bounds__(256) void k_pixel_prep(PixelDims d, const float* __
 }
 
 // ---------------------------------------------------------------------------------------
-// Value fold in both layouts: Wf[c][o][kk] and WfT[c][kk][o] = sum_j WeT[c][kk][j] Wv[k][o][j] (WeT: the tokenizer weights
-// transposed); for 4 x 4 patches also member-major rows Wg[k][o][(member, pixel)] (pitch 16 gq, zeros for missing members).
-// Tile rows: (member, pixel), tile columns: o.
+// Value fold of 4 x 4 patches in three layouts: Wf[c][o][kk], WfT[c][kk][o] = sum_j WeT[c][kk][j] Wv[k][o][j] (WeT: the
+// tokenizer weights transposed) and member-major rows Wg[k][o][(member, pixel)] (pitch 16 gq, zeros for missing members).
+// Tile rows: (member, pixel), tile columns: o.  (8 x 8 patches: k_fold_value_dl and a transposing copy, 0.105 against
+// 0.134 ms for 512 bands.)
 // ---------------------------------------------------------------------------------------
-template <int PP>
-__global__ __launch_bounds__(256, 2) void k_pixel_fold(PixelDims d, TileWork tw, const bf16* __restrict__ WeT,
+__global__ __launch_bounds__(512) void k_pixel_fold(PixelDims d, TileWork tw, const bf16* __restrict__ WeT,
                                                        const bf16* __restrict__ Wv, bf16* __restrict__ Wf,
                                                        bf16* __restrict__ WfT, bf16* __restrict__ Wg) {
+  constexpr int PP = 16;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int k, b, mt, nt;
   if (!tw.decode(blockIdx.x, k, b, nt, mt)) return;        // row tiles fastest: they share the rows of Wv
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D;
-  PairLane L;
+  PairLane<2> L;
   L.init();
-  const bf16 *pa[4], *pb[4];
+  const bf16 *pa[2], *pb[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = L.row_a(i);
+    pa[i] = WeT + ((size_t)c0 * PP + min(mt * 128 + row, gk * PP - 1)) * D + L.chunk(row) * 8;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = L.row(i), ch = L.chunk(row) * 8;
-    pa[i] = WeT + ((size_t)c0 * PP + min(mt * 128 + row, gk * PP - 1)) * D + ch;
-    pb[i] = Wv + ((size_t)k * D + nt * 128 + row) * D + ch;
+    const int row = L.row_b(i);
+    pb[i] = Wv + ((size_t)k * D + nt * 256 + row) * D + L.chunk(row) * 8;
   }
   f32x16 acc[2][2];
   zero_acc(acc);
-  pair_loop(
-      smem, 0, D / 64,
+  pair_loop<2>(
+      smem, 0, D / 64, L,
       [&](int, unsigned char* st) {
         L.fill(pa, pb, st);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { pa[i] += 64; pb[i] += 64; }
+        for (int i = 0; i < 2; ++i) pa[i] += 64;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pb[i] += 64;
       },
-      [&](int, const unsigned char* st) { pair_products(acc, st, L); });
+      [&](int, int, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char*) { pair_products(acc, a, bb); },
+      [](int) {});
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int o = nt * 128 + L.wn * 64 + j * 32 + L.l32;
+    const int o = nt * 256 + L.wn * 64 + j * 32 + L.l32;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -263,7 +300,7 @@ __global__ __launch_bounds__(256, 2) void k_pixel_fold(PixelDims d, TileWork tw,
 #pragma unroll
           for (int e = 0; e < 4; ++e) WfT[((size_t)c0 * PP + r0 + e) * D + o] = v[e];
         }
-        if (PP == 16 && cl < d.gq)
+        if (cl < d.gq)
           *reinterpret_cast<bf16x4*>(Wg + ((size_t)k * D + o) * (d.gq * 16) + r0) = cl < gk ? v : bf16x4{};
       }
   }
@@ -275,7 +312,7 @@ __global__ __launch_bounds__(256, 2) void k_pixel_fold(PixelDims d, TileWork tw,
 // columns of the head.  dal[b][k][member][piece][n], pieces of min(dh, 64) columns (k_pixel_jacobian adds a head's pieces).
 // ---------------------------------------------------------------------------------------
 template <int PP, bool H32>   // H32: heads of 32 columns (two pieces per wavefront)
-__global__ __launch_bounds__(256, 2) void k_pixel_dalpha(PixelDims d, TileWork tw, const bf16* __restrict__ x,
+__global__ __launch_bounds__(512) void k_pixel_dalpha(PixelDims d, TileWork tw, const bf16* __restrict__ x,
                                                          const bf16* __restrict__ Wf, const bf16* __restrict__ fb,
                                                          const bf16* __restrict__ d_o, float* __restrict__ dal) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -283,32 +320,25 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dalpha(PixelDims d, TileWork t
   if (!tw.decode(blockIdx.x, k, b, nt, mt)) return;        // nt: patches, mt: columns (fastest: they share the patches)
   constexpr int MS = PP == 64 ? 1 : 4;                     // members of a slice
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, N = d.N;
-  PairLane L;
+  PairLane<4> L;
   L.init();
-  const bf16 *pa[4], *pb[4];
-  size_t sa, sb;                                           // advance per slice
-  if (PP == 64) {
-    const int pw = d.W / 8;
-    sa = (size_t)D * 64;
-    sb = (size_t)d.H * d.W;
+  const bf16 *pa[4], *pb[2];
+  const size_t sa = PP == 64 ? (size_t)D * 64 : 64, sb = PP == 64 ? (size_t)d.H * d.W : 64;   // advance per slice
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = L.row(i), ch = L.chunk(row), n = min(nt * 128 + row, N - 1);
-      pa[i] = Wf + ((size_t)c0 * D + mt * 128 + row) * 64 + ch * 8;
-      pb[i] = x + ((size_t)b * d.C + c0) * sb + (size_t)((n / pw) * 8 + ch) * d.W + (n % pw) * 8;   // chunk = pixel row
-    }
-  } else {
-    sa = sb = 64;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = L.row(i), ch = L.chunk(row), n = min(nt * 128 + row, N - 1);
-      pa[i] = Wf + ((size_t)k * D + mt * 128 + row) * (d.gq * 16) + ch * 8;
-      pb[i] = x + (((size_t)b * d.G + k) * N + n) * (d.gq * 16) + ch * 8;
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int row = L.row_a(i), ch = L.chunk(row) * 8;
+    pa[i] = PP == 64 ? Wf + ((size_t)c0 * D + mt * 256 + row) * 64 + ch
+                     : Wf + ((size_t)k * D + mt * 256 + row) * (d.gq * 16) + ch;
   }
-  const int slices = (gk + MS - 1) / MS;
-  // 16 pixels: a slice of 64 runs past the row's end when 16 gq is no multiple of 64 -- it is: gq is a multiple of 4
-  const int dcol = mt * 128 + L.wm * 64 + 4 * L.lhi;       // first of this lane's columns of d_o
+  const int pw = d.W / 8;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = L.row_b(i), ch = L.chunk(row), n = min(nt * 128 + row, N - 1);
+    pb[i] = PP == 64 ? x + ((size_t)b * d.C + c0) * sb + (size_t)((n / pw) * 8 + ch) * d.W + (n % pw) * 8   // chunk: pixel row
+                     : x + (((size_t)b * d.G + k) * N + n) * (d.gq * 16) + ch * 8;
+  }
+  const int slices = (gk + MS - 1) / MS;                   // 16 pixels: rows of 16 gq pixels, gq a multiple of 4
+  const int dcol = mt * 256 + L.wm * 64 + 4 * L.lhi;       // first of this lane's columns of d_o
   float dv[2][2][16];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -323,17 +353,8 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dalpha(PixelDims d, TileWork t
         for (int e = 0; e < 4; ++e) dv[i][j][4 * q + e] = (float)v[e];
       }
   }
-  bf16x4 fbn[2][4];                                        // folded token bias of the next member, this lane's rows
-  auto fetch_fb = [&](int m) {
-    const bf16* p = fb + (size_t)(c0 + min(m, gk - 1)) * D + dcol;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) fbn[i][q] = fb ? *reinterpret_cast<const bf16x4*>(p + i * 32 + 8 * q) : bf16x4{};
-  };
-  fetch_fb(0);
   const int PC = H32 ? D / 32 : D / 64;                    // pieces of all heads
-  const int piece0 = H32 ? (mt * 128 + L.wm * 64) / 32 : (mt * 128 + L.wm * 64) / 64;
+  const int piece0 = H32 ? (mt * 256 + L.wm * 64) / 32 : (mt * 256 + L.wm * 64) / 64;
   const int n_out = nt * 128 + L.wn * 64 + L.lhi * 32 + L.l32;
   float* out = dal + ((((size_t)b * d.G + k) * d.gpad) * PC + piece0) * d.Np + n_out;
   auto finish = [&](int m, const f32x16 (&acc)[2][2]) {
@@ -358,45 +379,52 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dalpha(PixelDims d, TileWork t
       if (n_out < d.Np) out[((size_t)m * PC + i) * d.Np] = v;
     }
   };
-  pair_loop(
-      smem, 0, slices,
-      [&](int, unsigned char* st) {
+  // The folded token bias of a slice's members (256 columns each) travels with the slice: for a vector load of its own the
+  // compiler waits until NO load is in flight, the next slices' included (512 bands: 159 us like that, 107 us like this).
+  f32x16 init[2], acc[2][2];
+  bf16x4 fbl[2][4];                                        // bias of the member about to be multiplied
+  const bool bias_wave = fb && L.wave < (MS + 1) / 2;      // two members' columns per load
+  const int bm = L.wave * 2 + (L.lane >> 5);
+  auto read_fb = [&](const unsigned char* st, int t) {
+    const bf16* p = reinterpret_cast<const bf16*>(st + kPairTileBytes + t * 512) + L.wm * 64 + 4 * L.lhi;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) fbl[i][q] = fb ? *reinterpret_cast<const bf16x4*>(p + i * 32 + 8 * q) : bf16x4{};
+  };
+  pair_loop<4>(
+      smem, 0, slices, L,
+      [&](int s, unsigned char* st) {
         L.fill(pa, pb, st);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { pa[i] += sa; pb[i] += sb; }
+        for (int i = 0; i < 4; ++i) pa[i] += sa;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) pb[i] += sb;
+        if (bias_wave)
+          load16_to_lds(fb + (size_t)(c0 + min(s * MS + bm, gk - 1)) * D + mt * 256 + (L.lane & 31) * 8,
+                        st + kPairTileBytes + L.wave * 1024);
       },
-      [&](int s, const unsigned char* st) {
-        bf16x8 a[4][2], bb[4][2];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) L.read(st, kk, a[kk], bb[kk]);
-#pragma unroll
-        for (int t = 0; t < MS; ++t) {
-          const int m = s * MS + t;
-          if (MS > 1 && m >= gk) break;                    // uniform
-          f32x16 init[2];
+      [&](int s, int kk, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char* st) {
+        if (PP == 16 && s * MS + kk >= gk) return;         // uniform
+        if (PP == 16 || kk == 0) {
+          if (kk == 0) read_fb(st, 0);
 #pragma unroll
           for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) init[i][4 * q + e] = (float)fbn[i][q][e];
-          fetch_fb(m + 1);
-          f32x16 acc[2][2];
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              if (PP == 64) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], bb[0][j], init[i], 0, 0, 0);
-#pragma unroll
-                for (int kk = 1; kk < 4; ++kk)
-                  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][i], bb[kk][j], acc[i][j], 0, 0, 0);
-              } else {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][i], bb[t][j], init[i], 0, 0, 0);
-              }
-            }
-          finish(m, acc);
+              for (int e = 0; e < 4; ++e) init[i][4 * q + e] = (float)fbl[i][q][e];
+          if (PP == 16 && kk < 3) read_fb(st, kk + 1);     // step 3 must not read the stage
         }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bb[j], PP == 16 || kk == 0 ? init[i] : acc[i][j], 0, 0, 0);
+        if (PP == 16) finish(s * MS + kk, acc);
+      },
+      [&](int s) {
+        if (PP == 64) finish(s, acc);
       });
 }
 
@@ -443,8 +471,8 @@ __global__ __launch_bounds__(256) void k_pixel_jacobian(PixelDims d, int ppc, co
 // key path sum_a ds[c,a] Ms[c][a] starts the sum off (ds as hi + lo bf16 parts).  A lane ends up with four adjacent
 // pixels of a patch row and stores them straight into the image.
 // ---------------------------------------------------------------------------------------
-template <int PP, bool H32>
-__global__ __launch_bounds__(256, 2) void k_pixel_dx(PixelDims d, TileWork tw, int ppc, const bf16* __restrict__ WfT,
+template <int PP, bool H32, int WM>   // WM = 4: 256 rows x 128 patches; 2: 128 rows (groups of few pixels) x 256 patches
+__global__ __launch_bounds__(512) void k_pixel_dx(PixelDims d, TileWork tw, int ppc, const bf16* __restrict__ WfT,
                                                      const bf16* __restrict__ d_o, const float* __restrict__ alpha,
                                                      const float* __restrict__ ds, const bf16* __restrict__ Msb,
                                                      bf16* __restrict__ dx) {
@@ -454,20 +482,25 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dx(PixelDims d, TileWork tw, i
   constexpr int P = PP == 64 ? 8 : 4, MB = PP == 64 ? 1 : 4;   // members of a wavefront's 64 rows
   constexpr int HH = H32 ? 2 : 1;
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, N = d.N, dh = D / d.heads;
-  if (mt * 128 >= gk * PP) return;                         // uniform: a short last group has fewer rows
-  PairLane L;
+  typedef PairLane<WM> Lane;
+  if (mt * Lane::ROWS >= gk * PP) return;                  // uniform: a short last group has fewer rows
+  Lane L;
   L.init();
-  const bf16 *pa[4], *pb[4];
+  const bf16 *pa[Lane::AL], *pb[Lane::BL];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = L.row(i), ch = L.chunk(row) * 8;
-    pa[i] = WfT + ((size_t)c0 * PP + min(mt * 128 + row, gk * PP - 1)) * D + ch;
-    pb[i] = d_o + (((size_t)b * d.G + k) * N + min(nt * 128 + row, N - 1)) * D + ch;
+  for (int i = 0; i < Lane::AL; ++i) {
+    const int row = L.row_a(i);
+    pa[i] = WfT + ((size_t)c0 * PP + min(mt * Lane::ROWS + row, gk * PP - 1)) * D + L.chunk(row) * 8;
   }
-  const int cl0 = (mt * 128 + L.wm * 64) / PP;             // this wavefront's first member
+#pragma unroll
+  for (int i = 0; i < Lane::BL; ++i) {
+    const int row = L.row_b(i);
+    pb[i] = d_o + (((size_t)b * d.G + k) * N + min(nt * Lane::COLS + row, N - 1)) * D + L.chunk(row) * 8;
+  }
+  const int cl0 = (mt * Lane::ROWS + L.wm * 64) / PP;      // this wavefront's first member
   int nn[2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) nn[j] = min(nt * 128 + L.wn * 64 + j * 32 + L.l32, d.Np - 1);
+  for (int j = 0; j < 2; ++j) nn[j] = min(nt * Lane::COLS + L.wn * 64 + j * 32 + L.l32, d.Np - 1);
   f32x16 o[2][2];
   zero_acc(o);
   // key path
@@ -508,71 +541,78 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dx(PixelDims d, TileWork tw, i
       }
     }
   }
-  // softmax weights of the next slice's head(s)
-  float aln[HH][MB][2];
-  auto fetch_alpha = [&](int s) {
+  // Softmax weights of a slice's head(s).  64 pixels: segments [head][member of the tile][patch of the tile] in the stage (see
+  // k_pixel_dalpha); 16 pixels: a tile holds 8 or 16 members, too many for the stage, and few slices: vector loads.
+  float al[HH][MB][2];
+  constexpr int TMB = Lane::ROWS / 64, LPS = Lane::COLS / 4;   // 64-pixel members of a tile, lanes of one segment
+  constexpr int SEGS = HH * TMB, WSEG = 64 / LPS;              // segments of a slice, per load
+  const int sg = L.wave * WSEG + L.lane / LPS;
+  const bool alpha_wave = PP == 64 && L.wave < SEGS / WSEG;
+  const float* asrc = alpha + (((size_t)b * d.G + k) * d.gpad + min(mt * TMB + sg % TMB, d.gpad - 1)) * d.heads * d.Np +
+                      min(nt * Lane::COLS + (L.lane % LPS) * 4, d.Np - 4);
+  auto from_memory = [&](int s) {
 #pragma unroll
     for (int hh = 0; hh < HH; ++hh)
 #pragma unroll
       for (int m = 0; m < MB; ++m) {
-        const int head = min((s * 64 + hh * 32) / dh, d.heads - 1), cl = min(cl0 + m, d.gpad - 1);
+        const int head = (s * 64 + hh * 32) / dh, cl = min(cl0 + m, d.gpad - 1);
         const float* p = alpha + ((((size_t)b * d.G + k) * d.gpad + cl) * d.heads + head) * d.Np;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) aln[hh][m][j] = p[nn[j]];
+        for (int j = 0; j < 2; ++j) al[hh][m][j] = p[nn[j]];
       }
   };
-  fetch_alpha(0);
-  pair_loop(
-      smem, 0, D / 64,
-      [&](int, unsigned char* st) {
+  f32x16 acc[2][2];
+  auto scale_in = [&](int hh) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[i][j][r] += al[hh][PP == 64 ? 0 : 2 * i + (r >> 3)][j] * acc[i][j][r];
+  };
+  pair_loop<WM>(
+      smem, 0, D / 64, L,
+      [&](int s, unsigned char* st) {
         L.fill(pa, pb, st);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { pa[i] += 64; pb[i] += 64; }
+        for (int i = 0; i < Lane::AL; ++i) pa[i] += 64;
+#pragma unroll
+        for (int i = 0; i < Lane::BL; ++i) pb[i] += 64;
+        if (alpha_wave)
+          load16_to_lds(asrc + (size_t)((s * 64 + sg / TMB * 32) / dh) * d.Np, st + kPairTileBytes + L.wave * 1024);
       },
-      [&](int s, const unsigned char* st) {
-        float al[HH][MB][2];
+      [&](int s, int kk, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char* st) {
+        if (kk == 0) {
+          if (PP == 64) {
+            const float* p = reinterpret_cast<const float*>(st + kPairTileBytes) + L.wm * Lane::COLS + L.wn * 64 + L.l32;
 #pragma unroll
-        for (int hh = 0; hh < HH; ++hh)
+            for (int hh = 0; hh < HH; ++hh)
 #pragma unroll
-          for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) al[hh][m][j] = aln[hh][m][j];
-        fetch_alpha(s + 1);
-        bf16x8 a[4][2], bb[4][2];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) L.read(st, kk, a[kk], bb[kk]);
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int hh = 0; hh < HH; ++hh) {
-          f32x16 acc[2][2];
-          constexpr int KS = 4 / HH;
-#pragma unroll
-          for (int kk = 0; kk < KS; ++kk)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-              for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[hh * KS + kk][i], bb[hh * KS + kk][j],
-                                                                   kk == 0 ? zero : acc[i][j], 0, 0, 0);
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) o[i][j][r] += al[hh][PP == 64 ? 0 : 2 * i + (r >> 3)][j] * acc[i][j][r];
+              for (int j = 0; j < 2; ++j) al[hh][0][j] = p[hh * TMB * Lane::COLS + j * 32];
+          } else {
+            from_memory(s);
+          }
         }
-      });
+        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (H32 && kk == 2) scale_in(0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bb[j], kk % (4 / HH) == 0 ? zero : acc[i][j], 0, 0, 0);
+      },
+      [&](int) { scale_in(HH - 1); });
   const int pw = d.W / P;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int n = nt * 128 + L.wn * 64 + j * 32 + L.l32;
+    const int n = nt * Lane::COLS + L.wn * 64 + j * 32 + L.l32;
     if (n >= N) continue;
     const int pi = n / pw, pj = n % pw;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int r0 = mt * 128 + L.wm * 64 + i * 32 + 8 * q + 4 * L.lhi, cl = r0 / PP, kk = r0 % PP;
+        const int r0 = mt * Lane::ROWS + L.wm * 64 + i * 32 + 8 * q + 4 * L.lhi, cl = r0 / PP, kk = r0 % PP;
         if (cl >= gk) continue;
         bf16x4 v;
 #pragma unroll
@@ -583,128 +623,138 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dx(PixelDims d, TileWork tw, i
 }
 
 // ---------------------------------------------------------------------------------------
-// E and e: tile rows (member, pixel) then one row per member (its "pixel" is 1), tile columns the columns d of d_o, the
-// contraction runs over all patches (n contiguous: UT, dOT) in slices of 64.  The softmax weight depends on the contraction
-// index, so it is multiplied into the pixel fragments (fp32, rounded once to bf16 as the token gradients it replaces were).
-// Leaves E with (member, pixel) contiguous, Er[k][d][KE] (the member columns twice), and with d contiguous, ET[k][row][d];
-// with splits > 1 (few tiles) fp32 partial sums part[split][k][row][d] for k_pixel_outer_merge.
+// E: tile rows (member, pixel), tile columns the columns d of d_o, the contraction runs over all patches (n contiguous: UT,
+// dOT) in slices of 64.  The softmax weight depends on the contraction index, so it is multiplied into the pixel fragments
+// (fp32, rounded once to bf16 as the token gradients it replaces were); the weights of a slice -- (member of the tile,
+// wavefront column) segments of 64 patches -- travel with the slice through LDS (as vector loads, the same 16 bytes for every
+// lane of a half-wavefront, they saturated the L1 return path: 430 us for 512 bands).
+// Leaves E with (member, pixel) contiguous, Er[k][d][KE], and with d contiguous, ET[k][row][d]; with splits > 1 (few tiles)
+// fp32 partial sums part[split][k][row][d] for k_pixel_outer_merge.
 // ---------------------------------------------------------------------------------------
 template <int PP>
 __device__ __forceinline__ void store_outer(const PixelDims& d, int k, int r0, int col, const bf16x4& v,
                                             bf16* __restrict__ Er, bf16* __restrict__ ET) {
-  const int rows = d.gq * PP;
-  if (r0 >= d.RE) return;
-  bf16* er = Er + ((size_t)k * d.D + col) * d.KE + r0;
-  *reinterpret_cast<bf16x4*>(er) = v;
-  if (r0 >= rows) *reinterpret_cast<bf16x4*>(er + d.gp) = v;
+  if (r0 >= d.gq * PP) return;
+  *reinterpret_cast<bf16x4*>(Er + ((size_t)k * d.D + col) * d.KE + r0) = v;
 #pragma unroll
   for (int e = 0; e < 4; ++e) ET[((size_t)k * d.RE + r0 + e) * d.D + col] = v[e];
 }
 
 template <int PP, bool H32>
-__global__ __launch_bounds__(256, 2) void k_pixel_outer(PixelDims d, TileWork tw, int splits, const bf16* __restrict__ UT,
-                                                        const bf16* __restrict__ ones, const bf16* __restrict__ dOT,
-                                                        const float* __restrict__ alpha, bf16* __restrict__ Er,
-                                                        bf16* __restrict__ ET, float* __restrict__ part) {
+__global__ __launch_bounds__(512) void k_pixel_outer(PixelDims d, TileWork tw, int splits, const bf16* __restrict__ UT,
+                                                        const bf16* __restrict__ dOT, const float* __restrict__ alpha,
+                                                        bf16* __restrict__ Er, bf16* __restrict__ ET,
+                                                        float* __restrict__ part) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int k, sp, mt, nt;
   if (!tw.decode(blockIdx.x, k, sp, nt, mt)) return;       // sp: split; mt: rows (fastest: they share the rows of dOT)
-  constexpr int HH = H32 ? 2 : 1;
+  constexpr int HH = H32 ? 2 : 1;                          // heads of a wavefront's 64 columns
+  // 64 pixels: the weights of a slice in its stage, segments [member (2)][32- or 64-column piece of the tile][64 patches];
+  // 16 pixels: a tile holds eight members, too many for the stage and few slices in all, so vector loads one slice ahead
+  constexpr int NHT = 4 * HH, NSEG = 2 * NHT;
+  static_assert(NSEG * 256 <= kPairExtraBytes, "the softmax weights of a slice do not fit the stage");
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, dh = D / d.heads, rows = d.gq * PP;
-  PairLane L;
+  typedef PairLane<2> Lane;
+  Lane L;
   L.init();
-  const bf16 *pa[4], *pb[4];
-  bool is_one[4];
+  const bf16 *pa[2], *pb[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = L.row_a(i);
+    pa[i] = UT + ((size_t)c0 * PP + min(mt * 128 + row, gk * PP - 1)) * d.NT + L.chunk(row) * 8;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = L.row(i), ch = L.chunk(row) * 8, r = mt * 128 + row;
-    is_one[i] = r >= rows;
-    pa[i] = is_one[i] ? ones + ch : UT + ((size_t)c0 * PP + min(r, gk * PP - 1)) * d.NT + ch;
-    pb[i] = dOT + ((size_t)k * D + nt * 128 + row) * d.NT + ch;
+    const int row = L.row_b(i);
+    pb[i] = dOT + ((size_t)k * D + nt * 256 + row) * d.NT + L.chunk(row) * 8;
   }
   const int nsl = d.NT / 64, total = d.B * nsl;
   const int s_begin = (int)((long)sp * total / splits), s_end = (int)((long)(sp + 1) * total / splits);
-  // softmax weights: this lane's row of block i belongs to member cl[i]
-  int acl[2];
-  bool alive[2];
+  // wavefront w < NSEG / 4 loads segments 4 w .. 4 w + 3
+  const int seg = L.wave * 4 + (L.lane >> 4), sm = seg / NHT, sh = seg % NHT;
+  const int scl = min(mt * 2 + sm, d.gpad - 1), shead = min((nt * 256 + sh * (256 / NHT)) / dh, d.heads - 1);
+  const float* asrc = alpha + (((size_t)k * d.gpad + scl) * d.heads + shead) * d.Np;
+  const size_t asb = (size_t)d.G * d.gpad * d.heads * d.Np;
+  // 64 pixels: where this lane's weights lie in a stage; 16 pixels: its row of weights (block i, first head)
+  const int aoff = kPairTileBytes + (L.wm * NHT + L.wn * HH) * 256 + L.lhi * 32;
+  const float* arow[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int r = mt * 128 + L.wm * 64 + i * 32 + L.l32;
-    const int cl = r < rows ? r / PP : r - rows;
-    alive[i] = cl < gk;
-    acl[i] = min(cl, gk - 1);
+    const int cl = min((mt * 128 + L.wm * 64 + i * 32 + L.l32) / PP, d.gpad - 1);
+    arow[i] = alpha + (((size_t)k * d.gpad + cl) * d.heads + (nt * 256 + L.wn * 64) / dh) * d.Np + 8 * L.lhi;
   }
-  const int head0 = (nt * 128 + L.wn * 64) / dh;
-  f32x4 av[2][4][2];                                       // block, k-step, half of the 8 patches
-  auto fetch_alpha = [&](int s, int hh) {
-    const int b = s / nsl, n = (s % nsl) * 64 + 8 * L.lhi;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const float* p = alpha + ((((size_t)b * d.G + k) * d.gpad + acl[i]) * d.heads + head0 + hh) * d.Np;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const bool in = alive[i] && n + 16 * kk < d.Np;
-        const int nk = in ? n + 16 * kk : 0;
-        const f32x4 v0 = *reinterpret_cast<const f32x4*>(p + nk), v1 = *reinterpret_cast<const f32x4*>(p + nk + 4);
-        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        av[i][kk][0] = in ? v0 : z;
-        av[i][kk][1] = in ? v1 : z;
-      }
-    }
+  struct W8 { f32x4 lo, hi; };
+  W8 nxt[2][4];                                            // 16 pixels: block, k-step of the next slice (one head)
+  auto from_memory = [&](int s, int hh, int i, int kk) {
+    const int b = s / nsl, n = (s % nsl) * 64 + 16 * kk;
+    const float* p = arow[i] + b * asb + (size_t)hh * d.Np + (n + 8 * L.lhi < d.Np ? n : 0);   // past the pitch: zero pixels
+    return W8{*reinterpret_cast<const f32x4*>(p), *reinterpret_cast<const f32x4*>(p + 4)};
   };
+  auto from_stage = [&](const unsigned char* st, int hh, int kk) {
+    const unsigned char* p = st + aoff + hh * 256 + kk * 64;
+    return W8{*reinterpret_cast<const f32x4*>(p), *reinterpret_cast<const f32x4*>(p + 16)};
+  };
+  if (PP == 16 && !H32 && s_begin < s_end) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) nxt[i][kk] = from_memory(s_begin, 0, i, kk);
+  }
+  W8 last[HH];                                             // 64 pixels: weights of a slice's last k-step
   f32x16 acc[2][2];
   zero_acc(acc);
-  if (s_begin < s_end && !H32) fetch_alpha(s_begin, 0);
-  pair_loop(
-      smem, s_begin, s_end,
+  pair_loop<2>(
+      smem, s_begin, s_end, L,
       [&](int s, unsigned char* st) {
         const int b = s / nsl, n0 = (s % nsl) * 64;
         const size_t oa = (size_t)b * d.C * PP * d.NT + n0, ob = (size_t)b * d.G * D * d.NT + n0;
-        const bf16 *qa[4], *qb[4];
+        const bf16 *qa[2], *qb[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          qa[i] = pa[i] + (is_one[i] ? (size_t)n0 : oa);
-          qb[i] = pb[i] + ob;
-        }
+        for (int i = 0; i < 2; ++i) qa[i] = pa[i] + oa;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qb[i] = pb[i] + ob;
         L.fill(qa, qb, st);
+        if (PP == 64 && L.wave < NSEG / 4)                 // past the pitch: any finite weight (the pixels are zero there)
+          load16_to_lds(asrc + b * asb + min(n0 + (L.lane & 15) * 4, d.Np - 4), st + kPairTileBytes + L.wave * 1024);
       },
-      [&](int s, const unsigned char* st) {
-        bf16x8 a[4][2], bb[4][2];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) L.read(st, kk, a[kk], bb[kk]);
+      [&](int s, int kk, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char* st) {
 #pragma unroll
         for (int hh = 0; hh < HH; ++hh) {
-          if (H32) fetch_alpha(s, hh);
-          bf16x8 sc[4][2];
+          bf16x8 sc[2];
+          W8 w{};
+          if (PP == 64) w = kk == 3 ? last[hh] : from_stage(st, hh, kk);
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
+          for (int i = 0; i < 2; ++i) {
+            if (PP == 16) w = H32 ? from_memory(s, hh, i, kk) : nxt[i][kk];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int e = 0; e < 4; ++e) {
+              sc[i][e] = (bf16)((float)a[i][e] * w.lo[e]);
+              sc[i][4 + e] = (bf16)((float)a[i][4 + e] * w.hi[e]);
+            }
+            if (PP == 16 && !H32 && s + 1 < s_end) nxt[i][kk] = from_memory(s + 1, 0, i, kk);
+          }
+          if (PP == 64 && kk == 2) last[hh] = from_stage(st, hh, 3);
 #pragma unroll
-              for (int e = 0; e < 8; ++e) sc[kk][i][e] = (bf16)((float)a[kk][i][e] * av[i][kk][e >> 2][e & 3]);
-          if (!H32 && s + 1 < s_end) fetch_alpha(s + 1, 0);
+          for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-              for (int j = 0; j < 2; ++j)
-                if (!H32 || j == hh)
-                  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sc[kk][i], bb[kk][j], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < 2; ++j)
+              if (!H32 || j == hh)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sc[i], bb[j], acc[i][j], 0, 0, 0);
         }
-      });
+      },
+      [](int) {});
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int col = nt * 128 + L.wn * 64 + j * 32 + L.l32;
+    const int col = nt * 256 + L.wn * 64 + j * 32 + L.l32;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int r0 = mt * 128 + L.wm * 64 + i * 32 + 8 * q + 4 * L.lhi;
         if (splits > 1) {
+          if (r0 < rows)
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (r0 + e < d.RE) part[(((size_t)sp * d.G + k) * d.RE + r0 + e) * D + col] = acc[i][j][4 * q + e];
+            for (int e = 0; e < 4; ++e) part[(((size_t)sp * d.G + k) * rows + r0 + e) * D + col] = acc[i][j][4 * q + e];
         } else {
           bf16x4 v;
 #pragma unroll
@@ -716,32 +766,76 @@ __global__ __launch_bounds__(256, 2) void k_pixel_outer(PixelDims d, TileWork tw
 }
 
 // Adds the partial sums of k_pixel_outer up in a fixed order.  A thread takes four adjacent rows of one column.
-// grid (D / 64, ceil(RE / 16), G), block 256.
+// grid (D / 64, ceil(gq pp / 16), G), block 256.
 template <int PP>
 __global__ __launch_bounds__(256) void k_pixel_outer_merge(PixelDims d, int splits, const float* __restrict__ part,
                                                            bf16* __restrict__ Er, bf16* __restrict__ ET) {
   const int k = blockIdx.z, col = blockIdx.x * 64 + (threadIdx.x & 63), r0 = blockIdx.y * 16 + (threadIdx.x >> 6) * 4;
-  if (r0 >= d.RE) return;
+  if (r0 >= d.gq * PP) return;
   float v[4] = {0.f, 0.f, 0.f, 0.f};
   for (int sp = 0; sp < splits; ++sp)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] += part[(((size_t)sp * d.G + k) * d.RE + r0 + e) * d.D + col];
+    for (int e = 0; e < 4; ++e) v[e] += part[(((size_t)sp * d.G + k) * (d.gq * PP) + r0 + e) * d.D + col];
   store_outer<PP>(d, k, r0, col, bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]}, Er, ET);
+}
+
+// e[c][d] = sum_n alpha[c,a(d),n] d_o[n,d] (softmax weights as hi + lo bf16 parts), rows behind the pixels' rows of ET and the
+// two member columns of Er; zeros for members a group lacks.  A block takes 32 columns d (inside one head) and 32 members,
+// its eight wavefronts the patches in steps of 16, merged in LDS in a fixed order.  grid (D / 32, gp / 32, G), block 512.
+template <int PP>
+__global__ __launch_bounds__(512) void k_pixel_member_sums(PixelDims d, const float* __restrict__ alpha,
+                                                           const bf16* __restrict__ dOT, bf16* __restrict__ Er,
+                                                           bf16* __restrict__ ET) {
+  __shared__ float part[8][16][64];
+  const int k = blockIdx.z, d0 = blockIdx.x * 32, m0 = blockIdx.y * 32, gk = min(d.g, d.C - k * d.g);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
+  const int head = d0 / (d.D / d.heads), cl = min(m0 + l32, gk - 1);
+  const bool live = m0 + l32 < gk;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const int per = d.Np / 16, steps = d.B * per;
+#pragma unroll 4
+  for (int s = wave; s < steps; s += 8) {
+    const int b = s / per, n = (s % per) * 16 + 8 * lhi;
+    const float* p = alpha + ((((size_t)b * d.G + k) * d.gpad + cl) * d.heads + head) * d.Np + n;
+    f32x4 v0 = *reinterpret_cast<const f32x4*>(p), v1 = *reinterpret_cast<const f32x4*>(p + 4);
+    if (!live) v0 = v1 = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 hi, lo;
+    split_bf16(v0, v1, hi, lo);
+    const bf16x8 o = *reinterpret_cast<const bf16x8*>(dOT + (((size_t)b * d.G + k) * d.D + d0 + l32) * d.NT + n);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, o, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, o, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part[wave][r][lane] = acc[r];
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < 1024; idx += 512) {
+    const int r = idx >> 6, ln = idx & 63, m = m0 + 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3), col = d0 + (ln & 31);
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) v += part[w][r][ln];
+    const int row = d.gq * PP + m;
+    ET[((size_t)k * d.RE + row) * d.D + col] = (bf16)v;
+    bf16* er = Er + ((size_t)k * d.D + col) * d.KE + row;
+    er[0] = er[d.gp] = (bf16)v;
+  }
 }
 
 // ---------------------------------------------------------------------------------------
 // F and f, as hi + lo bf16 parts in the two layouts the products below read: Fr[k][row][KE] with rows 0 .. 31 the heads'
 // hi parts and 32 .. 63 their lo parts, FT[k][(member, pixel) / member row][64] with the same 64 as columns.  One block
-// per (member, group), four wavefronts over the patches (16 a step), partial blocks merged in LDS in a fixed order.
-// grid (gp, G), block 256.
+// per (member, group), eight wavefronts over the patches (16 a step), partial blocks merged in LDS in a fixed order.
+// grid (gp, G), block 512, dynamic LDS 8 (NB 4096 + 256) bytes.
 // ---------------------------------------------------------------------------------------
 template <int PP>
-__global__ __launch_bounds__(256) void k_pixel_key_sums(PixelDims d, int ppc, const float* __restrict__ ds,
+__global__ __launch_bounds__(512) void k_pixel_key_sums(PixelDims d, int ppc, const float* __restrict__ ds,
                                                         const bf16* __restrict__ UT, bf16* __restrict__ Fr,
                                                         bf16* __restrict__ FT) {
   constexpr int NB = PP == 64 ? 2 : 1;
-  __shared__ float part[4][NB][16][64];
-  __shared__ float fpart[4][64];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float (*part)[NB][16][64] = reinterpret_cast<float (*)[NB][16][64]>(smem);
+  float (*fpart)[64] = reinterpret_cast<float (*)[64]>(smem + 8 * NB * 4096);
   const int cl = blockIdx.x, k = blockIdx.y, c0 = k * d.g, gk = min(d.g, d.C - c0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
   const bool live = cl < gk;
@@ -756,7 +850,7 @@ __global__ __launch_bounds__(256) void k_pixel_key_sums(PixelDims d, int ppc, co
     const int head = min(l32, d.heads - 1);
     const bool hv = l32 < d.heads;
 #pragma unroll 4
-    for (int s = wave; s < steps; s += 4) {
+    for (int s = wave; s < steps; s += 8) {
       const int b = s / per, n = (s % per) * 16 + 8 * lhi;
       const float* dp = ds + ((((size_t)b * d.G + k) * d.gpad + cl) * d.heads + head) * ppc * d.Np + n;
       f32x4 v0 = *reinterpret_cast<const f32x4*>(dp), v1 = *reinterpret_cast<const f32x4*>(dp + 4);
@@ -783,13 +877,13 @@ __global__ __launch_bounds__(256) void k_pixel_key_sums(PixelDims d, int ppc, co
   bf16* fr = Fr + (size_t)k * 64 * d.KE;
   if (cl < d.gq) {
     // thread: (block j, register r, lane) -> head 8 (r / 4) + 4 (lane / 32) + r % 4, pixel 32 j + lane % 32
-    for (int idx = threadIdx.x; idx < NB * 16 * 64; idx += 256) {
+    for (int idx = threadIdx.x; idx < NB * 16 * 64; idx += 512) {
       const int ln = idx & 63, r = (idx >> 6) & 15, j = idx >> 10;
       const int a = 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3), kk = j * 32 + (ln & 31);
       if (kk >= PP) continue;
       float v = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) v += part[w][j][r][ln];
+      for (int w = 0; w < 8; ++w) v += part[w][j][r][ln];
       const bf16 hi = (bf16)v, lo = (bf16)(v - (float)hi);
       const int row = cl * PP + kk;
       fr[(size_t)a * d.KE + row] = hi;
@@ -802,7 +896,7 @@ __global__ __launch_bounds__(256) void k_pixel_key_sums(PixelDims d, int ppc, co
     const int a = threadIdx.x;
     float v = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) v += fpart[w][a] + fpart[w][a + 32];
+    for (int w = 0; w < 8; ++w) v += fpart[w][a] + fpart[w][a + 32];
     const bf16 hi = (bf16)v, lo = (bf16)(v - (float)hi);
     const int row = rows + cl;
     fr[(size_t)a * d.KE + row] = fr[(size_t)a * d.KE + row + d.gp] = hi;
@@ -817,7 +911,7 @@ __global__ __launch_bounds__(256) void k_pixel_key_sums(PixelDims d, int ppc, co
 // transposed value weights, one slice of FT against the folded keys (M2).  dWe[c][j][kk], dtb[c][j]; either may be NULL.
 // ---------------------------------------------------------------------------------------
 template <int PP>
-__global__ __launch_bounds__(256, 2) void k_pixel_dwe(PixelDims d, TileWork tw, const bf16* __restrict__ ET,
+__global__ __launch_bounds__(512) void k_pixel_dwe(PixelDims d, TileWork tw, const bf16* __restrict__ ET,
                                                       const bf16* __restrict__ FT, const bf16* __restrict__ WvT,
                                                       const bf16* __restrict__ M2, bf16* __restrict__ dWe,
                                                       bf16* __restrict__ dtb) {
@@ -825,23 +919,28 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dwe(PixelDims d, TileWork tw, 
   int k, b, mt, nt;
   if (!tw.decode(blockIdx.x, k, b, nt, mt)) return;
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, rows = d.gq * PP;
-  PairLane L;
+  PairLane<2> L;
   L.init();
-  const bf16 *pa[4], *pb[4], *xa[4], *xb[4];
+  const bf16 *pa[2], *pb[4], *xa[2], *xb[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = L.row_a(i), ch = L.chunk(row) * 8;
+    const size_t ra = (size_t)k * d.RE + min(mt * 128 + row, d.RE - 1);
+    pa[i] = ET + ra * D + ch;
+    xa[i] = FT + ra * 64 + ch;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = L.row(i), ch = L.chunk(row) * 8;
-    const size_t ra = (size_t)k * d.RE + min(mt * 128 + row, d.RE - 1), rb = (size_t)k * D + nt * 128 + row;
-    pa[i] = ET + ra * D + ch;
+    const int row = L.row_b(i), ch = L.chunk(row) * 8;
+    const size_t rb = (size_t)k * D + nt * 256 + row;
     pb[i] = WvT + rb * D + ch;
-    xa[i] = FT + ra * 64 + ch;
     xb[i] = M2 + rb * 64 + ch;
   }
   const int KT = D / 64;
   f32x16 acc[2][2];
   zero_acc(acc);
-  pair_loop(
-      smem, 0, KT + 1,
+  pair_loop<2>(
+      smem, 0, KT + 1, L,
       [&](int s, unsigned char* st) {
         if (s == KT) {
           L.fill(xa, xb, st);
@@ -849,12 +948,15 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dwe(PixelDims d, TileWork tw, 
         }
         L.fill(pa, pb, st);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { pa[i] += 64; pb[i] += 64; }
+        for (int i = 0; i < 2; ++i) pa[i] += 64;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pb[i] += 64;
       },
-      [&](int, const unsigned char* st) { pair_products(acc, st, L); });
+      [&](int, int, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char*) { pair_products(acc, a, bb); },
+      [](int) {});
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int col = nt * 128 + L.wn * 64 + j * 32 + L.l32;
+    const int col = nt * 256 + L.wn * 64 + j * 32 + L.l32;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -876,12 +978,13 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dwe(PixelDims d, TileWork tw, 
 }
 
 // ---------------------------------------------------------------------------------------
-// Value-weight gradient and key-path sums: tile rows the D rows of Er then the 64 rows of Fr, tile columns j, the
-// contraction runs over (member, pixel) (slices of We, or of X's rows for 16 pixels) and then over the members (be, ce).
-// dWv[k][d][j] (or NULL) and r[k][head][j] = its hi + lo rows, fp32.
+// Value-weight gradient (KEYS = false): tile rows the D rows of Er, tile columns j, the contraction runs over (member, pixel)
+// (slices of We, or of X's rows for 16 pixels) and then over the members (be, ce).  KEYS = true: the same with the 64 rows of
+// Fr, the contraction dealt to `splits` blocks (a row tile of its own would be a third round of tiles at 512 bands): the
+// hi and lo rows added, r[k][split][head][j] in fp32.
 // ---------------------------------------------------------------------------------------
-template <int PP>
-__global__ __launch_bounds__(256, 2) void k_pixel_dwv(PixelDims d, TileWork tw, const bf16* __restrict__ Er,
+template <int PP, bool KEYS>
+__global__ __launch_bounds__(512) void k_pixel_dwv(PixelDims d, TileWork tw, int splits, const bf16* __restrict__ Er,
                                                       const bf16* __restrict__ Fr, const bf16* __restrict__ We,
                                                       const bf16* __restrict__ X, bf16* __restrict__ dWv,
                                                       float* __restrict__ r) {
@@ -889,48 +992,49 @@ __global__ __launch_bounds__(256, 2) void k_pixel_dwv(PixelDims d, TileWork tw, 
   int k, b, mt, nt;
   if (!tw.decode(blockIdx.x, k, b, mt, nt)) return;
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D;
-  const bool tail = mt * 128 >= D;                         // the tile of Fr's rows
-  if (tail ? !r : !dWv) return;                            // uniform
-  PairLane L;
+  typedef PairLane<2> Lane;
+  Lane L;
   L.init();
   const int XE = (PP == 16 ? d.gq * 16 : 0) + 2 * d.gp;
-  const bf16 *pa[4], *pb[4], *xb[4];
+  const bf16 *pa[2], *pb[4], *xb[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = L.row_a(i), ch = L.chunk(row) * 8;
+    pa[i] = KEYS ? Fr + ((size_t)k * 64 + min(row, 63)) * d.KE + ch : Er + ((size_t)k * D + mt * 128 + row) * d.KE + ch;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = L.row(i), ch = L.chunk(row) * 8;
-    pa[i] = tail ? Fr + ((size_t)k * 64 + min(row, 63)) * d.KE + ch : Er + ((size_t)k * D + mt * 128 + row) * d.KE + ch;
-    pb[i] = We + ((size_t)c0 * D + nt * 128 + row) * 64 + ch;
-    xb[i] = X + ((size_t)k * D + nt * 128 + row) * XE + ch;
+    const int row = L.row_b(i), ch = L.chunk(row) * 8;
+    pb[i] = We + ((size_t)c0 * D + nt * 256 + row) * 64 + ch;
+    xb[i] = X + ((size_t)k * D + nt * 256 + row) * XE + ch;
   }
   const int KM = PP == 64 ? d.g : 0, KT = d.KE / 64;       // slices whose right operand is We itself; all slices
+  const int s_begin = KEYS ? (int)((long)b * KT / splits) : 0, s_end = KEYS ? (int)((long)(b + 1) * KT / splits) : KT;
   f32x16 acc[2][2];
   zero_acc(acc);
-  pair_loop(
-      smem, 0, KT,
+  pair_loop<2>(
+      smem, s_begin, s_end, L,
       [&](int s, unsigned char* st) {
-        if (s < KM) {
-          L.fill(pa, pb, st);
-          if (s + 1 < gk)                                  // members a short group lacks meet zeros of Er: any row will do
+        const bf16 *qa[2], *qb[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) pb[i] += (size_t)D * 64;
-        } else {
-          L.fill(pa, xb, st);
+        for (int i = 0; i < 2; ++i) qa[i] = pa[i] + s * 64;
+        // members a short group lacks meet zeros of Er / Fr: any row will do
+        const size_t ob = s < KM ? (size_t)min(s, gk - 1) * D * 64 : (size_t)(s - KM) * 64;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) xb[i] += 64;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pa[i] += 64;
+        for (int i = 0; i < 4; ++i) qb[i] = (s < KM ? pb[i] : xb[i]) + ob;
+        L.fill(qa, qb, st);
       },
-      [&](int, const unsigned char* st) { pair_products(acc, st, L); });
+      [&](int, int, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char*) { pair_products(acc, a, bb); },
+      [](int) {});
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int col = nt * 128 + L.wn * 64 + j * 32 + L.l32;
-    if (tail) {
+    const int col = nt * 256 + L.wn * 64 + j * 32 + L.l32;
+    if (KEYS) {
       if (L.wm) continue;
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int a = 8 * (q >> 2) + 4 * L.lhi + (q & 3);
-        if (a < d.heads) r[((size_t)k * d.heads + a) * D + col] = acc[0][j][q] + acc[1][j][q];
+        if (a < d.heads) r[(((size_t)k * splits + b) * d.heads + a) * D + col] = acc[0][j][q] + acc[1][j][q];
       }
       continue;
     }

@@ -31,13 +31,13 @@ SHAPES = [
 
 
 @pytest.mark.parametrize("kw", SHAPES)
-@pytest.mark.parametrize("tokens", [False, True])
-def test_training_step_from_the_pixels_and_through_the_tokens(kw, tokens, monkeypatch):
-    say(f"pixel training {kw} tokens={tokens}")
-    if tokens:
-        monkeypatch.setenv("DCHAG_TRAIN_TOKENS", "1")
+@pytest.mark.parametrize("route", ["pixels", "tokens"])
+def test_training_step_from_the_pixels_and_through_the_tokens(kw, route, monkeypatch):
+    say(f"training through the {route} {kw}")
+    monkeypatch.setenv("DCHAG_TRAIN_ROUTE", route)
     check_training_step(ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=21, **kw))
 
 
-def test_training_step_from_the_pixels_without_biases():
+def test_training_step_from_the_pixels_without_biases(monkeypatch):
+    monkeypatch.setenv("DCHAG_TRAIN_ROUTE", "pixels")
     check_training_step(ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=22, **SHAPES[0]), biases=False)
