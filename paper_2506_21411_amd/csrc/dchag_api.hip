@@ -46,6 +46,7 @@ enum Switch {
   SW_GEMM_SCALAR_STORES,
   SW_GENERIC_LEVEL,
   SW_GENERIC_TOKENIZE,
+  SW_LEVEL_UNFUSED,
   SW_LINEAR_SMALL_REGS,
   SW_LINEAR_TOKENS,
   SW_MFMA_TILE,
@@ -80,6 +81,7 @@ struct SwitchTable {
     "DCHAG_GEMM_SCALAR_STORES",
     "DCHAG_GENERIC_LEVEL",
     "DCHAG_GENERIC_TOKENIZE",
+    "DCHAG_LEVEL_UNFUSED",
     "DCHAG_LINEAR_SMALL_REGS",
     "DCHAG_LINEAR_TOKENS",
     "DCHAG_MFMA_TILE",

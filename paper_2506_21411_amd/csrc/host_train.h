@@ -459,6 +459,34 @@ inline int head_sums(int B, int Cin, int N, int D, int heads, int g, const float
   return launch_status();
 }
 
+// Scores, softmax and head sums of a level from its tokens in one launch (k_level_sums), while a group's weights fit LDS.  Whole
+// calls against the separate kernels: 80 variables served at 128 patches, D 256: 55.1 -> 44.0 us; 512 bands served: 245 -> 235 us;
+// 16 x 16 patches, 64 channels, N 1024, D 1024, groups of 32: 633 -> 626 us.  Wide embeddings with more than 16 heads keep the
+// separate ones, which hold the keys in registers (D 4096, 32 heads, groups of 8: 996 against 1004 us).
+inline bool level_sums_ok(int D, int heads, int g) {
+  return D % 256 == 0 && heads <= 64 && !(D > 2048 && heads > 16) &&
+         level_sums_lds(1, heads <= 16 ? 1 : heads <= 32 ? 2 : 4, g) <= 150 * 1024 && !dbg(SW_LEVEL_UNFUSED);
+}
+// Patches a block: one while the chip is not full, else as many as share the keys without an accumulator's worth of registers more;
+// two beyond D 1024 (1000 bands, D 2048: 2014 us with two, 2031 with four).  Heads an item: all of a block of 16, fewer where
+// the items of one patch would not occupy the block (D < 1024: 66.6 against 67.7 us for 80 variables, weights not prepared).
+inline int level_sums(int B, int Cin, int N, int D, int heads, int g0, const bf16* z, const LevelBufs<bf16>& lb,
+                      hipStream_t st) {
+  const int g = std::min(g0, Cin), G = groups_of(Cin, g0), NB = heads <= 16 ? 1 : heads <= 32 ? 2 : 4;
+  int PN = 1;
+  if ((long)B * G * N >= 16L * compute_units()) PN = NB == 1 ? (D <= 1024 ? 4 : 2) : NB == 2 ? 2 : 1;
+  if (level_sums_lds(PN, NB, g) > 64 * 1024) PN = 1;
+  auto kern = NB == 4 ? k_level_sums<4, 1, 16>
+            : NB == 2 ? (PN == 2 ? k_level_sums<2, 2, 16> : (D < 1024 ? k_level_sums<2, 1, 4> : k_level_sums<2, 1, 16>))
+            : PN == 4 ? (heads <= 8 ? k_level_sums<1, 4, 8> : k_level_sums<1, 4, 16>)
+            : PN == 2 ? (heads <= 8 ? k_level_sums<1, 2, 8> : k_level_sums<1, 2, 16>)
+                      : (D < 1024 ? k_level_sums<1, 1, 4> : heads <= 8 ? k_level_sums<1, 1, 8> : k_level_sums<1, 1, 16>);
+  const size_t lds = level_sums_lds(PN, NB, g);
+  if (ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return DCHAG_ERR_LAUNCH;
+  kern<<<dim3((N + PN - 1) / PN, G, B), 256, lds, st>>>(Cin, N, D, heads, g0, z, lb.Mb, lb.alpha, lb.u);
+  return launch_status();
+}
+
 inline int oproj(int B, int D, RowBlocks rb, const float* o, const float* Wo, const float* bo, float* y, hipStream_t st) {
   return launch_linear<float>(B, D, rb, o, Wo, bo, y, st);
 }
@@ -475,15 +503,28 @@ int folded_level_forward(dchag_dtype dt, int B, int Cin, int N, int D, int heads
                          T* zout, const LevelBufs<T>& lb, hipStream_t st, const PixelScores* px, int phase = 0) {
   const int g = lv->group_size, G = groups_of(Cin, g), dh = D / heads;
   const T* Wv = static_cast<const T*>(lv->Wv);
-  int rc;
+  int rc = DCHAG_OK;
+  bool summed = false;
   if constexpr (std::is_same<T, bf16>::value) {
-    if (train_fast(dt, D, heads)) rc = fast_alpha(B, Cin, N, D, heads, lv, zin, lb, st, px, phase);
-    else rc = generic_alpha<T>(B, Cin, N, D, heads, lv, zin, lb, st);
+    if (train_fast(dt, D, heads)) {
+      summed = !px && level_sums_ok(D, heads, std::min(g, Cin));
+      if (summed) {
+        if (phase == 0) rc = fast_scores(B, Cin, N, D, heads, lv, zin, lb.Qp, lb.Mf, lb.Mb, lb.alpha_f, st, nullptr, nullptr,
+                                         nullptr, 1);
+        if (rc) return rc;
+        StageTimer tm(DCHAG_STAGE_HEAD_SUMS, st);
+        rc = level_sums(B, Cin, N, D, heads, g, zin, lb, st);
+      } else {
+        rc = fast_alpha(B, Cin, N, D, heads, lv, zin, lb, st, px, phase);
+      }
+    } else {
+      rc = generic_alpha<T>(B, Cin, N, D, heads, lv, zin, lb, st);
+    }
   } else {
     rc = generic_alpha<T>(B, Cin, N, D, heads, lv, zin, lb, st);
   }
   if (rc) return rc;
-  {
+  if (!summed) {
     StageTimer tm(DCHAG_STAGE_HEAD_SUMS, st);
     if ((rc = head_sums(B, Cin, N, D, heads, g, lb.alpha, zin, lb.u, st))) return rc;
   }

@@ -1125,6 +1125,150 @@ __global__ __launch_bounds__(256) void k_head_sums_bf16(int Cin, int N, int D, i
 }
 
 // ---------------------------------------------------------------------------------------
+// Scores, softmax and per-head weighted token sums of a level whose tokens are in HBM, in one kernel (bf16, D % 256 == 0,
+// heads <= 16 NB):
+//   alpha[b,c,n,a] = softmax over the group's members c of z[b,c,n,:] . M[k][a][:]       (token-major)
+//   u[b,k,n,a,:]   = sum_c alpha[b,c,n,a] z[b,c,n,:]
+// A block owns PN patches of one (b, k).  Scores: a wavefront contracts its quarter of the D features on 16x16x32 MFMA (16
+// members x 16 heads a tile, the key fragments shared by the PN patches), the quarters meet in LDS.  Softmax: a wavefront per
+// (patch, 16 heads), four lanes to a head.  Sums: an item is (patch, HB heads, 4 columns), fp32, members in order; the tokens come
+// a second time from the L2.  Replaces four launches (scores, softmax, re-layout, sums) whose weights went through HBM twice:
+// bound by the read of z and the write of u, at small sizes by the launch itself (128 patches, 10 members, D 256: the whole
+// served call went from 55 to 44 us).
+// grid (ceil(N/PN), G, B), block 256, dynamic LDS level_sums_lds(PN, NB, g).
+// ---------------------------------------------------------------------------------------
+constexpr size_t level_sums_lds(int PN, int NB, int g) { return (size_t)PN * NB * (4096 + 64 * (size_t)g); }
+
+template <int NB, int PN, int HB>
+__global__ __launch_bounds__(256) void k_level_sums(int Cin, int N, int D, int heads, int g, const bf16* __restrict__ z,
+                                                    const bf16* __restrict__ Mb, float* __restrict__ alpha,
+                                                    bf16* __restrict__ u) {
+  constexpr int HS = NB * 16;                                     // pitch of a member's weights
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  float* part = lds;                                              // [source wavefront][patch, head block, register][lane]
+  float* sc = lds + 4 * PN * NB * 256;                            // [patch][member][HS]
+  const int k = blockIdx.y, b = blockIdx.z, G = gridDim.y, n0 = blockIdx.x * PN;
+  const int c0 = k * g, gk = min(g, Cin - c0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, lq = lane >> 4;
+  const size_t cstride = (size_t)N * D;
+  const bf16* zg = z + ((size_t)b * Cin + c0) * cstride;
+  const int koff = wave * (D / 4) + lq * 16;                      // two steps take the halves of a lane's 32 bytes
+  const bf16* mrow[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) mrow[nb] = Mb + ((size_t)k * heads + min(nb * 16 + l16, heads - 1)) * D + koff;
+  for (int m0 = 0; m0 < gk; m0 += 16) {
+    const bf16* zp[PN];
+#pragma unroll
+    for (int p = 0; p < PN; ++p)
+      zp[p] = zg + (size_t)min(m0 + l16, gk - 1) * cstride + (size_t)min(n0 + p, N - 1) * D + koff;
+    f32x4 acc[PN][NB];
+#pragma unroll
+    for (int p = 0; p < PN; ++p)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[p][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int f = 0; f < D / 4; f += 64) {
+      bf16x8 zf[PN][2], mf[NB][2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int p = 0; p < PN; ++p) zf[p][h] = *reinterpret_cast<const bf16x8*>(zp[p] + f + 8 * h);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) mf[nb][h] = *reinterpret_cast<const bf16x8*>(mrow[nb] + f + 8 * h);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int p = 0; p < PN; ++p)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            acc[p][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[p][h], mf[nb][h], acc[p][nb], 0, 0, 0);
+    }
+    if (m0) __syncthreads();                                      // the last tile's partial blocks have been read
+#pragma unroll
+    for (int p = 0; p < PN; ++p)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[((wave * PN + p) * NB + nb) * 256 + e * 64 + lane] = acc[p][nb][e];
+    __syncthreads();
+    // accumulator block: lane holds head lane % 16, members 4 (lane / 16) + 0..3; wavefront e adds up register e
+    const int cl = m0 + lq * 4 + wave;
+    if (cl < gk) {
+#pragma unroll
+      for (int p = 0; p < PN; ++p)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const float* q = part + (p * NB + nb) * 256 + wave * 64 + lane;
+          constexpr int S = PN * NB * 256;
+          sc[(p * gk + cl) * HS + nb * 16 + l16] = ((q[0] + q[S]) + q[2 * S]) + q[3 * S];
+        }
+    }
+  }
+  __syncthreads();
+  for (int it = wave; it < PN * NB; it += 4) {
+    const int p = it / NB, a = (it % NB) * 16 + l16, n = n0 + p;
+    float* s = sc + (size_t)p * gk * HS + a;
+    float mx = -INFINITY;
+    for (int cl = lq; cl < gk; cl += 4) mx = fmaxf(mx, s[cl * HS]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+    float den = 0.f;
+    for (int cl = lq; cl < gk; cl += 4) den += __expf(s[cl * HS] - mx);
+    den += __shfl_xor(den, 16, kWave);
+    den += __shfl_xor(den, 32, kWave);
+    const float inv = 1.f / den;
+    for (int cl = lq; cl < gk; cl += 4) {
+      const float v = __expf(s[cl * HS] - mx) * inv;
+      s[cl * HS] = v;
+      if (n < N && a < heads) alpha[(((size_t)b * Cin + c0 + cl) * N + n) * heads + a] = v;
+    }
+  }
+  __syncthreads();
+  const int DC = D / 4, items = PN * (HS / HB) * DC;              // DC % 64 == 0: a wavefront shares patch and heads
+  for (int it = threadIdx.x; it < items; it += 256) {
+    const int d0 = (it % DC) * 4, t = it / DC, a0 = (t % (HS / HB)) * HB, p = t / (HS / HB), n = n0 + p;
+    if (n >= N || a0 >= heads) continue;
+    const bf16* zp = zg + (size_t)n * D + d0;
+    const float* al = sc + (size_t)p * gk * HS + a0;
+    float acc[HB][4];
+#pragma unroll
+    for (int a = 0; a < HB; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[a][e] = 0.f;
+    auto add = [&](int cl, const bf16x4& zv) {
+      const f32x4* ar = reinterpret_cast<const f32x4*>(al + (size_t)cl * HS);
+#pragma unroll
+      for (int q = 0; q < HB / 4; ++q) {
+        const f32x4 av = ar[q];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[q * 4 + a][e] += av[a] * (float)zv[e];
+      }
+    };
+    int cl = 0;
+    for (; cl + 4 <= gk; cl += 4) {
+      bf16x4 zv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) zv[i] = *reinterpret_cast<const bf16x4*>(zp + (size_t)(cl + i) * cstride);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) add(cl + i, zv[i]);
+    }
+    for (; cl < gk; ++cl) add(cl, *reinterpret_cast<const bf16x4*>(zp + (size_t)cl * cstride));
+    bf16* up = u + ((((size_t)b * G + k) * N + n) * heads + a0) * D + d0;
+#pragma unroll
+    for (int a = 0; a < HB; ++a)
+      if (a0 + a < heads) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (bf16)acc[a][e];
+        *reinterpret_cast<bf16x4*>(up + (size_t)a * D) = o;
+      }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // d alpha and the softmax Jacobian in one kernel (bf16, D % 32 == 0, group size <= 16 MT):
 //   dalpha[c,a] = w[b,k,n,a,:] . z[b,c,n,:]            (16x16x32 MFMA: 16 members x 16 heads per block)
 //   ds[c,a]     = alpha[c,a] * (dalpha[c,a] - sum_c' alpha[c',a] dalpha[c',a])
