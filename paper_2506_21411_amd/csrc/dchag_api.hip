@@ -47,6 +47,7 @@ enum Switch {
   SW_GENERIC_LEVEL,
   SW_GENERIC_TOKENIZE,
   SW_LEVEL_UNFUSED,
+  SW_LINEAR_ROUTE,
   SW_LINEAR_SMALL_REGS,
   SW_LINEAR_TOKENS,
   SW_MFMA_TILE,
@@ -82,6 +83,7 @@ struct SwitchTable {
     "DCHAG_GENERIC_LEVEL",
     "DCHAG_GENERIC_TOKENIZE",
     "DCHAG_LEVEL_UNFUSED",
+    "DCHAG_LINEAR_ROUTE",
     "DCHAG_LINEAR_SMALL_REGS",
     "DCHAG_LINEAR_TOKENS",
     "DCHAG_MFMA_TILE",

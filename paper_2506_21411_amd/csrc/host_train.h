@@ -1210,6 +1210,33 @@ int tokenizer_backward(int B, int C, int H, int W, int p, int D, const T* x, con
   return DCHAG_OK;
 }
 
+// Reverse step of a linear first level on tiles of (member, pixel) rows (k_linear_outer, k_linear_dx): its scratch, inside the
+// region the tokens would have taken.  Whole steps, products per channel / tiles: 512 bands x 4 x 256 patches, D 1024: 741 / 585 us;
+// 1000 channels x 2 x 256 patches of 4 x 4, D 2048: 2114 / 1692; 512 x 4 x 15, D 1024: 318 / 205; small ones fill a fraction of the
+// chip with tiles of 128 x 256: 80 x 2 x 64, D 512 (5 million elements): 133 / 135; 9 x 512, D 512: 163 / 168; 80 x 2 x 256, D 512 (21
+// million): 171 / 171, so the line lies at 2^24.  DCHAG_LINEAR_ROUTE (debugging aid) = tiles / channels overrides the rule, never the
+// limits.
+struct LinearTiles {
+  size_t s, dyt, ut, wst, total;
+};
+inline bool linear_tiles(int B, int C, int N, int p, int D, int g0, size_t room, LinearTiles* w) {
+  const int pp = p * p, G = groups_of(C, g0), g = std::min(g0, C), NT = round_up(N, 64);
+  if ((p != 4 && p != 8) || D % 256) return false;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { const size_t o = off; off += align_up(bytes); return o; };
+  w->s = take((size_t)G * D * 4);
+  w->dyt = take((size_t)B * G * D * NT * 2);
+  w->ut = take((size_t)B * C * pp * NT * 2);
+  w->wst = take((size_t)C * pp * D * 2);
+  w->total = off;
+  const long rows = (long)g * pp, tiles_p = (rows + 127) / 128 * (D / 256) * G;
+  if (off > room || (long)B * G > 65535 || (long)G * round_up(g, 4) * (pp / 8) / 32 > 65534 || tiles_p > (1L << 26) ||
+      (rows + 127) / 128 * ((N + 127) / 128) * B * G > (1L << 26))
+    return false;
+  if (const char* e = dbg(SW_LINEAR_ROUTE)) return e[0] == 't';
+  return (double)B * C * N * D >= (double)(1L << 24);
+}
+
 // A linear first level needs neither its input tokens nor their gradients in HBM (see k_linear_first_grads): true
 // when the reverse sweep takes that route.  The products' intermediates (P fp32, the scaled weights, S) go where the
 // tokens would have been.  DCHAG_LINEAR_TOKENS (debugging aid) keeps the route through the tokens.
@@ -1221,7 +1248,9 @@ inline bool linear_first_without_tokens(dchag_dtype dt, int B, int C, int N, int
   if (pp % 8 || (cpr & (cpr - 1)) || cpr > 64 || D % 8) return false;
   const size_t G = groups_of(C, levels[0].group_size);
   const size_t need = align_up((size_t)C * D * pp * 4) + align_up((size_t)C * D * pp * 2) + align_up(G * D * 4);
-  return need <= align_up((size_t)B * C * N * D * 2);
+  const size_t room = align_up((size_t)B * C * N * D * 2);
+  LinearTiles lt;
+  return need <= room || linear_tiles(B, C, N, pp == 64 ? 8 : pp == 16 ? 4 : 0, D, levels[0].group_size, room, &lt);
 }
 
 // One product per channel with the group's operand shared by its members: full groups in one launch, a short last
@@ -1245,11 +1274,59 @@ int gemm_per_channel(GemmDesc d, int C, int g, long a_grp, long b_ch, long c_ch,
   return rc;
 }
 
+inline TileWork pixel_tiles(int fast, int slow, int nb, int G) {
+  TileWork tw{};
+  tw.n_tiles = fast; tw.m_tiles = slow; tw.nb = nb; tw.total = fast * slow * nb * G;
+  return tw;
+}
+inline unsigned tile_grid(const TileWork& tw) { return (unsigned)((tw.total + kXcds - 1) / kXcds * kXcds); }
+
+inline int transpose_rows(int batch, int R, int RT, int Cc, const bf16* in, bf16* out, hipStream_t st) {
+  k_transpose<<<dim3((unsigned)((RT + 63) / 64), (unsigned)((Cc + 255) / 256), (unsigned)batch), 256, 0, st>>>(R, RT, Cc, in,
+                                                                                                            out);
+  return launch_status();
+}
+
+template <class K>
+int raise_pair_lds(K kern) { return ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kPairLdsBytes); }
+
+template <int PP>
+int linear_tiles_backward(int B, int C, int H, int W, int D, const dchag_level* lv, const bf16* x, const bf16* We,
+                          const bf16* be, const bf16* ce, const bf16* dy, bf16* dx, bf16* dWe, bf16* dtok_bias, bf16* dmix,
+                          bf16* dbias, unsigned char* scratch, const LinearTiles& w, hipStream_t st) {
+  constexpr int P = PP == 64 ? 8 : 4;
+  PixelDims d = pixel_dims(B, C, (H / P) * (W / P), PP, D, 1, lv->group_size);
+  d.H = H; d.W = W;
+  const int rows = std::min(d.g, C) * PP;
+  auto at = [&](size_t off) { return reinterpret_cast<bf16*>(scratch + off); };
+  int rc;
+  if ((rc = transpose_rows(B * d.G, d.N, d.NT, D, dy, at(w.dyt), st))) return rc;
+  k_pixel_rows<P><<<dim3((unsigned)(d.NT / 64), (unsigned)((d.G * d.gq * (PP / 8) + 31) / 32), (unsigned)B), 256, 0, st>>>(
+      d, x, at(w.ut), nullptr);
+  if ((rc = launch_status())) return rc;
+  {
+    const TileWork tw = pixel_tiles((rows + 127) / 128, D / 256, 1, d.G);
+    if ((rc = raise_pair_lds(k_linear_outer<PP>))) return rc;
+    k_linear_outer<PP><<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(
+        d, tw, at(w.ut), at(w.dyt), reinterpret_cast<const float*>(scratch + w.s), We, be, ce,
+        static_cast<const bf16*>(lv->Wv), dWe, dtok_bias, dmix, dbias, dx ? at(w.wst) : nullptr);
+    if ((rc = launch_status())) return rc;
+  }
+  if (!dx) return DCHAG_OK;
+  const bool tall = rows > 128;                            // 256 rows x 128 patches, or 128 x 256
+  const TileWork tw = tall ? pixel_tiles((rows + 255) / 256, (d.N + 127) / 128, B, d.G)
+                           : pixel_tiles(1, (d.N + 255) / 256, B, d.G);
+  auto kern = tall ? k_linear_dx<PP, 4> : k_linear_dx<PP, 2>;
+  if ((rc = raise_pair_lds(kern))) return rc;
+  kern<<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, at(w.wst), dy, dx);
+  return launch_status();
+}
+
 // Reverse of (tokenizer, linear first level) given dy [B,G,N,D]: dmix / dbias of the level, dWe, dtok_bias, dx.
 inline int linear_first_backward(int B, int C, int H, int W, int p, int D, const dchag_level* lv,
                                  const dchag_level_grads* gr, const bf16* x, const bf16* We, const bf16* be,
                                  const bf16* ce, const bf16* dy, bf16* dx, bf16* dWe, bf16* dtok_bias, bf16* patches,
-                                 unsigned char* scratch, hipStream_t st) {
+                                 unsigned char* scratch, size_t scratch_bytes, hipStream_t st) {
   const int N = (H / p) * (W / p), pp = p * p, g = lv->group_size, G = groups_of(C, g);
   float* P = reinterpret_cast<float*>(scratch);
   bf16* Ws = reinterpret_cast<bf16*>(scratch + align_up((size_t)C * D * pp * 4));
@@ -1259,11 +1336,16 @@ inline int linear_first_backward(int B, int C, int H, int W, int p, int D, const
   int rc;
   bf16* dmix = static_cast<bf16*>(gr->dWv);
   const bool want_p = dWe || dmix;
+  LinearTiles lt;
+  // dx alone needs no products with the patches, but their scratch may be the larger one
+  const size_t channels_need = (size_t)(reinterpret_cast<unsigned char*>(S + (size_t)G * D) - scratch);
+  const bool tiles = (want_p || channels_need > scratch_bytes) && linear_tiles(B, C, N, p, D, g, scratch_bytes, &lt);
+  if (tiles) S = reinterpret_cast<float*>(scratch + lt.s);
   {
     StageTimer tm(DCHAG_STAGE_BWD_CHANNEL_MIX, st);
     k_colsum<bf16, float><<<dim3((D + 63) / 64, G), 1024, 0, st>>>(B, D, RowBlocks{G, G * N, N}, dy, S);
     if ((rc = launch_status())) return rc;
-    if (gr->dbv && (rc = colsum<bf16>(B, D, RowBlocks{G, G * N, N}, dy, static_cast<bf16*>(gr->dbv), st))) return rc;
+    if (!tiles && gr->dbv && (rc = colsum<bf16>(B, D, RowBlocks{G, G * N, N}, dy, static_cast<bf16*>(gr->dbv), st))) return rc;
     if (dmix && G * g > C) {                                      // members a short last group lacks: zero
       const long n = (long)(G * g - C) * D;
       k_fill_zero<bf16><<<dim3((unsigned)((n + 255) / 256)), 256, 0, st>>>(n, dmix + (size_t)C * D);
@@ -1271,6 +1353,10 @@ inline int linear_first_backward(int B, int C, int H, int W, int p, int D, const
     }
   }
   StageTimer tm(DCHAG_STAGE_BWD_TOKENIZE, st);
+  if (tiles) {
+    auto run = pp == 64 ? linear_tiles_backward<64> : linear_tiles_backward<16>;
+    return run(B, C, H, W, D, lv, x, We, be, ce, dy, dx, dWe, dtok_bias, dmix, static_cast<bf16*>(gr->dbv), scratch, lt, st);
+  }
   if (want_p) {
     if ((rc = patch_rows<bf16, false>(pixels, H, W, p, const_cast<bf16*>(x), patches, st))) return rc;
     GemmDesc d{};                                                 // P[c][d][kk] = sum_{b,n} dy[b,k,n,d] patch[b,c,n,kk]
@@ -1333,22 +1419,6 @@ inline size_t train_ws_bytes(dchag_dtype dt, int B, int C, int N, int p, int D, 
     total = std::max(total, backward_ws(dt, B, C, N, p * p, D, heads, n_levels, gs, nullptr, true).total);
   return total;
 }
-
-inline TileWork pixel_tiles(int fast, int slow, int nb, int G) {
-  TileWork tw{};
-  tw.n_tiles = fast; tw.m_tiles = slow; tw.nb = nb; tw.total = fast * slow * nb * G;
-  return tw;
-}
-inline unsigned tile_grid(const TileWork& tw) { return (unsigned)((tw.total + kXcds - 1) / kXcds * kXcds); }
-
-inline int transpose_rows(int batch, int R, int RT, int Cc, const bf16* in, bf16* out, hipStream_t st) {
-  k_transpose<<<dim3((unsigned)((RT + 63) / 64), (unsigned)((Cc + 255) / 256), (unsigned)batch), 256, 0, st>>>(R, RT, Cc, in,
-                                                                                                            out);
-  return launch_status();
-}
-
-template <class K>
-int raise_pair_lds(K kern) { return ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kPairLdsBytes); }
 
 // Forward half: folded weights (both layouts), softmax weights from the pixels, o; y is left to the caller.
 template <int PP>
@@ -1639,7 +1709,7 @@ int reverse_sweep(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int 
                                    static_cast<const bf16*>(We), static_cast<const bf16*>(be),
                                    static_cast<const bf16*>(ce), dy, static_cast<bf16*>(dx), static_cast<bf16*>(dWe),
                                    static_cast<bf16*>(dtok_bias), reinterpret_cast<bf16*>(ws + w.patches),
-                                   ws + w.tokens, st);
+                                   ws + w.tokens, w.patches - w.tokens, st);
         set_level(0);
         return rc;
       }

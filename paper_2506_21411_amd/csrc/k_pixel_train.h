@@ -135,6 +135,74 @@ __device__ __forceinline__ void pair_products(f32x16 (&acc)[2][2], const bf16x8 
     for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
 }
 
+// Four adjacent rows of a column (a register quad of an accumulator block: lane = column) as two packed words.
+struct Quad { unsigned w[2]; };
+__device__ __forceinline__ Quad pack_quad(const bf16x4& v) { return __builtin_bit_cast(Quad, v); }
+
+// Rows of two quads q, q + 1 dealt so that a lane holds eight adjacent rows, lanes 0 .. 31 those of quad q (rows 0 .. 7), lanes
+// 32 .. 63 those of quad q + 1 (rows 8 .. 15): 16-byte accesses where rows are contiguous, half as many.
+__device__ __forceinline__ bf16x8 join_quads(const bf16x4& a, const bf16x4& b) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  const Quad x = pack_quad(a), y = pack_quad(b);
+  const u32x2 s0 = __builtin_amdgcn_permlane32_swap(x.w[0], y.w[0], false, false);
+  const u32x2 s1 = __builtin_amdgcn_permlane32_swap(x.w[1], y.w[1], false, false);
+  return __builtin_bit_cast(bf16x8, u32x4{s0[0], s1[0], s0[1], s1[1]});
+}
+// The inverse: eight adjacent rows of a column (lanes as above) to the quads of the accumulator layout.
+__device__ __forceinline__ void split_quads(const bf16x8& v, bf16x4& a, bf16x4& b) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  const u32x4 w = __builtin_bit_cast(u32x4, v);
+  const u32x2 s0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+  const u32x2 s1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+  a = __builtin_bit_cast(bf16x4, u32x2{s0[0], s1[0]});
+  b = __builtin_bit_cast(bf16x4, u32x2{s0[1], s1[1]});
+}
+// A quad of rows x four adjacent columns (four adjacent lanes) transposed: lane l of the four holds row l, columns 0 .. 3, so that
+// a row leaves in 8-byte pieces instead of 2-byte ones.
+__device__ __forceinline__ bf16x4 transpose_quad(const bf16x4& v, int lane) {
+  const Quad q = pack_quad(v);
+  const bool b1 = lane & 2, b0 = lane & 1;
+  const unsigned send = b1 ? q.w[0] : q.w[1];
+  const unsigned recv = (unsigned)__builtin_amdgcn_update_dpp(0, (int)send, kDppSwapHalves, 0xF, 0xF, true);
+  const unsigned x = b1 ? recv : q.w[0], y = b1 ? q.w[1] : recv;      // this lane's two rows of column l & 1, and of that + 2
+  const unsigned xp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, kDppSwapPairs, 0xF, 0xF, true);
+  const unsigned yp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)y, kDppSwapPairs, 0xF, 0xF, true);
+  Quad o;
+  o.w[0] = b0 ? (xp >> 16) | (x & 0xFFFF0000u) : (x & 0xFFFFu) | (xp << 16);
+  o.w[1] = b0 ? (yp >> 16) | (y & 0xFFFF0000u) : (y & 0xFFFFu) | (yp << 16);
+  return __builtin_bit_cast(bf16x4, o);
+}
+
+// Column block j of a wavefront's 64 rows (member, pixel) from `row` on, lane = patch n, into the image: 16 rows are two 8-pixel rows
+// of a patch (8 x 8: a lane each) or a whole 4 x 4 patch.
+template <int PP>
+__device__ __forceinline__ void store_patch(const PixelDims& d, int b, int c0, int gk, int n, int row, int j,
+                                            const f32x16 (&acc)[2][2], int lhi, bf16* __restrict__ dx) {
+  constexpr int P = PP == 64 ? 8 : 4;
+  const int pw = d.W / P, pi = n / pw, pj = n % pw;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r0 = row + i * 32 + 16 * h, cl = r0 / PP, k0 = r0 % PP;
+      if (cl >= gk) continue;                              // uniform over the wavefront
+      bf16x4 v[2];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q >> 2][q & 3] = (bf16)acc[i][j][8 * h + q];
+      const bf16x8 v8 = join_quads(v[0], v[1]);
+      if (n >= d.N) continue;
+      bf16* dst = dx + (((size_t)b * d.C + c0 + cl) * d.H + pi * P) * d.W + pj * P;
+      if (PP == 64) {
+        *reinterpret_cast<bf16x8*>(dst + (size_t)(k0 / 8 + lhi) * d.W) = v8;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) *reinterpret_cast<bf16x4*>(dst + (size_t)(2 * q + lhi) * d.W) = v[q];
+      }
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // out[batch][c][r] = in[batch][r][c], zeros for R <= r < RT.  A wavefront takes a 64 x 64 tile: a lane reads eight rows of
 // one 8-column chunk (128 contiguous bytes per row and eight lanes), transposes the 8 x 8 block in registers and writes
@@ -164,7 +232,7 @@ __global__ __launch_bounds__(256) void k_transpose(int R, int RT, int Cc, const 
 }
 
 // ---------------------------------------------------------------------------------------
-// Patches with the patch index contiguous, UT[b,c,kk,n] (pitch NT, zeros past N), and for 4 x 4 patches also member-major
+// Patches with the patch index contiguous, UT[b,c,kk,n] (pitch NT, zeros past N), and for 4 x 4 patches also (where asked for) member-major
 // patch rows Ug[b,k,n,(member, pixel)] (pitch gq * 16, zeros for missing members).  A lane takes eight patches x eight
 // pixels of one channel.  grid (ceil(NT/64), ceil(G gq pp/8 / 32), B), block 256.
 // ---------------------------------------------------------------------------------------
@@ -197,7 +265,7 @@ __global__ __launch_bounds__(256) void k_pixel_rows(PixelDims d, const bf16* __r
         for (int e = 0; e < 4; ++e) { v[i][e] = lo[e]; v[i][4 + e] = hi[e]; }
       }
     }
-    if (P == 4 && n < d.N)
+    if (P == 4 && Ug && n < d.N)
       *reinterpret_cast<bf16x8*>(Ug + (((size_t)b * d.G + k) * d.N + n) * (d.gq * 16) + cl * 16 + kc * 8) = v[i];
   }
   if (!live) return;
@@ -602,23 +670,10 @@ __global__ __launch_bounds__(512) void k_pixel_dx(PixelDims d, TileWork tw, int 
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bb[j], kk % (4 / HH) == 0 ? zero : acc[i][j], 0, 0, 0);
       },
       [&](int) { scale_in(HH - 1); });
-  const int pw = d.W / P;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int n = nt * Lane::COLS + L.wn * 64 + j * 32 + L.l32;
-    if (n >= N) continue;
-    const int pi = n / pw, pj = n % pw;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r0 = mt * Lane::ROWS + L.wm * 64 + i * 32 + 8 * q + 4 * L.lhi, cl = r0 / PP, kk = r0 % PP;
-        if (cl >= gk) continue;
-        bf16x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (bf16)o[i][j][4 * q + e];
-        *reinterpret_cast<bf16x4*>(dx + (((size_t)b * d.C + c0 + cl) * d.H + pi * P + kk / P) * d.W + pj * P + kk % P) = v;
-      }
+    store_patch<PP>(d, b, c0, gk, n, mt * Lane::ROWS + L.wm * 64, j, o, L.lhi, dx);
   }
 }
 
@@ -639,7 +694,6 @@ __device__ __forceinline__ void store_outer(const PixelDims& d, int k, int r0, i
 #pragma unroll
   for (int e = 0; e < 4; ++e) ET[((size_t)k * d.RE + r0 + e) * d.D + col] = v[e];
 }
-
 template <int PP, bool H32>
 __global__ __launch_bounds__(512) void k_pixel_outer(PixelDims d, TileWork tw, int splits, const bf16* __restrict__ UT,
                                                         const bf16* __restrict__ dOT, const float* __restrict__ alpha,
@@ -960,18 +1014,22 @@ __global__ __launch_bounds__(512) void k_pixel_dwe(PixelDims d, TileWork tw, con
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r0 = mt * 128 + L.wm * 64 + i * 32 + 8 * q + 4 * L.lhi;
-        bf16x4 v;
+      for (int h = 0; h < 2; ++h) {
+        const int r0 = mt * 128 + L.wm * 64 + i * 32 + 16 * h;    // 16 rows: of one member, or all behind the pixels' rows
+        bf16x4 v[2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (bf16)acc[i][j][4 * q + e];
+        for (int q = 0; q < 8; ++q) v[q >> 2][q & 3] = (bf16)acc[i][j][8 * h + q];
         if (r0 < rows) {
           const int cl = r0 / PP;
-          if (dWe && cl < gk) *reinterpret_cast<bf16x4*>(dWe + ((size_t)(c0 + cl) * D + col) * PP + r0 % PP) = v;
+          const bf16x8 v8 = join_quads(v[0], v[1]);
+          if (dWe && cl < gk)
+            *reinterpret_cast<bf16x8*>(dWe + ((size_t)(c0 + cl) * D + col) * PP + r0 % PP + 8 * L.lhi) = v8;
         } else if (dtb) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (r0 - rows + e < gk) dtb[(size_t)(c0 + r0 - rows + e) * D + col] = v[e];
+          for (int q = 0; q < 8; ++q) {
+            const int m = r0 - rows + 8 * (q >> 2) + 4 * L.lhi + (q & 3);
+            if (m < gk) dtb[(size_t)(c0 + m) * D + col] = v[q >> 2][q & 3];
+          }
         }
       }
   }
@@ -1045,6 +1103,153 @@ __global__ __launch_bounds__(512) void k_pixel_dwv(PixelDims d, TileWork tw, int
         const int row = mt * 128 + L.wm * 64 + i * 32 + 8 * (q >> 2) + 4 * L.lhi + (q & 3);
         dWv[((size_t)k * D + row) * D + col] = (bf16)acc[i][j][q];
       }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// Reverse step of a LINEAR first level from the pixels (formulas at k_linear_first_grads), both products on pair_loop.
+// k_linear_outer: P[(member, pixel)][d] = sum_n u[n] dy[n][d] over all patches (UT, dyT: patch index contiguous), tile rows
+// (member, pixel), columns d; P stays in the accumulators and leaves as dWe = mix P, dmix = sum_pixels We P + (be + ce) S,
+// dtok_bias = mix S, dbias = S and the scaled weights WsT[(member, pixel)][d] = mix We that k_linear_dx contracts dy with.
+// Any gradient pointer may be NULL.  512 bands, 4 x 256 patches, D 1024: the per-channel products (1024 x 64 outputs each, operands
+// transposed in registers on every load), the pass over P and two copies between image and patch rows took 430 us; these kernels and
+// the two transposes before them take 265 (k_linear_outer 129, of which about 40 for the weights and gradients its epilogue moves;
+// k_linear_dx 88; transposes 11 + 37).
+// ---------------------------------------------------------------------------------------
+template <int PP>
+__global__ __launch_bounds__(512) void k_linear_outer(PixelDims d, TileWork tw, const bf16* __restrict__ UT,
+                                                      const bf16* __restrict__ dyT, const float* __restrict__ S,
+                                                      const bf16* __restrict__ We, const bf16* __restrict__ be,
+                                                      const bf16* __restrict__ ce, const bf16* __restrict__ mix,
+                                                      bf16* __restrict__ dWe, bf16* __restrict__ dtok_bias,
+                                                      bf16* __restrict__ dmix, bf16* __restrict__ dbias,
+                                                      bf16* __restrict__ WsT) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  int k, b, mt, nt;
+  if (!tw.decode(blockIdx.x, k, b, nt, mt)) return;        // mt: rows (fastest: they share the rows of dyT)
+  const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, rows = gk * PP;
+  if (mt * 128 >= rows) return;                            // uniform: a short last group has fewer rows
+  PairLane<2> L;
+  L.init();
+  const bf16 *pa[2], *pb[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = L.row_a(i);
+    pa[i] = UT + ((size_t)c0 * PP + min(mt * 128 + row, rows - 1)) * d.NT + L.chunk(row) * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = L.row_b(i);
+    pb[i] = dyT + ((size_t)k * D + nt * 256 + row) * d.NT + L.chunk(row) * 8;
+  }
+  const int nsl = d.NT / 64;
+  f32x16 acc[2][2];
+  zero_acc(acc);
+  pair_loop<2>(
+      smem, 0, d.B * nsl, L,
+      [&](int s, unsigned char* st) {
+        const int bb = s / nsl, n0 = (s % nsl) * 64;
+        const size_t oa = (size_t)bb * d.C * PP * d.NT + n0, ob = (size_t)bb * d.G * D * d.NT + n0;
+        const bf16 *qa[2], *qb[4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) qa[i] = pa[i] + oa;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qb[i] = pb[i] + ob;
+        L.fill(qa, qb, st);
+      },
+      [&](int, int, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char*) { pair_products(acc, a, bb); },
+      [](int) {});
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int col = nt * 256 + L.wn * 64 + j * 32 + L.l32;
+    const float sv = S[(size_t)k * D + col];
+    if (dbias && mt == 0 && L.wm == 0 && L.lhi == 0) dbias[(size_t)k * D + col] = (bf16)sv;
+    float dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {                        // 16 rows: of one member
+        const int r0 = mt * 128 + L.wm * 64 + i * 32 + 16 * h, cl = r0 / PP;
+        if (cl >= gk) continue;                            // uniform over the wavefront
+        const size_t cd = (size_t)(c0 + cl) * D + col;
+        const float sm = (float)mix[cd];
+        const int k0 = r0 % PP;                            // pixels k0 .. k0 + 15: quads 2 h and 2 h + 1 of the block
+        bf16x4 w[2], gw[2];
+        split_quads(*reinterpret_cast<const bf16x8*>(We + cd * PP + k0 + 8 * L.lhi), w[0], w[1]);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          bf16x4 t;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float pv = acc[i][j][8 * h + 4 * q + e];
+            dot += (float)w[q][e] * pv;
+            gw[q][e] = (bf16)(sm * pv);
+            t[e] = (bf16)((float)w[q][e] * sm);
+          }
+          if (WsT) {
+            const int kk = k0 + 8 * q + 4 * L.lhi + (L.lane & 3);
+            *reinterpret_cast<bf16x4*>(WsT + ((size_t)(c0 + cl) * PP + kk) * D + (col & ~3)) = transpose_quad(t, L.lane);
+          }
+        }
+        const bf16x8 g8 = join_quads(gw[0], gw[1]);
+        if (dWe) *reinterpret_cast<bf16x8*>(dWe + cd * PP + k0 + 8 * L.lhi) = g8;
+        if (PP == 16 || (i == 1 && h == 1)) {              // the member's last rows
+          dot += __shfl_xor(dot, 32, kWave);
+          if (L.lhi == 0) {
+            float bias = 0.f;
+            if (be) bias += (float)be[cd];
+            if (ce) bias += (float)ce[cd];
+            if (dmix) dmix[cd] = (bf16)(dot + bias * sv);
+            if (dtok_bias) dtok_bias[cd] = (bf16)(sm * sv);
+          }
+          dot = 0.f;
+        }
+      }
+  }
+}
+
+// dx[b,c,pixel of patch n] = sum_d WsT[(c, pixel)][d] dy[b,k,n][d], written into the image.  Tile rows (member, pixel), columns
+// patches.
+template <int PP, int WM>
+__global__ __launch_bounds__(512) void k_linear_dx(PixelDims d, TileWork tw, const bf16* __restrict__ WsT,
+                                                   const bf16* __restrict__ dy, bf16* __restrict__ dx) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  int k, b, mt, nt;
+  if (!tw.decode(blockIdx.x, k, b, nt, mt)) return;        // nt: patches, mt: rows (fastest: they share the rows of dy)
+  constexpr int P = PP == 64 ? 8 : 4;
+  const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, N = d.N, rows = gk * PP;
+  typedef PairLane<WM> Lane;
+  if (mt * Lane::ROWS >= rows) return;                     // uniform
+  Lane L;
+  L.init();
+  const bf16 *pa[Lane::AL], *pb[Lane::BL];
+#pragma unroll
+  for (int i = 0; i < Lane::AL; ++i) {
+    const int row = L.row_a(i);
+    pa[i] = WsT + ((size_t)c0 * PP + min(mt * Lane::ROWS + row, rows - 1)) * D + L.chunk(row) * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < Lane::BL; ++i) {
+    const int row = L.row_b(i);
+    pb[i] = dy + (((size_t)b * d.G + k) * N + min(nt * Lane::COLS + row, N - 1)) * D + L.chunk(row) * 8;
+  }
+  f32x16 acc[2][2];
+  zero_acc(acc);
+  pair_loop<WM>(
+      smem, 0, D / 64, L,
+      [&](int, unsigned char* st) {
+        L.fill(pa, pb, st);
+#pragma unroll
+        for (int i = 0; i < Lane::AL; ++i) pa[i] += 64;
+#pragma unroll
+        for (int i = 0; i < Lane::BL; ++i) pb[i] += 64;
+      },
+      [&](int, int, const bf16x8 (&a)[2], const bf16x8 (&bb)[2], const unsigned char*) { pair_products(acc, a, bb); },
+      [](int) {});
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int n = nt * Lane::COLS + L.wn * 64 + j * 32 + L.l32;
+    store_patch<PP>(d, b, c0, gk, n, mt * Lane::ROWS + L.wm * 64, j, acc, L.lhi, dx);
   }
 }
 
