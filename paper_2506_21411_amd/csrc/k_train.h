@@ -241,6 +241,129 @@ __global__ __launch_bounds__(256) void k_dz_attention(int Cin, int N, int D, int
 }
 
 // ---------------------------------------------------------------------------------------
+// The two kernels above, fp32, by groups: w[b,k,n] is read once for all members of its group instead of once per member.
+// k_dalpha_group: one wavefront per (b, k, n), 16 members x 16 heads a tile on v_mfma_f32_16x16x4f32 (a lane's 16-byte load feeds
+// four of them: any assignment of features to contraction steps serves as long as both operands share it), the softmax Jacobian
+// over the members behind it: ds[c,a] = alpha[c,a] (dalpha[c,a] - sum_c' alpha[c',a] dalpha[c',a]).  Groups of up to 16 MT.
+// grid ceil(B G N / 4), block 256.  D % 16 == 0.  Bound by the read of w and z (80 variables, 512 patches, D 512, 8 heads: 168 MB;
+// 37 us, one wavefront per token and a softmax pass 137 + 7).
+// ---------------------------------------------------------------------------------------
+template <int MT>
+__global__ __launch_bounds__(256) void k_dalpha_group(long items, int Cin, int N, int D, int heads, int g, int G,
+                                                      const float* __restrict__ z, const float* __restrict__ w,
+                                                      const float* __restrict__ alpha, float* __restrict__ ds) {
+  const long item = (long)blockIdx.x * 4 + (threadIdx.x >> 6);     // (b * G + k) * N + n
+  if (item >= items) return;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int n = (int)(item % N), k = (int)((item / N) % G), b = (int)(item / ((long)N * G));
+  const int c0 = k * g, gk = min(g, Cin - c0);
+  const size_t cstride = (size_t)N * D;
+  const float* zb = z + (((size_t)b * Cin + c0) * N + n) * D + lq * 4;
+  for (int a0 = 0; a0 < heads; a0 += 16) {
+    const float* wr = w + ((size_t)item * heads + min(a0 + l16, heads - 1)) * D + lq * 4;
+    const float* zr[MT];
+    f32x4 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      zr[mt] = zb + (size_t)min(mt * 16 + l16, gk - 1) * cstride;
+      acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int t = 0; t < D; t += 64) {                              // four steps of 16 per trip, loads first
+      f32x4 wf[4], zf[MT][4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int tt = min(t + q * 16, D - 16);
+        wf[q] = *reinterpret_cast<const f32x4*>(wr + tt);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) zf[mt][q] = *reinterpret_cast<const f32x4*>(zr[mt] + tt);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (t + q * 16 < D) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+              acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(zf[mt][q][e], wf[q][e], acc[mt], 0, 0, 0);
+        }
+    }
+    // accumulator block: lane holds head lane % 16, members 4 (lane / 16) + 0..3 of the tile
+    float al[MT][4];
+    float dot = 0.f;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int cl = mt * 16 + lq * 4 + r;
+        al[mt][r] = (cl < gk && a0 + l16 < heads)
+                        ? alpha[(((size_t)b * Cin + c0 + cl) * N + n) * heads + a0 + l16] : 0.f;
+        dot += al[mt][r] * acc[mt][r];
+      }
+    dot += __shfl_xor(dot, 16, kWave);
+    dot += __shfl_xor(dot, 32, kWave);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int cl = mt * 16 + lq * 4 + r;
+        if (cl < gk && a0 + l16 < heads)
+          ds[(((size_t)b * Cin + c0 + cl) * N + n) * heads + a0 + l16] = al[mt][r] * (acc[mt][r] - dot);
+      }
+  }
+}
+
+// k_dz_group: a block takes PN patches of one (b, k); an item is (patch, 4 columns), its HB head rows of w and of the keys in registers,
+// the members' weights and score gradients broadcast from LDS.  heads <= HB, D % 4 == 0.  grid (ceil(N/PN), G, B), block 256,
+// dynamic LDS PN g 2 HB floats.  Bound by the read of w and the write of dz (same shape: 168 MB; 28 us, a block per token 137).
+template <int HB, int PN>
+__global__ __launch_bounds__(256) void k_dz_group(int Cin, int N, int D, int heads, int g, const float* __restrict__ alpha,
+                                                  const float* __restrict__ ds, const float* __restrict__ w,
+                                                  const float* __restrict__ Mf, float* __restrict__ dz) {
+  extern __shared__ __attribute__((aligned(16))) float wt[];       // [patch][member][alpha HB, ds HB]
+  const int k = blockIdx.y, b = blockIdx.z, G = gridDim.y, n0 = blockIdx.x * PN;
+  const int c0 = k * g, gk = min(g, Cin - c0);
+  for (int idx = threadIdx.x; idx < PN * gk * HB; idx += 256) {
+    const int a = idx % HB, t = idx / HB, p = t % PN, cl = t / PN;
+    const bool live = a < heads && n0 + p < N;
+    const size_t o = (((size_t)b * Cin + c0 + cl) * N + min(n0 + p, N - 1)) * heads + min(a, heads - 1);
+    float* q = wt + ((size_t)p * gk + cl) * 2 * HB + a;
+    q[0] = live ? alpha[o] : 0.f;
+    q[HB] = live ? ds[o] : 0.f;
+  }
+  __syncthreads();
+  const int DC = D / 4;
+  for (int it = threadIdx.x; it < PN * DC; it += 256) {
+    const int d0 = (it % DC) * 4, p = it / DC, n = n0 + p;
+    if (n >= N) break;
+    const float* wr = w + ((((size_t)b * G + k) * N + n) * heads) * D + d0;
+    const float* mr = Mf + (size_t)k * heads * D + d0;
+    f32x4 wv[HB], mv[HB];
+#pragma unroll
+    for (int a = 0; a < HB; ++a) {
+      wv[a] = mv[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (a < heads) {
+        wv[a] = *reinterpret_cast<const f32x4*>(wr + (size_t)a * D);
+        mv[a] = *reinterpret_cast<const f32x4*>(mr + (size_t)a * D);
+      }
+    }
+    float* out = dz + (((size_t)b * Cin + c0) * N + n) * D + d0;
+    for (int cl = 0; cl < gk; ++cl) {
+      const f32x4* q = reinterpret_cast<const f32x4*>(wt + ((size_t)p * gk + cl) * 2 * HB);
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < HB / 4; ++t) {
+        const f32x4 al = q[t], dv = q[HB / 4 + t];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] += al[a] * wv[t * 4 + a][e] + dv[a] * mv[t * 4 + a][e];
+      }
+      *reinterpret_cast<f32x4*>(out + (size_t)cl * N * D) = acc;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // Column sums over the rows of every group:  out[k][i] = sum_b sum_{r < rows_of(k)} X[first_row(b,k) + r][i]
 // grid (ceil(D/64), G), block 1024: a block owns 64 columns; lane l of a wavefront takes the 4 columns 4 (l % 16) .. of
 // row 4 wave + l / 16 and every 64th row after it (one 8- or 16-byte load per row); the four row groups of a

@@ -69,6 +69,10 @@ PRODUCTS = [
     dict(dtype="f32", B=2, C=9, H=2, W=14, p=2, D=136, heads=8, group_sizes=(4, 3)),
     # 5 heads (rows of 5 floats: no 16-byte loads), 33 patches, 40 columns
     dict(dtype="f32", B=1, C=11, H=6, W=22, p=2, D=40, heads=5, group_sizes=(11,)),
+    # f32 by groups: 35 members (three tiles of 16, one of them past the group) + 1, 17 heads (two blocks; no dz by groups), 272 columns
+    dict(dtype="f32", B=1, C=36, H=6, W=10, p=2, D=272, heads=17, group_sizes=(35, 2)),
+    # 20 members + 9, 12 heads (three quarters of a block), an odd number of patches
+    dict(dtype="f32", B=2, C=29, H=6, W=6, p=2, D=48, heads=12, group_sizes=(20, 2)),
     # a contraction over 16 x 200 tokens dealt to several blocks, the last group shorter (13 members)
     dict(dtype="f32", B=1, C=29, H=40, W=80, p=4, D=64, heads=2, group_sizes=(16, 2)),
 ]
