@@ -581,6 +581,13 @@ inline bool values_from_pixels(dchag_dtype dt, int p, int D, int heads, const dc
 }
 
 // The weight-only part: fold (value_fold_bytes(C, D, p*p) bytes) receives Wf [C,D,p*p] and Wv (be + ce) [C,D].
+// Two row tiles a block share the members' vectors once that leaves four blocks to a compute unit.
+inline int fold_token_bias(int C, int D, int g, const bf16* Wv, const bf16* be, const bf16* ce, bf16* fb, hipStream_t st) {
+  const int G = groups_of(C, g);
+  if ((long)(D / 64) * G >= 4L * compute_units()) k_fold_token_bias<2><<<dim3(D / 64, G), 256, 0, st>>>(C, D, g, Wv, be, ce, fb);
+  else k_fold_token_bias<1><<<dim3(D / 32, G), 256, 0, st>>>(C, D, g, Wv, be, ce, fb);
+  return launch_status();
+}
 inline int fold_value_weights(int C, int p, int D, const dchag_level* lv, const bf16* We, const bf16* be, const bf16* ce,
                               unsigned char* fold, hipStream_t st) {
   const int g = lv->group_size, G = groups_of(C, g), pp = p * p;
@@ -613,9 +620,9 @@ inline int fold_value_weights(int C, int p, int D, const dchag_level* lv, const 
     d.scale = 1.f;
     if ((rc = gemm_per_channel<bf16>(d, C, g, (long)D * D, (long)D * pp, (long)D * pp, Wv, We, Wf, st))) return rc;
   }
-  if ((be || ce) && aligned16(Wv) && aligned16(be) && aligned16(ce) && G <= 65535 && !dbg(SW_FOLD_VALUE_GEMM)) {
-    k_fold_token_bias<<<dim3(D / 32, G), 256, 0, st>>>(C, D, g, Wv, be, ce, fb);
-    if ((rc = launch_status())) return rc;
+  if ((be || ce) && aligned16(Wv) && aligned16(be) && aligned16(ce) && G <= 65535 && D % 256 == 0 &&
+      !dbg(SW_FOLD_VALUE_GEMM)) {
+    if ((rc = fold_token_bias(C, D, g, Wv, be, ce, fb, st))) return rc;
   } else if (be || ce) {
     // (Wv (be + ce))[c](o) = sum over the vectors v present, sum_d v[c](d) Wv[k](o, d): one product whose batch
     // index walks from be to ce (their distance in elements, taken on the integer addresses: the two are separate
@@ -1468,8 +1475,7 @@ int pixel_level_forward(int B, int C, int H, int W, int p, int D, int heads, con
       k_pixel_fold<<<dim3(tile_grid(tw)), 512, kPairLdsBytes, st>>>(d, tw, at(w.wet), Wv, Wf, at(w.wft), at(w.wg));
       if ((rc = launch_status())) return rc;
       if (be || ce) {
-        k_fold_token_bias<<<dim3(D / 32, d.G), 256, 0, st>>>(C, D, d.g, Wv, be, ce, fb);
-        if ((rc = launch_status())) return rc;
+        if ((rc = fold_token_bias(C, D, d.g, Wv, be, ce, fb, st))) return rc;
       }
     }
   }
