@@ -234,7 +234,8 @@ __global__ __launch_bounds__(256) void k_transpose(int R, int RT, int Cc, const 
 // ---------------------------------------------------------------------------------------
 // Patches with the patch index contiguous, UT[b,c,kk,n] (pitch NT, zeros past N), and for 4 x 4 patches also (where asked for) member-major
 // patch rows Ug[b,k,n,(member, pixel)] (pitch gq * 16, zeros for missing members).  A lane takes eight patches x eight
-// pixels of one channel.  grid (ceil(NT/64), ceil(G gq pp/8 / 32), B), block 256.
+// pixels of one channel.  8 x 8 patches: eight lanes load 128 contiguous bytes of an image row and trade patches through LDS (each
+// lane its own eight patches, 128 bytes, overran the L1 by the time the line's last 16 were wanted: 512 bands, 67 MB each way, 38 -> 25 us).  grid (ceil(NT/64), ceil(G gq pp/8 / 32), B), block 256.
 // ---------------------------------------------------------------------------------------
 template <int P>
 __global__ __launch_bounds__(256) void k_pixel_rows(PixelDims d, const bf16* __restrict__ x, bf16* __restrict__ UT,
@@ -250,23 +251,37 @@ __global__ __launch_bounds__(256) void k_pixel_rows(PixelDims d, const bf16* __r
   const int pw = d.W / P;
   const bf16* img = x + ((size_t)b * d.C + min(c, d.C - 1)) * d.H * d.W;
   bf16x8 v[8];
+  if constexpr (P == 8) {
+    __shared__ bf16x8 st[4][512];
+    const int o = lane & 7;
+    bf16x8* row = st[wave] + (lane >> 3) * 64;              // the 64 patches of this lane's pixel row
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    v[i] = bf16x8{};
-    const int n = n0 + i;
-    if (live && n < d.N) {
-      const int pi = n / pw, pj = n % pw;
-      if (P == 8) {
-        v[i] = *reinterpret_cast<const bf16x8*>(img + (size_t)(pi * 8 + kc) * d.W + pj * 8);
-      } else {
+    for (int i = 0; i < 8; ++i) {
+      v[i] = bf16x8{};
+      const int n = blockIdx.x * 64 + i * 8 + o;
+      if (live && n < d.N) v[i] = *reinterpret_cast<const bf16x8*>(img + (size_t)((n / pw) * 8 + kc) * d.W + (n % pw) * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) row[i * 8 + (o ^ i)] = v[i];
+    asm volatile("" ::: "memory");                          // the wavefront's own LDS accesses stay in order
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = row[o * 8 + (i ^ o)];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[i] = bf16x8{};
+      const int n = n0 + i;
+      if (live && n < d.N) {
+        const int pi = n / pw, pj = n % pw;
         const bf16x4 lo = *reinterpret_cast<const bf16x4*>(img + (size_t)(pi * 4 + 2 * kc) * d.W + pj * 4);
         const bf16x4 hi = *reinterpret_cast<const bf16x4*>(img + (size_t)(pi * 4 + 2 * kc + 1) * d.W + pj * 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v[i][e] = lo[e]; v[i][4 + e] = hi[e]; }
       }
+      if (Ug && n < d.N)
+        *reinterpret_cast<bf16x8*>(Ug + (((size_t)b * d.G + k) * d.N + n) * (d.gq * 16) + cl * 16 + kc * 8) = v[i];
     }
-    if (P == 4 && Ug && n < d.N)
-      *reinterpret_cast<bf16x8*>(Ug + (((size_t)b * d.G + k) * d.N + n) * (d.gq * 16) + cl * 16 + kc * 8) = v[i];
   }
   if (!live) return;
   bf16* dst = UT + (((size_t)b * d.C + c) * (P * P) + kc * 8) * d.NT + n0;
@@ -1113,8 +1128,8 @@ __global__ __launch_bounds__(512) void k_pixel_dwv(PixelDims d, TileWork tw, int
 // dtok_bias = mix S, dbias = S and the scaled weights WsT[(member, pixel)][d] = mix We that k_linear_dx contracts dy with.
 // Any gradient pointer may be NULL.  512 bands, 4 x 256 patches, D 1024: the per-channel products (1024 x 64 outputs each, operands
 // transposed in registers on every load), the pass over P and two copies between image and patch rows took 430 us; these kernels and
-// the two transposes before them take 265 (k_linear_outer 129, of which about 40 for the weights and gradients its epilogue moves;
-// k_linear_dx 88; transposes 11 + 37).
+// the two transposes before them take 252 (k_linear_outer 129, of which about 40 for the weights and gradients its epilogue moves;
+// k_linear_dx 88; transposes 11 + 25).
 // ---------------------------------------------------------------------------------------
 template <int PP>
 __global__ __launch_bounds__(512) void k_linear_outer(PixelDims d, TileWork tw, const bf16* __restrict__ UT,
