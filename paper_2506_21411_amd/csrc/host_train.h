@@ -315,6 +315,13 @@ int launch_gemm_bf16(const GemmDesc& d0, const bf16* A, const bf16* Bm, const bf
 inline bool gemm_rowsum_ok(const GemmDesc& d) { return gemm_mfma_ok(d) && d.A.s1 != 1 && !dbg(SW_COLSUM); }
 
 // Y[r][o] = sum_j X[r][j] W[k][o][j] + bias[k][o] (+ rowadd[r][o]) over row blocks, as a product of the kernels above.
+// Row tiles lie on the grid's second dimension, so a row block of more rows than fit there keeps the kernels of k_generic.h.  A group
+// has no more rows than there are: a nominal group size may exceed the channel count.
+inline bool product_rows_ok(long rows) { return (rows + 63) / 64 <= 65535; }
+inline RowBlocks actual_rows(RowBlocks rb) {
+  rb.rows_per_group = std::min(rb.rows_per_group, rb.rows_per_b);
+  return rb;
+}
 inline GemmDesc linear_desc(int B, int D, RowBlocks rb, const void* rowadd) {
   GemmDesc d{};
   d.M = rb.rows_per_group; d.N = D; d.K = D; d.nb = B; d.nk = rb.G; d.na = 1;
@@ -329,15 +336,27 @@ inline GemmDesc linear_desc(int B, int D, RowBlocks rb, const void* rowadd) {
 }
 inline int linear_as_gemm(int B, int D, RowBlocks rb, const float* X, const float* W, const float* bias, float* Y,
                           hipStream_t st, const float* rowadd) {
+  rb = actual_rows(rb);
+  if (!product_rows_ok(rb.rows_per_group)) return launch_linear_generic<float>(B, D, rb, X, W, bias, Y, st, rowadd);
   return launch_gemm_f32(linear_desc(B, D, rb, rowadd), X, W, bias, Y, st);
 }
 inline int linear_as_gemm(int B, int D, RowBlocks rb, const bf16* X, const bf16* W, const bf16* bias, bf16* Y,
                           hipStream_t st, const bf16* rowadd) {
+  rb = actual_rows(rb);
+  if (!product_rows_ok(rb.rows_per_group)) return launch_linear_generic<bf16>(B, D, rb, X, W, bias, Y, st, rowadd);
   return launch_gemm_bf16<bf16>(linear_desc(B, D, rb, rowadd), X, W, bias, Y, st);
 }
 // Raw scores S[b,c,n,a] = z[b,c,n,:] . M[k][a][:] of the shape-generic path.
-inline int token_scores(int B, int Cin, int N, int D, int heads, int g, const float* z, const float* Mf, float* S,
+template <typename T>
+int scores_by_token(int B, int Cin, int N, int D, int heads, int g, const T* z, const float* Mf, float* S, hipStream_t st) {
+  const long T_total = (long)B * Cin * N;
+  k_scores_generic<T, 8><<<dim3((unsigned)((T_total + 3) / 4)), 256, 0, st>>>(T_total, Cin, N, D, heads, g, z, Mf, S);
+  return launch_status();
+}
+inline int token_scores(int B, int Cin, int N, int D, int heads, int g0, const float* z, const float* Mf, float* S,
                         hipStream_t st) {
+  const int g = std::min(g0, Cin);
+  if (!product_rows_ok((long)g * N)) return scores_by_token<float>(B, Cin, N, D, heads, g, z, Mf, S, st);
   GemmDesc d{};
   d.M = g * N; d.N = heads; d.K = D; d.nb = B; d.nk = groups_of(Cin, g); d.na = 1;
   d.ragged = 1; d.ragged_total = Cin * N; d.ragged_nominal = g * N;
@@ -349,9 +368,7 @@ inline int token_scores(int B, int Cin, int N, int D, int heads, int g, const fl
 }
 inline int token_scores(int B, int Cin, int N, int D, int heads, int g, const bf16* z, const float* Mf, float* S,
                         hipStream_t st) {
-  const long T_total = (long)B * Cin * N;
-  k_scores_generic<bf16, 8><<<dim3((unsigned)((T_total + 3) / 4)), 256, 0, st>>>(T_total, Cin, N, D, heads, g, z, Mf, S);
-  return launch_status();
+  return scores_by_token<bf16>(B, Cin, N, D, heads, g, z, Mf, S, st);
 }
 
 // Same-type products of the level kernels: MFMA for bf16 where it tiles, the fp32-FMA kernel otherwise.

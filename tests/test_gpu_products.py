@@ -98,3 +98,28 @@ def test_positional_embedding_is_added_by_the_products(kw):
     err = rel_err(host(out), want + host(pos_d)[None])
     say(f"  err {err:.3e}")
     assert err < TOL[d]
+
+
+# More rows a group than the row tiles of the products' grids hold (65535 tiles of 64 rows in fp32, of 128 in bf16): real ones, and
+# rows of members that a nominal group size larger than the channel count only promises.
+MANY_ROWS = [
+    dict(dtype="f32", B=1, C=65, H=256, W=256, p=1, D=8, heads=2, group_sizes=(65,)),
+    dict(dtype="f32", B=1, C=8, H=16, W=16, p=2, D=24, heads=3, group_sizes=(100000,)),
+    dict(dtype="bf16", B=1, C=8, H=16, W=16, p=2, D=24, heads=3, group_sizes=(300000,)),
+]
+
+
+@pytest.mark.parametrize("kw", MANY_ROWS)
+@pytest.mark.parametrize("call", ["forward", "folded"])
+def test_more_rows_than_the_grid_has_row_tiles(kw, call):
+    cfg = ShapeCfg(name="t", x_kind="gauss_mu_sigma", seed=13, **kw)
+    say(f"many rows, {call} {kw}")
+    pr = make_problem(cfg)
+    d = cfg.dtype
+    run = dchag.dchag_forward if call == "forward" else dchag.dchag_forward_folded
+    out = run(dev(pr.x, d), dev(pr.We, d), dev(pr.be, d), dev(pr.ce, d), [dev_level(lv, d) for lv in pr.levels], cfg.p,
+              cfg.heads)
+    n = np.unique(np.linspace(0, cfg.N - 1, 40).astype(np.int32))
+    want = oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads, sample=(np.zeros_like(n), n))
+    assert rel_err(host(out[0, torch.from_numpy(n).long().cuda()]), want) < TOL[d]
+    assert torch.isfinite(out.float()).all()
