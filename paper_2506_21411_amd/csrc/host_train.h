@@ -337,14 +337,18 @@ inline GemmDesc linear_desc(int B, int D, RowBlocks rb, const void* rowadd) {
 inline int linear_as_gemm(int B, int D, RowBlocks rb, const float* X, const float* W, const float* bias, float* Y,
                           hipStream_t st, const float* rowadd) {
   rb = actual_rows(rb);
-  if (!product_rows_ok(rb.rows_per_group)) return launch_linear_generic<float>(B, D, rb, X, W, bias, Y, st, rowadd);
+  if (!product_rows_ok(rb.rows_per_group) || dbg(SW_GEMM_GENERIC))
+    return launch_linear_generic<float>(B, D, rb, X, W, bias, Y, st, rowadd);
   return launch_gemm_f32(linear_desc(B, D, rb, rowadd), X, W, bias, Y, st);
 }
 inline int linear_as_gemm(int B, int D, RowBlocks rb, const bf16* X, const bf16* W, const bf16* bias, bf16* Y,
                           hipStream_t st, const bf16* rowadd) {
   rb = actual_rows(rb);
-  if (!product_rows_ok(rb.rows_per_group)) return launch_linear_generic<bf16>(B, D, rb, X, W, bias, Y, st, rowadd);
-  return launch_gemm_bf16<bf16>(linear_desc(B, D, rb, rowadd), X, W, bias, Y, st);
+  const GemmDesc d = linear_desc(B, D, rb, rowadd);
+  // k_gemm_generic, which launch_gemm_bf16 would fall back to, has no row addend
+  if (!product_rows_ok(rb.rows_per_group) || !gemm_mfma_ok(d))
+    return launch_linear_generic<bf16>(B, D, rb, X, W, bias, Y, st, rowadd);
+  return launch_gemm_bf16<bf16>(d, X, W, bias, Y, st);
 }
 // Raw scores S[b,c,n,a] = z[b,c,n,:] . M[k][a][:] of the shape-generic path.
 template <typename T>
@@ -356,7 +360,7 @@ int scores_by_token(int B, int Cin, int N, int D, int heads, int g, const T* z, 
 inline int token_scores(int B, int Cin, int N, int D, int heads, int g0, const float* z, const float* Mf, float* S,
                         hipStream_t st) {
   const int g = std::min(g0, Cin);
-  if (!product_rows_ok((long)g * N)) return scores_by_token<float>(B, Cin, N, D, heads, g, z, Mf, S, st);
+  if (!product_rows_ok((long)g * N) || dbg(SW_GEMM_GENERIC)) return scores_by_token<float>(B, Cin, N, D, heads, g, z, Mf, S, st);
   GemmDesc d{};
   d.M = g * N; d.N = heads; d.K = D; d.nb = B; d.nk = groups_of(Cin, g); d.na = 1;
   d.ragged = 1; d.ragged_total = Cin * N; d.ragged_nominal = g * N;
@@ -371,8 +375,10 @@ inline int token_scores(int B, int Cin, int N, int D, int heads, int g, const bf
   return scores_by_token<bf16>(B, Cin, N, D, heads, g, z, Mf, S, st);
 }
 
-// Same-type products of the level kernels: MFMA for bf16 where it tiles, the fp32-FMA kernel otherwise.
+// Same-type products of the level kernels: matrix instructions, for bf16 where they tile; the fp32-FMA kernel otherwise
+// (DCHAG_GEMM_GENERIC, a debugging aid: always).
 inline int gemm_tt(const GemmDesc& d, const float* A, const float* Bm, const float* bias, float* C, hipStream_t st) {
+  if (dbg(SW_GEMM_GENERIC)) return launch_gemm<float, float, float>(d, A, Bm, bias, C, st);
   return launch_gemm_f32(d, A, Bm, bias, C, st);
 }
 inline int gemm_tt(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias, bf16* C, hipStream_t st) {
@@ -389,7 +395,7 @@ inline int gemm_with_bias_grad(GemmDesc d, int B, int D, RowBlocks rb, const flo
     k_colsum<float, float><<<dim3((D + 63) / 64, rb.G), 1024, 0, st>>>(B, D, rb, X, db);
     if ((rc = launch_status())) return rc;
   }
-  return dW ? launch_gemm_f32(d, X, Y, nullptr, dW, st) : DCHAG_OK;
+  return dW ? gemm_tt(d, X, Y, nullptr, dW, st) : DCHAG_OK;
 }
 inline int gemm_with_bias_grad(GemmDesc d, int B, int D, RowBlocks rb, const bf16* X, const bf16* Y, bf16* dW, bf16* db,
                                hipStream_t st) {
@@ -992,20 +998,21 @@ int tokens_backward_generic(int B, int Cin, int N, int D, int heads, int g, cons
   d.C = {0, (long)heads * D, 0, (long)D, 1};
   d.scale = 1.f;
   if constexpr (std::is_same<T, float>::value) {
-    // few rows (heads) against a contraction over all tokens of a group: dealt to enough blocks to fill the chip, at least
-    // four slices of 32 tokens each and no more partial sums than the tiles the buffer is sized for
-    const int pt = dz_patches(B, G, N, D, g), n_tiles = (N + pt - 1) / pt;
-    const long blocks = (long)((D + 63) / 64) * ((heads + 63) / 64) * B * G;
-    int S = 1;
-    while (blocks * S < 4L * compute_units() && 2 * S <= n_tiles && (long)g * N / 32 >= 8L * S && B * G * 2L * S <= 65535) S *= 2;
-    const long per = (long)heads * D;
-    d.reduce_b = 0;
-    d.C = {(long)G * S * per, (long)S * per, 0, (long)D, 1};
-    if ((rc = launch_gemm_f32(d, ds, zin, nullptr, rpart, st, S, per))) return rc;
-    return sum_key_path_partials(B, G, S, heads, D, rpart, r, st);
-  } else {
-    return launch_gemm<float, T, float>(d, ds, zin, nullptr, r, st);
+    if (!dbg(SW_GEMM_GENERIC)) {
+      // few rows (heads) against a contraction over all tokens of a group: dealt to enough blocks to fill the chip, at least
+      // four slices of 32 tokens each and no more partial sums than the tiles the buffer is sized for
+      const int pt = dz_patches(B, G, N, D, g), n_tiles = (N + pt - 1) / pt;
+      const long blocks = (long)((D + 63) / 64) * ((heads + 63) / 64) * B * G;
+      int S = 1;
+      while (blocks * S < 4L * compute_units() && 2 * S <= n_tiles && (long)g * N / 32 >= 8L * S && B * G * 2L * S <= 65535) S *= 2;
+      const long per = (long)heads * D;
+      d.reduce_b = 0;
+      d.C = {(long)G * S * per, (long)S * per, 0, (long)D, 1};
+      if ((rc = launch_gemm_f32(d, ds, zin, nullptr, rpart, st, S, per))) return rc;
+      return sum_key_path_partials(B, G, S, heads, D, rpart, r, st);
+    }
   }
+  return launch_gemm<float, T, float>(d, ds, zin, nullptr, r, st);
 }
 
 inline int tokens_backward(int B, int Cin, int N, int D, int heads, int g, const float* zin, const float* w,

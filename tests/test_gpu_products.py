@@ -123,3 +123,16 @@ def test_more_rows_than_the_grid_has_row_tiles(kw, call):
     want = oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads, sample=(np.zeros_like(n), n))
     assert rel_err(host(out[0, torch.from_numpy(n).long().cuda()]), want) < TOL[d]
     assert torch.isfinite(out.float()).all()
+
+
+@pytest.mark.parametrize("kw", [PRODUCTS[0], PRODUCTS[3]])
+def test_positional_embedding_is_added_without_the_matrix_instructions(kw, monkeypatch):
+    monkeypatch.setenv("DCHAG_GEMM_GENERIC", "1")
+    test_positional_embedding_is_added_by_the_products(kw)
+
+
+@pytest.mark.parametrize("kw", [PRODUCTS[0], PRODUCTS[3], PRODUCTS[7]])
+def test_training_step_without_the_matrix_instructions(kw, monkeypatch):
+    """The fp32-FMA kernels behind the products, fp32 and bf16, on the shapes the products are checked at."""
+    monkeypatch.setenv("DCHAG_GEMM_GENERIC", "1")
+    check_training_step(ShapeCfg(name="t", x_kind="gauss_mu_sigma", seed=11, **kw))
