@@ -114,8 +114,10 @@ struct PixelWs {
   int splits, key_splits;
 };
 
-inline PixelDims pixel_dims(int B, int C, int N, int pp, int D, int heads, int g) {
+// A nominal group size may exceed the channel count: buffers and grids count the members there are.
+inline PixelDims pixel_dims(int B, int C, int N, int pp, int D, int heads, int nominal) {
   PixelDims d{};
+  const int g = std::min(nominal, C);
   d.B = B; d.C = C; d.N = N; d.D = D; d.g = g; d.G = groups_of(C, g); d.heads = heads;
   d.gpad = round_up(g, 8); d.Np = round_up(N, 32); d.NT = round_up(N, 64);
   d.gq = pp == 16 ? round_up(g, 4) : g; d.gp = round_up(g, 32);
@@ -1473,12 +1475,15 @@ inline size_t train_ws_bytes(dchag_dtype dt, int B, int C, int N, int p, int D, 
 
 // Forward half: folded weights (both layouts), softmax weights from the pixels, o; y is left to the caller.
 template <int PP>
-int pixel_level_forward(int B, int C, int H, int W, int p, int D, int heads, const dchag_level* lv, const bf16* x,
+int pixel_level_forward(int B, int C, int H, int W, int p, int D, int heads, const dchag_level* level, const bf16* x,
                         const bf16* We, const bf16* be, const bf16* ce, unsigned char* ws, const BackwardWs& bw, PixelScores px,
                         hipStream_t st) {
   const PixelWs& w = bw.px;
-  PixelDims d = pixel_dims(B, C, (H / p) * (W / p), PP, D, heads, lv->group_size);
+  PixelDims d = pixel_dims(B, C, (H / p) * (W / p), PP, D, heads, level->group_size);
   d.H = H; d.W = W;
+  dchag_level own = *level;                                // the softmax weights' layout follows the group size
+  own.group_size = d.g;
+  const dchag_level* lv = &own;
   auto at = [&](size_t off) { return reinterpret_cast<bf16*>(ws + off); };
   bf16 *Wf = at(w.fold), *fb = at(w.fold + align_up((size_t)C * D * PP * 2));
   const bf16* Wv = static_cast<const bf16*>(lv->Wv);

@@ -177,3 +177,13 @@ def test_workspace_bytes(lib):
     # bf16 tensors are half the size of fp32 ones
     b = dchag.dchag_workspace_bytes(dchag.DCHAG_BF16, 4, 512, 128, 128, 8, 1024, 16, [32, 16], 1)
     assert b >= 4 * 512 * 256 * 1024 * 2
+
+
+def test_workspace_of_a_training_step_counts_the_members_there_are(lib):
+    """A nominal group size larger than the channel count promises members that do not exist: the training step's buffers of a
+    first level taken from the pixels do not grow with it."""
+    def need(g):
+        return dchag.dchag_workspace_bytes(dchag.DCHAG_BF16, 4, 512, 128, 128, 8, 1024, 16, [g], 3)
+    # the layout of a level that keeps its tokens has softmax weights of nominal size, [B, g, heads, N] floats, and no more
+    assert need(512) <= need(8192) <= need(512) + (8192 - 512) * 4 * 16 * 256 * 4
+    assert need(1 << 17) <= need(512) + ((1 << 17) - 512) * 4 * 16 * 256 * 4

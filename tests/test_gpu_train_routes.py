@@ -1,0 +1,99 @@
+"""Training steps whose first level is taken from the pixels, attention or linear: what must hold bit for bit between calls that form
+the same thing.  Every output starts at a sentinel and every workspace as NaN bytes, so that an element no kernel writes, or scratch
+read before it is written, shows."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2506_21411_amd as dchag
+from workloads import ShapeCfg, make_problem
+
+from .test_gpu_train import ATT, TOL, dev, dev_level, host, rel_err, say
+
+pytestmark = pytest.mark.gpu
+
+LINEAR = ("linear", "attention")
+
+
+def problem(kw, linear=False, biases=True, seed=51):
+    cfg = ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=seed, level_kinds=LINEAR if linear else None, **kw)
+    pr = make_problem(cfg, biases=biases)
+    args = (dev(pr.x, "bf16"), dev(pr.We, "bf16"), dev(pr.be, "bf16"), dev(pr.ce, "bf16"), [dev_level(lv, "bf16") for lv in pr.levels],
+            cfg.p, cfg.heads)
+    return cfg, pr, args
+
+
+def nan_workspace(cfg, group_sizes, which):
+    need = dchag.dchag_workspace_bytes(dchag.DCHAG_BF16, cfg.B, cfg.C, cfg.H, cfg.W, cfg.p, cfg.D, cfg.heads, group_sizes, which)
+    return torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+
+
+def upstream(cfg, seed=77):
+    return dev(np.random.Generator(np.random.PCG64(seed)).standard_normal((cfg.B, cfg.N, cfg.D)).astype(np.float32), "bf16")
+
+
+def gradients(cfg, args, dout, ws, kept, want=None):
+    """Gradients by name ("dx", "dWe", "dtok_bias", "l0.dWv", ...): all of them, or those in `want`."""
+    x, We, _, ce, levels = args[:5]
+    made = {}
+
+    def out(name, like):
+        if like is None or (want is not None and name not in want):
+            return None
+        made[name] = torch.full_like(like, 7.0)
+        return made[name]
+
+    grads = []
+    for i, lv in enumerate(levels):
+        names = ("Wv", "bv") if lv.kind else ATT
+        grads.append(dchag.LevelGrads(**{"d" + n: out(f"l{i}.d{n}", getattr(lv, n)) for n in names}))
+    dx, dWe, dtb = out("dx", x), out("dWe", We), out("dtok_bias", We[:, :, 0].contiguous() if ce is None else ce)
+    dchag.dchag_backward(*args, dout, grads, dx=dx, dWe=dWe, dtok_bias=dtb, workspace=ws, kept=kept)
+    torch.cuda.synchronize()
+    return made
+
+
+def training_step(cfg, args, dout, want=None):
+    gs = [lv.group_size for lv in args[4]]
+    ws = nan_workspace(cfg, gs, 3)
+    out = dchag.dchag_forward_keep(*args, ws)
+    return out, gradients(cfg, args, dout, ws, True, want)
+
+
+def assert_same(a, b):
+    assert a.keys() == b.keys()
+    for n in a:
+        assert torch.isfinite(a[n].float()).all(), n
+        assert torch.equal(a[n], b[n]), n
+
+
+NOMINAL = [
+    (dict(B=1, C=11, H=32, W=64, p=8, D=256, heads=4, group_sizes=(11,)), False),
+    (dict(B=1, C=11, H=32, W=64, p=4, D=256, heads=4, group_sizes=(11,)), False),
+    (dict(B=2, C=11, H=32, W=64, p=8, D=256, heads=4, group_sizes=(11, 1)), True),
+]
+
+
+@pytest.mark.parametrize("kw,linear", NOMINAL)
+def test_nominal_group_sizes_beyond_the_channel_count(kw, linear, monkeypatch):
+    """A first level of one group, its size given as the channel count and as far more: the same numbers."""
+    monkeypatch.setenv("DCHAG_LINEAR_ROUTE" if linear else "DCHAG_TRAIN_ROUTE", "tiles" if linear else "pixels")
+    say(f"nominal group sizes {kw}")
+    cfg, pr, args = problem(kw, linear)
+    dout = upstream(cfg)
+    out, want = training_step(cfg, args, dout)
+    first, nominal = args[4][0], 500
+    wide = dchag.LevelWeights(nominal, first.query, first.Wq, first.Wk, first.Wv, first.Wo, first.bq, first.bk, first.bv, first.bo,
+                              kind=first.kind)
+    if linear:
+        wide.Wv = torch.zeros((1, nominal, cfg.D), dtype=torch.bfloat16, device="cuda")
+        wide.Wv[:, :cfg.C] = first.Wv
+    out2, got = training_step(cfg, (*args[:4], [wide, *args[4][1:]], *args[5:]), dout)
+    assert torch.equal(out, out2)
+    if linear:
+        assert not got["l0.dWv"][:, cfg.C:].any()
+        got["l0.dWv"] = got["l0.dWv"][:, :cfg.C]
+    assert_same(want, got)
+    ref = oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads).reshape(cfg.B, cfg.N, cfg.D)
+    assert rel_err(host(out), ref) < TOL["bf16"]
