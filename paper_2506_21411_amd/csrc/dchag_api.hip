@@ -761,6 +761,31 @@ inline bool reduce_ring_ok(int p, int W, int D, const void* x, const void* Wt, c
   return p == 8 && W % 8 == 0 && D % 256 == 0 && aligned16(x) && aligned16(Wt) && aligned16(v0) && aligned16(v1) &&
          aligned16(v2) && !dbg(SW_FIRST_LEVEL_REGS);
 }
+// Workgroups a tile's members are dealt to, each to its own partial sums: while there are too few tiles to give every compute unit
+// two rounds of workgroups, up to 16 (DCHAG_FIRST_LEVEL_SPLIT overrides the count).  It follows from the sizes alone, so that every call
+// that forms a level this way adds its members in the same order; the workspaces have room for it (ring_part_bytes).
+inline long ring_tiles(int B, int N, int D, int G, int patches, int cols) {
+  return (long)G * B * ((N + patches - 1) / patches) * (D / cols);
+}
+template <int CFG>
+int ring_splits(int B, int C, int N, int D, int g) {
+  typedef RedCfg<CFG> Cfg;
+  const int G = groups_of(C, g), gmin = std::min(g, C - (G - 1) * g);       // members of the shortest group
+  if (const char* e = dbg(SW_FIRST_LEVEL_SPLIT)) return std::max(1, std::min(std::min(16, gmin), atoi(e)));
+  const long total = ring_tiles(B, N, D, G, Cfg::kPatches, Cfg::kCols);
+  const long fill = 2L * Cfg::kPerCu * compute_units();
+  int S = 1;
+  while (total * S < fill && 2 * S <= std::min(16, gmin)) S *= 2;
+  return S;
+}
+inline bool small_ring() {
+  const char* e = dbg(SW_RING_SHAPE);
+  return e && atoi(e) == 1;
+}
+inline size_t ring_part_bytes(int B, int C, int N, int D, int g) {
+  const int S = small_ring() ? ring_splits<1>(B, C, N, D, g) : ring_splits<0>(B, C, N, D, g);
+  return S > 1 ? (size_t)S * B * groups_of(C, g) * N * D * 4 : 0;
+}
 template <bool ATT, int CFG>
 int launch_reduce_ring_cols(int B, int C, int H, int W, int D, int g, int heads, const bf16* x, const bf16* Wt,
                             const bf16* wmix, const bf16* v1, const bf16* v2, const float* alpha, const bf16* bias,
@@ -771,16 +796,12 @@ int launch_reduce_ring_cols(int B, int C, int H, int W, int D, int g, int heads,
   tw.n_tiles = D / Cfg::kCols;
   tw.m_tiles = (N + Cfg::kPatches - 1) / Cfg::kPatches;
   tw.nb = B;
-  const long total = (long)G * B * tw.m_tiles * tw.n_tiles;
+  const long total = ring_tiles(B, N, D, G, Cfg::kPatches, Cfg::kCols);
   if (total > (1L << 26)) return DCHAG_ERR_SHAPE;
   tw.total = (int)total;
   const size_t per_split = (size_t)B * G * N * D;
-  const int gmin = std::min(g, C - (G - 1) * g);                  // members of the shortest group
-  const long fill = 2L * Cfg::kPerCu * compute_units();           // workgroups that give every compute unit two rounds
-  int S = 1;
-  while (total * S < fill && 2 * S <= std::min(16, gmin)) S *= 2;
-  if (const char* e = dbg(SW_FIRST_LEVEL_SPLIT)) S = std::max(1, std::min(std::min(16, gmin), atoi(e)));
-  while (S > 1 && (!part || (size_t)S * per_split * 4 > part_bytes)) S >>= 1;
+  const int S = part ? ring_splits<CFG>(B, C, N, D, g) : 1;
+  if (S > 1 && (size_t)S * per_split * 4 > part_bytes) return DCHAG_ERR_WORKSPACE;
   const int per = (int)((total * S + kXcds - 1) / kXcds);
   if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_tokenize_reduce_ring<ATT, CFG>), Cfg::kLdsBytes)) return DCHAG_ERR_LAUNCH;
   k_tokenize_reduce_ring<ATT, CFG><<<dim3((unsigned)(per * kXcds)), Cfg::kThreads, Cfg::kLdsBytes, st>>>(
@@ -792,16 +813,14 @@ int launch_reduce_ring_cols(int B, int C, int H, int W, int D, int g, int heads,
   return launch_status();
 }
 
-// part / part_bytes: optional fp32 scratch for partial sums; with it, and too few tiles to give every compute unit two
-// rounds of workgroups, a group's members are dealt to up to 16 workgroups per tile (DCHAG_FIRST_LEVEL_SPLIT overrides
-// the count).  Workgroups of 128 patches x 256 columns, one per compute unit, three stages (DCHAG_RING_SHAPE = 1:
-// 128 x 128, two per compute unit, two stages).
+// part / part_bytes: optional fp32 scratch for partial sums (ring_part_bytes); without it a tile's members stay in one workgroup.
+// Workgroups of 128 patches x 256 columns, one per compute unit, three stages (DCHAG_RING_SHAPE = 1: 128 x 128, two per compute
+// unit, two stages).
 template <bool ATT>
 int launch_reduce_ring(int B, int C, int H, int W, int D, int g, int heads, const bf16* x, const bf16* Wt,
                        const bf16* wmix, const bf16* v1, const bf16* v2, const float* alpha, const bf16* bias, bf16* y,
                        hipStream_t st, float* part = nullptr, size_t part_bytes = 0) {
-  const char* e = dbg(SW_RING_SHAPE);
-  if (e && atoi(e) == 1)
+  if (small_ring())
     return launch_reduce_ring_cols<ATT, 1>(B, C, H, W, D, g, heads, x, Wt, wmix, v1, v2, alpha, bias, y, st, part,
                                            part_bytes);
   return launch_reduce_ring_cols<ATT, 0>(B, C, H, W, D, g, heads, x, Wt, wmix, v1, v2, alpha, bias, y, st, part,

@@ -67,8 +67,12 @@ inline FoldedWs folded_ws(dchag_dtype dt, int B, int C, int N, int pp, int D, in
   FoldedWs w{};
   const size_t es = elem_size(dt);
   size_t off = 0;
-  // the tokens, or (bf16, 16 or 64 pixels per patch) what replaces them when the first level's values come from the pixels
-  w.tokens = off; off += std::max(align_up((size_t)B * C * N * D * es), dt == DCHAG_BF16 && (pp == 16 || pp == 64) ? value_fold_bytes(C, D, pp) : 0);
+  // the tokens, or (bf16, 16 or 64 pixels per patch) what replaces them when the first level's values come from the pixels: the
+  // folded weights and, behind them, the ring kernel's partial sums
+  size_t from_pixels = 0;
+  if (dt == DCHAG_BF16 && (pp == 16 || pp == 64)) from_pixels = value_fold_bytes(C, D, pp);
+  if (from_pixels && pp == 64 && D % 256 == 0) from_pixels += align_up(ring_part_bytes(B, C, N, D, group_sizes[0]));
+  w.tokens = off; off += std::max(align_up((size_t)B * C * N * D * es), from_pixels);
   int c_in = C;
   size_t lvl_max = 0, inter_max = 0;
   for (int l = 0; l < n_levels; ++l) {
@@ -110,7 +114,7 @@ inline int dz_patches(int B, int G, int N, int D, int g) {
 // Buffers of an attention first level trained from the pixels (k_pixel_train.h): what the forward sweep leaves for the
 // reverse sweep comes first, from `dot` on they are the reverse sweep's own.
 struct PixelWs {
-  size_t qp, mf, mb, alpha, o, y, fold, wft, wg, ug, ut, wet, dot, dal, er, et, part, fr, ft, wvt, m2, x, rk;
+  size_t qp, mf, mb, alpha, o, y, fold, wft, wg, ug, ut, wet, dot, dal, er, et, part, fr, ft, wvt, m2, x, rk, end;
   int splits, key_splits;
 };
 
@@ -169,6 +173,8 @@ inline size_t pixel_ws(const PixelDims& d, int pp, bool keep_y, size_t off, Pixe
   w->x = take(G * D * (size_t)((pp == 16 ? d.gq * 16 : 0) + 2 * d.gp) * 2);
   w->key_splits = pixel_key_splits(d);
   w->rk = take((size_t)w->key_splits * G * h * D * 4);
+  if (pp == 64) off = std::max(off, w->dot + align_up(ring_part_bytes(d.B, d.C, d.N, d.D, d.g)));
+  w->end = off;
   return off;
 }
 
@@ -1515,8 +1521,8 @@ int pixel_level_forward(int B, int C, int H, int W, int p, int D, int heads, con
     if ((rc = launch_status())) return rc;
   }
   // what the reverse sweep will use as scratch takes the partial sums of few tiles
-  return attend_pixels_forward(B, C, H, W, p, D, heads, lv, x, be || ce, alpha, ws + w.fold, ws + w.dot, w.m2 - w.dot, at(w.o),
-                               st);
+  return attend_pixels_forward(B, C, H, W, p, D, heads, lv, x, be || ce, alpha, ws + w.fold, ws + w.dot, w.end - w.dot,
+                               at(w.o), st);
 }
 
 // Reverse half, given dy = d L / d (level output) [B,G,N,D].

@@ -97,3 +97,29 @@ def test_nominal_group_sizes_beyond_the_channel_count(kw, linear, monkeypatch):
     assert_same(want, got)
     ref = oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads).reshape(cfg.B, cfg.N, cfg.D)
     assert rel_err(host(out), ref) < TOL["bf16"]
+
+
+SAME_FORWARD = [
+    # 32 groups of 4, one image: half the tiles that fill the chip, so a tile's members are dealt to two workgroups
+    dict(B=1, C=128, H=128, W=128, p=8, D=1024, heads=16, group_sizes=(4, 32)),
+    # few tiles and many members: dealt to sixteen
+    dict(B=1, C=40, H=32, W=40, p=8, D=256, heads=4, group_sizes=(20, 2)),
+    # 4 x 4 patches, a short last group
+    dict(B=2, C=21, H=48, W=52, p=4, D=512, heads=8, group_sizes=(8, 3)),
+]
+
+
+@pytest.mark.parametrize("kw", SAME_FORWARD)
+def test_calls_that_take_the_first_level_from_the_pixels_agree_bit_for_bit(kw, monkeypatch):
+    monkeypatch.setenv("DCHAG_TRAIN_ROUTE", "pixels")
+    say(f"same forward {kw}")
+    cfg, pr, args = problem(kw)
+    gs = [lv.group_size for lv in args[4]]
+    kept = dchag.dchag_forward_keep(*args, nan_workspace(cfg, gs, 3))
+    folded = dchag.dchag_forward_folded(*args, workspace=nan_workspace(cfg, gs, 2))
+    prepared = dchag.dchag_fold_value(*args[1:])
+    prefolded = dchag.dchag_forward_prefolded(*args, prepared, workspace=nan_workspace(cfg, gs, 2))
+    torch.cuda.synchronize()
+    assert torch.isfinite(folded.float()).all()
+    assert torch.equal(prefolded, folded)
+    assert torch.equal(kept, folded)
