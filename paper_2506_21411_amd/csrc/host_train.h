@@ -1449,19 +1449,28 @@ inline int linear_first_backward(int B, int C, int H, int W, int p, int D, const
 // ---- attention first level trained from the pixels (k_pixel_train.h) ----
 
 // Taken by the shapes whose first level dchag_forward_folded takes from the pixels, when it is the cheaper route.  The route
-// through the tokens streams tokens and per-head averages, Q = B N C D (1 + heads / g) elements; this one multiplies weight-sized
-// products, C D D pp, whatever B N is, and is a few launches longer.  Fitted to twelve shapes: 2.46 us per million of Q against
-// 8.8 us per 10^9 of C D D pp and 85 us.  Training steps, tokens / pixels: 512 bands x 4 x 256 patches, D 1024: 2.75 / 1.49 ms;
-// 512 x 2 x 256, D 2048: 5.31 / 3.87 ms; 512 x 1 x 256, D 2048: 3.38 / 3.27 ms; 256 x 1 x 256, D 1024: 652 / 679 us; 4 x 4 patches:
-// 64 x 1 x 512, D 512: 367 / 362 us; 40 x 2 x 256, D 512: 330 / 353 us.  DCHAG_TRAIN_ROUTE (debugging aid) = tokens / pixels
-// overrides the rule, never the shape limits.
+// through the tokens streams tokens, T = B N C D elements, and per-head averages, T heads / g; this one multiplies weight-sized
+// products, F = C D D pp, whatever B N is, and is a few launches longer.  464 shapes were timed on both routes (5 to 1024 channels,
+// D 256 to 4096, 4 to 32 heads, groups of 4 to 32, nine tenths of them within a factor of two of the line).  The first line is a fit
+// to all of them.  Where the route through the tokens has its reverse step in one kernel (tokens_fused) it is cheaper, most of all in
+// large groups, whose products here leave the chip partly idle: the second line, with the level's output T / g.  Of the 354 shapes
+// taken, 8 are slower by more than 0.5 %, the worst by 5 % (24 x 4 x 252, D 768, 24 heads, groups of 24: 365 / 384 us).  Training
+// steps, tokens / pixels (group sizes): 512 bands x 4 x 256 patches, D 1024, 16 heads (32, 16): 2754 / 1463 us; 512 x 2 x 256, D 2048,
+// 16 heads (32, 16): 3344 / 2617; 256 x 1 x 256, D 1024, 16 heads (16, 16): 758 / 728, taken; the same shape in groups of (32, 8):
+// 639 / 674, not taken; 512 x 1 x 256, D 2048, 16 heads (32, 16): 2084 / 2304, not taken; 4 x 4 patches: 135 x 4 x 240, D 256, 4 heads
+// (21, 7): 486 / 405, taken; 40 x 2 x 256, D 512, 8 heads (8, 5): 317 / 340, not taken.  DCHAG_TRAIN_ROUTE (debugging aid) = tokens /
+// pixels overrides the rule, never the shape limits.
 inline bool pixel_train_ok(dchag_dtype dt, int B, int C, int N, int p, int D, int heads, const dchag_level* first, int g) {
   const int pp = p * p;
   if (!values_from_pixels(dt, p, D, heads, first)) return false;
   if (const char* e = dbg(SW_TRAIN_ROUTE)) {
     if (e[0] == 't') return false;
-  } else if ((double)B * N * C * D * (1. + (double)heads / std::min(g, C)) < (double)C * D * D * pp / 280. + 33.5e6) {
-    return false;
+  } else {
+    const int members = std::min(g, C);
+    const double T = (double)B * N * C * D, F = (double)C * D * D * pp;
+    const bool one_kernel = heads <= 16 && D <= 2048 && members <= 32;
+    if (T * (1. + (double)heads / members) < F / 280. + 33.5e6) return false;
+    if (one_kernel && T * (1. + (heads + 20.) / members) < F / 154. + 58e6) return false;
   }
   const PixelDims d = pixel_dims(B, C, N, pp, D, heads, g);
   const long tiles_n = (N + 127) / 128, tiles_d = D / 128, tiles_r = (d.RE + 127) / 128;
