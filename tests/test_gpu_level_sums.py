@@ -1,5 +1,5 @@
 """GPU parity of the one-kernel scores, softmax and head sums of a level (k_level_sums) in every form it is built in: head blocks,
-patches per block, member tiles and their remainders, against the oracle and against the separate kernels it stands for."""
+patches per block, member tiles and their remainders, and of the separate kernels it stands for on the same shapes, against the oracle."""
 import pytest
 
 from workloads import ShapeCfg
@@ -26,9 +26,22 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("kw", SHAPES)
-def test_training_step_with_one_kernel_level_sums(kw, monkeypatch):
-    say(f"level sums {kw}")
+# beyond D 2048 with more than 16 heads: the separate kernels by themselves
+WIDE = dict(B=1, C=10, H=16, W=24, p=8, D=4096, heads=32, group_sizes=(4, 3))
+
+
+# the separate kernels on all but the two largest shapes, whose host side takes half a minute
+@pytest.mark.parametrize("kw,separate", [(kw, False) for kw in SHAPES] + [(kw, True) for kw in SHAPES[:5]])
+def test_training_step_with_one_kernel_level_sums(kw, separate, monkeypatch):
+    say(f"level sums, {'separate kernels' if separate else 'one kernel'} {kw}")
     monkeypatch.setenv("DCHAG_TRAIN_ROUTE", "tokens")
     monkeypatch.setenv("DCHAG_TOKEN_SCORES", "1")          # the first level's scores from its tokens too
+    if separate:
+        monkeypatch.setenv("DCHAG_LEVEL_UNFUSED", "1")
     check_training_step(ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=31, **kw))
+
+
+def test_training_step_with_a_wide_upper_level(monkeypatch):
+    say(f"level sums {WIDE}")
+    monkeypatch.setenv("DCHAG_TRAIN_ROUTE", "tokens")
+    check_training_step(ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=31, **WIDE))

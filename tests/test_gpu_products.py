@@ -21,15 +21,16 @@ def check_training_step(cfg, seed=77, biases=True):
             cfg.heads)
     gs = [lv.group_size for lv in pr.levels]
     code = dchag.DCHAG_F32 if d == "f32" else dchag.DCHAG_BF16
-    ws = torch.empty(dchag.dchag_workspace_bytes(code, cfg.B, cfg.C, cfg.H, cfg.W, cfg.p, cfg.D, cfg.heads, gs, 3),
-                     dtype=torch.uint8, device="cuda")
+    # outputs start at a sentinel and the workspace as NaN bytes: an element no kernel writes shows
+    need = dchag.dchag_workspace_bytes(code, cfg.B, cfg.C, cfg.H, cfg.W, cfg.p, cfg.D, cfg.heads, gs, 3)
+    ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
     out = dchag.dchag_forward_keep(*args, ws)
     dout = dev(np.random.Generator(np.random.PCG64(seed)).standard_normal((cfg.B, cfg.N, cfg.D)).astype(np.float32), d)
-    dx, dWe, dtb = torch.empty_like(args[0]), torch.empty_like(args[1]), torch.empty_like(args[3])
+    dx, dWe, dtb = torch.full_like(args[0], 7.0), torch.full_like(args[1], 7.0), torch.full_like(args[3], 7.0)
     grads = []
     for lv in args[4]:
         names = [n for n in (("Wv", "bv") if lv.kind else ATT) if getattr(lv, n) is not None]
-        grads.append(dchag.LevelGrads(**{"d" + n: torch.empty_like(getattr(lv, n)) for n in names}))
+        grads.append(dchag.LevelGrads(**{"d" + n: torch.full_like(getattr(lv, n), 7.0) for n in names}))
     dchag.dchag_backward(*args, dout, grads, dx=dx, dWe=dWe, dtok_bias=dtb, workspace=ws, kept=True)
     torch.cuda.synchronize()
     want = oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads).reshape(cfg.B, cfg.N, cfg.D)

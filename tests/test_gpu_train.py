@@ -392,8 +392,8 @@ def test_backward_linear_first_level_through_the_tokens_still_matches(monkeypatc
 @pytest.mark.parametrize("kw", [SMALL[0], SMALL[3], SMALL[4], SMALL[10], SMALL[13]])
 def test_forward_keep_and_backward_kept_equal_the_recomputing_calls(monkeypatch, kw):
     """A training step that keeps its activations: the output equals dchag_forward_folded's (on its route through the
-    tokens at the first level, which the kept forward always takes) and every gradient equals dchag_backward's bit for
-    bit (same kernels on the same buffers), for two upstream gradients in a row after one forward."""
+    tokens at the first level, which the kept forward takes at these sizes) and every gradient equals dchag_backward's bit
+    for bit (same kernels on the same buffers), for two upstream gradients in a row after one forward."""
     cfg = cfg_of(**kw)
     say(f"keep / kept {kw}")
     pr = make_problem(cfg)

@@ -146,3 +146,71 @@ def test_route_of_a_training_step(group_sizes, from_pixels):
     stages = {name for name, _, _ in dchag.dchag_profile_end()}
     assert ("fold_value" in stages) == from_pixels, stages
     assert ("tokenize" in stages) != from_pixels, stages
+
+
+ROUTES = [
+    # 8 x 8 patches, groups of 5 + 5 + 1, 130 patches (a tile and two more)
+    (dict(B=2, C=11, H=80, W=104, p=8, D=512, heads=8, group_sizes=(5, 3)), False),
+    # 4 x 4 patches, heads of 32, groups of 6 + 3
+    (dict(B=1, C=9, H=48, W=52, p=4, D=256, heads=8, group_sizes=(6, 2)), False),
+    # linear first levels, a short last group
+    (dict(B=2, C=7, H=72, W=120, p=8, D=512, heads=8, group_sizes=(5, 2)), True),
+    (dict(B=1, C=17, H=12, W=44, p=4, D=256, heads=4, group_sizes=(9, 2)), True),
+]
+IN_PART = [("dx",), ("dWe",), ("dtok_bias",), ("l0.dWv",), ("l0.dWk",), ("l0.dWq",), ("l0.dquery",), ("l0.dbq",), ("l0.dbk",),
+           ("l0.dbv",), ("l0.dWo",), ("l0.dbo",), ("dx", "l0.dWv"), ("dWe", "l0.dbv"), ("dtok_bias", "l0.dWk"), ()]
+
+
+def take_route(monkeypatch, linear):
+    monkeypatch.setenv("DCHAG_LINEAR_ROUTE" if linear else "DCHAG_TRAIN_ROUTE", "tiles" if linear else "pixels")
+
+
+@pytest.mark.parametrize("kw,linear", ROUTES)
+def test_gradients_asked_for_in_part(kw, linear, monkeypatch):
+    """Gradients of the first level and the tokenizer alone, in pairs and none: what the full call gives.  The second level's are
+    always asked for: without them its token gradients come from other kernels."""
+    take_route(monkeypatch, linear)
+    say(f"gradients in part {kw}")
+    cfg, pr, args = problem(kw, linear)
+    dout = upstream(cfg)
+    _, full = training_step(cfg, args, dout)
+    assert all(torch.isfinite(v.float()).all() for v in full.values())
+    second = tuple(n for n in full if n.startswith("l1."))
+    for want in IN_PART:
+        if linear and any(n.startswith("l0.") and n not in ("l0.dWv", "l0.dbv") for n in want):
+            continue
+        say(f"  {want}")
+        _, got = training_step(cfg, args, dout, want + second)
+        assert set(got) == set(want + second)
+        for n in got:
+            if linear and want == ("dx",) and n == "dx":    # dx alone: products per channel, which sum in another order
+                assert rel_err(host(got[n]), host(full[n])) < TOL["bf16"]
+            else:
+                assert torch.equal(got[n], full[n]), n
+
+
+@pytest.mark.parametrize("kw,linear", ROUTES)
+def test_two_reverse_sweeps_after_one_forward(kw, linear, monkeypatch):
+    """Two upstream gradients in a row on one kept workspace, against dchag_backward, which forms the forward again."""
+    take_route(monkeypatch, linear)
+    say(f"two reverse sweeps {kw}")
+    cfg, pr, args = problem(kw, linear)
+    gs = [lv.group_size for lv in args[4]]
+    ws = nan_workspace(cfg, gs, 3)
+    dchag.dchag_forward_keep(*args, ws)
+    for seed in (61, 62):
+        dout = upstream(cfg, seed)
+        assert_same(gradients(cfg, args, dout, nan_workspace(cfg, gs, 3), False), gradients(cfg, args, dout, ws, True))
+
+
+@pytest.mark.parametrize("kw,linear", ROUTES)
+def test_training_step_repeats_itself(kw, linear, monkeypatch):
+    take_route(monkeypatch, linear)
+    say(f"repeats itself {kw}")
+    cfg, pr, args = problem(kw, linear, biases=False)
+    dout = upstream(cfg)
+    out, want = training_step(cfg, args, dout)
+    for _ in range(2):
+        out2, got = training_step(cfg, args, dout)
+        assert torch.equal(out, out2)
+        assert_same(want, got)
