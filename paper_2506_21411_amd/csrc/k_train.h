@@ -245,6 +245,7 @@ __global__ __launch_bounds__(256) void k_dz_attention(int Cin, int N, int D, int
 // k_dalpha_group: one wavefront per (b, k, n), 16 members x 16 heads a tile on v_mfma_f32_16x16x4f32 (a lane's 16-byte load feeds
 // four of them: any assignment of features to contraction steps serves as long as both operands share it), the softmax Jacobian
 // over the members behind it: ds[c,a] = alpha[c,a] (dalpha[c,a] - sum_c' alpha[c',a] dalpha[c',a]).  Groups of up to 16 MT.
+// 64 features are added up in four chains of 16 and then to the sum (one chain over D lost precision against a wavefront-wide sum).
 // grid ceil(B G N / 4), block 256.  D % 16 == 0.  Bound by the read of w and z (80 variables, 512 patches, D 512, 8 heads: 168 MB;
 // 37 us, one wavefront per token and a softmax pass 137 + 7).
 // ---------------------------------------------------------------------------------------
@@ -262,11 +263,12 @@ __global__ __launch_bounds__(256) void k_dalpha_group(long items, int Cin, int N
   for (int a0 = 0; a0 < heads; a0 += 16) {
     const float* wr = w + ((size_t)item * heads + min(a0 + l16, heads - 1)) * D + lq * 4;
     const float* zr[MT];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       zr[mt] = zb + (size_t)min(mt * 16 + l16, gk - 1) * cstride;
-      acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      acc[mt] = zero;
     }
     for (int t = 0; t < D; t += 64) {                              // four steps of 16 per trip, loads first
       f32x4 wf[4], zf[MT][4];
@@ -277,6 +279,7 @@ __global__ __launch_bounds__(256) void k_dalpha_group(long items, int Cin, int N
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) zf[mt][q] = *reinterpret_cast<const f32x4*>(zr[mt] + tt);
       }
+      f32x4 trip[MT][4];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (t + q * 16 < D) {
@@ -284,8 +287,10 @@ __global__ __launch_bounds__(256) void k_dalpha_group(long items, int Cin, int N
           for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-              acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(zf[mt][q][e], wf[q][e], acc[mt], 0, 0, 0);
+              trip[mt][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(zf[mt][q][e], wf[q][e], q ? trip[mt][e] : zero, 0, 0, 0);
         }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[mt] += (trip[mt][0] + trip[mt][1]) + (trip[mt][2] + trip[mt][3]);
     }
     // accumulator block: lane holds head lane % 16, members 4 (lane / 16) + 0..3 of the tile
     float al[MT][4];
@@ -1026,6 +1031,10 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
 //   index is read as 4 x 4 blocks and transposed in registers.  Two slices are in flight in registers ahead of the
 //   one being multiplied: what bounded the FMA kernels it replaces was a load round trip per 16 steps (2 to 3 us each;
 //   24 us for a product over 128 steps).
+//   A slice is added up on its own and then to the sum of the slices: chains of 32 and K / 32 instead of K.  One chain has the
+//   error of the FMA kernels, more than the wavefront-wide sums that the scores had (outputs 1.18 times the error over 40 drawn
+//   calls, up to 1.44); with slices 0.51 times (0.86 at most), for 1 % of a training step of 80 variables (947 -> 960 us; adding the
+//   last slice under the next one's products takes 16 registers more and 1018 us).
 //   split > 1: the contraction is dealt to `split` blocks, block t takes slices [t, t + 1) * per of it and writes its own
 //   partial result at offset split_stride * t (per batch item); bias and addend are then not applied.
 // grid (ceil(N/64), ceil(M/64), batch * split), block 256.
@@ -1059,9 +1068,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmDesc d, int va, int vb, in
   const int per = ((b1 - b0) * KT + split - 1) / split;
   const int s_begin = part * per, s_end = min(s_begin + per, (b1 - b0) * KT);
 
-  f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 acc = zero;
 
   // one operand's share of a slice in registers: four 16-byte pieces (row-fast operands: a 4 x 4 block; others: two pieces)
   auto load_op = [&](bool T, int vec, const float* P, long srow, long sk, int r0, int R, int k0, int t, f32x4 (&reg)[4]) {
@@ -1121,12 +1129,14 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmDesc d, int va, int vb, in
   auto multiply = [&](int buf) {
     const float* Ap = As[buf] + (wm * 32 + l32) * PITCH + lhi * 4;
     const float* Bp = Bs[buf] + (wn * 32 + l32) * PITCH + lhi * 4;
+    f32x16 slice = zero;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const f32x4 av = *reinterpret_cast<const f32x4*>(Ap + q * 8), bv = *reinterpret_cast<const f32x4*>(Bp + q * 8);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[e], acc, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) slice = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[e], slice, 0, 0, 0);
     }
+    acc += slice;
   };
   // slice s goes to LDS buffer s & 1 one step before it is multiplied; its registers then take slice s + 2
   auto step = [&](int s, int buf, f32x4 (&ra)[4], f32x4 (&rb)[4]) {   // ra, rb: slice s + 1's registers

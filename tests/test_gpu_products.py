@@ -137,3 +137,47 @@ def test_training_step_without_the_matrix_instructions(kw, monkeypatch):
     """The fp32-FMA kernels behind the products, fp32 and bf16, on the shapes the products are checked at."""
     monkeypatch.setenv("DCHAG_GEMM_GENERIC", "1")
     check_training_step(ShapeCfg(name="t", x_kind="gauss_mu_sigma", seed=11, **kw))
+
+
+# Contractions of 512 and 1024 steps, key-path sums dealt to several blocks.
+PRECISION = [
+    dict(dtype="f32", B=1, C=24, H=32, W=64, p=4, D=512, heads=8, group_sizes=(8, 3)),
+    dict(dtype="f32", B=2, C=14, H=24, W=40, p=4, D=1024, heads=16, group_sizes=(14,)),
+]
+
+
+@pytest.mark.parametrize("kw", PRECISION)
+def test_fp32_products_round_no_more_than_the_vector_kernels(kw, monkeypatch):
+    """2-norm errors against the fp64 oracle of everything a training step gives, on the matrix instructions and on the fp32-FMA
+    kernels: two orders of the same sums, so a tenth is left for chance."""
+    cfg = ShapeCfg(name="t", x_kind="gauss_mu_sigma", seed=14, **kw)
+    say(f"precision {kw}")
+    pr = make_problem(cfg)
+    dout = np.random.Generator(np.random.PCG64(78)).standard_normal((cfg.B, cfg.N, cfg.D)).astype(np.float32)
+    want = {"out": oracle.forward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads).reshape(cfg.B, cfg.N, cfg.D)}
+    ref = oracle.backward(pr.x, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads, dout.reshape(-1, cfg.D).astype(np.float64))
+    hp, wp = cfg.H // cfg.p, cfg.W // cfg.p
+    want["dx"] = ref["dx"].reshape(cfg.B, hp, wp, cfg.C, cfg.p, cfg.p).transpose(0, 3, 1, 4, 2, 5).reshape(pr.x.shape)
+    want["dWe"], want["dtok_bias"] = ref["dWe"], ref["dtok_bias"]
+    for i, r in enumerate(ref["levels"]):
+        want.update({f"l{i}.{n}": v for n, v in r.items() if n != "dbk"})
+    args = (dev(pr.x, "f32"), dev(pr.We, "f32"), dev(pr.be, "f32"), dev(pr.ce, "f32"), [dev_level(lv, "f32") for lv in pr.levels],
+            cfg.p, cfg.heads)
+
+    def errors():
+        got = {"out": dchag.dchag_forward_folded(*args)}
+        dx, dWe, dtb = torch.full_like(args[0], 7.0), torch.full_like(args[1], 7.0), torch.full_like(args[3], 7.0)
+        grads = [dchag.LevelGrads(**{"d" + n: torch.full_like(getattr(lv, n), 7.0) for n in ATT}) for lv in args[4]]
+        dchag.dchag_backward(*args, dev(dout, "f32"), grads, dx=dx, dWe=dWe, dtok_bias=dtb)
+        got.update(dx=dx, dWe=dWe, dtok_bias=dtb)
+        for i, g in enumerate(grads):
+            got.update({f"l{i}.{n}": v for n, v in vars(g).items() if n != "dbk"})
+        return {n: float(np.linalg.norm(host(got[n]) - want[n]) / np.linalg.norm(want[n])) for n in want}
+
+    matrix = errors()
+    monkeypatch.setenv("DCHAG_GEMM_GENERIC", "1")
+    vector = errors()
+    ratio = {n: matrix[n] / vector[n] for n in want if vector[n] > 0}
+    worst = max(ratio, key=ratio.get)
+    say(f"  out {vector['out']:.2e} -> {matrix['out']:.2e}, worst {worst} {ratio[worst]:.2f}")
+    assert ratio[worst] < 1.1, ratio
