@@ -66,11 +66,35 @@ def error_report(got, want):
                           "max(|r_i|, rms r); rms = rms(y-r)/rms(r)"}
 
 
-def stage_model(cfg, levels_in, stage, level, fused_tokens=False):
+def first_level_route(stages):
+    """How a training step took its first level, from the (stage, level) pairs it ran: "pixels" (an attention level whose values
+    are folded into the tokenizer), "linear" (a linear level that forms no tokens) or "tokens"."""
+    if not any(name.startswith("bwd_") for name, _ in stages):
+        return "tokens"
+    if ("fold_value", 1) in stages:
+        return "pixels"
+    return "linear" if ("tokenize_mix", 1) in stages else "tokens"
+
+
+def stage_model(cfg, levels_in, stage, level, fused_tokens=False, first="tokens"):
     """Algorithmic work of one launch of a stage: (bound, amount, unit) with amount in flops or bytes.
-    fused_tokens: the level's reverse step at the tokens ran as one kernel (no separate softmax stage)."""
+    fused_tokens: the level's reverse step at the tokens ran as one kernel (no separate softmax stage).
+    first: see first_level_route."""
     es = 4 if cfg.dtype == "f32" else 2
     B, N, D, h = cfg.B, cfg.N, cfg.D, cfg.heads
+    if first != "tokens" and level == 1:
+        # neither tokens nor their gradients exist: products over (patch, pixel) pairs, products of the weights' size
+        over_patches = 2.0 * B * cfg.C * N * D * cfg.p * cfg.p
+        of_weights = 2.0 * cfg.C * D * D * cfg.p * cfg.p
+        G1 = (cfg.C + cfg.group_sizes[0] - 1) // cfg.group_sizes[0]
+        if first == "pixels":
+            model = {"bwd_softmax": ("mfma", over_patches), "bwd_tokens": ("mfma", over_patches),
+                     "bwd_value": ("mfma", over_patches + of_weights), "bwd_tokenize": ("mfma", of_weights),
+                     "bwd_key_query": ("hbm", (B * cfg.C * cfg.H * cfg.W + 3 * G1 * D * D) * es + B * cfg.C * N * h * 4)}
+        else:
+            model = {"bwd_tokenize": ("mfma", 2 * over_patches), "bwd_channel_mix": ("hbm", B * G1 * N * D * es)}
+        if stage in model:
+            return model[stage]
     if stage == "tokenize":
         by = B * cfg.C * cfg.H * cfg.W * es + cfg.C * D * cfg.p * cfg.p * es + B * cfg.C * N * D * es
         return "hbm", by
@@ -319,10 +343,10 @@ def main() -> int:
             a = agg.setdefault((name, level), [0.0, 0])
             a[0] += dur
             a[1] += 1
-        stages = []
+        stages, first = [], first_level_route(agg)
         for (name, level), (tot, cnt) in agg.items():
             fused = name == "bwd_tokens" and ("bwd_softmax", level) not in agg
-            bound, amount = stage_model(cfg, lv_in, name, level, fused)
+            bound, amount = stage_model(cfg, lv_in, name, level, fused, first)
             avg = tot / steps                            # per step: a stage may take several launches
             if bound == "mfma":
                 ach, peak, unit = amount / (avg * 1e-3) / 1e12, PEAK["mfma_bf16_tflops"] if cfg.dtype == "bf16" else PEAK["fp32_tflops"], "TFLOP/s"

@@ -107,6 +107,26 @@ def test_stage_model_counts_what_is_executed():
     assert bench.stage_model(cfg, lv_in, "key_prep", 2)[1] == 2 * cfg.D * cfg.D * 2
 
 
+def test_stage_model_of_a_training_step_without_first_level_tokens():
+    """The reverse step of a first level taken from the pixels, and of a linear one that forms no tokens: products over patches and
+    of the weights' size, no pass over tokens (whose bytes over those kernels' time would read as more than the HBM can move)."""
+    bench = load_bench()
+    cfg = get_config("hyperspectral")
+    lv_in = workloads.level_inputs(cfg.C, cfg.group_sizes)
+    ran = {("fold_value", 1), ("bwd_tokens", 1), ("bwd_tokens", 2)}
+    assert bench.first_level_route(ran) == "pixels"
+    assert bench.first_level_route({("fold_value", 1), ("tokenize_attend", 1)}) == "tokens"        # a forward call
+    assert bench.first_level_route({("tokenize", 0), ("bwd_tokens", 1)}) == "tokens"
+    assert bench.first_level_route({("tokenize_mix", 1), ("bwd_channel_mix", 1)}) == "linear"
+    over_patches, of_weights = 2.0 * 524288 * 1024 * 64, 2.0 * 512 * 1024 * 1024 * 64
+    assert bench.stage_model(cfg, lv_in, "bwd_tokens", 1, False, "pixels") == ("mfma", over_patches)
+    assert bench.stage_model(cfg, lv_in, "bwd_value", 1, False, "pixels") == ("mfma", over_patches + of_weights)
+    assert bench.stage_model(cfg, lv_in, "bwd_tokenize", 1, False, "linear") == ("mfma", 2 * over_patches)
+    assert bench.stage_model(cfg, lv_in, "bwd_channel_mix", 1, False, "linear") == ("hbm", 4 * 16 * 256 * 1024 * 2)
+    assert bench.stage_model(cfg, lv_in, "bwd_tokens", 2, True, "pixels") == bench.stage_model(cfg, lv_in, "bwd_tokens", 2, True)
+
+
+
 def test_probe_builds_need_their_own_output_file():
     from paper_2506_21411_amd.build import LIB, build
     with pytest.raises(ValueError):
