@@ -260,7 +260,8 @@ typedef struct {
  * patches and members are fp32 in a fixed order (results are reproducible run to run).  The key bias
  * shifts all scores of a softmax equally, so dbk is written as zeros.  Nothing is kept from a forward
  * call: the activations the reverse sweep needs (tokens, softmax weights, per-head token averages,
- * pre-projection outputs) are recomputed into the workspace first, with the value projection applied
+ * pre-projection outputs, or what takes their place at a first level taken from the pixels; see
+ * dchag_forward_keep) are recomputed into the workspace first, with the value projection applied
  * after the weighted sum (see dchag_forward_folded), so a training step is dchag_forward (or nothing,
  * if `out` is not needed) followed by this call.
  * workspace: dchag_workspace_bytes(..., which = 3).
@@ -329,14 +330,18 @@ typedef enum {
                                       group in its epilogue (weights computed beforehand)      */
   DCHAG_STAGE_CHANNEL_MIX = 8,     /* linear (D-CHAG-L) level: weighted sum over the group      */
   DCHAG_STAGE_TOKENIZE_MIX = 9,    /* tokenizer fused with a linear first level                 */
-  DCHAG_STAGE_HEAD_SUMS = 10,      /* per-head softmax-weighted token averages u_a              */
+  DCHAG_STAGE_HEAD_SUMS = 10,      /* per-head softmax-weighted token averages u_a (where one
+                                      kernel forms them from the tokens: scores and softmax too) */
   DCHAG_STAGE_HEAD_VPROJ = 11,     /* value projection applied to u_a, one head at a time       */
   DCHAG_STAGE_BWD_OPROJ = 12,      /* backward of the output projection (dWo, dbo, d o)         */
   DCHAG_STAGE_BWD_VALUE = 13,      /* backward of the value path (dWv, dbv, w = Wv_a^T d o_a)   */
   DCHAG_STAGE_BWD_SOFTMAX = 14,    /* d alpha, softmax Jacobian                                 */
-  DCHAG_STAGE_BWD_TOKENS = 15,     /* gradient at the level's input tokens                      */
+  DCHAG_STAGE_BWD_TOKENS = 15,     /* gradient at the level's input tokens (first level taken
+                                      from the pixels: at the pixels)                           */
   DCHAG_STAGE_BWD_KEY_QUERY = 16,  /* key / query weight gradients (rank-one per head)          */
-  DCHAG_STAGE_BWD_TOKENIZE = 17,   /* tokenizer backward (dWe, token bias, dx)                  */
+  DCHAG_STAGE_BWD_TOKENIZE = 17,   /* tokenizer backward (dWe, token bias, dx), and the patch
+                                      rows it reads (level taken from the pixels: kept by the
+                                      forward pass)                                             */
   DCHAG_STAGE_BWD_CHANNEL_MIX = 18,/* backward of a linear level                                */
   DCHAG_STAGE_FOLD_VALUE = 19,     /* value projection folded into the tokenizer (weight-only)  */
   DCHAG_STAGE_TOKENIZE_ATTEND = 20,/* tokenizer fused with an attention first level             */

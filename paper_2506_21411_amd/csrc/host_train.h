@@ -491,9 +491,12 @@ inline int head_sums(int B, int Cin, int N, int D, int heads, int g, const float
 }
 
 // Scores, softmax and head sums of a level from its tokens in one launch (k_level_sums), while a group's weights fit LDS.  Whole
-// calls against the separate kernels: 80 variables served at 128 patches, D 256: 55.1 -> 44.0 us; 512 bands served: 245 -> 235 us;
-// 16 x 16 patches, 64 channels, N 1024, D 1024, groups of 32: 633 -> 626 us.  Wide embeddings with more than 16 heads keep the
-// separate ones, which hold the keys in registers (D 4096, 32 heads, groups of 8: 996 against 1004 us).
+// calls against the separate kernels: 80 variables served at 128 patches, D 256: 55.1 -> 44.0 us; 512 bands served: 245 -> 235 us.
+// Few patches and large groups, where a block walks a whole group and most of the chip idles, need no line of their own: folded
+// calls of one level whose scores come from its tokens, 16 heads, D 1024: 256 members x 32 patches 264 -> 172 us, 512 x 16 489 -> 297;
+// D 2048, 64 heads, 512 x 4: 1290 -> 1189; of 207 such calls (4 to 256 patches, groups of 8 to 512, D 256 to 2048, 8 to 64 heads) none
+// was slower.  Wide embeddings with more than 16 heads keep the separate kernels, which hold the keys in registers (D 4096, 32
+// heads, groups of 8: 996 against 1004 us).
 inline bool level_sums_ok(int D, int heads, int g) {
   return D % 256 == 0 && heads <= 64 && !(D > 2048 && heads > 16) &&
          level_sums_lds(1, heads <= 16 ? 1 : heads <= 32 ? 2 : 4, g) <= 150 * 1024 && !dbg(SW_LEVEL_UNFUSED);

@@ -15,6 +15,10 @@
 // Every sum over patches contracts against 16 or 64 pixels instead of D columns, and the two D x D factors meet weight-sized
 // operands: 4 products of the tokenizer's size and 3 of the value fold's, where the route through the tokens streams
 // tokens, averages, their gradients and the token gradients (about ten passes over B C N D elements).
+// Rounded to bf16 on the way: Wf, fb, alpha u per member and the finished sums E and e (F, f and ds go on as hi + lo parts, sums are
+// fp32), where the route through the tokens rounds tokens, per-head averages, their gradients and the token gradients.  Against
+// float64 the errors of the first level's gradients are the smaller ones here (64 bands in groups of 16: dWv 4.9e-3 / 5.2e-3, dx 5.0e-3 /
+// 5.5e-3).
 //
 // All products run on one loop (pair_loop): tiles of 128 x 256 or 256 x 128 outputs, eight wavefronts of 64 x 64, contraction in
 // slices of 64 through three 48-KiB stages that are filled by direct-to-LDS loads two slices ahead.  The barrier sits behind a
