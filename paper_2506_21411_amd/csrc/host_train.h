@@ -1276,8 +1276,8 @@ int tokenizer_backward(int B, int C, int H, int W, int p, int D, const T* x, con
 // region the tokens would have taken.  Whole steps, products per channel / tiles: 512 bands x 4 x 256 patches, D 1024: 741 / 585 us;
 // 1000 channels x 2 x 256 patches of 4 x 4, D 2048: 2114 / 1692; 512 x 4 x 15, D 1024: 318 / 205; small ones fill a fraction of the
 // chip with tiles of 128 x 256: 80 x 2 x 64, D 512 (5 million elements): 133 / 135; 9 x 512, D 512: 163 / 168; 80 x 2 x 256, D 512 (21
-// million): 171 / 171, so the line lies at 2^24.  DCHAG_LINEAR_ROUTE (debugging aid) = tiles / channels overrides the rule, never the
-// limits.
+// million): 171 / 171, so the line lies at 2^24 (none of 71 drawn shapes beyond it was slower).  DCHAG_LINEAR_ROUTE (debugging aid)
+// = tiles / channels overrides the rule, never the limits.
 struct LinearTiles {
   size_t s, dyt, ut, wst, total;
 };

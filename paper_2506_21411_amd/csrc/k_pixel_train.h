@@ -566,7 +566,7 @@ __global__ __launch_bounds__(512) void k_pixel_dx(PixelDims d, TileWork tw, int 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int k, b, mt, nt;
   if (!tw.decode(blockIdx.x, k, b, nt, mt)) return;        // nt: patches, mt: rows (fastest: they share the rows of d_o)
-  constexpr int P = PP == 64 ? 8 : 4, MB = PP == 64 ? 1 : 4;   // members of a wavefront's 64 rows
+  constexpr int MB = PP == 64 ? 1 : 4;                     // members of a wavefront's 64 rows
   constexpr int HH = H32 ? 2 : 1;
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, N = d.N, dh = D / d.heads;
   typedef PairLane<WM> Lane;
@@ -1235,7 +1235,6 @@ __global__ __launch_bounds__(512) void k_linear_dx(PixelDims d, TileWork tw, con
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int k, b, mt, nt;
   if (!tw.decode(blockIdx.x, k, b, nt, mt)) return;        // nt: patches, mt: rows (fastest: they share the rows of dy)
-  constexpr int P = PP == 64 ? 8 : 4;
   const int c0 = k * d.g, gk = min(d.g, d.C - c0), D = d.D, N = d.N, rows = gk * PP;
   typedef PairLane<WM> Lane;
   if (mt * Lane::ROWS >= rows) return;                     // uniform
