@@ -464,6 +464,16 @@ int run_level(dchag_dtype dt, int B, int Cin, int N, int D, int heads, const dch
                           rowadd);
 }
 
+// One persistent workgroup per compute unit (the LDS ring allows no more), an eighth of the tiles to an XCD.
+template <int KIND>
+int launch_product(ProductArgs& pa, hipStream_t st) {
+  const int per = (pa.tw.total + kXcds - 1) / kXcds;
+  pa.slots = per < compute_units() / kXcds ? per : compute_units() / kXcds;
+  if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_product_dl<KIND>), kGemmRingBytes)) return DCHAG_ERR_LAUNCH;
+  k_product_dl<KIND><<<dim3(pa.slots * kXcds), dim3(512), kGemmRingBytes, st>>>(pa);
+  return launch_status();
+}
+
 int launch_linear_dl(int B, int D, RowBlocks rb, const bf16* A, const bf16* Wt, const bf16* bias, bf16* Y,
                      hipStream_t st, const bf16* rowadd = nullptr) {
   TileWork tw;
@@ -484,10 +494,17 @@ int launch_linear_dl(int B, int D, RowBlocks rb, const bf16* A, const bf16* Wt, 
     k_linear_ring<<<dim3(pers * kXcds), dim3(256), kSmallRingBytes, st>>>(D, rb, ts, A, Wt, bias, Y, rowadd);
     return launch_status();
   }
-  const int per = (tw.total + kXcds - 1) / kXcds;
-  if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_linear_dl), kGemmRingBytes)) return DCHAG_ERR_LAUNCH;
-  k_linear_dl<<<dim3(per * kXcds), dim3(512), kGemmRingBytes, st>>>(D, rb, tw, A, Wt, bias, Y, rowadd);
-  return launch_status();
+  ProductArgs pa{};
+  pa.A = A; pa.B = Wt; pa.bias = bias; pa.rowadd = rowadd; pa.C = Y;
+  pa.a_sb = pa.c_sb = (long)rb.rows_per_b * D;
+  pa.a_sk = pa.c_sk = (long)rb.rows_per_group * D;
+  pa.b_sk = (long)D * D;
+  pa.lda = pa.ldb = pa.ldc = pa.ldbias = D;
+  pa.rb = rb;
+  pa.kt = D / kGemmBK;
+  pa.segs = 1;
+  pa.tw = tw;
+  return launch_product<kProductLinear>(pa, st);
 }
 
 // Inputs of the first level's score shortcut: scores computed from the pixels through the

@@ -641,10 +641,17 @@ inline int fold_value_weights(int C, int p, int D, const dchag_level* lv, const 
     const long total = (long)G * tw.m_tiles * tw.n_tiles;
     if (total > (1L << 30)) return DCHAG_ERR_SHAPE;
     tw.total = (int)total;
-    const int per = (tw.total + kXcds - 1) / kXcds;
-    if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_fold_value_dl), kGemmRingBytes)) return DCHAG_ERR_LAUNCH;
-    k_fold_value_dl<<<dim3((unsigned)(per * kXcds)), 512, kGemmRingBytes, st>>>(C, D, g, tw, Wv, We, Wf);
-    if ((rc = launch_status())) return rc;
+    ProductArgs pa{};
+    pa.A = Wv; pa.B = We; pa.C = Wf;
+    pa.a_sk = (long)D * D;
+    pa.b_sk = (long)D * 64;
+    pa.c_sk = (long)g * D * 64;
+    pa.lda = D; pa.ldc = 64;
+    pa.kt = D / kGemmBK;
+    pa.segs = 1;
+    pa.C_all = C; pa.g = std::min(g, C);
+    pa.tw = tw;
+    if ((rc = launch_product<kProductFold>(pa, st))) return rc;
   } else {
     GemmDesc d{};
     d.M = D; d.N = pp; d.K = D; d.nb = 1;
@@ -1086,6 +1093,44 @@ int outer_rows(int D, int G, int rows_per_vec, float scale, const float* rowv, c
   return launch_status();
 }
 
+// The same on the large products' core.  Taken where its 256 x 256 tiles of either product keep half of the compute units busy.
+inline bool projection_products_ok(int B, int G, int N, int D, const dchag_level_grads* gr) {
+  const long m = D / kGemmBM;
+  return D % 256 == 0 && N % 128 == 0 && N >= 256 && gr->dWo && G * m * m * 2 >= compute_units() &&
+         (long)B * G * (N / 256) * m * 2 >= compute_units() && (long)B * G * N * m < (1L << 28) && !dbg(SW_GEMM_GENERIC) &&
+         !dbg(SW_COLSUM);
+}
+inline int projection_products(int B, int G, int N, int D, const dchag_level* lv, const dchag_level_grads* gr, const bf16* dy,
+                               const bf16* o, bf16* d_o, hipStream_t st) {
+  const long sBG = (long)G * N * D, sG = (long)N * D;
+  ProductArgs pa{};
+  pa.A = dy; pa.B = o; pa.C = static_cast<bf16*>(gr->dWo); pa.rowsum = static_cast<bf16*>(gr->dbo);
+  pa.a_sb = pa.b_sb = sBG;
+  pa.a_sk = pa.b_sk = sG;
+  pa.c_sk = (long)D * D;
+  pa.lda = pa.ldb = pa.ldc = pa.ldbias = D;
+  pa.kt = N / kGemmBK;
+  pa.segs = B;
+  pa.tw.n_tiles = pa.tw.m_tiles = D / kGemmBM;
+  pa.tw.nb = 1;
+  pa.tw.total = G * pa.tw.m_tiles * pa.tw.n_tiles;
+  if (int rc = launch_product<kProductWeights>(pa, st)) return rc;
+  ProductArgs pb{};
+  pb.A = dy; pb.B = static_cast<const bf16*>(lv->Wo); pb.C = d_o;
+  pb.a_sb = pb.c_sb = sBG;
+  pb.a_sk = pb.c_sk = sG;
+  pb.b_sk = (long)D * D;
+  pb.lda = pb.ldb = pb.ldc = D;
+  pb.rb = {G, G * N, N};
+  pb.kt = D / kGemmBK;
+  pb.segs = 1;
+  pb.tw.n_tiles = D / kGemmBN;
+  pb.tw.m_tiles = (N + kGemmBM - 1) / kGemmBM;
+  pb.tw.nb = B;
+  pb.tw.total = pb.tw.n_tiles * pb.tw.m_tiles * B * G;
+  return launch_product<kProductBack>(pb, st);
+}
+
 // Reverse of a level's output projection: dWo, dbo and d_o, the gradient at its input o [B,G,N,D].
 template <typename T>
 int output_projection_backward(int B, int G, int N, int D, const dchag_level* lv, const dchag_level_grads* gr, const T* dy,
@@ -1094,6 +1139,10 @@ int output_projection_backward(int B, int G, int N, int D, const dchag_level* lv
   const long sBG = (long)G * N * D, sG = (long)N * D;          // strides of a [B,G,N,D] tensor
   int rc;
   StageTimer tm(DCHAG_STAGE_BWD_OPROJ, st);
+  if constexpr (std::is_same<T, bf16>::value) {
+    if (projection_products_ok(B, G, N, D, gr))
+      return projection_products(B, G, N, D, lv, gr, dy, o, d_o, st);
+  }
   {                                                             // dWo[k][i][j] = sum_{b,n} dy[..,i] o[..,j];  dbo = sum dy
     GemmDesc d{};
     d.M = D; d.N = D; d.K = N; d.nb = B; d.nk = G; d.na = 1; d.reduce_b = 1;

@@ -5,17 +5,17 @@
 //   k_softmax_alpha   softmax of the scores over the members of each group
 //   k_vagg_mfma       value projection GEMM whose epilogue takes the softmax-weighted sum over
 //                     the channels of the group, so that the projected values never leave the CU
-//   k_linear_dl       plain per-group projection GEMM (output projection)
-//   k_fold_value_dl   weight-only product Wv We[c] (value projection folded into the tokenizer weights)
+//   k_product_dl      plain per-group products: output projections, their gradients, and the weight-only product
+//                     Wv We[c] (value projection folded into the tokenizer weights)
 //   k_scores_pixels*, k_compose_score_weights*   first-level scores straight from the pixels
 //   k_tokenize_ws, k_tokenize_mfma               the per-channel tokenizer (paper Section 2.1)
 //   k_tokenize_reduce_ring, k_tokenize_mix_*, k_tokenize_attend_wide   tokenizer fused with the first level
 //                     (linear level of D-CHAG-L, or attention level with folded value weights): no tokens in HBM
 //
-// The two GEMM kernels share one core: 256x256 block tile, 8 wavefronts (2 x 4), 32x32x16 bf16
+// The GEMM kernels share one core: 256x256 block tile, 8 wavefronts (2 x 4), 16x16x32 bf16
 // MFMA, K staged in 64-element slices through two LDS stages that are filled by direct-to-LDS
 // global loads of 128-byte row segments (no register staging; L2 delivers 128-byte segments at
-// about twice the rate of 64-byte ones) and read with conflict-free swizzled ds_read_b128.
+// about twice the rate of 64-byte ones) and read with conflict-free swizzled LDS reads.
 //
 // Softmax weights are exchanged between the kernels in the layout
 //   alpha[b][k][cl][head][n]   (n fastest, pitch Np = N rounded up to 32; cl < gpad = g rounded up to 8)
@@ -52,7 +52,7 @@ __device__ __forceinline__ void load16_to_lds(const void* src, void* lds_base) {
 // then fall into 16 different 16-byte bank groups (64 banks x 4 bytes), so ds_read_b128 is conflict-free.
 __device__ __forceinline__ int swz_chunk(int row) { return (row >> 1) & 7; }
 
-constexpr int kGemmBM = 256, kGemmBN = 256, kGemmBK = 64, kGemmWM = 2, kGemmWN = 4, kGemmStages = 2;
+constexpr int kGemmBM = 256, kGemmBN = 256, kGemmBK = 64, kGemmStages = 2;
 constexpr int kGemmStageBytes = (kGemmBM + kGemmBN) * kGemmBK * 2;             // 64 KiB
 constexpr int kGemmRingBytes = kGemmStages * kGemmStageBytes;                  // 128 KiB
 
@@ -491,136 +491,191 @@ __global__ __launch_bounds__(256) void k_softmax_alpha(int Cin, int N, int heads
 }
 
 // ---------------------------------------------------------------------------------------------
-// GEMM core pieces shared by k_vagg_mfma and k_linear_dl.
-//   Block tile 256 x 256 x 64, wavefront (wm, wn) of 2 x 4 owns rows [128 wm, +128) x cols [64 wn, +64):
-//   TM = 4 by TN = 2 MFMA blocks of 32 x 32.  One stage = A rows 0..255 then B rows 0..255, 128 bytes each;
-//   two stages: while one is multiplied the other is filled by direct-to-LDS loads of 128-byte row
-//   segments (8 lanes per row), issued a whole slice ahead.
-//   Global -> LDS: wavefront w issues 4 A loads and 4 B loads per slice; load i covers tile rows
-//   w*32 + i*8 + lane/8, i.e. the A rows of wavefront w are the 32 patches of ONE channel of the chunk.
+// The 256 x 256 x 64 core of the large products (k_vagg_mfma, k_product_dl).
+//
+// Instruction: v_mfma_f32_16x16x32.  These kernels run into the card's power limit, so what counts is the work done per joule:
+// a loop of nothing but products on normally distributed operands reaches 1.95 PFLOP/s with 16x16x32 and 1.34 with
+// 32x32x16 (2.45 and 1.67 on constant operands; 256 x 8 wavefronts, a 128 x 64 tile each).
+//
+// Eight wavefronts (2 x 4).  A stage of the ring holds one slice of 64 contraction elements as four slots of 16 KiB (128
+// rows x 128 bytes, swizzled): A0, A1 (tile rows 0..127, 128..255) and B0, B1; two stages.  Wavefront (wm, wn) owns rows
+// [64 wm, +64) of BOTH A slots and columns [32 wn, +32) of BOTH B slots, so that a slice is four phases of sixteen
+// products, one per pair of slots: (A0,B0) (A0,B1) (A1,B1) (A1,B0).  Each phase reads the fragments of ONE slot,
+// the one whose first use comes next (B1, A1, the next slice's A0, the next slice's B0): after the phase's barrier that slot
+// holds nothing anybody needs and takes its rows of the slice after the next one.  So seven slots (112 KiB) are on their
+// way at any time and a load has seven phases (1.75 slices) to arrive; a stage handed over as a whole leaves it one slice.
+// The barrier of a phase sits in front of its last products, which cover it; every wait is a counted one (vmcnt 12: all but
+// the six youngest slots).
 // ---------------------------------------------------------------------------------------------
-struct GemmLane {
-  int lane, wave, wm, wn, l32, lhi;
-  int a_base, b_base;             // byte offsets of this lane's first A / B fragment row inside a stage
-  int ck[4];                      // swizzled chunk byte offset of k-step kk
+constexpr int kSlotBytes = 128 * 128;                    // A stages at 0 and 2 slots, B stages at 4 and 6 slots
+enum CoreSlot { kSlotA0 = 0, kSlotA1 = 1, kSlotB0 = 4, kSlotB1 = 5 };
+
+// A copy that the compiler knows nothing about: what is computed from it is computed where it is used.  The fragments and
+// sums need every register of the loops, so what a loop needs rarely is formed again instead of being kept (lane_id: the lane's
+// number, from no register at all).
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ int lane_id() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
+struct CoreLane {
+  int wave, wm, wn;
+  int a_ad, b_ad;                                        // byte of this lane's first fragment in A0 / B0, stage 0
+  template <class OA, class OB>
   __device__ __forceinline__ void init() {
-    lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: lives in a scalar register
-    wm = wave / kGemmWN;
-    wn = wave % kGemmWN;
-    l32 = lane & 31;
-    lhi = lane >> 5;
-    a_base = (wm * 128 + l32) * 128;
-    b_base = kGemmBM * 128 + (wn * 64 + l32) * 128;
-    const int sw = swz_chunk(l32);               // row offsets of the other fragments are multiples of 32
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) ck[kk] = ((kk * 2 + lhi) ^ sw) * 16;
+    wm = wave >> 2;
+    wn = wave & 3;
+    a_ad = OA::base(wm * 64, lane_id());
+    b_ad = 4 * kSlotBytes + OB::base(wn * 32, lane_id());
   }
-  // load i of this wavefront covers tile row wave*32 + i*8 + lane/8, logical chunk (lane%8) ^ swz(row)
-  __device__ __forceinline__ int load_row(int i) const { return wave * 32 + i * 8 + (lane >> 3); }
-  __device__ __forceinline__ int load_chunk(int row) const { return (lane & 7) ^ swz_chunk(row); }
+  // Wavefront w fills rows 16 w + 8 u + lane / 8 (u = 0, 1) of a RowOperand's slot; the byte of the chunk that belongs there:
+  static __device__ __forceinline__ int ld_chunk(int lane, int u) { return ((lane & 7) ^ swz_chunk(u * 8 + (lane >> 3))) * 16; }
 };
 
-struct Frags {
-  bf16x8 a[4], b[2];
+// 16 bytes a lane from base + voff (base wave-uniform) to lds_off + 16 * lane; an asm statement for the reason given at
+// load16_to_lds.
+__device__ __forceinline__ void load16_to_lds_at(const void* base, unsigned voff, unsigned lds_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_off), "v"(voff), "s"(base) : "memory", "m0");
+}
+
+struct CoreFrags {
+  bf16x8 a0[4][2], a1[4][2], bx[2][2], by[2][2];         // [block][k-step]; bx / by: B0 / B1 of an even slice, B1 / B0 of an odd one
+};
+typedef f32x4 CoreAcc[2][4][2][2];                       // [A slot][block of 16 rows][B slot][block of 16 columns]
+
+// How an operand lies in its slots, and how a fragment (16 of its rows or columns x 32 contraction elements, eight to a lane)
+// of block blk and k-step kk is read; base: the lane's address for block 0 and k-step 0 of the wavefront's part of slot 0.
+//
+// RowOperand: rows of 64 contraction elements, 128 rows a slot.  k-step kk flips bit 6 of the address (its chunk is
+// (4 kk + lane / 16) ^ swizzle).
+struct RowOperand {
+  static __device__ __forceinline__ int base(int part, int lane) {
+    const int l16 = lane & 15;
+    return (part + l16) * 128 + ((lane >> 4) ^ swz_chunk(l16)) * 16;         // part: a multiple of 16
+  }
+  static __device__ __forceinline__ bf16x8 frag(const unsigned char* smem, int ad, int blk, int kk, int imm) {
+    return *reinterpret_cast<const bf16x8*>(smem + (opaque(ad) ^ (kk * 64)) + imm + blk * 2048);
+  }
+};
+// ColOperand: the contraction index runs over the rows, PITCH / 2 of the operand's columns to a row (128 columns and all 64
+// contraction elements a slot, or 64 columns of two matrices).  ds_read_b64_tr_b16 transposes on the way: lane l of 16 names
+// four columns (l % 4) of contraction row l / 4 and receives column l of the four rows; two of them make the lane's eight
+// elements.  The chunk swizzle is twice f(row), f one of PITCH / 32 values, so that the eight rows (0..3 and 8..11, 4..7 and
+// 12..15) that half a wavefront reads at one pair of chunks lie in different banks; block blk flips bits 5 and 6.
+template <int PITCH>
+struct ColOperand {
+  static __device__ __forceinline__ int swz(int row) {
+    return PITCH == 256 ? ((row & 3) | ((row >> 3) & 1) << 2) * 2 : (((row >> 1) & 1) | ((row >> 3) & 1) << 1) * 2;
+  }
+  static __device__ __forceinline__ int base(int part, int lane) {
+    const int l16 = lane & 15, row = (lane >> 4) * 8 + (l16 >> 2);
+    const int first = PITCH == 256 ? 0 : (part >> 6) * 64 * 128, col = PITCH == 256 ? part : part & 63;
+    return first + row * PITCH + (((col >> 3) + ((l16 & 3) >> 1)) ^ swz(row)) * 16 + (l16 & 1) * 8;
+  }
+  static __device__ __forceinline__ bf16x8 frag(const unsigned char* smem, int ad, int blk, int kk, int imm) {
+    typedef __attribute__((ext_vector_type(4))) short s16x4;
+    typedef __attribute__((ext_vector_type(8))) short s16x8;
+    typedef __attribute__((address_space(3))) s16x4* tptr;
+    const unsigned char* p = smem + (opaque(ad) ^ (blk * 32)) + imm + kk * 32 * PITCH;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr)(p + 4 * PITCH));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
 };
 
-// Timing probes of the GEMM core (compile-time; 0 in the product build).  `python -m paper_2506_21411_amd.build
-// --define DCHAG_GEMM_PROBE=n --out <file>` builds a library whose RESULTS ARE MEANINGLESS and whose timing tells what
-// each part of k_vagg_mfma costs: bit 1 = no MFMAs (the fragments are still read), 2 = no fragment reads, 4 = no
-// barrier per slice, 8 = no global -> LDS loads (32 = none of the A operand, 64 = none of the B operand, k_vagg_mfma only),
-// 16 = k_linear_dl stores (next to) nothing.  Every access stays in bounds
-// and every loop keeps its trip count.
-#ifndef DCHAG_GEMM_PROBE
-#define DCHAG_GEMM_PROBE 0
-#endif
-
-__device__ __forceinline__ void read_frags(Frags& f, const unsigned char* stage, const GemmLane& L, int kk) {
-  if (DCHAG_GEMM_PROBE & 2) {                            // keep the registers opaque, read nothing
+// One phase: c += a x b over the slice; the reads of the next phase's slot (NR of them, rd(t)) behind the first products,
+// the hand-over (wait, barrier, issue) in front of the last four.  SWAP multiplies b x a, which leaves the transposed block: a
+// lane then holds one tile row and four adjacent columns.
+template <bool FIRST, bool SWAP, int NR, int HA, int HB, class Read, class Issue>
+__device__ __forceinline__ void core_phase(CoreAcc& acc, const bf16x8 (&a)[4][2], const bf16x8 (&b)[2][2], Read rd, Issue issue) {
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(f.a[i]));
+  for (int m = 0; m < 16; ++m) {
+    const int kk = m >> 3, i = (m >> 1) & 3, j = m & 1;
+    f32x4& c = acc[HA][i][HB][j];
+    if (m == 12) {
+      __builtin_amdgcn_s_waitcnt((12 & 15) | (0 << 14) | (7 << 4) | (0 << 8));   // vmcnt(12) lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      issue();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (SWAP) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][kk], a[i][kk], FIRST && kk == 0 ? zero : c, 0, 0, 0);
+    else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][kk], b[j][kk], FIRST && kk == 0 ? zero : c, 0, 0, 0);
+    if (m < 8) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(f.b[j]));
-    return;
+      for (int t = m * NR / 8; t < (m + 1) * NR / 8; ++t) rd(t);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f.a[i] = *reinterpret_cast<const bf16x8*>(stage + L.a_base + i * 4096 + L.ck[kk]);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) f.b[j] = *reinterpret_cast<const bf16x8*>(stage + L.b_base + j * 4096 + L.ck[kk]);
 }
 
-__device__ __forceinline__ void mfma_step(f32x16 (&acc)[4][2], const Frags& f) {
-  if (DCHAG_GEMM_PROBE & 1) {                            // the fragments count as used, nothing is multiplied
-#pragma unroll
-    for (int i = 0; i < 4; ++i) asm volatile("" : : "v"(f.a[i]));
-#pragma unroll
-    for (int j = 0; j < 2; ++j) asm volatile("" : : "v"(f.b[j]));
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+// Slice of stage S (0 even, 1 odd).  issue(slot constant): the next pair of loads of that slot (see CoreSlot).  In stage 1 the
+// roles of bx and by are exchanged.  held(slot, fragments): called once a slice with all fragments of A0, and of A1.
+template <bool FIRST, bool SWAP, int S, class OA, class OB, class Issue, class Held>
+__device__ __forceinline__ void core_slice(CoreAcc& acc, CoreFrags& f, const unsigned char* smem, const CoreLane& L, Issue issue,
+                                           Held held) {
+  bf16x8 (&b0)[2][2] = S ? f.by : f.bx;
+  bf16x8 (&b1)[2][2] = S ? f.bx : f.by;
+  constexpr int here = S * 2 * kSlotBytes, next = (S ^ 1) * 2 * kSlotBytes;
+  core_phase<FIRST, SWAP, 4, 0, 0>(acc, f.a0, b0,
+      [&](int t) { b1[t & 1][t >> 1] = OB::frag(smem, L.b_ad, t & 1, t >> 1, here + kSlotBytes); },
+      [&]() { issue(kSlotB1 + 2 * S); });
+  held(0, f.a0);
+  core_phase<FIRST, SWAP, 8, 0, 1>(acc, f.a0, b1,
+      [&](int t) { f.a1[t & 3][t >> 2] = OA::frag(smem, L.a_ad, t & 3, t >> 2, here + kSlotBytes); },
+      [&]() { issue(kSlotA1 + 2 * S); });
+  core_phase<FIRST, SWAP, 8, 1, 1>(acc, f.a1, b1,
+      [&](int t) { f.a0[t & 3][t >> 2] = OA::frag(smem, L.a_ad, t & 3, t >> 2, next); },
+      [&]() { issue(kSlotA0 + 2 * (S ^ 1)); });
+  held(1, f.a1);
+  core_phase<FIRST, SWAP, 4, 1, 0>(acc, f.a1, b0,
+      [&](int t) { b1[t & 1][t >> 1] = OB::frag(smem, L.b_ad, t & 1, t >> 1, next); },
+      [&]() { issue(kSlotB0 + 2 * (S ^ 1)); });
 }
 
-// First k-step of an accumulation: C = 0 is an inline operand of the MFMA, the accumulators need no clearing.
-__device__ __forceinline__ void mfma_step_first(f32x16 (&acc)[4][2], const Frags& f) {
-  if (DCHAG_GEMM_PROBE & 1) {
+// Fills the ring and reads the first slice's A0 and B0.  Slots are issued in the order A0 B0 B1 A1 of slice 0, of slice 1,
+// then A0 B0 of slice 2; the phases go on with B1 A1 A0 B0 ...
+template <class OA, class OB, class Issue>
+__device__ __forceinline__ void core_prologue(CoreFrags& f, const unsigned char* smem, const CoreLane& L, Issue issue) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    mfma_step(acc, f);
-    return;
+  for (int s = 0; s < 2; ++s) {
+    issue(kSlotA0 + 2 * s);
+    issue(kSlotB0 + 2 * s);
+    issue(kSlotB1 + 2 * s);
+    issue(kSlotA1 + 2 * s);
   }
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  wait_vmcnt<12>();
+  __builtin_amdgcn_s_barrier();
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int t = 0; t < 8; ++t) f.a0[t & 3][t >> 2] = OA::frag(smem, L.a_ad, t & 3, t >> 2, 0);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], zero, 0, 0, 0);
-}
-
-// Scheduling of one k-step of the GEMM loops: the six fragment reads of step kk + 1 and the eight products of step kk
-// that were written since the last scheduling barrier are issued as product, read, product, read, ... (a read behind
-// each of the first six products), and nothing moves across the end of the step.  Left alone, the compiler sinks the
-// reads next to their use to save registers and then waits for each of them in turn; in this order every wait is a
-// counted one for fragments that were requested a whole step earlier.
-__device__ __forceinline__ void pin_step_schedule() {
-#pragma unroll
-  for (int t = 0; t < 6; ++t) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+  for (int t = 0; t < 4; ++t) f.bx[t & 1][t >> 1] = OB::frag(smem, L.b_ad, t & 1, t >> 1, 0);
+  __builtin_amdgcn_s_waitcnt((10 & 15) | (0 << 14) | (7 << 4) | (0 << 8));       // vmcnt(10) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  issue(kSlotA0);
+  issue(kSlotB0);
   __builtin_amdgcn_sched_barrier(0);
-}
-
-// One 64-deep slice: four k-steps with the fragments of step kk+1 read while step kk multiplies.
-__device__ __forceinline__ void mfma_slice(f32x16 (&acc)[4][2], const unsigned char* stage, const GemmLane& L) {
-  Frags f0, f1;
-  read_frags(f0, stage, L, 0);
-  read_frags(f1, stage, L, 1);
-  mfma_step(acc, f0);
-  read_frags(f0, stage, L, 2);
-  mfma_step(acc, f1);
-  read_frags(f1, stage, L, 3);
-  mfma_step(acc, f0);
-  mfma_step(acc, f1);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Value projection with the channel aggregation in its epilogue:
 //   O[b,k,n,o] = sum_{cl < gk} alpha[b][k][cl][head(o)][n] * (z[b, k*g + cl, n, :] . Wv[k][o][:]) + bv[k][o]
 // Work item (decoded by TileWork with m = patch tile): group k, batch b, 32 patches, 256 columns; the group
-// is walked in chunks of 8 channels.  LDS tile row (wm*128 + i*32 + l) holds channel 2i + l/16 of the chunk,
-// patch 16*wm + l%16, so wavefront (wm, wn) sees all 8 channels of ITS 16 patches: the weighted sum over
-// the channels stays inside the wavefront's registers (rows q = 0,1 of an accumulator block belong to
-// channel 2i, rows q = 2,3 to channel 2i+1) and no cross-wavefront merge is needed.
+// is walked in chunks of 8 channels.  Tile row 128 h + 64 wm + 16 i + l holds channel 4h + i of the chunk, patch
+// 16*wm + l, so wavefront (wm, wn) sees all 8 channels of ITS 16 patches, a channel to a block of rows: the weighted
+// sum over the channels stays inside the wavefront's registers and no cross-wavefront merge is needed.
 // The kernel is persistent: workgroup L takes items L/8, L/8 + slots, ... of its XCD's contiguous
-// range, and the two-stage ring keeps prefetching across chunk and item boundaries (one slice ahead).
+// range, and the ring keeps prefetching across chunk and item boundaries.
 // Requires D % 256 == 0, dh = D / heads a multiple of 32, and 256 % dh == 0 or dh % 256 == 0.
+// Bound by the card's power limit: at 512 channels, D 1024, B 4, N 256 the matrix units are busy 64 % of the cycles at
+// 1.95 GHz (a library product of the same operands' size: 87 % at 1.57 GHz, 8 % more work a second), 835 us against 865 with
+// 32x32x16 instructions and whole stages (68 % at 1.79 GHz).
 // Dynamic LDS: ring (128 KiB) + 3 alpha tiles of 8 * NHS * 32 floats, used round-robin by chunk.
 // ---------------------------------------------------------------------------------------------
 struct VaggItem {
@@ -633,9 +688,10 @@ __global__ __launch_bounds__(512) void k_vagg_mfma(int Cin, int N, int D, int he
                                                    const float* __restrict__ alpha, bf16* __restrict__ O, int S,
                                                    float* __restrict__ Opart) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const int KT = D / kGemmBK;
+  const int KT = D / kGemmBK;                            // a multiple of 4: every chunk starts in stage 0
   const int dh = D / heads;
   const int NHS = dh >= kGemmBN ? 1 : kGemmBN / dh;      // heads inside a 256-column slice
+  const int nhs_log = __builtin_ctz(NHS);                // dh is 32, 64, 128 or a multiple of 256: NHS is a power of two
   unsigned char* alds = smem + kGemmRingBytes;           // 3 tiles of [8][NHS][32] floats
   const int atile = 8 * NHS * 32 * 4;
 
@@ -660,170 +716,132 @@ __global__ __launch_bounds__(512) void k_vagg_mfma(int Cin, int N, int D, int he
     return true;
   };
 
-  GemmLane L;
-  L.init();
-  // A loads of wavefront w fill LDS rows w*32 + i*8 + lane/8: channel 2*(w%4) + (l>>4), patch 16*(w/4) + (l&15)
-  int a_ch[4], a_patch[4], ld_chunk[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int l = i * 8 + (L.lane >> 3);
-    a_ch[i] = 2 * (L.wave & 3) + (l >> 4);
-    a_patch[i] = 16 * (L.wave >> 2) + (l & 15);
-    ld_chunk[i] = L.load_chunk(L.load_row(i)) * 8;
-  }
+  CoreLane L;
+  L.init<RowOperand, RowOperand>();
+  const unsigned smem_off = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem);
+  const unsigned wave_off = smem_off + L.wave * 2048;    // this wavefront's 16 rows of a slot
 
-  // ---- issue side ----
-  VaggItem ii;
-  int ti = 0;
-  bool live = item_of(0, ii);
-  if (!live) return;                                     // uniform: the whole workgroup has nothing to do
-  size_t a_rowoff[4];
-  const bf16* b_src[4];
-  const bf16* zb;
-  const bf16* a_cur[4];                                  // running source pointers: advance 64 elements per slice
-  const bf16* b_cur[4];
-  int ci = 0, ki = 0, si = 0, gci = 0;                   // chunk, k-slice, stage, running chunk count (alpha buffer)
-  auto setup_chunk = [&]() {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = ii.c0 + min((ii.ch0 + ci) * 8 + a_ch[i], ii.gk - 1);
-      a_cur[i] = zb + (size_t)c * N * D + a_rowoff[i];
-      b_cur[i] = b_src[i];
-    }
+  // ---- issue side: the wavefront's 16 rows of slot A_h are channel 4h + w % 4 of the chunk, patches 16 (w / 4) .. + 15 ----
+  VaggItem ic, nx;                                       // the item that is multiplied, and the next chunk's
+  if (!item_of(0, ic)) return;                           // uniform: the whole workgroup has nothing to do
+  struct Src {
+    const bf16 *a0, *a1, *b0, *b1;                       // origins of a chunk's tile in its running slice, per slot
+    const float* al;                                     // its softmax weights
+    int n0;
+  } run, nxt;
+  auto source = [&](const VaggItem& it, int chunk, Src& s) {
+    const int cl = (it.ch0 + chunk) * 8;
+    const bf16* zb = z + ((size_t)it.b * Cin * N + it.n0) * D;
+    s.a0 = zb + (size_t)(it.c0 + min(cl + (L.wave & 3), it.gk - 1)) * N * D;
+    s.a1 = zb + (size_t)(it.c0 + min(cl + (L.wave & 3) + 4, it.gk - 1)) * N * D;
+    s.b0 = Wv + ((size_t)it.k * D + it.o0 + L.wave * 16) * D;
+    s.b1 = s.b0 + (size_t)128 * D;
+    s.al = alpha + ((((size_t)it.b * G + it.k) * gpad + cl) * heads + it.h0) * Np + it.n0;
+    s.n0 = it.n0;
   };
-  auto setup_issue = [&]() {
-    zb = z + (size_t)ii.b * Cin * N * D;
-    const bf16* Wb = Wv + (size_t)ii.k * D * D;
+  unsigned a_off[2];                                     // byte of a lane's 16 behind those origins
+  auto patch_rows = [&](int n0) {
+    const int lane = lane_id();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a_rowoff[i] = (size_t)min(ii.n0 + a_patch[i], N - 1) * D + ld_chunk[i];
-      b_src[i] = Wb + (size_t)(ii.o0 + L.load_row(i)) * D + ld_chunk[i];
-    }
+    for (int u = 0; u < 2; ++u)
+      a_off[u] = (unsigned)(min(n0 + 16 * (L.wave >> 2) + u * 8 + (lane >> 3), N - 1) - n0) * D * 2 + L.ld_chunk(lane, u);
   };
-  setup_issue();
-  setup_chunk();
-  auto issue = [&]() {
-    if (live) {
-      if (ki == 0 && L.wave < NHS) {                     // entering a chunk: fetch its softmax weights
-        const int sgm = L.wave * 8 + (L.lane >> 3);      // segment = (channel of the chunk, head of the slice)
-        const int cl = (ii.ch0 + ci) * 8 + sgm / NHS, hd = sgm % NHS;
-        const float* src = alpha + ((((size_t)ii.b * G + ii.k) * gpad + cl) * heads + ii.h0 + hd) * Np + ii.n0 +
-                           (L.lane & 7) * 4;
-        load16_to_lds(src, alds + (gci % 3) * atile + L.wave * 1024);
-      }
-      unsigned char* st = smem + si * kGemmStageBytes + L.wave * 4096;
+  const int b_off = (lane_id() >> 3) * D * 2 + L.ld_chunk(lane_id(), 0);  // eight rows further: bit 6 (the chunk's) flips, 16 D bytes
+  source(ic, 0, run);
+  patch_rows(run.n0);
+  int ki = 0, gci = 0;                                   // slices issued of the chunk, running chunk count (alpha buffer)
+  auto issue = [&](int sl) {                             // sl: a constant once inlined
+    const unsigned dst = wave_off + sl * kSlotBytes;
+    const int kind = sl & ~2;
+    if (sl == kSlotA0 && ki == 0 && L.wave < NHS) {      // entering a chunk (its slices are even in number): its softmax weights
+      const int l = lane_id(), sgm = L.wave * 8 + (l >> 3);   // segment = (channel of the chunk, head of the slice)
+      load16_to_lds_at(run.al, ((unsigned)((sgm >> nhs_log) * heads + (sgm & (NHS - 1))) * Np + (l & 7) * 4) * 4,
+                       smem_off + kGemmRingBytes + (gci % 3) * atile + L.wave * 1024);
+    }
+    const bf16*& p = kind == kSlotA0 ? run.a0 : kind == kSlotA1 ? run.a1 : kind == kSlotB0 ? run.b0 : run.b1;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (!(DCHAG_GEMM_PROBE & (8 | 32))) load16_to_lds(a_cur[i], st + i * 1024);
-        a_cur[i] += kGemmBK;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (!(DCHAG_GEMM_PROBE & (8 | 64))) load16_to_lds(b_cur[i], st + kGemmBM * 128 + i * 1024);
-        b_cur[i] += kGemmBK;
-      }
-      if (++ki == KT) {
+    for (int u = 0; u < 2; ++u) {
+      if (kind == kSlotA0 || kind == kSlotA1) load16_to_lds_at(p, a_off[u], dst + u * 1024);
+      else load16_to_lds_at(p + (size_t)u * 8 * D, opaque(b_off) ^ (u * 64), dst + u * 1024);
+    }
+    p += kGemmBK;
+    if (sl == kSlotA1 + 2) {                             // the last slot of an odd slice
+      ki += 2;
+      if (ki == KT) {
         ki = 0;
         ++gci;
-        if (++ci == ii.nch) {
-          ci = 0;
-          live = item_of(++ti, ii);
-          if (live) setup_issue();
-        }
-        if (live) setup_chunk();
+        run = nxt;
+        patch_rows(run.n0);
       }
     }
-    si ^= 1;
   };
 
   // ---- compute side ----
-  issue();                                               // first slice -> stage 0
-  int sc = 0, gcc = 0;
-  Frags f0, f1;
-  wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-  if (L.wm == 0) issue();                                // second slice -> stage 1 (wm = 1 issues inside the loop)
-  read_frags(f0, smem, L, 0);
-  VaggItem ic;
-  for (int tc = 0; item_of(tc, ic); ++tc) {
-    f32x16 o[2];
+  auto nothing = [](int, const bf16x8 (&)[4][2]) {};
+  CoreFrags f;
+  core_prologue<RowOperand, RowOperand>(f, smem, L, issue);
+  f32x4 o[2][2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[j][r] = 0.f;      // only entries 0..7 are used
-    for (int chunk = 0; chunk < ic.nch; ++chunk, ++gcc) {
-      f32x16 acc[4][2];
-      for (int kt = 0; kt < KT; ++kt) {
-        // k-steps 0..2 of the current slice; the fragments of step 0 were read across the last barrier.  Each step's
-        // products are issued with the reads of the step after it between them (pin_step_schedule).
-        const unsigned char* st = smem + sc * kGemmStageBytes;
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(f1, st, L, 1);
-        if (kt == 0) mfma_step_first(acc, f0);           // a chunk starts from C = 0
-        else mfma_step(acc, f0);
-        pin_step_schedule();
-        if (L.wm == 1) issue();                          // slice after next -> the stage released at the last barrier
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(f0, st, L, 2);
-        mfma_step(acc, f1);
-        pin_step_schedule();
-        read_frags(f1, st, L, 3);
-        mfma_step(acc, f0);
-        pin_step_schedule();
-        // every read of this stage is in registers and the next slice has landed: swap stages
-        __builtin_amdgcn_s_waitcnt(0);                   // vmcnt(0) and lgkmcnt(0)
-        if (!(DCHAG_GEMM_PROBE & 4)) __builtin_amdgcn_s_barrier();
-        if (L.wm == 0) issue();                          // slice after next -> the stage just released
-        sc ^= 1;
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(f0, smem + sc * kGemmStageBytes, L, 0);
-        mfma_step(acc, f1);
-        pin_step_schedule();
+  for (int j = 0; j < 4; ++j) o[j >> 1][j & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int t = 0, chunk = 0, gcc = 0;
+  for (;;) {
+    nx = ic;
+    int nchunk = chunk + 1;
+    bool more = true;
+    if (nchunk == ic.nch) {
+      nchunk = 0;
+      more = item_of(++t, nx);                           // past the last item: this one again, loaded and not used
+    }
+    source(nx, nchunk, nxt);
+    {
+      CoreAcc acc;
+      core_slice<true, false, 0, RowOperand, RowOperand>(acc, f, smem, L, issue, nothing);
+      core_slice<false, false, 1, RowOperand, RowOperand>(acc, f, smem, L, issue, nothing);
+      for (int kt = 2; kt < KT; kt += 2) {
+        core_slice<false, false, 0, RowOperand, RowOperand>(acc, f, smem, L, issue, nothing);
+        core_slice<false, false, 1, RowOperand, RowOperand>(acc, f, smem, L, issue, nothing);
       }
-      // o += alpha * acc over the 8 channels of the chunk (channel 2i in rows q = 0,1; 2i+1 in rows q = 2,3)
-      const float* al = reinterpret_cast<const float*>(alds + (gcc % 3) * atile);
+      // o += alpha * acc over the 8 channels of the chunk
+      const float* al = reinterpret_cast<const float*>(alds + (gcc % 3) * atile) + 16 * L.wm + 4 * (lane_id() >> 4);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int hrel = (ic.o0 + L.wn * 64 + j * 32) / dh - ic.h0;
+      for (int hb = 0; hb < 2; ++hb) {
+        const float* ap = al + ((ic.o0 + hb * 128 + L.wn * 32) / dh - ic.h0) * 32;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int c = 0; c < 8; ++c) {
+          const f32x4 a4 = *reinterpret_cast<const f32x4*>(ap + c * NHS * 32);
 #pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            const float* ap = al + ((2 * i + half) * NHS + hrel) * 32 + 16 * L.wm + 4 * L.lhi;
+          for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const f32x4 a4 = *reinterpret_cast<const f32x4*>(ap + 8 * q);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o[j][4 * q + e] += a4[e] * acc[i][j][8 * half + 4 * q + e];
-            }
-          }
+            for (int e = 0; e < 4; ++e) o[hb][j][e] += a4[e] * acc[c >> 2][c & 3][hb][j][e];
         }
       }
     }
-    if (S == 1) {
-      bf16* Ob = O + (((size_t)ic.b * G + ic.k) * N) * D;
+    ++gcc;
+    if (nchunk != 0) {
+      chunk = nchunk;
+      continue;
+    }
+    const size_t first = S == 1 ? (((size_t)ic.b * G + ic.k) * N) * D
+                                : ((((size_t)ic.split * tw.nb + ic.b) * G + ic.k) * N) * D;   // S > 1: partial sums, added up by k_vagg_merge
+    const int lane = lane_id();
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = ic.o0 + L.wn * 64 + j * 32 + L.l32;
-        const float bias = bv ? (float)bv[(size_t)ic.k * D + col] : 0.f;
+    for (int j = 0; j < 4; ++j) {
+      const int col = ic.o0 + (j >> 1) * 128 + L.wn * 32 + (j & 1) * 16 + (lane & 15);
+      const float bias = S == 1 && bv ? (float)bv[(size_t)ic.k * D + col] : 0.f;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int nrow = ic.n0 + 16 * L.wm + 8 * (r >> 2) + 4 * L.lhi + (r & 3);
-          if (nrow < N) Ob[(size_t)nrow * D + col] = (bf16)(o[j][r] + bias);
-        }
-      }
-    } else {                                             // partial sum over this item's chunks; k_vagg_merge adds them up
-      float* Pb = Opart + ((((size_t)ic.split * tw.nb + ic.b) * G + ic.k) * N) * D;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = ic.o0 + L.wn * 64 + j * 32 + L.l32;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int nrow = ic.n0 + 16 * L.wm + 8 * (r >> 2) + 4 * L.lhi + (r & 3);
-          if (nrow < N) Pb[(size_t)nrow * D + col] = o[j][r];
+      for (int e = 0; e < 4; ++e) {
+        const int nrow = ic.n0 + 16 * L.wm + 4 * (lane >> 4) + e;
+        if (nrow < N) {
+          if (S == 1) O[first + (size_t)nrow * D + col] = (bf16)(o[j >> 1][j & 1][e] + bias);
+          else Opart[first + (size_t)nrow * D + col] = o[j >> 1][j & 1][e];
         }
       }
     }
+    if (!more) break;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j >> 1][j & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    ic = nx;
+    chunk = 0;
   }
   wait_vmcnt<0>();                                       // nothing may still target LDS when the block retires
 }
@@ -846,92 +864,249 @@ __global__ __launch_bounds__(256) void k_vagg_merge(long quads, int S, int G, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Plain per-group projection  Y[r][o] = sum_j A[r][j] * Wt[k][o][j] + bias[k][o] (+ rowadd[r][o])  on the same core.
-// Requires D % 256 == 0.  Dynamic LDS: the ring (128 KiB).
+// Batched bf16 products on the same core, persistent over 256 x 256 tiles of the (group k, batch b, row tile, column tile)
+// order as k_vagg_mfma is over its items; the operands of each instruction are exchanged, so that a lane ends with one row and
+// four adjacent columns of a block, trades with lane ^ 16 and stores 16 bytes at a time (16 stores a lane for its tile).
+//   kProductLinear   C[r][o] = sum_j A[r][j] B[k][o][j] + bias[k][o] (+ rowadd[r][o])      an output projection
+//   kProductBack     C[r][j] = sum_o A[r][o] B[k][o][j]                                     the gradient at its input
+//   kProductWeights  C[k][i][j] = sum_{b,n} A[b,k,n,i] B[b,k,n,j], rowsum[k][i] = sum_{b,n} A[b,k,n,i]
+//                                                                                            its weight and bias gradients
+//   kProductFold     C[c][o][kk] = sum_d A[k][o][d] B[c][d][kk], 64 kk, k = c / g           value weights into the tokenizer's
+// Rows of A of a group may be ragged (Linear, Back: loads clamped, stores masked); every other extent is a multiple of 256,
+// of 64 kt slices of the contraction kt is even and at least 4, and every row is 16-byte aligned (host).  An operand whose
+// contraction index is its row index is read by the transposing LDS reads (ColOperand): no transposed copy, no 2-byte reads.
+// Bound by the card's power limit where there are many tiles (the clock falls to 1.7 to 1.9 GHz) and by the last round of tiles.
+// One workgroup a tile, 2-byte stores and 32x32x16 instructions before, this after: 640 tiles of 16 slices (10 groups x 4096
+// rows, D 1024) 117 -> 95 us, 256 tiles 46 -> 38, 1008 tiles of 32 slices (63 x 512 rows, D 2048) 294 -> 255; against the general
+// 128 x 128 product kernel: Back 640 tiles 142 -> 90, 256 tiles 62 -> 36; Weights 160 tiles of 64 slices 214 -> 108, 256 of
+// 16 slices 70 -> 40.  Fold, eight 2-byte LDS reads a fragment before: 512 channels, D 1024 81 -> 65, 1000 channels, D 2048 550 -> 446.
+// Dynamic LDS: the ring (128 KiB).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(512) void k_linear_dl(int D, RowBlocks rb, TileWork tw, const bf16* __restrict__ A,
-                                                   const bf16* __restrict__ Wt, const bf16* __restrict__ bias,
-                                                   bf16* __restrict__ Y, const bf16* __restrict__ rowadd) {
+enum ProductKind { kProductLinear, kProductBack, kProductWeights, kProductFold };
+struct ProductArgs {
+  const bf16 *A, *B, *bias, *rowadd;
+  bf16 *C, *rowsum;
+  long a_sb, a_sk, b_sb, b_sk, c_sb, c_sk;               // strides of a batch element and of a group
+  int lda, ldb, ldc, ldbias;                             // row strides; elements of bias / rowsum a group
+  RowBlocks rb;                                          // Linear, Back: rows of a group
+  int kt, segs;                                          // slices of a segment of the contraction, and segments (batch elements)
+  int C_all, g;                                          // Fold: channels, channels of a group
+  TileWork tw;
+  int slots;                                             // workgroups an XCD
+};
+
+template <int KIND>
+__global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
+  constexpr bool A_COL = KIND == kProductWeights, FOLD = KIND == kProductFold;
+  typedef std::conditional_t<A_COL, ColOperand<256>, RowOperand> OA;
+  typedef std::conditional_t<FOLD, ColOperand<128>, std::conditional_t<KIND == kProductLinear, RowOperand, ColOperand<256>>> OB;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  int k, b, mt, nt;
-  if (!tw.decode(blockIdx.x, k, b, mt, nt)) return;
-  const int rows = rb.rows_of(k);
-  const int r0 = mt * kGemmBM, o0 = nt * kGemmBN;
-  if (r0 >= rows) return;
-  const int KT = D / kGemmBK;
-  GemmLane L;
-  L.init();
-  const bf16* Ab = A + (size_t)rb.first_row(b, k) * D;
-  bf16* Yb = Y + (size_t)rb.first_row(b, k) * D;
-  const bf16* Wb = Wt + (size_t)k * D * D;
-  const bf16* a_src[4];
-  const bf16* b_src[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = L.load_row(i);
-    a_src[i] = Ab + (size_t)min(r0 + row, rows - 1) * D + L.load_chunk(row) * 8;
-    b_src[i] = Wb + (size_t)(o0 + row) * D + L.load_chunk(row) * 8;
-  }
-  int ki = 0, si = 0;
-  auto issue = [&]() {
-    unsigned char* st = smem + si * kGemmStageBytes;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) load16_to_lds(a_src[i] + ki * kGemmBK, st + (L.wave * 4 + i) * 1024);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      load16_to_lds(b_src[i] + ki * kGemmBK, st + kGemmBM * 128 + (L.wave * 4 + i) * 1024);
-    si ^= 1;
-    ki = (ki + 1 < KT) ? ki + 1 : ki;                    // past the end: harmless re-load of the last slice
+  const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+  const int per = (p.tw.total + kXcds - 1) / kXcds;
+  const int xcd_end = min((xcd + 1) * per, p.tw.total);
+  struct Item {
+    int k, b, mt, nt;
   };
-  // The pipeline of k_vagg_mfma: the fragments of a slice's first k-step are read across the barrier that hands the
-  // slice over, the products of its last k-step are issued behind that barrier, and the two wavefronts of a SIMD
-  // (wm = 0 and 1) issue their loads at different points of the slice.
-  f32x16 acc[4][2];
-  Frags f0, f1;
-  issue();                                               // slice 0 -> stage 0
-  wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-  if (L.wm == 0) issue();                                // slice 1 -> stage 1 (wm = 1 issues inside the loop)
-  read_frags(f0, smem, L, 0);
-  int sc = 0;
-  for (int kt = 0; kt < KT; ++kt) {
-    const unsigned char* st = smem + sc * kGemmStageBytes;
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(f1, st, L, 1);
-    if (kt == 0) mfma_step_first(acc, f0);
-    else mfma_step(acc, f0);
-    pin_step_schedule();
-    if (L.wm == 1) issue();                              // slice kt + 1 -> the stage released at the last barrier
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(f0, st, L, 2);
-    mfma_step(acc, f1);
-    pin_step_schedule();
-    read_frags(f1, st, L, 3);
-    mfma_step(acc, f0);
-    pin_step_schedule();
-    __builtin_amdgcn_s_waitcnt(0);                       // vmcnt(0) and lgkmcnt(0): slice kt + 1 has landed
-    __builtin_amdgcn_s_barrier();
-    if (L.wm == 0) issue();                              // slice kt + 2 -> the stage just released
-    sc ^= 1;
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(f0, smem + sc * kGemmStageBytes, L, 0);   // past the last slice: a re-load of it, read and not used
-    mfma_step(acc, f1);
-    pin_step_schedule();
+  auto item_of = [&](int& t, Item& it) -> bool {         // the first item from the t-th on that has rows (Fold: channels)
+    for (;; ++t) {
+      const int w = xcd * per + t * p.slots + slot;
+      if (w >= xcd_end) return false;
+      p.tw.decode_linear(w, it.k, it.b, it.mt, it.nt);
+      if (FOLD ? it.nt * 4 < min(p.g, p.C_all - it.k * p.g) : A_COL || it.mt * kGemmBM < p.rb.rows_of(it.k)) return true;
+    }
+  };
+
+  CoreLane L;
+  L.init<OA, OB>();
+  const unsigned wave_off = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem) + L.wave * 2048;
+
+  Item ic, nx;                                           // the tile that is multiplied, and the next segment's
+  int t = 0;
+  if (!item_of(t, ic)) return;                           // uniform: the whole workgroup has nothing to do
+  struct Src {
+    const bf16 *a, *b0, *b1;                             // origins of a segment's tile in its running slice (b1: slot B1)
+    int rows;                                            // rows of A behind the tile's first
+  } run, nxt;
+  auto source = [&](const Item& it, int seg, Src& s) {
+    s.a = p.A + seg * p.a_sb + it.b * p.a_sb + it.k * p.a_sk;
+    if (A_COL) s.a += it.mt * kGemmBM + (size_t)L.wave * 8 * p.lda;
+    else s.a += (size_t)it.mt * kGemmBM * p.lda;
+    s.rows = FOLD || A_COL ? 256 : p.rb.rows_of(it.k) - it.mt * kGemmBM;
+    if (FOLD) {
+      const int c0 = it.k * p.g, last = min(p.g, p.C_all - c0) - 1, q = it.nt * 4 + (L.wave >> 2);
+      const int in = (L.wave & 3) * 16 * 64;             // a wavefront's 16 of a channel's 64 contraction rows
+      s.b0 = p.B + (c0 + min(q, last)) * p.b_sk + in;    // a missing channel of the four repeats the last one; not stored
+      s.b1 = p.B + (c0 + min(q + 2, last)) * p.b_sk + in;
+    } else {
+      s.b0 = p.B + seg * p.b_sb + it.k * p.b_sk;
+      if (KIND == kProductLinear) s.b0 += ((size_t)it.nt * kGemmBN + L.wave * 16) * p.ldb;
+      else s.b0 += it.nt * kGemmBN + (size_t)L.wave * 8 * p.ldb;
+      s.b1 = s.b0 + (KIND == kProductLinear ? (size_t)128 * p.ldb : 128);
+    }
+  };
+  // Byte of a lane's 16 behind those origins.  RowOperand: row lane / 8 and the chunk that belongs there; eight rows further bit 6
+  // (the chunk's) flips.  ColOperand<256>: contraction row lane / 16, four rows further nothing changes.
+  auto col_off = [&](int ld) {
+    const int lane = lane_id(), row = L.wave * 8 + (lane >> 4);
+    return (lane >> 4) * ld * 2 + ((lane & 15) ^ ColOperand<256>::swz(row)) * 16;
+  };
+  unsigned a_off[2][2];
+  auto a_rows = [&](int rows) {
+    const int lane = lane_id();
+    if (A_COL) {
+      a_off[0][0] = col_off(p.lda);
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          a_off[h][u] = (unsigned)min(h * 128 + L.wave * 16 + u * 8 + (lane >> 3), rows - 1) * p.lda * 2 + L.ld_chunk(lane, u);
+    }
+  };
+  int b_off;
+  if (FOLD) b_off = (lane_id() >> 3) * 128 + ((lane_id() & 7) ^ ColOperand<128>::swz(lane_id() >> 3)) * 16;
+  else if (KIND == kProductLinear) b_off = (lane_id() >> 3) * p.ldb * 2 + L.ld_chunk(lane_id(), 0);
+  else b_off = col_off(p.ldb);
+  source(ic, 0, run);
+  a_rows(run.rows);
+  int ki = 0;                                            // slices issued of the segment
+  auto issue = [&](int sl) {                             // sl: a constant once inlined
+    const unsigned dst = wave_off + sl * kSlotBytes;
+    const int kind = sl & ~2;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (kind == kSlotA0 || kind == kSlotA1) {
+        const int h = kind == kSlotA1;
+        if (A_COL) load16_to_lds_at(run.a + h * 128 + (size_t)u * 4 * p.lda, a_off[0][0], dst + u * 1024);
+        else load16_to_lds_at(run.a, a_off[h][u], dst + u * 1024);
+      } else {
+        const bf16* s = kind == kSlotB1 ? run.b1 : run.b0;
+        if (FOLD) load16_to_lds_at(s + u * 8 * 64, opaque(b_off) ^ (u * 64), dst + u * 1024);
+        else if (KIND == kProductLinear) load16_to_lds_at(s + (size_t)u * 8 * p.ldb, opaque(b_off) ^ (u * 64), dst + u * 1024);
+        else load16_to_lds_at(s + (size_t)u * 4 * p.ldb, b_off, dst + u * 1024);
+      }
+    }
+    if (kind == kSlotA1) {                               // the last slot of a slice
+      run.a += A_COL ? (size_t)64 * p.lda : 64;
+      const size_t bs = FOLD ? 64 * 64 : KIND == kProductLinear ? 64 : (size_t)64 * p.ldb;
+      run.b0 += bs;
+      run.b1 += bs;
+      if (sl & 2) {
+        ki += 2;
+        if (ki == p.kt) {
+          ki = 0;
+          run = nxt;
+          a_rows(run.rows);
+        }
+      }
+    }
+  };
+
+  CoreFrags f;
+  CoreAcc acc;
+  // Row sums of A (Weights, tiles of the first columns): wavefront wn adds up block wn of both slots, by products with ones.
+  f32x4 rs[2];
+  bool sums = false;
+  auto held = [&](int h, const bf16x8 (&a)[4][2]) {
+    if (A_COL && sums) {
+      bf16x8 ones;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (L.wn == i) {                                 // uniform
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk) rs[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, a[i][kk], rs[h], 0, 0, 0);
+        }
+    }
+  };
+  core_prologue<OA, OB>(f, smem, L, issue);
+  int seg = 0;
+  for (;;) {
+    nx = ic;
+    int nseg = seg + 1;
+    bool more = true;
+    if (nseg == p.segs) {
+      nseg = 0;
+      ++t;
+      more = item_of(t, nx);
+      if (!more) nx = ic;                                // past the last tile: this one again, loaded and not used
+    }
+    source(nx, nseg, nxt);
+    int kt = 0;
+    if (seg == 0) {
+      if (A_COL) {
+        sums = p.rowsum && ic.nt == 0;
+        rs[0] = rs[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      core_slice<true, true, 0, OA, OB>(acc, f, smem, L, issue, held);
+      core_slice<false, true, 1, OA, OB>(acc, f, smem, L, issue, held);
+      kt = 2;
+    }
+    for (; kt < p.kt; kt += 2) {
+      core_slice<false, true, 0, OA, OB>(acc, f, smem, L, issue, held);
+      core_slice<false, true, 1, OA, OB>(acc, f, smem, L, issue, held);
+    }
+    if (nseg != 0) {
+      seg = nseg;
+      continue;
+    }
+    // block (h, i, hb, j), lane (l16, lq), register e: row 128 h + 64 wm + 16 i + l16, column 128 hb + 32 wn + 16 j + 4 lq + e
+    const int l16 = lane_id() & 15, lq = lane_id() >> 4;
+    const int o0 = ic.nt * kGemmBN, r0 = ic.mt * kGemmBM;
+    const int rows = FOLD || A_COL ? 256 : p.rb.rows_of(ic.k) - r0;
+    if (A_COL && sums && lq == 0) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        p.rowsum[(size_t)ic.k * p.ldbias + r0 + h * 128 + L.wm * 64 + L.wn * 16 + l16] = (bf16)rs[h][0];
+    }
+    bf16* Cb = p.C + ic.b * p.c_sb + ic.k * p.c_sk + (size_t)r0 * p.ldc + (FOLD ? (size_t)ic.nt * 4 * p.ldc * p.lda : o0);
+    const int left = FOLD ? min(p.g, p.C_all - ic.k * p.g) - ic.nt * 4 : 4;      // channels from the tile's first on
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      const int col = hb * 128 + L.wn * 32;
+      f32x4 bq[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        bq[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (KIND == kProductLinear && p.bias) {
+          const bf16x4 v = *reinterpret_cast<const bf16x4*>(p.bias + (size_t)ic.k * p.ldbias + o0 + col + 16 * j + 4 * lq);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bq[j][e] = (float)v[e];
+        }
+      }
+#pragma unroll
+      for (int hi = 0; hi < 8; ++hi) {
+        const int row = (hi >> 2) * 128 + L.wm * 64 + (hi & 3) * 16 + l16;
+        const bool in = row < rows && (!FOLD || (col >> 6) < left);
+        typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+        typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+        u32x2 w[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          f32x4 v = acc[hi >> 2][hi & 3][hb][j] + bq[j];
+          if (KIND == kProductLinear && p.rowadd && in) {
+            const bf16x4 ra = *reinterpret_cast<const bf16x4*>(p.rowadd + (size_t)(r0 + row) * p.ldc + o0 + col + 16 * j + 4 * lq);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += (float)ra[e];
+          }
+          bf16x4 q;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) q[e] = (bf16)v[e];
+          w[j] = __builtin_bit_cast(u32x2, q);
+        }
+        // lane rows 0 and 2 (of 16) keep block 0 and take the next row's columns of it; rows 1 and 3 the same of block 1
+        const auto s0 = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
+        bf16* dst = FOLD ? Cb + (size_t)(col >> 6) * p.ldc * p.lda + (size_t)row * p.ldc + (col & 63) : Cb + (size_t)row * p.ldc + col;
+        if (in) *reinterpret_cast<u32x4*>(dst + (lq & 1) * 16 + (lq >> 1) * 8) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+      }
+    }
+    if (!more) break;
+    ic = nx;
+    seg = 0;
   }
   wait_vmcnt<0>();                                       // no load may still target LDS when the block retires
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int col = o0 + L.wn * 64 + j * 32 + L.l32;
-    const float bvv = bias ? (float)bias[(size_t)k * D + col] : 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = r0 + L.wm * 128 + i * 32 + 8 * (r >> 2) + 4 * L.lhi + (r & 3);
-        if (row < rows && !((DCHAG_GEMM_PROBE & 16) && acc[i][j][r] != 12345.f))
-          Yb[(size_t)row * D + col] = (bf16)(acc[i][j][r] + bvv + (rowadd ? (float)rowadd[(size_t)row * D + col] : 0.f));
-      }
-  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1033,94 +1208,6 @@ __global__ __launch_bounds__(256) void k_linear_ring(int D, RowBlocks rb, TileWo
           Yb[(size_t)row * D + col] = (bf16)(acc[i][j][r] + bvv + (rowadd ? (float)rowadd[(size_t)row * D + col] : 0.f));
       }
   }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Value projection folded into the tokenizer weights (weight-only; 64 pixels per patch), on the same core:
-//   Wf[c][o][kk] = sum_d Wv[k][o][d] * We[c][d][kk],   k = c / g.
-// Work item: group k, 256 rows o, four channels of the group (one per wavefront column wn).  The A operand (rows of
-// Wv, contraction index contiguous) goes through the ring as in k_linear_dl; the B stage holds, per channel, the 64
-// rows d of the slice as they lie in memory (128 bytes of kk each), so a B fragment (8 consecutive d of one column
-// kk) is put together from eight 2-byte LDS reads -- the operand is small, the A tile is shared by the four channels,
-// which is what the product's L2 traffic hinges on.  Requires D % 256 == 0.  Dynamic LDS: the ring (128 KiB).
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(512) void k_fold_value_dl(int C, int D, int g, TileWork tw, const bf16* __restrict__ Wv,
-                                                       const bf16* __restrict__ We, bf16* __restrict__ Wf) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  int k, b, mt, nt;
-  if (!tw.decode(blockIdx.x, k, b, mt, nt)) return;
-  const int c0 = k * g, gk = min(g, C - c0), q0 = nt * 4;
-  if (q0 >= gk) return;                                  // uniform: a short last group has fewer quads
-  const int r0 = mt * kGemmBM;
-  const int KT = D / kGemmBK;
-  GemmLane L;
-  L.init();
-  const bf16* a_src[4];
-  const bf16* b_src[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = L.load_row(i);
-    a_src[i] = Wv + ((size_t)k * D + r0 + row) * D + L.load_chunk(row) * 8;
-    const int c = c0 + min(q0 + (row >> 6), gk - 1);     // a missing channel of the quad repeats the last one; not stored
-    b_src[i] = We + ((size_t)c * D + (row & 63)) * 64 + L.load_chunk(row) * 8;
-  }
-  int ki = 0, si = 0;
-  auto issue = [&]() {
-    unsigned char* st = smem + si * kGemmStageBytes;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) load16_to_lds(a_src[i] + ki * kGemmBK, st + (L.wave * 4 + i) * 1024);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      load16_to_lds(b_src[i] + (size_t)ki * 64 * 64, st + kGemmBM * 128 + (L.wave * 4 + i) * 1024);
-    si ^= 1;
-    ki = (ki + 1 < KT) ? ki + 1 : ki;                    // past the end: harmless re-load of the last slice
-  };
-  // byte offset, inside a stage's B half, of element (d = 8 lhi + i of a 16-deep k-step, column kk = 32 j + l32) of this
-  // wavefront's channel; the k-step adds 16 rows (2048 bytes, no change of the row's chunk swizzle)
-  int boff[2][8];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = L.wn * 64 + L.lhi * 8 + i, col = j * 32 + L.l32;
-      boff[j][i] = kGemmBM * 128 + row * 128 + (((col >> 3) ^ swz_chunk(row)) * 16) + (col & 7) * 2;
-    }
-  f32x16 acc[4][2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  issue();
-  int sc = 0;
-  for (int kt = 0; kt < KT; ++kt) {
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    issue();
-    const unsigned char* st = smem + sc * kGemmStageBytes;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      Frags f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) f.a[i] = *reinterpret_cast<const bf16x8*>(st + L.a_base + i * 4096 + L.ck[kk]);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) f.b[j][i] = *reinterpret_cast<const bf16*>(st + boff[j][i] + kk * 2048);
-      mfma_step(acc, f);
-    }
-    sc ^= 1;
-  }
-  wait_vmcnt<0>();                                       // no load may still target LDS when the block retires
-  if (q0 + L.wn >= gk) return;
-  bf16* out = Wf + ((size_t)(c0 + q0 + L.wn) * D + r0 + L.wm * 128 + 4 * L.lhi) * 64 + L.l32;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) out[(size_t)(i * 32 + 8 * (r >> 2) + (r & 3)) * 64 + j * 32] = (bf16)acc[i][j][r];
 }
 
 // The token biases under the same fold (weight-only):  fb[c][o] = sum_d (be[c][d] + ce[c][d]) * Wv[k][o][d],  k = c / g;

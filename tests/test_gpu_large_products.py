@@ -1,0 +1,48 @@
+"""GPU parity of the products on 256 x 256 tiles (output projections, their input and weight gradients) where their tiles, segments
+and ragged rows end, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2506_21411_amd as dchag
+from workloads import ShapeCfg, make_problem
+
+from .test_gpu_products import check_training_step, say
+from .test_gpu_train import TOL, dev, dev_level, host, rel_err
+
+pytestmark = pytest.mark.gpu
+
+TRAIN = [
+    # two segments of the contraction of six slices each; rows of one and a half tiles; 33 groups, the last of one member
+    dict(B=2, C=65, H=64, W=96, p=4, D=512, heads=8, group_sizes=(2, 33)),
+    # one segment of four slices (the shortest), three tiles of columns, a workgroup of no or of two tiles
+    dict(B=1, C=30, H=64, W=64, p=4, D=768, heads=12, group_sizes=(2, 15)),
+]
+
+
+@pytest.mark.parametrize("kw,biases", [(TRAIN[0], True), (TRAIN[1], True), (TRAIN[1], False)])
+def test_output_projection_gradients(kw, biases, monkeypatch):
+    say(f"large products, training {kw}")
+    monkeypatch.setenv("DCHAG_TRAIN_ROUTE", "tokens")
+    check_training_step(ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=61, **kw), biases=biases)
+
+
+@pytest.mark.parametrize("biases", [True, False])
+def test_projection_of_ragged_rows(biases):
+    """260 rows a group: one tile of 256 and one of 4, 16 groups, 128 tiles; the value product with 4 rows in its last tile."""
+    cfg = ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=62, B=1, C=32, H=80, W=208, p=8, D=1024, heads=16,
+                   group_sizes=(2, 16))
+    pr = make_problem(cfg, biases=biases)
+    args = (dev(pr.x, "bf16"), dev(pr.We, "bf16"), dev(pr.be, "bf16"), dev(pr.ce, "bf16"), [dev_level(lv, "bf16") for lv in pr.levels],
+            cfg.p, cfg.heads)
+    say(f"large products, forward {cfg}")
+    got = host(dchag.dchag_forward(*args))
+    folded = host(dchag.dchag_forward_folded(*args))
+    rows = np.r_[0:8, 120:136, 252:260]                   # patches at the edges of the tiles
+    xs = pr.x.reshape(1, cfg.C, 10, 8, 26, 8).transpose(0, 2, 4, 1, 3, 5).reshape(cfg.N, cfg.C, 64)[rows]
+    xs = xs.reshape(1, len(rows), cfg.C, 8, 8).transpose(0, 2, 3, 1, 4).reshape(1, cfg.C, 8, 8 * len(rows))
+    want = oracle.forward(xs, pr.We, pr.be, pr.ce, pr.levels, cfg.p, cfg.heads).reshape(len(rows), cfg.D)
+    for name, y in (("forward", got), ("folded", folded)):
+        err = rel_err(y.reshape(cfg.N, cfg.D)[rows], want)
+        say(f"  {name} {err:.3e}")
+        assert err < TOL["bf16"], (name, err)
