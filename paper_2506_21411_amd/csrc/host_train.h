@@ -1077,23 +1077,7 @@ inline int tokens_backward(int B, int Cin, int N, int D, int heads, int g, const
   return sum_key_path_partials(B, G, n_tiles, heads, D, rpart, r, st);
 }
 
-// Rank-one weight gradient out[k][i][:] = scale * rowv[k][i] * colv[k][i / rows_per_vec][:]: 16 bytes per thread where
-// the rows allow it.
-template <typename TV, typename T>
-int outer_rows(int D, int G, int rows_per_vec, float scale, const float* rowv, const TV* colv, T* out, hipStream_t st) {
-  const bool vec = D % 8 == 0 && !((reinterpret_cast<uintptr_t>(colv) | reinterpret_cast<uintptr_t>(out)) & 15) &&
-                   !dbg(SW_GEMM_SCALAR_STORES);
-  if (vec) {
-    const long chunks = (long)D * (D / 8);
-    k_outer_rows_vec<TV, T><<<dim3((unsigned)((chunks + 2047) / 2048), G), 256, 0, st>>>(D, rows_per_vec, scale, rowv,
-                                                                                       colv, out);
-  } else {
-    k_outer_rows<TV, T><<<dim3((D + 255) / 256, D, G), 256, 0, st>>>(D, rows_per_vec, scale, rowv, colv, out);
-  }
-  return launch_status();
-}
-
-// The same on the large products' core.  Taken where its 256 x 256 tiles of either product keep half of the compute units busy.
+// A level's output projection, its weight and input gradients on the large products' core.  Taken where its 256 x 256 tiles of either product keep half of the compute units busy.
 inline bool projection_products_ok(int B, int G, int N, int D, const dchag_level_grads* gr) {
   const long m = D / kGemmBM;
   return D % 256 == 0 && N % 128 == 0 && N >= 256 && gr->dWo && G * m * m * 2 >= compute_units() &&
@@ -1170,19 +1154,14 @@ int key_query_backward(int G, int D, int heads, const dchag_level* lv, const dch
   const int dh = D / heads;
   int rc;
   StageTimer tm(DCHAG_STAGE_BWD_KEY_QUERY, st);
-  if (gr->dbk) {
-    const long n = (long)G * D;
-    k_fill_zero<T><<<dim3((unsigned)((n + 255) / 256)), 256, 0, st>>>(n, static_cast<T*>(gr->dbk));
+  const bool want_q = gr->dWq || gr->dbq || gr->dquery;
+  if (gr->dWk || gr->dbk || want_q) {
+    constexpr int V = 16 / sizeof(T);
+    k_key_query_grads<T, V><<<dim3((unsigned)(heads * ((dh + 3) / 4)), G), 64, 0, st>>>(
+        D, heads, 1.f / sqrtf((float)dh), static_cast<const T*>(lv->Wk), static_cast<const T*>(lv->query), Qp, r,
+        want_q ? dQ : nullptr, static_cast<T*>(gr->dWk), static_cast<T*>(gr->dWq), static_cast<T*>(gr->dbk), static_cast<T*>(gr->dbq));
     if ((rc = launch_status())) return rc;
   }
-  if (gr->dWk && (rc = outer_rows<float, T>(D, G, dh, 1.f / sqrtf((float)dh), Qp, r, static_cast<T*>(gr->dWk), st)))
-    return rc;
-  if (!gr->dWq && !gr->dbq && !gr->dquery) return DCHAG_OK;
-  k_query_grad<T><<<dim3((D + 3) / 4, G), 256, 0, st>>>(D, heads, static_cast<const T*>(lv->Wk), r, dQ,
-                                                        static_cast<T*>(gr->dbq));
-  if ((rc = launch_status())) return rc;
-  if (gr->dWq && (rc = outer_rows<T, T>(D, G, D, 1.f, dQ, static_cast<const T*>(lv->query), static_cast<T*>(gr->dWq), st)))
-    return rc;
   if (gr->dquery) {
     k_query_input_grad<T><<<dim3((D + 63) / 64, G), 1024, 0, st>>>(D, static_cast<const T*>(lv->Wq), dQ,
                                                                    static_cast<T*>(gr->dquery));

@@ -413,33 +413,84 @@ __global__ __launch_bounds__(1024) void k_colsum(int B, int D, RowBlocks rb, con
 }
 
 // ---------------------------------------------------------------------------------------
-// dQ[k][i] = (1/sqrt(dh)) * sum_j Wk[k][i][j] * r[k][a(i)][j]   with  r[k][a][:] = sum over the group's tokens
-// of ds[.,a] * z  (one wave per row).  Also writes the query-bias gradient, which equals dQ.
-// grid (ceil(D/4), G), block 256.
+// Everything of the key and query path that belongs to one row i of a level's weights (a(i): its head, r[k][a][:]: the sum over
+// the group's tokens of ds[.,a] * z):
+//   dWk[k][i][:] = scale Qp[k][i] r[k][a(i)][:]      dQ[k][i] = scale sum_j Wk[k][i][j] r[k][a(i)][j]
+//   dWq[k][i][:] = dQ[k][i] query[k][:]              dbq[k][i] = dQ[k][i]       dbk[k][i] = 0
+// A wavefront (a block of its own: a level of one group then reaches every compute unit) takes four rows of a head, V adjacent
+// columns a lane: r is read once for the four.  Any output may be NULL; dQ NULL: no query path.  One launch where there were four
+// (zeros, dWk, dQ and dbq, dWq), each of them a few us for one group: D 1024, bf16, one group 26 -> 8 us, 16 groups 45 -> 21 (bound
+// by the 134 MB it moves: 6.3 TB/s).
+// Requires D % V == 0 and 16-byte aligned rows.  grid (heads ceil(dh / 4), G), block 64.
 // ---------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_query_grad(int D, int heads, const T* __restrict__ Wk,
-                                                    const float* __restrict__ r, float* __restrict__ dQ,
-                                                    T* __restrict__ dbq) {
-  const int k = blockIdx.y;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (i >= D) return;
-  const int dh = D / heads;
-  const T* w = Wk + ((size_t)k * D + i) * D;
-  const float* rv = r + ((size_t)k * heads + i / dh) * D;
-  float acc = 0.f;
-  for (int j = lane; j < D; j += kWave) acc += to_f32(w[j]) * rv[j];
-  acc = wave_sum(acc) * rsqrtf((float)dh);
-  if (lane == 0) {
-    dQ[(size_t)k * D + i] = acc;
-    if (dbq) dbq[(size_t)k * D + i] = from_f32<T>(acc);
+template <typename T, int V>
+__global__ __launch_bounds__(64) void k_key_query_grads(int D, int heads, float scale, const T* __restrict__ Wk,
+                                                        const T* __restrict__ query, const float* __restrict__ Qp,
+                                                        const float* __restrict__ r, float* __restrict__ dQ, T* __restrict__ dWk,
+                                                        T* __restrict__ dWq, T* __restrict__ dbk, T* __restrict__ dbq) {
+  typedef T vec __attribute__((ext_vector_type(V)));
+  typedef float fvec __attribute__((ext_vector_type(V)));
+  const int lane = threadIdx.x, dh = D / heads, quads = (dh + 3) / 4;
+  const int k = blockIdx.y, a = blockIdx.x / quads, first = (blockIdx.x % quads) * 4;
+  const size_t i0 = (size_t)k * D + (size_t)a * dh + first;
+  const int rows = min(4, dh - first);
+  const float* rv = r + ((size_t)k * heads + a) * D;
+  float q[4], acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) q[t] = Qp[i0 + min(t, rows - 1)] * scale;
+  for (int j = lane * V; j < D; j += kWave * V) {
+    const fvec c = *reinterpret_cast<const fvec*>(rv + j);
+    if (dQ) {
+      vec w[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) w[t] = *reinterpret_cast<const vec*>(Wk + (i0 + min(t, rows - 1)) * D + j);
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int e = 0; e < V; ++e) acc[t] += to_f32(w[t][e]) * c[e];
+    }
+    if (dWk) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        vec o;
+#pragma unroll
+        for (int e = 0; e < V; ++e) o[e] = from_f32<T>(q[t] * c[e]);
+        if (t < rows) *reinterpret_cast<vec*>(dWk + (i0 + t) * D + j) = o;
+      }
+    }
+  }
+  if (dbk && lane < rows) dbk[i0 + lane] = from_f32<T>(0.f);
+  if (!dQ) return;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    acc[t] = wave_sum(acc[t]) * scale;
+    if (lane == t && t < rows) {
+      dQ[i0 + t] = acc[t];
+      if (dbq) dbq[i0 + t] = from_f32<T>(acc[t]);
+    }
+  }
+  if (!dWq) return;
+  for (int j = lane * V; j < D; j += kWave * V) {
+    const vec c = *reinterpret_cast<const vec*>(query + (size_t)k * D + j);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      vec o;
+#pragma unroll
+      for (int e = 0; e < V; ++e) o[e] = from_f32<T>(acc[t] * to_f32(c[e]));
+      if (t < rows) *reinterpret_cast<vec*>(dWq + (i0 + t) * D + j) = o;
+    }
   }
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void k_fill_zero(long n, T* __restrict__ out) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) out[i] = from_f32<T>(0.f);
+}
+
 // dquery[k][j] = sum_i Wq[k][i][j] * dQ[k][i].  grid (ceil(D/64), G), block 1024: a block owns 64 columns; lane l of a
-// wavefront takes the 4 columns 4 (l % 16) .. of row 4 wave + l / 16 and every 64th row after it; the four row groups
-// of a wavefront meet by lane exchange, the 16 wavefronts in LDS, both in a fixed order.  Requires D % 4 == 0.
+// wavefront takes the 4 columns 4 (l % 16) .. of row 4 wave + l / 16 and every 64th row after it, eight of them in flight (one group of
+// D 1024: 10.5 -> 6.3 us); the four row groups of a wavefront meet by lane exchange, the 16 wavefronts in LDS, both in a fixed order.  Requires D % 4 == 0.
 template <typename T>
 __global__ __launch_bounds__(1024) void k_query_input_grad(int D, const T* __restrict__ Wq,
                                                            const float* __restrict__ dQ, T* __restrict__ dquery) {
@@ -452,10 +503,26 @@ __global__ __launch_bounds__(1024) void k_query_input_grad(int D, const T* __res
   if (j < D) {
     const T* w = Wq + (size_t)k * D * D + j;
     const float* dq = dQ + (size_t)k * D;
-    for (int i = wave * 4 + rs; i < D; i += 64) {
+    typedef T vec __attribute__((ext_vector_type(4)));
+    int i = wave * 4 + rs;
+    for (; i + 7 * 64 < D; i += 8 * 64) {                          // eight rows in flight
+      vec v[8];
+      float q[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        v[t] = *reinterpret_cast<const vec*>(w + (size_t)(i + 64 * t) * D);
+        q[t] = dq[i + 64 * t];
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += to_f32(v[t][e]) * q[t];
+    }
+    for (; i < D; i += 64) {
+      const vec v = *reinterpret_cast<const vec*>(w + (size_t)i * D);
       const float q = dq[i];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += to_f32(w[(size_t)i * D + e]) * q;
+      for (int e = 0; e < 4; ++e) acc[e] += to_f32(v[e]) * q;
     }
   }
 #pragma unroll
@@ -475,70 +542,6 @@ __global__ __launch_bounds__(1024) void k_query_input_grad(int D, const T* __res
     for (int w16 = 0; w16 < 16; ++w16) sum += part[w16][threadIdx.x];
     if (jj < D) dquery[(size_t)k * D + jj] = from_f32<T>(sum);
   }
-}
-
-// ---------------------------------------------------------------------------------------
-// Rank-one weight gradients:  out[k][i][j] = scale * rowv[k][i] * colv[k][i / rows_per_vec][j]
-//   key weights:   rowv = projected query, colv = r[k][a][:], rows_per_vec = dh, scale = 1/sqrt(dh)
-//   query weights: rowv = dQ, colv = the learned query, rows_per_vec = D
-// grid (ceil(D/256), D, G), block 256.
-// ---------------------------------------------------------------------------------------
-// The same for D % 8 == 0 and 16-byte aligned tensors: a thread writes 8 adjacent columns at once and takes 8 such
-// chunks, 256 * 8 chunks per block.  grid (ceil(D * D / 8 / 2048), G), block 256.
-template <typename TV, typename T>
-__global__ __launch_bounds__(256) void k_outer_rows_vec(int D, int rows_per_vec, float scale,
-                                                        const float* __restrict__ rowv, const TV* __restrict__ colv,
-                                                        T* __restrict__ out) {
-  const int k = blockIdx.y;
-  const int cpr = D / 8;                                           // chunks per row
-  const long chunks = (long)D * cpr;
-  const int nvec = D / rows_per_vec;
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const long idx = ((long)blockIdx.x * 8 + u) * 256 + threadIdx.x;
-    if (idx >= chunks) return;
-    const int i = (int)(idx / cpr), j = (int)(idx % cpr) * 8;
-    const float rv = rowv[(size_t)k * D + i] * scale;
-    const TV* cv = colv + ((size_t)k * nvec + i / rows_per_vec) * D + j;
-    T* o = out + ((size_t)k * D + i) * D + j;
-    float c[8];
-    if constexpr (sizeof(TV) == 2) {
-      const bf16x8 v = *reinterpret_cast<const bf16x8*>(cv);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) c[e] = (float)v[e];
-    } else {
-      const f32x4 v0 = *reinterpret_cast<const f32x4*>(cv), v1 = *reinterpret_cast<const f32x4*>(cv + 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { c[e] = v0[e]; c[4 + e] = v1[e]; }
-    }
-    if constexpr (sizeof(T) == 2) {
-      bf16x8 r;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) r[e] = (bf16)(rv * c[e]);
-      *reinterpret_cast<bf16x8*>(o) = r;
-    } else {
-      *reinterpret_cast<f32x4*>(o) = f32x4{rv * c[0], rv * c[1], rv * c[2], rv * c[3]};
-      *reinterpret_cast<f32x4*>(o + 4) = f32x4{rv * c[4], rv * c[5], rv * c[6], rv * c[7]};
-    }
-  }
-}
-
-template <typename TV, typename T>
-__global__ __launch_bounds__(256) void k_outer_rows(int D, int rows_per_vec, float scale,
-                                                    const float* __restrict__ rowv, const TV* __restrict__ colv,
-                                                    T* __restrict__ out) {
-  const int k = blockIdx.z, i = blockIdx.y;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= D) return;
-  const int nvec = D / rows_per_vec;
-  const float rv = rowv[(size_t)k * D + i] * scale;
-  out[((size_t)k * D + i) * D + j] = from_f32<T>(rv * to_f32(colv[((size_t)k * nvec + i / rows_per_vec) * D + j]));
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_fill_zero(long n, T* __restrict__ out) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) out[i] = from_f32<T>(0.f);
 }
 
 // ---------------------------------------------------------------------------------------
