@@ -259,6 +259,16 @@ inline int launch_gemm_f32(const GemmDesc& d, const float* A, const float* Bm, c
     return !((o.sb | o.sk | o.sa | row) & 3) && !(reinterpret_cast<uintptr_t>(p) & 15);
   };
   const int va = vec_ok(d.A, at ? d.A.s1 : d.A.s0, A), vb = vec_ok(d.Bm, bt ? d.Bm.s0 : d.Bm.s1, Bm);
+  // whole slices and whole 16-byte pieces (32-bit offsets inside a tile): the ring
+  const bool whole_k = d.ragged == 2 ? d.ragged_total % 32 == 0 && d.ragged_nominal % 32 == 0 : d.K % 32 == 0;
+  const long reach = (1L << 29) / 64;
+  if (va && vb && whole_k && (!at || (d.M % 4 == 0 && d.ragged != 1)) && (!bt || d.N % 4 == 0) && (at ? d.A.s1 : d.A.s0) < reach &&
+      (bt ? d.Bm.s0 : d.Bm.s1) < reach) {
+    auto ring = at ? (bt ? k_gemm_f32_ring<true, true> : k_gemm_f32_ring<true, false>)
+                   : (bt ? k_gemm_f32_ring<false, true> : k_gemm_f32_ring<false, false>);
+    ring<<<dim3((d.N + 63) / 64, (unsigned)mt, (unsigned)(batch * split)), 256, 0, st>>>(d, split, split_stride, A, Bm, bias, C);
+    return launch_status();
+  }
   auto kern = at ? (bt ? k_gemm_f32<true, true> : k_gemm_f32<true, false>)
                  : (bt ? k_gemm_f32<false, true> : k_gemm_f32<false, false>);
   kern<<<dim3((d.N + 63) / 64, (unsigned)mt, (unsigned)(batch * split)), 256, 0, st>>>(d, va, vb, split, split_stride, A, Bm,

@@ -1177,6 +1177,138 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmDesc d, int va, int vb, in
 }
 
 // ---------------------------------------------------------------------------------------
+// The same products where every row is 16-byte aligned, every contraction a multiple of 32 and the extent of an operand whose
+// unit stride is its row index a multiple of 4 (host): the same tiles, instructions and order of sums, with the slices brought in by
+// direct-to-LDS loads two slices ahead (three 16-KiB stages, three blocks to a compute unit).  What the kernel above waits for is
+// itself: 64-bit addresses, range checks and register copies of every piece.  640 blocks of 16 slices 41 .. 46 -> 34 .. 35 us (60 % of
+// the matrix units' time), with two transposed operands 55 -> 34; 64 blocks 21 .. 26 -> 16.
+//   A slice of an operand whose unit stride is the contraction index is 64 rows of 128 bytes, chunks swizzled as in the bf16
+//   kernels (lane l of 32 reads 16 bytes of row l, half h of the wavefront steps 8 q + 4 h ..).  One whose unit stride is its
+//   row index is 32 steps of 64 rows, 256 bytes each, read four bytes a lane; the two halves of a wavefront read steps four
+//   apart, so every second four steps have the halves of their 256 bytes exchanged and the 64 lanes meet 64 banks.
+//   Four sets of wavefronts a block with a quarter of the slices each (few tiles) gained a tenth at 64 blocks of 16 slices (16 -> 15
+//   us) and lost as much at four slices, and tiles dealt to the XCDs by rows changed nothing: neither is kept.
+// grid (ceil(N/64), ceil(M/64), batch * split), block 256.
+// ---------------------------------------------------------------------------------------
+template <bool AT, bool BT>
+__global__ __launch_bounds__(256) void k_gemm_f32_ring(GemmDesc d, int split, long split_stride, const float* __restrict__ A,
+                                                       const float* __restrict__ Bm, const float* __restrict__ bias,
+                                                       float* __restrict__ C) {
+  constexpr int STAGE = 16384, OPB = 8192;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * STAGE];
+  int z = blockIdx.z;
+  const int part = z % split;
+  z /= split;
+  const int a = z % d.na;
+  z /= d.na;
+  const int k = z % d.nk;
+  const int b0 = d.reduce_b ? 0 : z / d.nk;
+  const int b1 = d.reduce_b ? d.nb : b0 + 1;
+  int M = d.M, K = d.K;
+  if (d.ragged) {
+    int left = d.ragged_total - k * d.ragged_nominal;
+    left = left < d.ragged_nominal ? left : d.ragged_nominal;
+    if (d.ragged == 1) M = left; else K = left;
+  }
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  if (m0 >= M) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lhi = lane >> 5;
+  const int KT = K / 32;
+  const int per = ((b1 - b0) * KT + split - 1) / split;
+  const int s_begin = part * per, s_end = min(s_begin + per, (b1 - b0) * KT);
+
+  // loads 2 w and 2 w + 1 of an operand's eight (1 KiB each): rows 8 i .. 8 i + 7, or steps 4 i .. 4 i + 3
+  auto offsets = [&](bool T, int r0, int R, long srow, long sk, unsigned (&off)[2]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = wave * 2 + u;
+      if (!T) {
+        const int row = i * 8 + (lane >> 3);
+        off[u] = (unsigned)min(row, R - 1 - r0) * (unsigned)srow * 4 + ((lane & 7) ^ swz_chunk(row)) * 16;
+      } else {
+        const int col = min(((lane & 15) ^ (8 * (i & 1))) * 4, R - 4 - r0);
+        off[u] = (unsigned)(i * 4 + (lane >> 4)) * (unsigned)sk * 4 + col * 4;
+      }
+    }
+  };
+  unsigned a_off[2], b_off[2];
+  offsets(AT, m0, M, d.A.s0, d.A.s1, a_off);
+  offsets(BT, n0, d.N, d.Bm.s1, d.Bm.s0, b_off);
+  const float* Ab = A + d.A.sk * k + d.A.sa * a + d.A.s0 * m0;
+  const float* Bb = Bm + d.Bm.sk * k + d.Bm.sa * a + d.Bm.s1 * n0;
+  int ib = b0 + s_begin / KT, ik = s_begin % KT;             // batch element and slice of the next loads
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem) + wave * 2048;
+  int is = 0;
+  auto issue = [&]() {
+    const float* pa = Ab + d.A.sb * ib + (AT ? d.A.s1 * 32 : 32) * (long)ik;
+    const float* pb = Bb + d.Bm.sb * ib + (BT ? d.Bm.s0 * 32 : 32) * (long)ik;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      load16_to_lds_at(pa, a_off[u], lds0 + is * STAGE + u * 1024);
+      load16_to_lds_at(pb, b_off[u], lds0 + is * STAGE + OPB + u * 1024);
+    }
+    is = is == 2 ? 0 : is + 1;
+    if (++ik == KT) {
+      ik = 0;
+      ++ib;
+    }
+  };
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 acc = zero;
+  // steps 8 q + 4 lhi + e, e = 0 .. 3, of this lane's row
+  auto read = [&](bool T, const unsigned char* st, int w, int q, float (&v)[4]) {
+    if (!T) {
+      const int row = w * 32 + l32;
+      const f32x4 t = *reinterpret_cast<const f32x4*>(st + row * 128 + ((2 * q + lhi) ^ swz_chunk(row)) * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = t[e];
+    } else {
+      const unsigned char* p = st + (8 * q + 4 * lhi) * 256 + ((w * 32 + l32) ^ (32 * lhi)) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const float*>(p + e * 256);
+    }
+  };
+  if (s_begin < s_end) issue();
+  if (s_begin + 1 < s_end) issue();
+  int sc = 0;
+  for (int s = s_begin; s < s_end; ++s) {
+    // slice s has landed (this wavefront's share; slice s + 1 may stay in flight), and every wavefront is done with slice s - 1
+    if (s + 1 < s_end) wait_vmcnt<4>();
+    else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (s + 2 < s_end) issue();
+    const unsigned char* st = smem + sc * STAGE;
+    sc = sc == 2 ? 0 : sc + 1;
+    float av[4][4], bv[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      read(AT, st, wm, q, av[q]);
+      read(BT, st + OPB, wn, q, bv[q]);
+    }
+    f32x16 slice = zero;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) slice = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q][e], bv[q][e], slice, 0, 0, 0);
+    acc += slice;
+  }
+  // lane: column l32, register r: row 8 (r / 4) + 4 (lane / 32) + r % 4
+  const int n = n0 + wn * 32 + l32;
+  if (n >= d.N) return;
+  float* Cb = C + d.C.sb * b0 + d.C.sk * k + d.C.sa * a + split_stride * part;
+  const float bv = bias && split == 1 ? bias[d.bias_sk * k + d.bias_sa * a + n] : 0.f;
+  const float* radd = split == 1 ? static_cast<const float*>(d.rowadd) : nullptr;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
+    if (m < M) Cb[d.C.s0 * m + d.C.s1 * n] = acc[r] * d.scale + bv + (radd ? radd[(size_t)m * d.N + n] : 0.f);
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // Softmax weights from the layout of the forward kernels, alpha_f[b][k][cl][head][n] (pitch Np, gpad
 // members per group), to token-major alpha[b,c,n,head].  One thread per output element.
 // ---------------------------------------------------------------------------------------
