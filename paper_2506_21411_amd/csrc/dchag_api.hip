@@ -416,36 +416,96 @@ int launch_linear<bf16>(int B, int D, RowBlocks rb, const bf16* A, const bf16* W
   return launch_linear_generic<bf16>(B, D, rb, A, Wt, bias, Y, st, rowadd);
 }
 
+// Projected queries and query-folded keys of n attention levels in one launch (a wavefront takes a quarter of a head's rows).
+inline bool query_keys_ok(int D, int heads) { return D % 8 == 0 && (D / heads) % 4 == 0 && D / heads <= 8192; }
+struct KeyPrepJob {
+  const dchag_level* lv;
+  int G;
+  PrepBufs out;
+  float* MfT;                      // optional transposed copy of the folded keys
+};
+template <typename T>
+int launch_query_keys(int D, int heads, const KeyPrepJob* jobs, int n, hipStream_t st) {
+  KeyPrepArgs args{};
+  int total = 0;
+  args.n_levels = n;
+  for (int i = 0; i < n; ++i) {
+    const dchag_level* lv = jobs[i].lv;
+    args.lv[i] = KeyPrepLevel{lv->query, lv->Wq, lv->bq, lv->Wk, jobs[i].out.Qp, jobs[i].out.Mf, jobs[i].MfT, jobs[i].out.Mb, total};
+    total += jobs[i].G;
+  }
+  if (heads > 65535) return DCHAG_ERR_SHAPE;
+  if (total > 65535) {             // more groups than a grid's second dimension holds: a launch a level
+    if (n == 1) return DCHAG_ERR_SHAPE;
+    for (int i = 0; i < n; ++i)
+      if (int rc = launch_query_keys<T>(D, heads, jobs + i, 1, st)) return rc;
+    return DCHAG_OK;
+  }
+  StageTimer tm(DCHAG_STAGE_KEY_PREP, st);
+  // shares of the columns per (head, group): enough blocks for two per compute unit, whole 512-column passes each
+  int shares = 1;
+  while ((long)heads * total * shares < 2L * compute_units() && D % (1024 * shares) == 0 && shares < 8) shares *= 2;
+  k_query_keys<T><<<dim3(heads, total, shares), 256, (size_t)(D / heads + 1536) * 4, st>>>(D, heads, args);
+  return launch_status();
+}
+
+// Projected query and folded keys of one level on the shape-generic path.
+template <typename T>
+int generic_query_keys(int G, int D, int heads, const dchag_level* lv, const PrepBufs& out, hipStream_t st) {
+  int rc;
+  if (query_keys_ok(D, heads) && !dbg(SW_GENERIC_LEVEL)) {
+    const KeyPrepJob job{lv, G, out, nullptr};
+    return launch_query_keys<T>(D, heads, &job, 1, st);
+  }
+  {
+    StageTimer tm(DCHAG_STAGE_QUERY, st);
+    k_project_query<T><<<dim3((D + 3) / 4, G), 256, 0, st>>>(
+        D, static_cast<const T*>(lv->query), static_cast<const T*>(lv->Wq), static_cast<const T*>(lv->bq), out.Qp);
+    if ((rc = launch_status())) return rc;
+  }
+  StageTimer tm(DCHAG_STAGE_FOLD, st);
+  k_fold_query_into_key<T><<<dim3((D + 63) / 64, heads, G), 256, 0, st>>>(D, heads, static_cast<const T*>(lv->Wk), out.Qp, out.Mf,
+                                                                          out.Mb, nullptr);
+  return launch_status();
+}
+
+// Scores, softmax and weighted sums in one kernel: while the partial scores of a patch fit 64 KiB of LDS.  Two patches a block, one
+// where two would leave compute units without a block or do not fit.
+inline long level_generic_lds(int heads, int g, int patches) { return 16L * patches * g * round_up(heads, 8); }
+inline bool level_generic_ok(int heads, int g) {
+  return level_generic_lds(heads, g, 1) <= 65536 && !dbg(SW_GENERIC_LEVEL) && !dbg(SW_LEVEL_UNFUSED);
+}
+template <typename T, bool VALUES>
+int launch_level_generic(int B, int Cin, int N, int D, int heads, int g0, const T* z, const float* Mf, const T* V, float* alpha,
+                         T* out, hipStream_t st) {
+  const int g = std::min(g0, Cin), G = groups_of(Cin, g);
+  const bool two = level_generic_lds(heads, g, 2) <= 65536 && (long)((N + 1) / 2) * G * B >= compute_units();
+  auto kern = two ? k_level_generic<T, VALUES, 2> : k_level_generic<T, VALUES, 1>;
+  const int pn = two ? 2 : 1;
+  kern<<<dim3((N + pn - 1) / pn, G, B), 256, level_generic_lds(heads, g, pn), st>>>(Cin, N, D, heads, round_up(heads, 8), g, z, Mf, V,
+                                                                                alpha, out);
+  return launch_status();
+}
+
 // One aggregation level: weight-only prep, scores, value projection, softmax-weighted sum,
 // output projection.
 template <typename T>
 int run_level(dchag_dtype dt, int B, int Cin, int N, int D, int heads, const dchag_level* lv, const T* zin,
-              T* zout, unsigned char* ws, hipStream_t st, const T* rowadd = nullptr) {
+              T* zout, unsigned char* ws, hipStream_t st, const T* rowadd = nullptr, const PrepBufs* ready = nullptr) {
   const int g = lv->group_size;
   const int G = groups_of(Cin, g);
   const LevelWs w = level_ws(dt, B, Cin, N, D, heads, g);
-  float* Qp = reinterpret_cast<float*>(ws + w.qp);
-  float* Mf = reinterpret_cast<float*>(ws + w.mf);
   float* S = reinterpret_cast<float*>(ws + w.s);
   T* V = reinterpret_cast<T*>(ws + w.v);
   T* O = reinterpret_cast<T*>(ws + w.o);
+  const PrepBufs own{reinterpret_cast<float*>(ws + w.qp), reinterpret_cast<float*>(ws + w.mf), nullptr};
+  const PrepBufs& pb = ready ? *ready : own;
   int rc;
-
-  {
-    StageTimer tm(DCHAG_STAGE_QUERY, st);
-    k_project_query<T><<<dim3((D + 3) / 4, G), 256, 0, st>>>(
-        D, static_cast<const T*>(lv->query), static_cast<const T*>(lv->Wq), static_cast<const T*>(lv->bq), Qp);
-    if ((rc = launch_status())) return rc;
-  }
-  {
-    StageTimer tm(DCHAG_STAGE_FOLD, st);
-    k_fold_query_into_key<T><<<dim3((D + 63) / 64, heads, G), 256, 0, st>>>(
-        D, heads, static_cast<const T*>(lv->Wk), Qp, Mf, nullptr, nullptr);
-    if ((rc = launch_status())) return rc;
-  }
-  {
+  if (!ready && (rc = generic_query_keys<T>(G, D, heads, lv, pb, st))) return rc;
+  const bool fused = level_generic_ok(heads, std::min(g, Cin));
+  if (!fused) {
     StageTimer tm(DCHAG_STAGE_SCORES, st);
-    if ((rc = token_scores(B, Cin, N, D, heads, g, zin, Mf, S, st))) return rc;
+    if ((rc = token_scores(B, Cin, N, D, heads, g, zin, pb.Mf, S, st))) return rc;
   }
   {
     StageTimer tm(DCHAG_STAGE_VPROJ, st);
@@ -455,8 +515,12 @@ int run_level(dchag_dtype dt, int B, int Cin, int N, int D, int heads, const dch
   }
   {
     StageTimer tm(DCHAG_STAGE_SOFTMAX_AGG, st);
-    k_softmax_aggregate_generic<T><<<dim3(N, G, B), 256, 0, st>>>(Cin, N, D, heads, g, S, V, O);
-    if ((rc = launch_status())) return rc;
+    if (fused) {
+      if ((rc = launch_level_generic<T, true>(B, Cin, N, D, heads, g, zin, pb.Mf, V, nullptr, O, st))) return rc;
+    } else {
+      k_softmax_aggregate_generic<T><<<dim3(N, G, B), 256, 0, st>>>(Cin, N, D, heads, g, S, V, O);
+      if ((rc = launch_status())) return rc;
+    }
   }
   StageTimer tm(DCHAG_STAGE_OPROJ, st);
   RowBlocks rbo{G, G * N, N};
@@ -524,33 +588,6 @@ bool pixel_scores_ok(int p, int heads) {
          pp <= 256 && !dbg(SW_TOKEN_SCORES);
 }
 
-// Projected queries and query-folded keys of n attention levels (bf16, D % 8 == 0) in one launch.
-struct KeyPrepJob {
-  const dchag_level* lv;
-  int G;
-  PrepBufs out;
-  float* MfT;                      // optional transposed copy of the folded keys
-};
-int launch_query_keys(int D, int heads, const KeyPrepJob* jobs, int n, hipStream_t st) {
-  KeyPrepArgs args{};
-  int total = 0;
-  args.n_levels = n;
-  for (int i = 0; i < n; ++i) {
-    const dchag_level* lv = jobs[i].lv;
-    args.lv[i] = KeyPrepLevel{static_cast<const bf16*>(lv->query), static_cast<const bf16*>(lv->Wq),
-                              static_cast<const bf16*>(lv->bq),    static_cast<const bf16*>(lv->Wk),
-                              jobs[i].out.Qp, jobs[i].out.Mf, jobs[i].MfT, jobs[i].out.Mb, total};
-    total += jobs[i].G;
-  }
-  if (total > 65535 || heads > 65535) return DCHAG_ERR_SHAPE;
-  StageTimer tm(DCHAG_STAGE_KEY_PREP, st);
-  // shares of the columns per (head, group): enough blocks for two per compute unit, whole 512-column passes each
-  int shares = 1;
-  while ((long)heads * total * shares < 2L * compute_units() && D % (1024 * shares) == 0 && shares < 8) shares *= 2;
-  k_query_keys<<<dim3(heads, total, shares), 256, (size_t)(D / heads + 1536) * 4, st>>>(D, heads, args);
-  return launch_status();
-}
-
 // Weight-only prep, scores and softmax of one level on the bf16 MFMA path: leaves the projected query in
 // Qp, the folded keys in Mf / Mb and the softmax weights in alpha, laid out [B][G][gpad][heads][Np].
 // alpha_tm (optional): where the softmax weights are also wanted token-major [B,Cin,N,heads]; *tm_done tells whether
@@ -568,7 +605,7 @@ int fast_scores(int B, int Cin, int N, int D, int heads, const dchag_level* lv, 
   int rc;
   if (phase != 2 && phase != 3) {
     const KeyPrepJob job{lv, G, PrepBufs{Qp, Mf, Mb}, px ? px->MfT : nullptr};
-    if ((rc = launch_query_keys(D, heads, &job, 1, st))) return rc;
+    if ((rc = launch_query_keys<bf16>(D, heads, &job, 1, st))) return rc;
   }
   if (phase == 1 && !px) return DCHAG_OK;
   if (px) {
@@ -1101,21 +1138,24 @@ static int forward_impl(dchag_dtype dt, int B, int C, int H, int W, int p, int D
     return rc;
   // every attention level's weight-only prep (projected query, query folded into the key weights) in ONE launch
   const bool fast = dt == DCHAG_BF16 && fast_level(dt, D, heads) && !dbg(SW_GENERIC_LEVEL);
+  const bool prepared = fast || (query_keys_ok(D, heads) && !dbg(SW_GENERIC_LEVEL));
   PrepBufs ready[16];
-  if (fast) {
+  if (prepared) {
     KeyPrepJob jobs[16];
     int nj = 0, cl = c_in;
     for (int l = first; l < n_levels; ++l) {
       const int G = groups_of(cl, gs[l]);
       if (levels[l].kind == DCHAG_LEVEL_ATTENTION) {
         ready[l] = prep_bufs(ws + w.prep[l], G, D, heads);
-        const bool px0 = l == 0 && pixel_scores_ok(p, heads);
+        if (dt == DCHAG_F32) ready[l].Mb = nullptr;
+        const bool px0 = fast && l == 0 && pixel_scores_ok(p, heads);
         jobs[nj++] = KeyPrepJob{&levels[l], G, ready[l], px0 ? reinterpret_cast<float*>(ws + w.mft) : nullptr};
       }
       cl = G;
     }
     set_level(0);
-    if (nj && (rc = launch_query_keys(D, heads, jobs, nj, st))) return rc;
+    if (nj) rc = dt == DCHAG_F32 ? launch_query_keys<float>(D, heads, jobs, nj, st) : launch_query_keys<bf16>(D, heads, jobs, nj, st);
+    if (nj && rc) return rc;
   }
   for (int l = first; l < n_levels; ++l) {
     set_level(l + 1);
@@ -1128,7 +1168,8 @@ static int forward_impl(dchag_dtype dt, int B, int C, int H, int W, int p, int D
                                                       static_cast<bf16*>(zout), st);
     else if (dt == DCHAG_F32)
       rc = run_level<float>(dt, B, c_in, N, D, heads, &levels[l], static_cast<const float*>(zin),
-                            static_cast<float*>(zout), ws + w.level, st, static_cast<const float*>(rowadd));
+                            static_cast<float*>(zout), ws + w.level, st, static_cast<const float*>(rowadd),
+                            prepared ? &ready[l] : nullptr);
     else if (fast_level(dt, D, heads) && !dbg(SW_GENERIC_LEVEL)) {
       PixelScores px{static_cast<const bf16*>(x), static_cast<const bf16*>(We), static_cast<const bf16*>(be),
                      static_cast<const bf16*>(ce), H, W, p, reinterpret_cast<float*>(ws + w.ms),
@@ -1141,7 +1182,8 @@ static int forward_impl(dchag_dtype dt, int B, int C, int H, int W, int p, int D
     }
     else
       rc = run_level<bf16>(dt, B, c_in, N, D, heads, &levels[l], static_cast<const bf16*>(zin),
-                           static_cast<bf16*>(zout), ws + w.level, st, static_cast<const bf16*>(rowadd));
+                           static_cast<bf16*>(zout), ws + w.level, st, static_cast<const bf16*>(rowadd),
+                           prepared ? &ready[l] : nullptr);
     if (rc) return rc;
     zin = zout;
     c_in = groups_of(c_in, gs[l]);

@@ -443,24 +443,18 @@ LevelBufs<T> level_bufs(unsigned char* lw, const KeptLevel& kl) {
                       reinterpret_cast<T*>(lw + kl.o)};
 }
 
-// alpha of one level, token-major [B,Cin,N,heads], on the shape-generic kernels.
+// alpha of one level, token-major [B,Cin,N,heads], and where one kernel makes both (*summed) the per-head token sums u, on the
+// shape-generic kernels.  prepared: the projected query and the folded keys are already in lb.
 template <typename T>
-int generic_alpha(int B, int Cin, int N, int D, int heads, const dchag_level* lv, const T* zin, const LevelBufs<T>& lb,
-                  hipStream_t st) {
+int generic_alpha(int B, int Cin, int N, int D, int heads, const dchag_level* lv, const T* zin, const LevelBufs<T>& lb, bool prepared,
+                  bool* summed, hipStream_t st) {
   const int g = lv->group_size, G = groups_of(Cin, g);
   int rc;
-  {
-    StageTimer tm(DCHAG_STAGE_QUERY, st);
-    k_project_query<T><<<dim3((D + 3) / 4, G), 256, 0, st>>>(D, static_cast<const T*>(lv->query),
-                                                             static_cast<const T*>(lv->Wq),
-                                                             static_cast<const T*>(lv->bq), lb.Qp);
-    if ((rc = launch_status())) return rc;
-  }
-  {
-    StageTimer tm(DCHAG_STAGE_FOLD, st);
-    k_fold_query_into_key<T><<<dim3((D + 63) / 64, heads, G), 256, 0, st>>>(D, heads, static_cast<const T*>(lv->Wk),
-                                                                            lb.Qp, lb.Mf, lb.Mb, nullptr);
-    if ((rc = launch_status())) return rc;
+  if (!prepared && (rc = generic_query_keys<T>(G, D, heads, lv, PrepBufs{lb.Qp, lb.Mf, lb.Mb}, st))) return rc;
+  *summed = level_generic_ok(heads, std::min(g, Cin));
+  if (*summed) {
+    StageTimer tm(DCHAG_STAGE_HEAD_SUMS, st);
+    return launch_level_generic<T, false>(B, Cin, N, D, heads, g, zin, lb.Mf, nullptr, lb.alpha, lb.u, st);
   }
   StageTimer tm(DCHAG_STAGE_SCORES, st);
   if ((rc = token_scores(B, Cin, N, D, heads, g, zin, lb.Mf, lb.alpha, st))) return rc;
@@ -562,10 +556,10 @@ int folded_level_forward(dchag_dtype dt, int B, int Cin, int N, int D, int heads
         rc = fast_alpha(B, Cin, N, D, heads, lv, zin, lb, st, px, phase);
       }
     } else {
-      rc = generic_alpha<T>(B, Cin, N, D, heads, lv, zin, lb, st);
+      rc = generic_alpha<T>(B, Cin, N, D, heads, lv, zin, lb, phase != 0, &summed, st);
     }
   } else {
-    rc = generic_alpha<T>(B, Cin, N, D, heads, lv, zin, lb, st);
+    rc = generic_alpha<T>(B, Cin, N, D, heads, lv, zin, lb, phase != 0, &summed, st);
   }
   if (rc) return rc;
   if (!summed) {
@@ -803,22 +797,21 @@ int forward_folded_impl(dchag_dtype dt, int B, int C, int H, int W, int p, int D
   // every attention level's weight-only prep (projected query, query folded into the key weights) in ONE launch
   PrepBufs ready[16];
   bool hoisted = false;
-  if constexpr (std::is_same<T, bf16>::value) {
-    if (!prefolded && train_fast(dt, D, heads)) {
-      KeyPrepJob jobs[16];
-      int nj = 0, cl = c_in;
-      for (int l = first; l < n_levels; ++l) {
-        const int G = groups_of(cl, gs[l]);
-        if (levels[l].kind != DCHAG_LEVEL_LINEAR) {
-          ready[l] = prep_bufs(ws + w.prep[l], G, D, heads);
-          jobs[nj++] = KeyPrepJob{&levels[l], G, ready[l], l == 0 ? px.MfT : nullptr};
-        }
-        cl = G;
+  const bool prep_fast = train_fast(dt, D, heads);
+  if (!prefolded && (prep_fast || (query_keys_ok(D, heads) && !dbg(SW_GENERIC_LEVEL)))) {
+    KeyPrepJob jobs[16];
+    int nj = 0, cl = c_in;
+    for (int l = first; l < n_levels; ++l) {
+      const int G = groups_of(cl, gs[l]);
+      if (levels[l].kind != DCHAG_LEVEL_LINEAR) {
+        ready[l] = prep_bufs(ws + w.prep[l], G, D, heads);
+        jobs[nj++] = KeyPrepJob{&levels[l], G, ready[l], prep_fast && l == 0 ? px.MfT : nullptr};
       }
-      set_level(0);
-      if (nj && (rc = launch_query_keys(D, heads, jobs, nj, st))) return rc;
-      hoisted = nj > 0;
+      cl = G;
     }
+    set_level(0);
+    if (nj && (rc = launch_query_keys<T>(D, heads, jobs, nj, st))) return rc;
+    hoisted = nj > 0;
   }
   if constexpr (std::is_same<T, bf16>::value) {
     // an attention first level straight from the pixels: scores through the composed score weights, values through
@@ -878,15 +871,16 @@ int forward_folded_impl(dchag_dtype dt, int B, int C, int H, int W, int p, int D
       const KeptLevel kl = kept_level(dt, B, c_in, N, D, heads, gs[l], false, false);
       LevelBufs<T> lb = level_bufs<T>(ws + w.level, kl);
       int phase = 0;
+      if (hoisted) {
+        lb.Qp = ready[l].Qp;
+        lb.Mf = ready[l].Mf;
+        lb.Mb = ready[l].Mb;
+        phase = 3;
+      }
       if constexpr (std::is_same<T, bf16>::value) {
         if (prefolded && l > 0 && train_fast(dt, D, heads)) {
           use_prepared(prefolded, PL, l, lb);
           phase = 2;
-        } else if (hoisted) {
-          lb.Qp = ready[l].Qp;
-          lb.Mf = ready[l].Mf;
-          lb.Mb = ready[l].Mb;
-          phase = 3;
         }
       }
       rc = folded_level_forward<T>(dt, B, c_in, N, D, heads, &levels[l], zin, zout, lb, st,
@@ -1714,29 +1708,26 @@ int keep_forward(dchag_dtype dt, int B, int C, int H, int W, int p, int D, int h
   const bool use_px = dt == DCHAG_BF16 && train_fast(dt, D, heads) && pixel_scores_ok(p, heads);
   // every attention level's weight-only prep in ONE launch, straight into the level's kept buffers
   int phase = 0;
-  if constexpr (std::is_same<T, bf16>::value) {
-    if (train_fast(dt, D, heads)) {
-      KeyPrepJob jobs[16];
-      int nj = 0, cl = c_in;
-      for (int l = first; l < n_levels; ++l) {
-        const bool linear = levels[l].kind == DCHAG_LEVEL_LINEAR;
-        const int G = groups_of(cl, gs[l]);
-        if (!linear) {
-          LevelBufs<bf16> lb = level_bufs<bf16>(ws + w.kept[l], kept_level(dt, B, cl, N, D, heads, gs[l], false,
-                                                                           l + 1 < n_levels));
-          if (l == 0 && w.pixels) {
-            lb.Qp = reinterpret_cast<float*>(ws + w.px.qp);
-            lb.Mf = reinterpret_cast<float*>(ws + w.px.mf);
-            lb.Mb = reinterpret_cast<bf16*>(ws + w.px.mb);
-          }
-          jobs[nj++] = KeyPrepJob{&levels[l], G, PrepBufs{lb.Qp, lb.Mf, lb.Mb}, (l == 0 && use_px) ? px.MfT : nullptr};
+  if (train_fast(dt, D, heads) || (query_keys_ok(D, heads) && !dbg(SW_GENERIC_LEVEL))) {
+    KeyPrepJob jobs[16];
+    int nj = 0, cl = c_in;
+    for (int l = first; l < n_levels; ++l) {
+      const bool linear = levels[l].kind == DCHAG_LEVEL_LINEAR;
+      const int G = groups_of(cl, gs[l]);
+      if (!linear) {
+        LevelBufs<T> lb = level_bufs<T>(ws + w.kept[l], kept_level(dt, B, cl, N, D, heads, gs[l], false, l + 1 < n_levels));
+        if (l == 0 && w.pixels) {
+          lb.Qp = reinterpret_cast<float*>(ws + w.px.qp);
+          lb.Mf = reinterpret_cast<float*>(ws + w.px.mf);
+          lb.Mb = reinterpret_cast<bf16*>(ws + w.px.mb);
         }
-        cl = G;
+        jobs[nj++] = KeyPrepJob{&levels[l], G, PrepBufs{lb.Qp, lb.Mf, lb.Mb}, (l == 0 && use_px) ? px.MfT : nullptr};
       }
-      set_level(0);
-      if (nj && (rc = launch_query_keys(D, heads, jobs, nj, st))) return rc;
-      if (nj) phase = 3;
+      cl = G;
     }
+    set_level(0);
+    if (nj && (rc = launch_query_keys<T>(D, heads, jobs, nj, st))) return rc;
+    if (nj) phase = 3;
   }
   if constexpr (std::is_same<T, bf16>::value) {
     if (w.pixels) {

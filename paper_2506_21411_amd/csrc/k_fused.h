@@ -65,11 +65,11 @@ constexpr int kGemmRingBytes = kGemmStages * kGemmStageBytes;                  /
 // so that the score of token z for head a is z . M[k][a][:].  grid (heads, all groups of all levels, column shares),
 // block 256: a block of (head a, group k) first forms the dh entries of Q of its head (a wavefront per row of Wq, the
 // rows dealt round-robin), leaves them in LDS (and, the first share, in Qp), then sums the dh rows of Wk of that head
-// into its share of M's columns (fixed summation order).  Writes M as fp32 (Mf), bf16 (Mb) and, where asked,
+// into its share of M's columns (fixed summation order).  Writes M as fp32 (Mf) and, where asked, bf16 (Mb) and
 // transposed fp32 MfT[G][D][heads].  Requires dh % 4 == 0 and (D / shares) % 8 == 0.  Dynamic LDS: dh + 1536 floats.
 // ---------------------------------------------------------------------------------------------
 struct KeyPrepLevel {
-  const bf16 *query, *Wq, *bq, *Wk;
+  const void *query, *Wq, *bq, *Wk;
   float *Qp, *Mf, *MfT;
   bf16* Mb;
   int g_first;                     // index of this level's first group in the launch's group axis
@@ -80,39 +80,42 @@ struct KeyPrepArgs {
   KeyPrepLevel lv[kKeyPrepMaxLevels];
 };
 
+template <typename T>
 __global__ __launch_bounds__(256) void k_query_keys(int D, int heads, KeyPrepArgs args) {
+  typedef T vec8 __attribute__((ext_vector_type(8), aligned(16)));
   extern __shared__ float qs[];                          // [dh] projected query of the head, then [3][512] partial sums
   const int a = blockIdx.x;
   int l = 0;
   while (l + 1 < args.n_levels && (int)blockIdx.y >= args.lv[l + 1].g_first) ++l;     // uniform over the block
   const KeyPrepLevel& P = args.lv[l];
+  const T *Wq = static_cast<const T*>(P.Wq), *Wk = static_cast<const T*>(P.Wk), *bq = static_cast<const T*>(P.bq);
   const int k = blockIdx.y - P.g_first;
   const int dh = D / heads;
   float* part = qs + dh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bf16* q = P.query + (size_t)k * D;
+  const T* q = static_cast<const T*>(P.query) + (size_t)k * D;
   const size_t row0 = (size_t)k * D + (size_t)a * dh;
   // Q of this head: wavefront w takes rows w, w + 4, ..., eight of them at a time so that their loads are in flight
   // together (every block of a head computes all of Q_a: the second block's reads come out of L2)
   for (int r0 = wave; r0 < dh; r0 += 32) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int j = lane * 8; j < D; j += kWave * 8) {
-      const bf16x8 qv = *reinterpret_cast<const bf16x8*>(q + j);
-      bf16x8 wv[8];
+      const vec8 qv = *reinterpret_cast<const vec8*>(q + j);
+      vec8 wv[8];
 #pragma unroll
       for (int t = 0; t < 8; ++t)
-        wv[t] = *reinterpret_cast<const bf16x8*>(P.Wq + (row0 + min(r0 + 4 * t, dh - 1)) * D + j);
+        wv[t] = *reinterpret_cast<const vec8*>(Wq + (row0 + min(r0 + 4 * t, dh - 1)) * D + j);
 #pragma unroll
       for (int t = 0; t < 8; ++t)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[t] += (float)wv[t][e] * (float)qv[e];
+        for (int e = 0; e < 8; ++e) acc[t] += to_f32(wv[t][e]) * to_f32(qv[e]);
     }
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const float v = wave_sum(acc[t]);
       const int r = r0 + 4 * t;
       if (lane == 0 && r < dh) {
-        const float qv = v + (P.bq ? (float)P.bq[row0 + r] : 0.f);
+        const float qv = v + (bq ? to_f32(bq[row0 + r]) : 0.f);
         if (blockIdx.z == 0) P.Qp[row0 + r] = qv;
         qs[r] = qv;
       }
@@ -129,14 +132,14 @@ __global__ __launch_bounds__(256) void k_query_keys(int D, int heads, KeyPrepArg
     const bool live = d0 < cend;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (live) {
-      const bf16* w = P.Wk + (row0 + (size_t)wave * qrows) * D + d0;
+      const T* w = Wk + (row0 + (size_t)wave * qrows) * D + d0;
       const float* qh = qs + wave * qrows;
 #pragma unroll 8
       for (int r = 0; r < qrows; ++r) {
-        const bf16x8 v = *reinterpret_cast<const bf16x8*>(w + (size_t)r * D);
+        const vec8 v = *reinterpret_cast<const vec8*>(w + (size_t)r * D);
         const float qr = qh[r];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += (float)v[e] * qr;
+        for (int e = 0; e < 8; ++e) acc[e] += to_f32(v[e]) * qr;
       }
     }
     if (wave > 0) {
@@ -154,7 +157,7 @@ __global__ __launch_bounds__(256) void k_query_keys(int D, int heads, KeyPrepArg
       }
       *reinterpret_cast<f32x4*>(P.Mf + o) = f32x4{acc[0], acc[1], acc[2], acc[3]};
       *reinterpret_cast<f32x4*>(P.Mf + o + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
-      *reinterpret_cast<bf16x8*>(P.Mb + o) = b8;
+      if (P.Mb) *reinterpret_cast<bf16x8*>(P.Mb + o) = b8;
       if (P.MfT) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) P.MfT[((size_t)k * D + d0 + e) * heads + a] = acc[e];

@@ -148,6 +148,144 @@ __global__ __launch_bounds__(256) void k_softmax_group_backward(int Cin, int N, 
 }
 
 // ---------------------------------------------------------------------------------------
+// Scores, softmax over the group and the weighted sums of a level in one launch, for the shapes that the bf16 kernels of
+// k_fused.h do not take (fp32; D % 256 != 0):
+//   s[c,a] = z[c] . M[k][a],  alpha = softmax over c,  and with VALUES  O[d] = sum_c alpha[c,a(d)] V[c][d],
+//   otherwise  u[a][:] = sum_c alpha[c,a] z[c][:]  (alpha is also written, token-major [b,c,n,a], where asked).
+// A block takes PN patches of a group.  Scores on v_mfma_f32_16x16x4_f32: 16 members x 16 heads; a lane loads four adjacent
+// columns of its row, each the k-step of a product of its own (both operands in the same order, so the contraction is complete),
+// in four sums; the wavefronts deal the columns among them by sixteens and the patches share the keys.  The partial scores meet in
+// LDS in a fixed order, where the weights stay; eight lanes share a softmax.
+// The separate kernels (scores, of which a product uses 8 of its 64 columns, a softmax, sums) took, us: fp32, D 512, 8 heads, 512
+// patches, 10 groups of 8: 75, here 46 (168 MB: 3.7 TB/s); its upper level, 10 members: 34, 11.5; bf16, D 384, 6 heads, 2 x 135
+// patches, 8 groups of 10: 54, 18; its upper level: 23, 7.  Eight patches a block left most compute units idle there (30 and 23).
+// grid (ceil(N/PN), G, B), block 256, dynamic LDS 4 * PN * min(g, Cin) * hp floats, hp = heads to a multiple of 8.
+// ---------------------------------------------------------------------------------------
+template <typename T, bool VALUES, int PN>
+__global__ __launch_bounds__(256) void k_level_generic(int Cin, int N, int D, int heads, int hp, int g, const T* __restrict__ z,
+                                                       const float* __restrict__ Mf, const T* __restrict__ V,
+                                                       float* __restrict__ alpha, T* __restrict__ out) {
+  typedef T vec4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __attribute__((aligned(16))) float sc[];   // [wavefront][patch][member][head], then the weights in part 0
+  const int n0 = blockIdx.x * PN, k = blockIdx.y, b = blockIdx.z, G = gridDim.y;
+  const int c0 = k * g, gk = min(g, Cin - c0), live = min(PN, N - n0);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lq = lane >> 4;
+  const int pitch = gk * hp, total = PN * pitch;
+  const size_t cs = (size_t)N * D;
+  const T* zb = z + ((size_t)b * Cin + c0) * cs + (size_t)n0 * D;
+  for (int m0 = 0; m0 < gk; m0 += 16)
+    for (int a0 = 0; a0 < heads; a0 += 16) {
+      const T* zp = zb + min(m0 + l16, gk - 1) * cs + lq * 4;
+      const float* mp = Mf + ((size_t)k * heads + min(a0 + l16, heads - 1)) * D + lq * 4;
+      f32x4 acc[PN][4];
+#pragma unroll
+      for (int p = 0; p < PN; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[p][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int j = wave * 16; j < D; j += 64) {
+        vec4 zv[PN] = {};
+        f32x4 mv = {0.f, 0.f, 0.f, 0.f};
+        if (j + lq * 4 < D) {                                // D % 8 == 0: the last 16 columns may be 8
+#pragma unroll
+          for (int p = 0; p < PN; ++p) zv[p] = *reinterpret_cast<const vec4*>(zp + (size_t)min(p, live - 1) * D + j);
+          mv = *reinterpret_cast<const f32x4*>(mp + j);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int p = 0; p < PN; ++p)
+            acc[p][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(to_f32(zv[p][e]), mv[e], acc[p][e], 0, 0, 0);
+      }
+      // lane: head l16, register r: member 4 lq + r
+#pragma unroll
+      for (int p = 0; p < PN; ++p) {
+        const f32x4 s = (acc[p][0] + acc[p][1]) + (acc[p][2] + acc[p][3]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + lq * 4 + r;
+          if (m < gk && a0 + l16 < hp) sc[wave * total + p * pitch + m * hp + a0 + l16] = s[r];
+        }
+      }
+    }
+  __syncthreads();
+  for (int i = tid; i < total; i += 256) sc[i] = (sc[i] + sc[total + i]) + (sc[2 * total + i] + sc[3 * total + i]);
+  __syncthreads();
+  for (int i = tid >> 3; i < live * hp; i += 32) {           // eight lanes a (patch, head); past `heads`: finite, not used
+    const int p = i / hp, a = i % hp, sub = tid & 7;
+    float* w = sc + p * pitch + a;
+    float mx = -INFINITY, den = 0.f;
+    for (int m = sub; m < gk; m += 8) mx = fmaxf(mx, w[m * hp]);
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, kWave));
+    for (int m = sub; m < gk; m += 8) {
+      const float v = __expf(w[m * hp] - mx);
+      w[m * hp] = v;
+      den += v;
+    }
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) den += __shfl_xor(den, o, kWave);
+    const float inv = 1.f / den;
+    for (int m = sub; m < gk; m += 8) {
+      const float v = w[m * hp] * inv;
+      w[m * hp] = v;
+      if (alpha && a < heads) alpha[(((size_t)b * Cin + c0 + m) * N + n0 + p) * heads + a] = v;
+    }
+  }
+  __syncthreads();
+  const int quads = D / 4, dh = D / heads;
+  for (int i = tid; i < live * quads; i += 256) {
+    const int p = i / quads, d0 = (i % quads) * 4;
+    const float* w = sc + p * pitch;
+    if (VALUES) {
+      const T* vp = V + ((size_t)b * Cin + c0) * cs + (size_t)(n0 + p) * D + d0;
+      int a[4];
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = (d0 + e) / dh;
+#pragma unroll 4
+      for (int m = 0; m < gk; ++m) {
+        const vec4 v = *reinterpret_cast<const vec4*>(vp + m * cs);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += w[m * hp + a[e]] * to_f32(v[e]);
+      }
+      vec4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = from_f32<T>(acc[e]);
+      *reinterpret_cast<vec4*>(out + (((size_t)b * G + k) * N + n0 + p) * D + d0) = o;
+    } else {
+      const T* zp = zb + (size_t)p * D + d0;
+      T* up = out + (((size_t)b * G + k) * N + n0 + p) * heads * D + d0;
+      for (int a0 = 0; a0 < heads; a0 += 8) {
+        f32x4 acc[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int m = 0; m < gk; ++m) {
+          const vec4 v = *reinterpret_cast<const vec4*>(zp + m * cs);
+          const f32x4 w0 = *reinterpret_cast<const f32x4*>(w + m * hp + a0), w1 = *reinterpret_cast<const f32x4*>(w + m * hp + a0 + 4);
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              acc[t][e] += w0[t] * to_f32(v[e]);
+              acc[4 + t][e] += w1[t] * to_f32(v[e]);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          if (a0 + t >= heads) break;
+          vec4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = from_f32<T>(acc[t][e]);
+          *reinterpret_cast<vec4*>(up + (size_t)(a0 + t) * D) = o;
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // Per-head weighted token sums:  u[b,k,n,a,:] = sum_{c in group k} alpha[b,c,n,a] * z[b,c,n,:]
 // grid (N, G, B), block 256; a thread owns columns d = tid, tid + 256, .. and HMAX heads at a time.
 // ---------------------------------------------------------------------------------------
