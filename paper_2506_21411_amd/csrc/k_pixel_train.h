@@ -103,11 +103,17 @@ __device__ __forceinline__ void pair_loop(unsigned char* smem, int begin, int en
   for (int s = begin; s < end; ++s) {
     const unsigned char* st = smem + sc * kPairStageBytes;
     L.read(st, 1, a1, b1);
+    __builtin_amdgcn_sched_barrier(0);
     step(s, 0, a0, b0, st);
+    __builtin_amdgcn_sched_barrier(0);
     L.read(st, 2, a0, b0);
+    __builtin_amdgcn_sched_barrier(0);
     step(s, 1, a1, b1, st);
+    __builtin_amdgcn_sched_barrier(0);
     L.read(st, 3, a1, b1);
+    __builtin_amdgcn_sched_barrier(0);
     step(s, 2, a0, b0, st);
+    __builtin_amdgcn_sched_barrier(0);
     // slice s + 1 has landed (this wavefront's share; the loads of slice s + 2 may stay in flight) and this slice's reads are
     // in registers
     if (s + 2 < end) wait_vmcnt<LD>();
@@ -119,8 +125,10 @@ __device__ __forceinline__ void pair_loop(unsigned char* smem, int begin, int en
     if (s + 3 < end) issue(s + 3, smem + sc * kPairStageBytes);                 // the stage just released
     sc = sc == 2 ? 0 : sc + 1;
     L.read(smem + sc * kPairStageBytes, 0, a0, b0);        // past the last slice: a stale stage, read and not used
+    __builtin_amdgcn_sched_barrier(0);
     step(s, 3, a1, b1, st);
     post(s);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
