@@ -43,6 +43,7 @@ enum Switch {
   SW_FOLD_VALUE_GEMM,
   SW_GEMM,
   SW_GEMM_GENERIC,
+  SW_GEMM_REGS,
   SW_GEMM_SCALAR_STORES,
   SW_GENERIC_LEVEL,
   SW_GENERIC_TOKENIZE,
@@ -79,6 +80,7 @@ struct SwitchTable {
     "DCHAG_FOLD_VALUE_GEMM",
     "DCHAG_GEMM",
     "DCHAG_GEMM_GENERIC",
+    "DCHAG_GEMM_REGS",
     "DCHAG_GEMM_SCALAR_STORES",
     "DCHAG_GENERIC_LEVEL",
     "DCHAG_GENERIC_TOKENIZE",
@@ -545,18 +547,10 @@ int launch_linear_dl(int B, int D, RowBlocks rb, const bf16* A, const bf16* Wt, 
   tw.m_tiles = (rb.rows_per_group + kGemmBM - 1) / kGemmBM;
   tw.nb = B;
   tw.total = tw.n_tiles * tw.m_tiles * B * rb.G;
-  if (tw.total * 2 < compute_units()) {                  // too few 256x256 tiles to fill the chip: 128x128 tiles, and
-    if (dbg(SW_LINEAR_SMALL_REGS))                         // loads three slices ahead (the debugging switch keeps the
-      return launch_linear_mfma_cfg<128, 128, 2, 2, 1>(B, D, rb, A, Wt, bias, Y, st, rowadd);   // register-staged kernel)
-    TileWork ts;
-    ts.n_tiles = D / 128;
-    ts.m_tiles = (rb.rows_per_group + 127) / 128;
-    ts.nb = B;
-    ts.total = ts.n_tiles * ts.m_tiles * B * rb.G;
-    const int pers = (ts.total + kXcds - 1) / kXcds;
-    if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_linear_ring), kSmallRingBytes)) return DCHAG_ERR_LAUNCH;
-    k_linear_ring<<<dim3(pers * kXcds), dim3(256), kSmallRingBytes, st>>>(D, rb, ts, A, Wt, bias, Y, rowadd);
-    return launch_status();
+  if (tw.total * 2 < compute_units()) {                  // too few 256 x 256 tiles to fill the chip: the smaller ones of
+    if (dbg(SW_LINEAR_SMALL_REGS))                         // k_gemm_ring (the debugging switch keeps a register-staged kernel)
+      return launch_linear_mfma_cfg<128, 128, 2, 2, 1>(B, D, rb, A, Wt, bias, Y, st, rowadd);
+    return linear_as_gemm(B, D, rb, A, Wt, bias, Y, st, rowadd);
   }
   ProductArgs pa{};
   pa.A = A; pa.B = Wt; pa.bias = bias; pa.rowadd = rowadd; pa.C = Y;

@@ -304,9 +304,38 @@ int launch_gemm_mfma_form(const GemmDesc& d, const bf16* A, const bf16* Bm, cons
   return launch_status();
 }
 
+// Whole slices, bf16 results in whole 16-byte pieces, 32-bit offsets inside a tile, 16-byte aligned operands: the ring.
+inline bool gemm_ring_ok(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias) {
+  const bool at = d.A.s1 != 1, bt = d.Bm.s0 != 1;
+  const long reach = (1L << 30) / 128;
+  return d.c_vec && d.K % 64 == 0 && d.M >= 1 && d.N >= 8 && (at ? d.A.s1 : d.A.s0) < reach &&
+         (bt ? d.Bm.s0 : d.Bm.s1) < reach && aligned16(A) && aligned16(Bm) && aligned16(bias) && aligned16(d.rowadd) && mult8(d.bias_sk) &&
+         mult8(d.bias_sa) && !dbg(SW_GEMM_REGS);
+}
+template <int BM, int BN, int WM, int WN, int ST>
+int launch_gemm_ring(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias, bf16* C, bf16* rowsum, dim3 grid,
+                     hipStream_t st) {
+  const bool at = d.A.s1 != 1, bt = d.Bm.s0 != 1;
+  auto kern = at ? (bt ? k_gemm_ring<BM, BN, WM, WN, true, true, ST> : k_gemm_ring<BM, BN, WM, WN, true, false, ST>)
+                 : (bt ? k_gemm_ring<BM, BN, WM, WN, false, true, ST> : k_gemm_ring<BM, BN, WM, WN, false, false, ST>);
+  constexpr int lds = ST * (BM + BN) * 128;
+  if (ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds)) return DCHAG_ERR_LAUNCH;
+  kern<<<grid, 256, lds, st>>>(d, A, Bm, bias, C, rowsum);
+  return launch_status();
+}
+
 template <int BM, int BN, int WM, int WN, typename TC>
 int launch_gemm_mfma_tile(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias, TC* C, TC* rowsum,
                           hipStream_t st) {
+  if constexpr (std::is_same<TC, bf16>::value) {
+    const long batch = (long)(d.reduce_b ? 1 : d.nb) * d.nk * d.na, mt = (d.M + BM - 1) / BM;
+    if (gemm_ring_ok(d, A, Bm, bias) && batch <= 65535 && mt <= 65535) {
+      const dim3 grid((d.N + BN - 1) / BN, (unsigned)mt, (unsigned)batch);
+      if ((long)grid.x * mt * batch <= compute_units())
+        return launch_gemm_ring<BM, BN, WM, WN, 4>(d, A, Bm, bias, C, rowsum, grid, st);
+      return launch_gemm_ring<BM, BN, WM, WN, 2>(d, A, Bm, bias, C, rowsum, grid, st);
+    }
+  }
   return d.K % 64 || d.rowadd ? launch_gemm_mfma_form<BM, BN, WM, WN, true, TC>(d, A, Bm, bias, C, rowsum, st)
                               : launch_gemm_mfma_form<BM, BN, WM, WN, false, TC>(d, A, Bm, bias, C, rowsum, st);
 }
@@ -325,7 +354,7 @@ int launch_gemm_bf16(const GemmDesc& d0, const bf16* A, const bf16* Bm, const bf
   if (d.M <= 64) return launch_gemm_mfma_tile<64, 128, 1, 4, TC>(d, A, Bm, bias, C, rowsum, st);
   // a product of few 128 x 128 tiles (the one-group top level) takes 64 x 64 tiles: four times the blocks
   const long batch = (long)(d.reduce_b ? 1 : d.nb) * d.nk * d.na;
-  if ((long)((d.N + 127) / 128) * ((d.M + 127) / 128) * batch * 2 < compute_units())
+  if ((long)((d.N + 127) / 128) * ((d.M + 127) / 128) * batch * 2 <= compute_units())
     return launch_gemm_mfma_tile<64, 64, 2, 2, TC>(d, A, Bm, bias, C, rowsum, st);
   return launch_gemm_mfma_tile<128, 128, 2, 2, TC>(d, A, Bm, bias, C, rowsum, st);
 }

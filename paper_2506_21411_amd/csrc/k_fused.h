@@ -1112,107 +1112,6 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
   wait_vmcnt<0>();                                       // no load may still target LDS when the block retires
 }
 
-// ---------------------------------------------------------------------------------------------
-// The same projection for a problem of FEW tiles (the output projection of an upper level: 64 tiles of 128 x 128 at the
-// headline shape).  With less than one 256 x 256 tile per compute unit the run time is the depth of the contraction times
-// the round trip of one slice's loads, so this form trades tile size for depth of prefetch: 128 x 128 tiles, four
-// wavefronts (2 x 2) of 64 x 64, FOUR 32-KiB stages filled by direct-to-LDS loads issued three slices ahead; a slice
-// then costs its transfer and its 16 MFMAs per wavefront, not a round trip.  One barrier per slice; the fragments of a
-// slice are read behind it.  Requires D % 128 == 0.  Dynamic LDS: 128 KiB.
-// ---------------------------------------------------------------------------------------------
-constexpr int kSmallStageBytes = 256 * 128, kSmallStages = 4, kSmallRingBytes = kSmallStages * kSmallStageBytes;
-
-__global__ __launch_bounds__(256) void k_linear_ring(int D, RowBlocks rb, TileWork tw, const bf16* __restrict__ A,
-                                                     const bf16* __restrict__ Wt, const bf16* __restrict__ bias,
-                                                     bf16* __restrict__ Y, const bf16* __restrict__ rowadd) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  int k, b, mt, nt;
-  if (!tw.decode(blockIdx.x, k, b, mt, nt)) return;
-  const int rows = rb.rows_of(k);
-  const int r0 = mt * 128, o0 = nt * 128;
-  if (r0 >= rows) return;
-  const int KT = D / kGemmBK;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lhi = lane >> 5;
-  const bf16* Ab = A + (size_t)rb.first_row(b, k) * D;
-  bf16* Yb = Y + (size_t)rb.first_row(b, k) * D;
-  const bf16* Wb = Wt + (size_t)k * D * D;
-  // a stage: A rows 0..127, then B rows 0..127, 128 bytes each, chunks swizzled as in the large core; wavefront w loads
-  // rows 32 w .. 32 w + 31 of both (four loads each per slice)
-  const bf16* a_src[4];
-  const bf16* b_src[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = wave * 32 + i * 8 + (lane >> 3);
-    const int ch = ((lane & 7) ^ swz_chunk(row)) * 8;
-    a_src[i] = Ab + (size_t)min(r0 + row, rows - 1) * D + ch;
-    b_src[i] = Wb + (size_t)(o0 + row) * D + ch;
-  }
-  int issued = 0;
-  auto issue = [&]() {                                   // slice `issued` -> stage issued % 4
-    unsigned char* st = smem + (issued & 3) * kSmallStageBytes + wave * 4096;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) load16_to_lds(a_src[i] + issued * kGemmBK, st + i * 1024);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) load16_to_lds(b_src[i] + issued * kGemmBK, st + 128 * 128 + i * 1024);
-    ++issued;
-  };
-  const int a_base = (wm * 64 + l32) * 128, b_base = 128 * 128 + (wn * 64 + l32) * 128;
-  int ck[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) ck[kk] = ((kk * 2 + lhi) ^ swz_chunk(l32)) * 16;
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  for (int s0 = 0; s0 < 3 && s0 < KT; ++s0) issue();
-  for (int kt = 0; kt < KT; ++kt) {
-    // slice kt has landed (this wavefront's share; the slices behind it may stay in flight: 8 loads each) ...
-    const int behind = issued - 1 - kt;                  // uniform
-    if (behind >= 2) wait_vmcnt<16>();
-    else if (behind == 1) wait_vmcnt<8>();
-    else wait_vmcnt<0>();
-    // ... and for everyone; all wavefronts are done with slice kt - 1, whose stage takes slice kt + 3
-    __builtin_amdgcn_s_barrier();
-    if (issued < KT) issue();
-    const unsigned char* st = smem + (kt & 3) * kSmallStageBytes;
-    bf16x8 af[4][2], bfr[4][2];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        af[kk][i] = *reinterpret_cast<const bf16x8*>(st + a_base + i * 4096 + ck[kk]);
-        bfr[kk][i] = *reinterpret_cast<const bf16x8*>(st + b_base + i * 4096 + ck[kk]);
-      }
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk][i], bfr[kk][j], acc[i][j], 0, 0, 0);
-  }
-  wait_vmcnt<0>();                                       // nothing may still target LDS when the block retires
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int col = o0 + wn * 64 + j * 32 + l32;
-    const float bvv = bias ? (float)bias[(size_t)k * D + col] : 0.f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = r0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-        if (row < rows)
-          Yb[(size_t)row * D + col] = (bf16)(acc[i][j][r] + bvv + (rowadd ? (float)rowadd[(size_t)row * D + col] : 0.f));
-      }
-  }
-}
-
 // The token biases under the same fold (weight-only):  fb[c][o] = sum_d (be[c][d] + ce[c][d]) * Wv[k][o][d],  k = c / g;
 // either vector may be absent.  grid (D / (32 RT), G), block 256: 32 RT rows o of Wv against the group's members, 32 per pass
 // (32 x 32 MFMA blocks: rows o, columns members, operands straight from memory), the four wavefronts a quarter of d each, their

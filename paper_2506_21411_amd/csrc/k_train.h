@@ -1162,6 +1162,193 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
 }
 
 // ---------------------------------------------------------------------------------------
+// The products of k_gemm_mfma where every contraction is whole slices of 64, every row 16-byte aligned, transposed extents multiples of
+// 8 and C's rows whole 16-byte pieces (host): the same contract (bias, scale, ragged M, sums over batch elements, row sums of a
+// transposed A), with slices brought in by direct-to-LDS loads, ST - 1 of them ahead, 16x16x32 instructions and transposing LDS reads
+// (RowOperand, ColOperand of the large products).  k_gemm_mfma stages through registers one slice ahead and transposes there.  Before / after,
+// us, D 1024: one group, 1024 rows: dWo 22 / 10, d_o 16.5 / 9, dWv 24 / 13.5, w 17 / 14, output projection (the 128 x 128 ring it had)
+// 16.5 / 10; one group, 4096 rows: dWo 75 / 29, dWv 82 / 39, d_o 24 / 17; eight groups of 512 rows, D 2048, u Wv: 103 / 90.
+// Four wavefronts (WM x WN).  Products are taken as B^T A^T: a lane holds one row and four adjacent columns a block, trades with lane ^ 16
+// and stores 16 bytes.  ST: 4 stages while there is at most a tile to a compute unit, 2 otherwise (two or more blocks to a unit).
+// grid (ceil(N/BN), ceil(M/BM), batch), block 256, dynamic LDS ST (BM + BN) 128 bytes.
+// ---------------------------------------------------------------------------------------
+template <int BM, int BN, int WM, int WN, bool AT, bool BT, int ST>
+__global__ __launch_bounds__(256) void k_gemm_ring(GemmDesc d, const bf16* __restrict__ A, const bf16* __restrict__ Bm,
+                                                   const bf16* __restrict__ bias, bf16* __restrict__ C, bf16* __restrict__ rowsum) {
+  typedef std::conditional_t<AT, ColOperand<BM * 2>, RowOperand> OA;
+  typedef std::conditional_t<BT, ColOperand<BN * 2>, RowOperand> OB;
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16, AL = BM / 32, BL = BN / 32, STAGE = (BM + BN) * 128;
+  static_assert(WM * WN == 4 && TN % 2 == 0 && (BM == 64 || BM == 128) && (BN == 64 || BN == 128), "tile");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  int z = blockIdx.z;
+  const int a = z % d.na;
+  z /= d.na;
+  const int k = z % d.nk;
+  const int b0 = d.reduce_b ? 0 : z / d.nk;
+  const int nb = d.reduce_b ? d.nb : 1;
+  int M = d.M;
+  if (d.ragged == 1) {
+    const int left = d.ragged_total - k * d.ragged_nominal;
+    M = left < d.ragged_nominal ? left : d.ragged_nominal;
+  }
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  if (m0 >= M) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, lq = lane >> 4;
+  const int KT = d.K / 64, steps = nb * KT;
+
+  // Loads of an operand: R / 8 of 1 KiB, R / 32 to a wavefront.  Row r of the operand (T false): 8 rows a load; step of the slice
+  // (T true): 1024 / (2 R) steps a load.  off: byte of a lane's 16 behind the tile's origin, the same for every slice.
+  auto offsets = [&](auto op, bool T, int R, int r0, int ext, long srow, long sk, unsigned* off, int n) {
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const int ld = wave * n + i;
+      if (!T) {
+        const int row = ld * 8 + (lane >> 3);
+        off[i] = (unsigned)min(row, ext - 1 - r0) * (unsigned)srow * 2 + ((lane & 7) ^ swz_chunk(row)) * 16;
+      } else {
+        const int cpr = R / 8, row = ld * (64 / cpr) + lane / cpr;       // chunks a step, step of the slice
+        const int col = min(((lane % cpr) ^ decltype(op)::swz(row)) * 8, ext - 8 - r0);
+        off[i] = (unsigned)row * (unsigned)sk * 2 + col * 2;
+      }
+    }
+  };
+  struct NoSwz { static __device__ __forceinline__ int swz(int) { return 0; } };
+  typedef std::conditional_t<AT, ColOperand<BM * 2>, NoSwz> SA;
+  typedef std::conditional_t<BT, ColOperand<BN * 2>, NoSwz> SB;
+  unsigned a_off[AL], b_off[BL];
+  offsets(SA{}, AT, BM, m0, M, d.A.s0, d.A.s1, a_off, AL);
+  offsets(SB{}, BT, BN, n0, d.N, d.Bm.s1, d.Bm.s0, b_off, BL);
+  const bf16* Ab = A + d.A.sb * b0 + d.A.sk * k + d.A.sa * a + d.A.s0 * m0;
+  const bf16* Bb = Bm + d.Bm.sb * b0 + d.Bm.sk * k + d.Bm.sa * a + d.Bm.s1 * n0;
+  const bf16 *pa = Ab, *pb = Bb;
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem);
+  int ki = 0, is = 0;
+  auto issue = [&]() {
+    const unsigned dst = lds0 + is * STAGE;
+#pragma unroll
+    for (int i = 0; i < AL; ++i) load16_to_lds_at(pa, a_off[i], dst + (wave * AL + i) * 1024);
+#pragma unroll
+    for (int i = 0; i < BL; ++i) load16_to_lds_at(pb, b_off[i], dst + BM * 128 + (wave * BL + i) * 1024);
+    is = is == ST - 1 ? 0 : is + 1;
+    pa += AT ? d.A.s1 * 64 : 64;
+    pb += BT ? d.Bm.s0 * 64 : 64;
+    if (++ki == KT) {                                      // the next batch element of the sum
+      ki = 0;
+      Ab += d.A.sb;
+      Bb += d.Bm.sb;
+      pa = Ab;
+      pb = Bb;
+    }
+  };
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // row sums of A: wavefront column wn takes the blocks i = wn, wn + WN, .. of its rows, by products with ones
+  constexpr int RS = (TM + WN - 1) / WN;
+  f32x4 rs[RS];
+#pragma unroll
+  for (int i = 0; i < RS; ++i) rs[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool want_rs = AT && rowsum != nullptr && blockIdx.x == 0;
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.f;
+
+  const int a_ad = OA::base(wm * (BM / WM), lane), b_ad = BM * 128 + OB::base(wn * (BN / WN), lane);
+#pragma unroll
+  for (int s = 0; s < ST - 1; ++s)
+    if (s < steps) issue();
+  int sc = 0;
+  for (int s = 0; s < steps; ++s) {
+    // slice s has landed (this wavefront's share; the ST - 2 behind it may stay in flight), every wavefront is done with slice s - 1
+    const int behind = min(steps - 1 - s, ST - 2);         // uniform
+    if (behind >= 2) wait_vmcnt<2 * (AL + BL)>();
+    else if (behind == 1) wait_vmcnt<AL + BL>();
+    else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (s + ST - 1 < steps) issue();
+    const unsigned char* st = smem + sc * STAGE;
+    sc = sc == ST - 1 ? 0 : sc + 1;
+    bf16x8 af[2][TM], bfr[2][TN];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[kk][i] = OA::frag(st, a_ad, i, kk, 0);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bfr[kk][j] = OB::frag(st, b_ad, j, kk, 0);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+      if (want_rs) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          if (i % WN == wn) rs[i / WN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, af[kk][i], rs[i / WN], 0, 0, 0);
+      }
+    }
+  }
+  // block (i, j): row 16 i + l16, columns 16 j + 4 lq + e
+  if (want_rs && lq == 0) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int m = m0 + wm * (BM / WM) + i * 16 + l16;
+      if (i % WN == wn && m < M) rowsum[d.rs_sk * k + d.rs_sa * a + m] = (bf16)rs[i / WN][0];
+    }
+  }
+  bf16* Cb = C + d.C.sb * b0 + d.C.sk * k + d.C.sa * a;
+  const bf16* radd = static_cast<const bf16*>(d.rowadd);
+  const bf16* bs = bias ? bias + d.bias_sk * k + d.bias_sa * a : nullptr;
+#pragma unroll
+  for (int jj = 0; jj < TN / 2; ++jj) {
+    const int col = n0 + wn * (BN / WN) + jj * 32;
+    f32x4 bq[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bq[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const int c = col + 16 * j + 4 * lq;
+      if (bs && c < d.N) {
+        const bf16x4 v = *reinterpret_cast<const bf16x4*>(bs + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bq[j][e] = (float)v[e];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+      typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+      u32x2 w[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        f32x4 v = acc[i][2 * jj + j] * d.scale + bq[j];
+        const int mr = m0 + wm * (BM / WM) + i * 16 + l16, cr = col + 16 * j + 4 * lq;
+        if (radd && mr < M && cr < d.N) {
+          const bf16x4 ra = *reinterpret_cast<const bf16x4*>(radd + (size_t)mr * d.N + cr);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += (float)ra[e];
+        }
+        bf16x4 q;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[e] = (bf16)v[e];
+        w[j] = __builtin_bit_cast(u32x2, q);
+      }
+      // lane rows 0 and 2 (of 16) keep block 2 jj and take the next row's columns of it; rows 1 and 3 the same of block 2 jj + 1
+      const auto s0 = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
+      const auto s1 = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
+      const int m = m0 + wm * (BM / WM) + i * 16 + l16, c = col + (lq & 1) * 16 + (lq >> 1) * 8;
+      if (m < M && c < d.N) *reinterpret_cast<u32x4*>(Cb + d.C.s0 * m + c) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // The same products in single precision: 64 x 64 tiles on v_mfma_f32_32x32x2_f32 (fp32 operands and accumulation, twice
 // the rate of unpacked vector FMAs), contraction in slices of 32, four wavefronts (2 x 2) of 32 x 32.  Takes the whole
 // GemmDesc contract (ragged M or K, any strides with one unit stride per operand, any alignment) plus a row addend.
