@@ -1100,8 +1100,11 @@ inline int tokens_backward(int B, int Cin, int N, int D, int heads, int g, const
         if ((rc = launch_status())) return rc;
       }
     } else {
-      if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_dz_rpart_bf16), (int)lds)) return DCHAG_ERR_LAUNCH;
-      k_dz_rpart_bf16<<<grid, 256, lds, st>>>(Cin, N, D, heads, g, n_tiles, pt, alpha, ds, zin, w, Mb, dz, rpart);
+      const int hb = heads <= 8 ? 8 : 16, nt = std::min(256, (D / 4 + 63) / 64 * 64);
+      auto kern = heads <= 8 ? k_dz_rpart_bf16<8> : k_dz_rpart_bf16<16>;
+      if (ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)(lds / 16 * hb))) return DCHAG_ERR_LAUNCH;
+      kern<<<dim3((unsigned)(n_tiles * ((D / 4 + nt - 1) / nt)), G, B), nt, lds / 16 * hb, st>>>(Cin, N, D, heads, g, n_tiles, pt, alpha,
+                                                                                            ds, zin, w, Mb, dz, rpart);
       if ((rc = launch_status())) return rc;
     }
   }

@@ -2010,35 +2010,37 @@ __global__ __launch_bounds__(256) void k_dalpha_softmax_group(int Cin, int N, in
 // Gradient at the input tokens and the key-path sums, bf16, heads <= 16, D % 4 == 0:
 //   dz[b,c,n,:]   = sum_a alpha[b,c,n,a] * w[b,k,n,a,:] + ds[b,c,n,a] * M[k][a][:]
 //   rpart[b,k,t][a][:] = sum over the PT patches of tile t and the members c of  ds[b,c,n,a] * z[b,c,n,:]
-// grid (n_tiles * ceil(D/1024), G, B), n_tiles = ceil(N/PT), block 256: a thread owns 4 adjacent columns, keeps the 16 rows
+// grid (n_tiles * ceil(D / (4 NT)), G, B), n_tiles = ceil(N/PT), block NT = D / 4 to a multiple of 64, at most 256: a thread owns 4
+// adjacent columns, keeps the HB rows (heads to 8 or 16)
 // of M and (per patch) of w for them in registers, and walks the members.  The softmax weights and ds of
-// the whole tile of PT patches sit in LDS (dynamic, 2 * PT * g * 16 floats).  The partial sums are added up in a fixed
-// order by k_sum_partials.
+// the whole tile of PT patches sit in LDS (dynamic, 2 * PT * g * HB floats).  The partial sums are added up in a fixed
+// order by k_sum_partials.  (16 rows and 256 threads whatever the shape: 6 heads and D 384 used a seventh of the arithmetic.)
 // ---------------------------------------------------------------------------------------
+template <int HB>
 __global__ __launch_bounds__(256) void k_dz_rpart_bf16(int Cin, int N, int D, int heads, int g, int n_tiles, int PT,
                                                        const float* __restrict__ alpha, const float* __restrict__ ds,
                                                        const bf16* __restrict__ z, const bf16* __restrict__ w,
                                                        const bf16* __restrict__ Mb, bf16* __restrict__ dz,
                                                        float* __restrict__ rpart) {
-  extern __shared__ __attribute__((aligned(16))) float sm[];       // al[PT][g][16], then dsv[PT][g][16]
+  extern __shared__ __attribute__((aligned(16))) float sm[];       // al[PT][g][HB], then dsv[PT][g][HB]
   const int tile = blockIdx.x % n_tiles, cb = blockIdx.x / n_tiles;
   const int k = blockIdx.y, b = blockIdx.z, G = gridDim.y;
   const int c0 = k * g, gk = min(g, Cin - c0);
   const int n0 = tile * PT, np = min(PT, N - n0);
   float* al = sm;
-  float* dsv = sm + PT * g * 16;
-  for (int idx = threadIdx.x; idx < np * gk * 16; idx += 256) {
-    const int a = idx & 15, cl = (idx >> 4) % gk, pi = (idx >> 4) / gk;
+  float* dsv = sm + PT * g * HB;
+  for (int idx = threadIdx.x; idx < np * gk * HB; idx += blockDim.x) {
+    const int a = idx % HB, cl = (idx / HB) % gk, pi = (idx / HB) / gk;
     const size_t src = (((size_t)b * Cin + c0 + cl) * N + n0 + pi) * heads + a;
-    al[(pi * g + cl) * 16 + a] = a < heads ? alpha[src] : 0.f;
-    dsv[(pi * g + cl) * 16 + a] = a < heads ? ds[src] : 0.f;
+    al[(pi * g + cl) * HB + a] = a < heads ? alpha[src] : 0.f;
+    dsv[(pi * g + cl) * HB + a] = a < heads ? ds[src] : 0.f;
   }
   __syncthreads();
-  const int d0 = cb * 1024 + threadIdx.x * 4;
+  const int d0 = (cb * blockDim.x + threadIdx.x) * 4;
   if (d0 >= D) return;
-  float mr[16][4], racc[16][4];
+  float mr[HB][4], racc[HB][4];
 #pragma unroll
-  for (int a = 0; a < 16; ++a) {
+  for (int a = 0; a < HB; ++a) {
     bf16x4 mv = {};
     if (a < heads) mv = *reinterpret_cast<const bf16x4*>(Mb + ((size_t)k * heads + a) * D + d0);
 #pragma unroll
@@ -2050,10 +2052,10 @@ __global__ __launch_bounds__(256) void k_dz_rpart_bf16(int Cin, int N, int D, in
   const size_t cstride = (size_t)N * D;
   for (int pi = 0; pi < np; ++pi) {
     const int n = n0 + pi;
-    float wr[16][4];
+    float wr[HB][4];
     const bf16* wp = w + ((((size_t)b * G + k) * N + n) * heads) * D + d0;
 #pragma unroll
-    for (int a = 0; a < 16; ++a) {
+    for (int a = 0; a < HB; ++a) {
       bf16x4 wv = {};
       if (a < heads) wv = *reinterpret_cast<const bf16x4*>(wp + (size_t)a * D);
 #pragma unroll
@@ -2065,14 +2067,14 @@ __global__ __launch_bounds__(256) void k_dz_rpart_bf16(int Cin, int N, int D, in
     for (int cl = 0; cl < gk; ++cl) {
       const bf16x4 zv = znext;
       if (cl + 1 < gk) znext = *reinterpret_cast<const bf16x4*>(zp + (size_t)(cl + 1) * cstride);
-      const f32x4* ar = reinterpret_cast<const f32x4*>(al + (pi * g + cl) * 16);
-      const f32x4* dr = reinterpret_cast<const f32x4*>(dsv + (pi * g + cl) * 16);
+      const f32x4* ar = reinterpret_cast<const f32x4*>(al + (pi * g + cl) * HB);
+      const f32x4* dr = reinterpret_cast<const f32x4*>(dsv + (pi * g + cl) * HB);
       float acc[4] = {0.f, 0.f, 0.f, 0.f};
       float zf[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) zf[e] = (float)zv[e];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < HB / 4; ++q) {
         const f32x4 av = ar[q], dv = dr[q];
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -2090,7 +2092,7 @@ __global__ __launch_bounds__(256) void k_dz_rpart_bf16(int Cin, int N, int D, in
   }
   float* rp = rpart + ((((size_t)b * G + k) * n_tiles + tile) * heads) * D + d0;
 #pragma unroll
-  for (int a = 0; a < 16; ++a)
+  for (int a = 0; a < HB; ++a)
     if (a < heads) *reinterpret_cast<f32x4*>(rp + (size_t)a * D) = f32x4{racc[a][0], racc[a][1], racc[a][2], racc[a][3]};
 }
 
