@@ -1600,18 +1600,23 @@ __global__ __launch_bounds__(256, 2) void k_tokenize_mfma(int C, int H, int W, i
   const int l32 = lane & 31, lhi = lane >> 5;
   const bf16* img = x + ((size_t)b * C + c) * H * W;
 
-  // gather: 4 pixels (8 bytes) at a time; p % 4 == 0 keeps every piece inside one patch row
-  const int pieces = pp / 4;
-  for (int idx = tid; idx < 128 * pieces; idx += 256) {
-    const int t = idx / pieces, q = idx % pieces;
-    const int r = (q * 4) / p, s0 = (q * 4) % p;
-    const int n = n0 + t;
-    bf16x4 v = {};
-    if (n < N) {
-      const int pi = n / pw, pj = n % pw;
-      v = *reinterpret_cast<const bf16x4*>(img + (size_t)(pi * p + r) * W + pj * p + s0);
+  // gather: 4 pixels (8 bytes) at a time, eight pieces of a thread in flight; p % 4 == 0 keeps every piece inside one patch
+  // row.  (One piece after another, 32 round trips to memory for 16 x 16 patches: 39 us for 2 x 77 channels of 135, D 384.)
+  const int pieces = pp / 4, prow = p / 4;
+  for (int i0 = tid; i0 < 128 * pieces; i0 += 8 * 256) {
+    bf16x4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int idx = i0 + u * 256, t = idx / pieces, q = idx % pieces, n = n0 + t;
+      v[u] = bf16x4{};
+      if (idx < 128 * pieces && n < N)
+        v[u] = *reinterpret_cast<const bf16x4*>(img + (size_t)((n / pw) * p + q / prow) * W + (n % pw) * p + (q % prow) * 4);
     }
-    *reinterpret_cast<bf16x4*>(smem + t * rbp + q * 8) = v;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int idx = i0 + u * 256;
+      if (idx < 128 * pieces) *reinterpret_cast<bf16x4*>(smem + (idx / pieces) * rbp + (idx % pieces) * 8) = v[u];
+    }
   }
   __syncthreads();
 
