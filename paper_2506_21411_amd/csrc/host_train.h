@@ -1416,6 +1416,14 @@ inline int transpose_rows(int batch, int R, int RT, int Cc, const bf16* in, bf16
 template <class K>
 int raise_pair_lds(K kern) { return ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kPairLdsBytes); }
 
+// 8 x 8 patches whose count is whole slices (an even number of them a batch element, at least four), 32-bit offsets inside a group's
+// images, and tiles of either product for half of the compute units.
+inline bool linear_products_ok(int B, int G, int N, int g, int H, int W, int D) {
+  const long tiles = (long)((g + 3) / 4) * G;
+  return N % 128 == 0 && N >= 256 && W >= 16 && (long)g * H * W < (1L << 30) && (long)N * (W / 8) < (1L << 31) &&
+         tiles * (D / kGemmBN) * 2 >= compute_units() && tiles * ((N + kGemmBN - 1) / kGemmBN) * B * 2 >= compute_units();
+}
+
 template <int PP>
 int linear_tiles_backward(int B, int C, int H, int W, int D, const dchag_level* lv, const bf16* x, const bf16* We,
                           const bf16* be, const bf16* ce, const bf16* dy, bf16* dx, bf16* dWe, bf16* dtok_bias, bf16* dmix,
@@ -1426,6 +1434,37 @@ int linear_tiles_backward(int B, int C, int H, int W, int D, const dchag_level* 
   const int rows = std::min(d.g, C) * PP;
   auto at = [&](size_t off) { return reinterpret_cast<bf16*>(scratch + off); };
   int rc;
+  if (PP == 64 && linear_products_ok(B, d.G, d.N, std::min(d.g, C), H, W, D)) {
+    // both products on the large products' core: no transposed copies of dy and of the patches
+    ProductArgs pa{};
+    pa.A = x; pa.B = dy;
+    pa.a_sb = (long)C * H * W; pa.a_sk = (long)d.g * H * W;
+    pa.b_sb = (long)d.G * d.N * D; pa.b_sk = (long)d.N * D;
+    pa.lda = pa.ldb = D;
+    pa.kt = d.N / kGemmBK;
+    pa.segs = B;
+    pa.C_all = C; pa.g = d.g;
+    pa.H = H; pa.W = W; pa.pw = W / 8; pa.N = d.N;
+    pa.pw_magic = (unsigned)(((1ULL << 32) + pa.pw - 1) / pa.pw);
+    pa.We = We; pa.be = be; pa.ce = ce; pa.mix = static_cast<const bf16*>(lv->Wv);
+    pa.S = reinterpret_cast<const float*>(scratch + w.s);
+    pa.dWe = dWe; pa.dtok = dtok_bias; pa.dmix = dmix; pa.dbias = dbias;
+    pa.WsT = dx ? at(w.wst) : nullptr;
+    pa.tw = pixel_tiles(D / kGemmBN, (std::min(d.g, C) + 3) / 4, 1, d.G);
+    if ((rc = launch_product<kProductOuter>(pa, st)) || !dx) return rc;
+    ProductArgs pb{};
+    pb.A = at(w.wst); pb.B = dy; pb.C = dx;
+    pb.a_sk = (long)d.g * 64 * D;
+    pb.b_sb = pa.b_sb; pb.b_sk = pa.b_sk;
+    pb.lda = pb.ldb = D;
+    pb.rb = {d.G, C * 64, d.g * 64};
+    pb.kt = D / kGemmBK;
+    pb.segs = 1;
+    pb.C_all = C; pb.g = d.g;
+    pb.H = H; pb.W = W; pb.pw = pa.pw; pb.N = d.N; pb.pw_magic = pa.pw_magic;
+    pb.tw = pixel_tiles((d.N + kGemmBN - 1) / kGemmBN, (std::min(d.g, C) * 64 + kGemmBM - 1) / kGemmBM, B, d.G);
+    return launch_product<kProductImage>(pb, st);
+  }
   if ((rc = transpose_rows(B * d.G, d.N, d.NT, D, dy, at(w.dyt), st))) return rc;
   k_pixel_rows<P><<<dim3((unsigned)(d.NT / 64), (unsigned)((d.G * d.gq * (PP / 8) + 31) / 32), (unsigned)B), 256, 0, st>>>(
       d, x, at(w.ut), nullptr);

@@ -875,6 +875,12 @@ __global__ __launch_bounds__(256) void k_vagg_merge(long quads, int S, int G, in
 //   kProductWeights  C[k][i][j] = sum_{b,n} A[b,k,n,i] B[b,k,n,j], rowsum[k][i] = sum_{b,n} A[b,k,n,i]
 //                                                                                            its weight and bias gradients
 //   kProductFold     C[c][o][kk] = sum_d A[k][o][d] B[c][d][kk], 64 kk, k = c / g           value weights into the tokenizer's
+//   kProductImage    image[b][c][pixel kk of patch n] = sum_d A[c, kk][d] B[b,k,n][d]        pixel gradients of a linear first level
+//   kProductOuter    P[c, kk][d] = sum_{b,n} u[b,c,n,kk] B[b,k,n][d], u: the 8 x 8 patches of the image A, which leaves as the linear
+//                    first level's gradients (see k_linear_outer)
+// The last two have tile rows (member, pixel), a member to a wavefront and slot, and multiply in plain order: a lane holds one column
+// and four adjacent pixels a block.  Outer reads its patches straight from the image, 16 bytes a lane (the eight pixel rows of two
+// members are the 16 chunks of a slot's row).
 // Rows of A of a group may be ragged (Linear, Back: loads clamped, stores masked); every other extent is a multiple of 256,
 // of 64 kt slices of the contraction kt is even and at least 4, and every row is 16-byte aligned (host).  An operand whose
 // contraction index is its row index is read by the transposing LDS reads (ColOperand): no transposed copy, no 2-byte reads.
@@ -885,7 +891,7 @@ __global__ __launch_bounds__(256) void k_vagg_merge(long quads, int S, int G, in
 // 16 slices 70 -> 40.  Fold, eight 2-byte LDS reads a fragment before: 512 channels, D 1024 81 -> 65, 1000 channels, D 2048 550 -> 446.
 // Dynamic LDS: the ring (128 KiB).
 // ---------------------------------------------------------------------------------------------
-enum ProductKind { kProductLinear, kProductBack, kProductWeights, kProductFold };
+enum ProductKind { kProductLinear, kProductBack, kProductWeights, kProductFold, kProductImage, kProductOuter };
 struct ProductArgs {
   const bf16 *A, *B, *bias, *rowadd;
   bf16 *C, *rowsum;
@@ -893,16 +899,127 @@ struct ProductArgs {
   int lda, ldb, ldc, ldbias;                             // row strides; elements of bias / rowsum a group
   RowBlocks rb;                                          // Linear, Back: rows of a group
   int kt, segs;                                          // slices of a segment of the contraction, and segments (batch elements)
-  int C_all, g;                                          // Fold: channels, channels of a group
+  int C_all, g;                                          // Fold, Image, Outer: channels, channels of a group
+  int H, W, pw, N;                                       // Image, Outer: image, patches of a row and in all
+  unsigned pw_magic;                                     // ceil(2^32 / pw): n / pw is the upper half of n * pw_magic
+  const bf16 *We, *be, *ce, *mix;                        // Outer: the operands and results of its epilogue
+  const float* S;
+  bf16 *dWe, *dtok, *dmix, *dbias, *WsT;
   TileWork tw;
   int slots;                                             // workgroups an XCD
 };
 
+// Four adjacent rows of a column (a register quad of an accumulator block: lane = column) as two packed words.
+struct Quad { unsigned w[2]; };
+__device__ __forceinline__ Quad pack_quad(const bf16x4& v) { return __builtin_bit_cast(Quad, v); }
+
+// A quad of rows x four adjacent columns (four adjacent lanes) transposed: lane l of the four holds row l, columns 0 .. 3, so that
+// a row leaves in 8-byte pieces instead of 2-byte ones.
+__device__ __forceinline__ bf16x4 transpose_quad(const bf16x4& v, int lane) {
+  const Quad q = pack_quad(v);
+  const bool b1 = lane & 2, b0 = lane & 1;
+  const unsigned send = b1 ? q.w[0] : q.w[1];
+  const unsigned recv = (unsigned)__builtin_amdgcn_update_dpp(0, (int)send, kDppSwapHalves, 0xF, 0xF, true);
+  const unsigned x = b1 ? recv : q.w[0], y = b1 ? q.w[1] : recv;      // this lane's two rows of column l & 1, and of that + 2
+  const unsigned xp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, kDppSwapPairs, 0xF, 0xF, true);
+  const unsigned yp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)y, kDppSwapPairs, 0xF, 0xF, true);
+  Quad o;
+  o.w[0] = b0 ? (xp >> 16) | (x & 0xFFFF0000u) : (x & 0xFFFFu) | (xp << 16);
+  o.w[1] = b0 ? (yp >> 16) | (y & 0xFFFF0000u) : (y & 0xFFFFu) | (yp << 16);
+  return __builtin_bit_cast(bf16x4, o);
+}
+
+// The tile of Image or Outer: block (h, i, hb, j), lane (l16, lq), register e: member 4 mt + 2 h + wm of the group, pixel 16 i + 4 lq + e,
+// column 256 nt + 128 hb + 32 wn + 16 j + l16.  Blocks 2 q and 2 q + 1 trade with lane ^ 16: lane row lq then holds the eight
+// pixels from 16 (2 q + lq % 2) + 8 (lq / 2) on, one row of the patch.
+template <bool OUTER>
+__device__ __forceinline__ void store_pixels(const ProductArgs& p, const CoreAcc& acc, const CoreLane& L, int k, int b, int mt,
+                                             int nt) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  const int lane = lane_id(), l16 = lane & 15, lq = lane >> 4;
+  const int c0 = k * p.g, gk = min(p.g, p.C_all - c0);
+  auto join = [](const bf16x4& x, const bf16x4& y) {
+    const u32x2 a = __builtin_bit_cast(u32x2, x), c = __builtin_bit_cast(u32x2, y);
+    const auto s0 = __builtin_amdgcn_permlane16_swap(a[0], c[0], false, false);
+    const auto s1 = __builtin_amdgcn_permlane16_swap(a[1], c[1], false, false);
+    return u32x4{s0[0], s1[0], s0[1], s1[1]};
+  };
+#pragma unroll
+  for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = nt * kGemmBN + hb * 128 + L.wn * 32 + j * 16 + l16;
+      const int pi = OUTER ? 0 : __umulhi(col, p.pw_magic);
+      float sv = 0.f;
+      if (OUTER) {
+        sv = p.S[(size_t)k * p.ldb + col];
+        if (p.dbias && mt == 0 && L.wm == 0 && lq == 0) p.dbias[(size_t)k * p.ldb + col] = (bf16)sv;
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int cl = mt * 4 + 2 * h + L.wm;
+        if (cl >= gk) continue;                            // uniform
+        const size_t cd = (size_t)(c0 + cl) * p.ldb + col;
+        const float sm = OUTER ? (float)p.mix[cd] : 0.f;
+        float dot = 0.f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          if (!OUTER) {
+            bf16x4 v[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[t][e] = (bf16)acc[h][2 * q + t][hb][j][e];
+            const u32x4 o = join(v[0], v[1]);
+            const int row = 2 * (2 * q + (lq & 1)) + (lq >> 1);
+            if (col < p.N)
+              *reinterpret_cast<u32x4*>(p.C + (((size_t)b * p.C_all + c0 + cl) * p.H + pi * 8 + row) * p.W + (col - pi * p.pw) * 8) = o;
+            continue;
+          }
+          const size_t at = cd * 64 + (2 * q + (lq & 1)) * 16 + (lq >> 1) * 8;
+          const u32x4 w8 = *reinterpret_cast<const u32x4*>(p.We + at);
+          const auto s0 = __builtin_amdgcn_permlane16_swap(w8[0], w8[2], false, false);   // the trade is its own inverse
+          const auto s1 = __builtin_amdgcn_permlane16_swap(w8[1], w8[3], false, false);
+          const bf16x4 w[2] = {__builtin_bit_cast(bf16x4, u32x2{s0[0], s1[0]}), __builtin_bit_cast(bf16x4, u32x2{s0[1], s1[1]})};
+          bf16x4 gw[2];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            bf16x4 ws;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float pv = acc[h][2 * q + t][hb][j][e];
+              dot += (float)w[t][e] * pv;
+              gw[t][e] = (bf16)(sm * pv);
+              ws[e] = (bf16)((float)w[t][e] * sm);
+            }
+            if (p.WsT)
+              *reinterpret_cast<bf16x4*>(p.WsT + ((size_t)(c0 + cl) * 64 + 16 * (2 * q + t) + 4 * lq + (lane & 3)) * p.ldb +
+                                         (col & ~3)) = transpose_quad(ws, lane);
+          }
+          if (p.dWe) *reinterpret_cast<u32x4*>(p.dWe + at) = join(gw[0], gw[1]);
+        }
+        if (OUTER) {
+          dot += __shfl_xor(dot, 16, kWave);
+          dot += __shfl_xor(dot, 32, kWave);
+          if (lq == 0) {
+            float bias = 0.f;
+            if (p.be) bias += (float)p.be[cd];
+            if (p.ce) bias += (float)p.ce[cd];
+            if (p.dmix) p.dmix[cd] = (bf16)(dot + bias * sv);
+            if (p.dtok) p.dtok[cd] = (bf16)(sm * sv);
+          }
+        }
+      }
+    }
+}
+
 template <int KIND>
 __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
-  constexpr bool A_COL = KIND == kProductWeights, FOLD = KIND == kProductFold;
+  constexpr bool FOLD = KIND == kProductFold, IMAGE = KIND == kProductImage, OUTER = KIND == kProductOuter;
+  constexpr bool A_COL = KIND == kProductWeights || OUTER, SWAP = !IMAGE && !OUTER;
   typedef std::conditional_t<A_COL, ColOperand<256>, RowOperand> OA;
-  typedef std::conditional_t<FOLD, ColOperand<128>, std::conditional_t<KIND == kProductLinear, RowOperand, ColOperand<256>>> OB;
+  typedef std::conditional_t<FOLD, ColOperand<128>, std::conditional_t<KIND == kProductLinear || IMAGE, RowOperand, ColOperand<256>>> OB;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
   const int per = (p.tw.total + kXcds - 1) / kXcds;
@@ -915,7 +1032,7 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
       const int w = xcd * per + t * p.slots + slot;
       if (w >= xcd_end) return false;
       p.tw.decode_linear(w, it.k, it.b, it.mt, it.nt);
-      if (FOLD ? it.nt * 4 < min(p.g, p.C_all - it.k * p.g) : A_COL || it.mt * kGemmBM < p.rb.rows_of(it.k)) return true;
+      if (FOLD || OUTER ? (FOLD ? it.nt : it.mt) * 4 < min(p.g, p.C_all - it.k * p.g) : A_COL || it.mt * kGemmBM < p.rb.rows_of(it.k)) return true;
     }
   };
 
@@ -928,11 +1045,24 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
   if (!item_of(t, ic)) return;                           // uniform: the whole workgroup has nothing to do
   struct Src {
     const bf16 *a, *b0, *b1;                             // origins of a segment's tile in its running slice (b1: slot B1)
-    int rows;                                            // rows of A behind the tile's first
+    int rows;                                            // rows of A behind the tile's first (Outer: members of the group)
+    int first;                                           // Outer: the tile's first member
+    const bf16* a1;                                      // Image: a and a1 are this wavefront's 16 rows of slots A0 and A1
   } run, nxt;
   auto source = [&](const Item& it, int seg, Src& s) {
     s.a = p.A + seg * p.a_sb + it.b * p.a_sb + it.k * p.a_sk;
-    if (A_COL) s.a += it.mt * kGemmBM + (size_t)L.wave * 8 * p.lda;
+    if (OUTER) {
+      s.first = it.mt * 4;
+      s.rows = min(p.g, p.C_all - it.k * p.g);
+      s.b0 = p.B + seg * p.b_sb + it.k * p.b_sk + it.nt * kGemmBN + (size_t)L.wave * 8 * p.ldb;
+      s.b1 = s.b0 + 128;
+      return;
+    }
+    if (IMAGE) {                                         // a slot is two members, of which the last of the group repeats
+      const int last = min(p.g, p.C_all - it.k * p.g) - 1, m = it.mt * 4 + (L.wave >> 2);
+      s.a1 = s.a + ((size_t)min(m + 2, last) * 64 + (L.wave & 3) * 16) * p.lda;
+      s.a += ((size_t)min(m, last) * 64 + (L.wave & 3) * 16) * p.lda;
+    } else if (A_COL) s.a += it.mt * kGemmBM + (size_t)L.wave * 8 * p.lda;
     else s.a += (size_t)it.mt * kGemmBM * p.lda;
     s.rows = FOLD || A_COL ? 256 : p.rb.rows_of(it.k) - it.mt * kGemmBM;
     if (FOLD) {
@@ -941,8 +1071,12 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
       s.b0 = p.B + (c0 + min(q, last)) * p.b_sk + in;    // a missing channel of the four repeats the last one; not stored
       s.b1 = p.B + (c0 + min(q + 2, last)) * p.b_sk + in;
     } else {
-      s.b0 = p.B + seg * p.b_sb + it.k * p.b_sk;
-      if (KIND == kProductLinear) s.b0 += ((size_t)it.nt * kGemmBN + L.wave * 16) * p.ldb;
+      s.b0 = p.B + seg * p.b_sb + it.b * p.b_sb + it.k * p.b_sk;
+      if (IMAGE) {
+        s.b0 += ((size_t)it.nt * kGemmBN + L.wave * 16) * p.ldb;
+        s.b1 = s.b0 + (it.nt * kGemmBN + 128 < p.N ? (size_t)128 * p.ldb : 0);   // half a tile of patches: the half again
+        return;
+      } else if (KIND == kProductLinear) s.b0 += ((size_t)it.nt * kGemmBN + L.wave * 16) * p.ldb;
       else s.b0 += it.nt * kGemmBN + (size_t)L.wave * 8 * p.ldb;
       s.b1 = s.b0 + (KIND == kProductLinear ? (size_t)128 * p.ldb : 128);
     }
@@ -953,25 +1087,33 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
     const int lane = lane_id(), row = L.wave * 8 + (lane >> 4);
     return (lane >> 4) * ld * 2 + ((lane & 15) ^ ColOperand<256>::swz(row)) * 16;
   };
+  // Outer: the part of a chunk's place in the image that its patch does not change, per slot: member and pixel row.
   unsigned a_off[2][2];
-  auto a_rows = [&](int rows) {
+  auto a_rows = [&](const Src& s) {
     const int lane = lane_id();
-    if (A_COL) {
+    if (OUTER) {
+      const int lc = (lane & 15) ^ ColOperand<256>::swz(L.wave * 8 + (lane >> 4));
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        a_off[h][0] = (unsigned)(min(s.first + 2 * h + (lc >> 3), s.rows - 1) * p.H + (lc & 7)) * p.W * 2;
+    } else if (A_COL) {
       a_off[0][0] = col_off(p.lda);
-    } else {
+    } else if (!IMAGE) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-          a_off[h][u] = (unsigned)min(h * 128 + L.wave * 16 + u * 8 + (lane >> 3), rows - 1) * p.lda * 2 + L.ld_chunk(lane, u);
+        for (int u = 0; u < 2; ++u) {
+          const int row = h * 128 + L.wave * 16 + u * 8 + (lane >> 3);
+          a_off[h][u] = (unsigned)min(row, s.rows - 1) * p.lda * 2 + L.ld_chunk(lane, u);
+        }
     }
   };
   int b_off;
   if (FOLD) b_off = (lane_id() >> 3) * 128 + ((lane_id() & 7) ^ ColOperand<128>::swz(lane_id() >> 3)) * 16;
-  else if (KIND == kProductLinear) b_off = (lane_id() >> 3) * p.ldb * 2 + L.ld_chunk(lane_id(), 0);
+  else if (KIND == kProductLinear || IMAGE) b_off = (lane_id() >> 3) * p.ldb * 2 + L.ld_chunk(lane_id(), 0);
   else b_off = col_off(p.ldb);
   source(ic, 0, run);
-  a_rows(run.rows);
+  a_rows(run);
   int ki = 0;                                            // slices issued of the segment
   auto issue = [&](int sl) {                             // sl: a constant once inlined
     const unsigned dst = wave_off + sl * kSlotBytes;
@@ -980,18 +1122,23 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
     for (int u = 0; u < 2; ++u) {
       if (kind == kSlotA0 || kind == kSlotA1) {
         const int h = kind == kSlotA1;
-        if (A_COL) load16_to_lds_at(run.a + h * 128 + (size_t)u * 4 * p.lda, a_off[0][0], dst + u * 1024);
+        if (OUTER) {
+          const int n = (ki + ((sl & 2) >> 1)) * 64 + L.wave * 8 + u * 4 + (lane_id() >> 4), pi = __umulhi(n, p.pw_magic);
+          load16_to_lds_at(run.a, a_off[h][0] + (unsigned)(pi * p.W + n - pi * p.pw) * 16, dst + u * 1024);
+        } else if (IMAGE) load16_to_lds_at((h ? run.a1 : run.a) + (size_t)u * 8 * p.lda, opaque(b_off) ^ (u * 64), dst + u * 1024);
+        else if (A_COL) load16_to_lds_at(run.a + h * 128 + (size_t)u * 4 * p.lda, a_off[0][0], dst + u * 1024);
         else load16_to_lds_at(run.a, a_off[h][u], dst + u * 1024);
       } else {
         const bf16* s = kind == kSlotB1 ? run.b1 : run.b0;
         if (FOLD) load16_to_lds_at(s + u * 8 * 64, opaque(b_off) ^ (u * 64), dst + u * 1024);
-        else if (KIND == kProductLinear) load16_to_lds_at(s + (size_t)u * 8 * p.ldb, opaque(b_off) ^ (u * 64), dst + u * 1024);
+        else if (KIND == kProductLinear || IMAGE) load16_to_lds_at(s + (size_t)u * 8 * p.ldb, opaque(b_off) ^ (u * 64), dst + u * 1024);
         else load16_to_lds_at(s + (size_t)u * 4 * p.ldb, b_off, dst + u * 1024);
       }
     }
     if (kind == kSlotA1) {                               // the last slot of a slice
-      run.a += A_COL ? (size_t)64 * p.lda : 64;
-      const size_t bs = FOLD ? 64 * 64 : KIND == kProductLinear ? 64 : (size_t)64 * p.ldb;
+      if (!OUTER) run.a += A_COL ? (size_t)64 * p.lda : 64;
+      if (IMAGE) run.a1 += 64;
+      const size_t bs = FOLD ? 64 * 64 : KIND == kProductLinear || IMAGE ? 64 : (size_t)64 * p.ldb;
       run.b0 += bs;
       run.b1 += bs;
       if (sl & 2) {
@@ -999,7 +1146,7 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
         if (ki == p.kt) {
           ki = 0;
           run = nxt;
-          a_rows(run.rows);
+          a_rows(run);
         }
       }
     }
@@ -1011,7 +1158,7 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
   f32x4 rs[2];
   bool sums = false;
   auto held = [&](int h, const bf16x8 (&a)[4][2]) {
-    if (A_COL && sums) {
+    if (KIND == kProductWeights && sums) {
       bf16x8 ones;
 #pragma unroll
       for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.f;
@@ -1038,27 +1185,34 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
     source(nx, nseg, nxt);
     int kt = 0;
     if (seg == 0) {
-      if (A_COL) {
+      if (KIND == kProductWeights) {
         sums = p.rowsum && ic.nt == 0;
         rs[0] = rs[1] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      core_slice<true, true, 0, OA, OB>(acc, f, smem, L, issue, held);
-      core_slice<false, true, 1, OA, OB>(acc, f, smem, L, issue, held);
+      core_slice<true, SWAP, 0, OA, OB>(acc, f, smem, L, issue, held);
+      core_slice<false, SWAP, 1, OA, OB>(acc, f, smem, L, issue, held);
       kt = 2;
     }
     for (; kt < p.kt; kt += 2) {
-      core_slice<false, true, 0, OA, OB>(acc, f, smem, L, issue, held);
-      core_slice<false, true, 1, OA, OB>(acc, f, smem, L, issue, held);
+      core_slice<false, SWAP, 0, OA, OB>(acc, f, smem, L, issue, held);
+      core_slice<false, SWAP, 1, OA, OB>(acc, f, smem, L, issue, held);
     }
     if (nseg != 0) {
       seg = nseg;
+      continue;
+    }
+    if constexpr (!SWAP) {
+      store_pixels<OUTER>(p, acc, L, ic.k, ic.b, ic.mt, ic.nt);
+      if (!more) break;
+      ic = nx;
+      seg = 0;
       continue;
     }
     // block (h, i, hb, j), lane (l16, lq), register e: row 128 h + 64 wm + 16 i + l16, column 128 hb + 32 wn + 16 j + 4 lq + e
     const int l16 = lane_id() & 15, lq = lane_id() >> 4;
     const int o0 = ic.nt * kGemmBN, r0 = ic.mt * kGemmBM;
     const int rows = FOLD || A_COL ? 256 : p.rb.rows_of(ic.k) - r0;
-    if (A_COL && sums && lq == 0) {
+    if (KIND == kProductWeights && sums && lq == 0) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
         p.rowsum[(size_t)ic.k * p.ldbias + r0 + h * 128 + L.wm * 64 + L.wn * 16 + l16] = (bf16)rs[h][0];

@@ -46,3 +46,14 @@ def test_projection_of_ragged_rows(biases):
         err = rel_err(y.reshape(cfg.N, cfg.D)[rows], want)
         say(f"  {name} {err:.3e}")
         assert err < TOL["bf16"], (name, err)
+
+
+@pytest.mark.parametrize("biases", [True, False])
+def test_linear_first_level_on_large_tiles(biases, monkeypatch):
+    """Tiles of four members: groups of five (one and a quarter), the last of three; 384 patches (one and a half tiles, two segments of
+    six slices), 16 patches a row of the image."""
+    monkeypatch.setenv("DCHAG_LINEAR_ROUTE", "tiles")
+    cfg = ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=68, B=2, C=163, H=192, W=128, p=8, D=512, heads=8,
+                   group_sizes=(5, 33), level_kinds=("linear", "attention"))
+    say(f"large products, linear first level {cfg}")
+    check_training_step(cfg, biases=biases)
