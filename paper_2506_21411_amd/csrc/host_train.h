@@ -1449,7 +1449,7 @@ int linear_tiles_backward(int B, int C, int H, int W, int D, const dchag_level* 
     pa.We = We; pa.be = be; pa.ce = ce; pa.mix = static_cast<const bf16*>(lv->Wv);
     pa.S = reinterpret_cast<const float*>(scratch + w.s);
     pa.dWe = dWe; pa.dtok = dtok_bias; pa.dmix = dmix; pa.dbias = dbias;
-    pa.WsT = dx ? at(w.wst) : nullptr;
+    pa.Ws = dx ? at(w.wst) : nullptr;
     pa.tw = pixel_tiles(D / kGemmBN, (std::min(d.g, C) + 3) / 4, 1, d.G);
     if ((rc = launch_product<kProductOuter>(pa, st)) || !dx) return rc;
     ProductArgs pb{};

@@ -875,9 +875,11 @@ __global__ __launch_bounds__(256) void k_vagg_merge(long quads, int S, int G, in
 //   kProductWeights  C[k][i][j] = sum_{b,n} A[b,k,n,i] B[b,k,n,j], rowsum[k][i] = sum_{b,n} A[b,k,n,i]
 //                                                                                            its weight and bias gradients
 //   kProductFold     C[c][o][kk] = sum_d A[k][o][d] B[c][d][kk], 64 kk, k = c / g           value weights into the tokenizer's
-//   kProductImage    image[b][c][pixel kk of patch n] = sum_d A[c, kk][d] B[b,k,n][d]        pixel gradients of a linear first level
+//   kProductImage    image[b][c][pixel kk of patch n] = sum_d A[c][d][kk] B[b,k,n][d]        pixel gradients of a linear first level
 //   kProductOuter    P[c, kk][d] = sum_{b,n} u[b,c,n,kk] B[b,k,n][d], u: the 8 x 8 patches of the image A, which leaves as the linear
 //                    first level's gradients (see k_linear_outer)
+// us, 512 bands, 4 x 256 patches, D 1024, 128 x 256 tiles of pair_loop before: Outer 129 and 37 for the copies it read / 125 (70 without
+// its epilogue, which moves 200 MB), Image 88 / 63.
 // The last two have tile rows (member, pixel), a member to a wavefront and slot, and multiply in plain order: a lane holds one column
 // and four adjacent pixels a block.  Outer reads its patches straight from the image, 16 bytes a lane (the eight pixel rows of two
 // members are the 16 chunks of a slot's row).
@@ -904,30 +906,10 @@ struct ProductArgs {
   unsigned pw_magic;                                     // ceil(2^32 / pw): n / pw is the upper half of n * pw_magic
   const bf16 *We, *be, *ce, *mix;                        // Outer: the operands and results of its epilogue
   const float* S;
-  bf16 *dWe, *dtok, *dmix, *dbias, *WsT;
+  bf16 *dWe, *dtok, *dmix, *dbias, *Ws;
   TileWork tw;
   int slots;                                             // workgroups an XCD
 };
-
-// Four adjacent rows of a column (a register quad of an accumulator block: lane = column) as two packed words.
-struct Quad { unsigned w[2]; };
-__device__ __forceinline__ Quad pack_quad(const bf16x4& v) { return __builtin_bit_cast(Quad, v); }
-
-// A quad of rows x four adjacent columns (four adjacent lanes) transposed: lane l of the four holds row l, columns 0 .. 3, so that
-// a row leaves in 8-byte pieces instead of 2-byte ones.
-__device__ __forceinline__ bf16x4 transpose_quad(const bf16x4& v, int lane) {
-  const Quad q = pack_quad(v);
-  const bool b1 = lane & 2, b0 = lane & 1;
-  const unsigned send = b1 ? q.w[0] : q.w[1];
-  const unsigned recv = (unsigned)__builtin_amdgcn_update_dpp(0, (int)send, kDppSwapHalves, 0xF, 0xF, true);
-  const unsigned x = b1 ? recv : q.w[0], y = b1 ? q.w[1] : recv;      // this lane's two rows of column l & 1, and of that + 2
-  const unsigned xp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, kDppSwapPairs, 0xF, 0xF, true);
-  const unsigned yp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)y, kDppSwapPairs, 0xF, 0xF, true);
-  Quad o;
-  o.w[0] = b0 ? (xp >> 16) | (x & 0xFFFF0000u) : (x & 0xFFFFu) | (xp << 16);
-  o.w[1] = b0 ? (yp >> 16) | (y & 0xFFFF0000u) : (y & 0xFFFFu) | (yp << 16);
-  return __builtin_bit_cast(bf16x4, o);
-}
 
 // The tile of Image or Outer: block (h, i, hb, j), lane (l16, lq), register e: member 4 mt + 2 h + wm of the group, pixel 16 i + 4 lq + e,
 // column 256 nt + 128 hb + 32 wn + 16 j + l16.  Blocks 2 q and 2 q + 1 trade with lane ^ 16: lane row lq then holds the eight
@@ -946,26 +928,18 @@ __device__ __forceinline__ void store_pixels(const ProductArgs& p, const CoreAcc
     return u32x4{s0[0], s1[0], s0[1], s1[1]};
   };
 #pragma unroll
-  for (int hb = 0; hb < 2; ++hb)
+  for (int hb = 0; hb < 2; ++hb) {
+    const int col0 = nt * kGemmBN + hb * 128 + L.wn * 32 + l16;
+    if constexpr (!OUTER) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = nt * kGemmBN + hb * 128 + L.wn * 32 + j * 16 + l16;
-      const int pi = OUTER ? 0 : __umulhi(col, p.pw_magic);
-      float sv = 0.f;
-      if (OUTER) {
-        sv = p.S[(size_t)k * p.ldb + col];
-        if (p.dbias && mt == 0 && L.wm == 0 && lq == 0) p.dbias[(size_t)k * p.ldb + col] = (bf16)sv;
-      }
+      for (int j = 0; j < 2; ++j) {
+        const int n = col0 + j * 16, pi = __umulhi(n, p.pw_magic);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int cl = mt * 4 + 2 * h + L.wm;
-        if (cl >= gk) continue;                            // uniform
-        const size_t cd = (size_t)(c0 + cl) * p.ldb + col;
-        const float sm = OUTER ? (float)p.mix[cd] : 0.f;
-        float dot = 0.f;
+        for (int h = 0; h < 2; ++h) {
+          const int cl = mt * 4 + 2 * h + L.wm;
+          if (cl >= gk) continue;                          // uniform
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          if (!OUTER) {
+          for (int q = 0; q < 2; ++q) {
             bf16x4 v[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t)
@@ -973,52 +947,72 @@ __device__ __forceinline__ void store_pixels(const ProductArgs& p, const CoreAcc
               for (int e = 0; e < 4; ++e) v[t][e] = (bf16)acc[h][2 * q + t][hb][j][e];
             const u32x4 o = join(v[0], v[1]);
             const int row = 2 * (2 * q + (lq & 1)) + (lq >> 1);
-            if (col < p.N)
-              *reinterpret_cast<u32x4*>(p.C + (((size_t)b * p.C_all + c0 + cl) * p.H + pi * 8 + row) * p.W + (col - pi * p.pw) * 8) = o;
-            continue;
+            if (n < p.N)
+              *reinterpret_cast<u32x4*>(p.C + (((size_t)b * p.C_all + c0 + cl) * p.H + pi * 8 + row) * p.W + (n - pi * p.pw) * 8) = o;
           }
-          const size_t at = cd * 64 + (2 * q + (lq & 1)) * 16 + (lq >> 1) * 8;
-          const u32x4 w8 = *reinterpret_cast<const u32x4*>(p.We + at);
-          const auto s0 = __builtin_amdgcn_permlane16_swap(w8[0], w8[2], false, false);   // the trade is its own inverse
-          const auto s1 = __builtin_amdgcn_permlane16_swap(w8[1], w8[3], false, false);
-          const bf16x4 w[2] = {__builtin_bit_cast(bf16x4, u32x2{s0[0], s1[0]}), __builtin_bit_cast(bf16x4, u32x2{s0[1], s1[1]})};
-          bf16x4 gw[2];
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            bf16x4 ws;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float pv = acc[h][2 * q + t][hb][j][e];
-              dot += (float)w[t][e] * pv;
-              gw[t][e] = (bf16)(sm * pv);
-              ws[e] = (bf16)((float)w[t][e] * sm);
-            }
-            if (p.WsT)
-              *reinterpret_cast<bf16x4*>(p.WsT + ((size_t)(c0 + cl) * 64 + 16 * (2 * q + t) + 4 * lq + (lane & 3)) * p.ldb +
-                                         (col & ~3)) = transpose_quad(ws, lane);
-          }
-          if (p.dWe) *reinterpret_cast<u32x4*>(p.dWe + at) = join(gw[0], gw[1]);
         }
-        if (OUTER) {
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        // what a block of columns reads, asked for before its first store: one load at a time cost a round trip each
+        const int col = col0 + j * 16;
+        const float sv = p.S[(size_t)k * p.ldb + col];
+        u32x4 w8[2][2];
+        float sm[2], bias[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const size_t cd = (size_t)(c0 + min(mt * 4 + 2 * h + L.wm, gk - 1)) * p.ldb + col;
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            w8[h][q] = *reinterpret_cast<const u32x4*>(p.We + cd * 64 + (2 * q + (lq & 1)) * 16 + (lq >> 1) * 8);
+          sm[h] = (float)p.mix[cd];
+          bias[h] = (p.be ? (float)p.be[cd] : 0.f) + (p.ce ? (float)p.ce[cd] : 0.f);
+        }
+        if (p.dbias && mt == 0 && L.wm == 0 && lq == 0) p.dbias[(size_t)k * p.ldb + col] = (bf16)sv;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int cl = mt * 4 + 2 * h + L.wm;
+          if (cl >= gk) continue;                          // uniform
+          const size_t cd = (size_t)(c0 + cl) * p.ldb + col;
+          float dot = 0.f;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const u32x4 v8 = w8[h][q];
+            const auto s0 = __builtin_amdgcn_permlane16_swap(v8[0], v8[2], false, false);   // the trade is its own inverse
+            const auto s1 = __builtin_amdgcn_permlane16_swap(v8[1], v8[3], false, false);
+            const bf16x4 w[2] = {__builtin_bit_cast(bf16x4, u32x2{s0[0], s1[0]}), __builtin_bit_cast(bf16x4, u32x2{s0[1], s1[1]})};
+            bf16x4 gw[2], ws[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float pv = acc[h][2 * q + t][hb][j][e];
+                dot += (float)w[t][e] * pv;
+                gw[t][e] = (bf16)(sm[h] * pv);
+                ws[t][e] = (bf16)((float)w[t][e] * sm[h]);
+              }
+            const size_t at = cd * 64 + (2 * q + (lq & 1)) * 16 + (lq >> 1) * 8;
+            if (p.Ws) *reinterpret_cast<u32x4*>(p.Ws + at) = join(ws[0], ws[1]);
+            if (p.dWe) *reinterpret_cast<u32x4*>(p.dWe + at) = join(gw[0], gw[1]);
+          }
           dot += __shfl_xor(dot, 16, kWave);
           dot += __shfl_xor(dot, 32, kWave);
           if (lq == 0) {
-            float bias = 0.f;
-            if (p.be) bias += (float)p.be[cd];
-            if (p.ce) bias += (float)p.ce[cd];
-            if (p.dmix) p.dmix[cd] = (bf16)(dot + bias * sv);
-            if (p.dtok) p.dtok[cd] = (bf16)(sm * sv);
+            if (p.dmix) p.dmix[cd] = (bf16)(dot + bias[h] * sv);
+            if (p.dtok) p.dtok[cd] = (bf16)(sm[h] * sv);
           }
         }
       }
     }
+  }
 }
 
 template <int KIND>
 __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
   constexpr bool FOLD = KIND == kProductFold, IMAGE = KIND == kProductImage, OUTER = KIND == kProductOuter;
   constexpr bool A_COL = KIND == kProductWeights || OUTER, SWAP = !IMAGE && !OUTER;
-  typedef std::conditional_t<A_COL, ColOperand<256>, RowOperand> OA;
+  typedef std::conditional_t<A_COL, ColOperand<256>, std::conditional_t<IMAGE, ColOperand<128>, RowOperand>> OA;
   typedef std::conditional_t<FOLD, ColOperand<128>, std::conditional_t<KIND == kProductLinear || IMAGE, RowOperand, ColOperand<256>>> OB;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
@@ -1047,7 +1041,7 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
     const bf16 *a, *b0, *b1;                             // origins of a segment's tile in its running slice (b1: slot B1)
     int rows;                                            // rows of A behind the tile's first (Outer: members of the group)
     int first;                                           // Outer: the tile's first member
-    const bf16* a1;                                      // Image: a and a1 are this wavefront's 16 rows of slots A0 and A1
+    const bf16* a1;                                      // Image: a and a1 are this wavefront's 16 of a member's rows in slots A0 and A1
   } run, nxt;
   auto source = [&](const Item& it, int seg, Src& s) {
     s.a = p.A + seg * p.a_sb + it.b * p.a_sb + it.k * p.a_sk;
@@ -1060,8 +1054,8 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
     }
     if (IMAGE) {                                         // a slot is two members, of which the last of the group repeats
       const int last = min(p.g, p.C_all - it.k * p.g) - 1, m = it.mt * 4 + (L.wave >> 2);
-      s.a1 = s.a + ((size_t)min(m + 2, last) * 64 + (L.wave & 3) * 16) * p.lda;
-      s.a += ((size_t)min(m, last) * 64 + (L.wave & 3) * 16) * p.lda;
+      s.a1 = s.a + (size_t)min(m + 2, last) * p.lda * 64 + (L.wave & 3) * 16 * 64;
+      s.a += (size_t)min(m, last) * p.lda * 64 + (L.wave & 3) * 16 * 64;
     } else if (A_COL) s.a += it.mt * kGemmBM + (size_t)L.wave * 8 * p.lda;
     else s.a += (size_t)it.mt * kGemmBM * p.lda;
     s.rows = FOLD || A_COL ? 256 : p.rb.rows_of(it.k) - it.mt * kGemmBM;
@@ -1098,7 +1092,9 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
         a_off[h][0] = (unsigned)(min(s.first + 2 * h + (lc >> 3), s.rows - 1) * p.H + (lc & 7)) * p.W * 2;
     } else if (A_COL) {
       a_off[0][0] = col_off(p.lda);
-    } else if (!IMAGE) {
+    } else if (IMAGE) {
+      a_off[0][0] = (lane >> 3) * 128 + ((lane & 7) ^ ColOperand<128>::swz(lane >> 3)) * 16;
+    } else {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1125,7 +1121,7 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
         if (OUTER) {
           const int n = (ki + ((sl & 2) >> 1)) * 64 + L.wave * 8 + u * 4 + (lane_id() >> 4), pi = __umulhi(n, p.pw_magic);
           load16_to_lds_at(run.a, a_off[h][0] + (unsigned)(pi * p.W + n - pi * p.pw) * 16, dst + u * 1024);
-        } else if (IMAGE) load16_to_lds_at((h ? run.a1 : run.a) + (size_t)u * 8 * p.lda, opaque(b_off) ^ (u * 64), dst + u * 1024);
+        } else if (IMAGE) load16_to_lds_at((h ? run.a1 : run.a) + u * 8 * 64, opaque(a_off[0][0]) ^ (u * 64), dst + u * 1024);
         else if (A_COL) load16_to_lds_at(run.a + h * 128 + (size_t)u * 4 * p.lda, a_off[0][0], dst + u * 1024);
         else load16_to_lds_at(run.a, a_off[h][u], dst + u * 1024);
       } else {
@@ -1136,8 +1132,8 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
       }
     }
     if (kind == kSlotA1) {                               // the last slot of a slice
-      if (!OUTER) run.a += A_COL ? (size_t)64 * p.lda : 64;
-      if (IMAGE) run.a1 += 64;
+      if (!OUTER) run.a += A_COL ? (size_t)64 * p.lda : IMAGE ? 64 * 64 : 64;
+      if (IMAGE) run.a1 += 64 * 64;
       const size_t bs = FOLD ? 64 * 64 : KIND == kProductLinear || IMAGE ? 64 : (size_t)64 * p.ldb;
       run.b0 += bs;
       run.b1 += bs;

@@ -147,6 +147,10 @@ __device__ __forceinline__ void pair_products(f32x16 (&acc)[2][2], const bf16x8 
     for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
 }
 
+// Four adjacent rows of a column (a register quad of an accumulator block: lane = column) as two packed words.
+struct Quad { unsigned w[2]; };
+__device__ __forceinline__ Quad pack_quad(const bf16x4& v) { return __builtin_bit_cast(Quad, v); }
+
 // Rows of two quads q, q + 1 dealt so that a lane holds eight adjacent rows, lanes 0 .. 31 those of quad q (rows 0 .. 7), lanes
 // 32 .. 63 those of quad q + 1 (rows 8 .. 15): 16-byte accesses where rows are contiguous, half as many.
 __device__ __forceinline__ bf16x8 join_quads(const bf16x4& a, const bf16x4& b) {
@@ -167,6 +171,22 @@ __device__ __forceinline__ void split_quads(const bf16x8& v, bf16x4& a, bf16x4& 
   a = __builtin_bit_cast(bf16x4, u32x2{s0[0], s1[0]});
   b = __builtin_bit_cast(bf16x4, u32x2{s0[1], s1[1]});
 }
+// A quad of rows x four adjacent columns (four adjacent lanes) transposed: lane l of the four holds row l, columns 0 .. 3, so that
+// a row leaves in 8-byte pieces instead of 2-byte ones.
+__device__ __forceinline__ bf16x4 transpose_quad(const bf16x4& v, int lane) {
+  const Quad q = pack_quad(v);
+  const bool b1 = lane & 2, b0 = lane & 1;
+  const unsigned send = b1 ? q.w[0] : q.w[1];
+  const unsigned recv = (unsigned)__builtin_amdgcn_update_dpp(0, (int)send, kDppSwapHalves, 0xF, 0xF, true);
+  const unsigned x = b1 ? recv : q.w[0], y = b1 ? q.w[1] : recv;      // this lane's two rows of column l & 1, and of that + 2
+  const unsigned xp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, kDppSwapPairs, 0xF, 0xF, true);
+  const unsigned yp = (unsigned)__builtin_amdgcn_update_dpp(0, (int)y, kDppSwapPairs, 0xF, 0xF, true);
+  Quad o;
+  o.w[0] = b0 ? (xp >> 16) | (x & 0xFFFF0000u) : (x & 0xFFFFu) | (xp << 16);
+  o.w[1] = b0 ? (yp >> 16) | (y & 0xFFFF0000u) : (y & 0xFFFFu) | (yp << 16);
+  return __builtin_bit_cast(bf16x4, o);
+}
+
 // Column block j of a wavefront's 64 rows (member, pixel) from `row` on, lane = patch n, into the image: 16 rows are two 8-pixel rows
 // of a patch (8 x 8: a lane each) or a whole 4 x 4 patch.
 template <int PP>
