@@ -142,8 +142,8 @@ struct LevelWs {
 int compute_units();
 
 // Items the value GEMM of a level deals a group's chunks of 8 channels to, so that a level of few groups (the flat
-// baseline, the top of a hierarchy) still fills the chip: doubled while there are fewer than two items per compute
-// unit, never more than the chunks of the smallest group, at most 8.  DCHAG_VAGG_SPLIT overrides (still clamped).
+// baseline, the top of a hierarchy) still fills the chip: at most what leaves two items per compute unit, the chunks of the
+// smallest group and 8, and of those the count that takes least.  DCHAG_VAGG_SPLIT overrides (still clamped).
 int vagg_splits(int B, int Cin, int N, int D, int g) {
   const int G = groups_of(Cin, g);
   const int last = Cin - (G - 1) * g;
@@ -153,7 +153,20 @@ int vagg_splits(int B, int Cin, int N, int D, int g) {
   if (const char* e = dbg(SW_VAGG_SPLIT)) S = std::max(1, atoi(e));
   else while (items * S < 2L * compute_units() && S < 8) S *= 2;
   while (S > nch_min) S >>= 1;
-  return std::max(S, 1);
+  S = std::max(S, 1);
+  if (dbg(SW_VAGG_SPLIT)) return S;
+  // Of the counts up to that one (which the workspace has room for), the one whose rounds of items take least: 1 / S of an item each, and
+  // the partial sums and their merge, a fortieth of an item per split (256 items of 4 chunks: 169 us whole, 176 in two, 186 in four).
+  int best = 1;
+  double least = 0;
+  for (int t = 1; t <= S; t *= 2) {
+    const double cost = (double)((items * t + compute_units() - 1) / compute_units()) / t + (t > 1 ? t / 40. : 0);
+    if (t == 1 || cost < least) {
+      best = t;
+      least = cost;
+    }
+  }
+  return best;
 }
 
 LevelWs level_ws(dchag_dtype dt, int B, int Cin, int N, int D, int heads, int g) {
