@@ -304,11 +304,11 @@ int launch_gemm_mfma_form(const GemmDesc& d, const bf16* A, const bf16* Bm, cons
   return launch_status();
 }
 
-// Whole slices, bf16 results in whole 16-byte pieces, 32-bit offsets inside a tile, 16-byte aligned operands: the ring.
+// bf16 results in whole 16-byte pieces, 32-bit offsets inside a tile, 16-byte aligned operands: the ring.
 inline bool gemm_ring_ok(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias) {
   const bool at = d.A.s1 != 1, bt = d.Bm.s0 != 1;
   const long reach = (1L << 30) / 128;
-  return d.c_vec && d.K % 64 == 0 && d.M >= 1 && d.N >= 8 && (at ? d.A.s1 : d.A.s0) < reach &&
+  return d.c_vec && d.K >= 1 && d.M >= 1 && d.N >= 8 && (at ? d.A.s1 : d.A.s0) < reach &&
          (bt ? d.Bm.s0 : d.Bm.s1) < reach && aligned16(A) && aligned16(Bm) && aligned16(bias) && aligned16(d.rowadd) && mult8(d.bias_sk) &&
          mult8(d.bias_sa) && !dbg(SW_GEMM_REGS);
 }

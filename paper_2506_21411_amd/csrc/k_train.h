@@ -1161,10 +1161,12 @@ __global__ __launch_bounds__(256) void k_gemm_mfma(GemmDesc d, const bf16* __res
   }
 }
 
+__device__ __align__(16) const bf16 kZeroPiece[8] = {};                 // what stands past the end of a contraction
+
 // ---------------------------------------------------------------------------------------
-// The products of k_gemm_mfma where every contraction is whole slices of 64, every row 16-byte aligned, transposed extents multiples of
-// 8 and C's rows whole 16-byte pieces (host): the same contract (bias, scale, ragged M, sums over batch elements, row sums of a
-// transposed A), with slices brought in by direct-to-LDS loads, ST - 1 of them ahead, 16x16x32 instructions and transposing LDS reads
+// The products of k_gemm_mfma where every row is 16-byte aligned, transposed extents multiples of 8 and C's rows whole 16-byte pieces
+// (host): the same contract (bias, row addend, scale, ragged M, sums over batch elements, row sums of a transposed A, a last slice of
+// fewer than 64 steps), with slices brought in by direct-to-LDS loads, ST - 1 of them ahead, 16x16x32 instructions and transposing LDS reads
 // (RowOperand, ColOperand of the large products).  k_gemm_mfma stages through registers one slice ahead and transposes there.  Before / after,
 // us, D 1024: one group, 1024 rows: dWo 22 / 10, d_o 16.5 / 9, dWv 24 / 13.5, w 17 / 14, output projection (the 128 x 128 ring it had)
 // 16.5 / 10; one group, 4096 rows: dWo 75 / 29, dWv 82 / 39, d_o 24 / 17; eight groups of 512 rows, D 2048, u Wv: 103 / 90.
@@ -1195,7 +1197,7 @@ __global__ __launch_bounds__(256) void k_gemm_ring(GemmDesc d, const bf16* __res
   if (m0 >= M) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, lq = lane >> 4;
-  const int KT = d.K / 64, steps = nb * KT;
+  const int KT = (d.K + 63) / 64, steps = nb * KT;
 
   // Loads of an operand: R / 8 of 1 KiB, R / 32 to a wavefront.  Row r of the operand (T false): 8 rows a load; step of the slice
   // (T true): 1024 / (2 R) steps a load.  off: byte of a lane's 16 behind the tile's origin, the same for every slice.
@@ -1224,12 +1226,29 @@ __global__ __launch_bounds__(256) void k_gemm_ring(GemmDesc d, const bf16* __res
   const bf16 *pa = Ab, *pb = Bb;
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem);
   int ki = 0, is = 0;
+  // A load of a segment's last, shorter slice: 16 bytes past the contraction's end come from the zeros instead.  at: the first
+  // contraction element of a lane's 16 bytes.
+  auto tail = [&](const bf16* base, unsigned off, int at, int dst) {
+    const bf16* src = at < d.K ? reinterpret_cast<const bf16*>(reinterpret_cast<const char*>(base) + off) : kZeroPiece;
+    load16_to_lds(src, smem + dst);
+  };
+  auto first_of = [&](bool T, int R, int ld) {             // contraction element of a lane's 16 bytes in load ld of a slice
+    return ki * 64 + (T ? ld * (512 / R) + lane / (R / 8) : ((lane & 7) ^ swz_chunk(ld * 8 + (lane >> 3))) * 8);
+  };
   auto issue = [&]() {
     const unsigned dst = lds0 + is * STAGE;
+    if (ki == KT - 1 && d.K % 64) {                        // uniform
 #pragma unroll
-    for (int i = 0; i < AL; ++i) load16_to_lds_at(pa, a_off[i], dst + (wave * AL + i) * 1024);
+      for (int i = 0; i < AL; ++i) tail(pa, a_off[i], first_of(AT, BM, wave * AL + i), is * STAGE + (wave * AL + i) * 1024);
 #pragma unroll
-    for (int i = 0; i < BL; ++i) load16_to_lds_at(pb, b_off[i], dst + BM * 128 + (wave * BL + i) * 1024);
+      for (int i = 0; i < BL; ++i)
+        tail(pb, b_off[i], first_of(BT, BN, wave * BL + i), is * STAGE + BM * 128 + (wave * BL + i) * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < AL; ++i) load16_to_lds_at(pa, a_off[i], dst + (wave * AL + i) * 1024);
+#pragma unroll
+      for (int i = 0; i < BL; ++i) load16_to_lds_at(pb, b_off[i], dst + BM * 128 + (wave * BL + i) * 1024);
+    }
     is = is == ST - 1 ? 0 : is + 1;
     pa += AT ? d.A.s1 * 64 : 64;
     pb += BT ? d.Bm.s0 * 64 : 64;
