@@ -39,7 +39,7 @@ if __name__ == "__main__":
     import argparse
     ap = argparse.ArgumentParser()
     ap.add_argument("--out", default=LIB)
-    ap.add_argument("--define", action="append", default=[], help="extra macro, e.g. DCHAG_GEMM_PROBE=8 (needs --out)")
+    ap.add_argument("--define", action="append", default=[], help="extra macro, e.g. DCHAG_RING_PROBE=1 (needs --out)")
     a = ap.parse_args()
     build(out=a.out, defines=a.define)
     sys.exit(0)

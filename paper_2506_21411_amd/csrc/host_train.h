@@ -648,11 +648,11 @@ inline bool values_from_pixels(dchag_dtype dt, int p, int D, int heads, const dc
 }
 
 // The weight-only part: fold (value_fold_bytes(C, D, p*p) bytes) receives Wf [C,D,p*p] and Wv (be + ce) [C,D].
-// Two row tiles a block share the members' vectors once that leaves four blocks to a compute unit.
+// Groups of up to 16 members multiply 16, others 32 a pass (Wv is read once per pass).
 inline int fold_token_bias(int C, int D, int g, const bf16* Wv, const bf16* be, const bf16* ce, bf16* fb, hipStream_t st) {
   const int G = groups_of(C, g);
-  if ((long)(D / 64) * G >= 4L * compute_units()) k_fold_token_bias<2><<<dim3(D / 64, G), 256, 0, st>>>(C, D, g, Wv, be, ce, fb);
-  else k_fold_token_bias<1><<<dim3(D / 32, G), 256, 0, st>>>(C, D, g, Wv, be, ce, fb);
+  if (std::min(g, C) <= 16) k_fold_token_bias<1><<<dim3(D / 64, G), 256, 0, st>>>(C, D, g, Wv, be, ce, fb);
+  else k_fold_token_bias<2><<<dim3(D / 64, G), 256, 0, st>>>(C, D, g, Wv, be, ce, fb);
   return launch_status();
 }
 inline int fold_value_weights(int C, int p, int D, const dchag_level* lv, const bf16* We, const bf16* be, const bf16* ce,
@@ -1417,7 +1417,8 @@ template <class K>
 int raise_pair_lds(K kern) { return ensure_dynamic_lds(reinterpret_cast<const void*>(kern), kPairLdsBytes); }
 
 // 8 x 8 patches whose count is whole slices (an even number of them a batch element, at least four), 32-bit offsets inside a group's
-// images, and tiles of either product for half of the compute units.
+// images, and tiles of either product for half of the compute units.  512 bands, 4 x 256 patches, D 1024, k_linear_outer, k_linear_dx and the
+// copies they read / these: 252 / 188 us; with fewer tiles (256 x 256 here, 128 x 256 there) half the chip would stand idle.
 inline bool linear_products_ok(int B, int G, int N, int g, int H, int W, int D) {
   const long tiles = (long)((g + 3) / 4) * G;
   return N % 128 == 0 && N >= 256 && W >= 16 && (long)g * H * W < (1L << 30) && (long)N * (W / 8) < (1L << 31) &&

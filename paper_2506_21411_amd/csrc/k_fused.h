@@ -12,10 +12,10 @@
 //   k_tokenize_reduce_ring, k_tokenize_mix_*, k_tokenize_attend_wide   tokenizer fused with the first level
 //                     (linear level of D-CHAG-L, or attention level with folded value weights): no tokens in HBM
 //
-// The GEMM kernels share one core: 256x256 block tile, 8 wavefronts (2 x 4), 16x16x32 bf16
-// MFMA, K staged in 64-element slices through two LDS stages that are filled by direct-to-LDS
+// The large products share one core: 256x256 block tile, 8 wavefronts (2 x 4), 16x16x32 bf16
+// MFMA, K staged in 64-element slices of four slots, two stages, each slot refilled by direct-to-LDS
 // global loads of 128-byte row segments (no register staging; L2 delivers 128-byte segments at
-// about twice the rate of 64-byte ones) and read with conflict-free swizzled LDS reads.
+// about twice the rate of 64-byte ones) and read with conflict-free swizzled or transposing LDS reads.
 //
 // Softmax weights are exchanged between the kernels in the layout
 //   alpha[b][k][cl][head][n]   (n fastest, pitch Np = N rounded up to 32; cl < gpad = g rounded up to 8)
@@ -1263,65 +1263,91 @@ __global__ __launch_bounds__(512) void k_product_dl(ProductArgs p) {
 }
 
 // The token biases under the same fold (weight-only):  fb[c][o] = sum_d (be[c][d] + ce[c][d]) * Wv[k][o][d],  k = c / g;
-// either vector may be absent.  grid (D / (32 RT), G), block 256: 32 RT rows o of Wv against the group's members, 32 per pass
-// (32 x 32 MFMA blocks: rows o, columns members, operands straight from memory), the four wavefronts a quarter of d each, their
-// partial blocks merged in LDS in a fixed order.  A lane reads 64 contiguous bytes of its row per trip, the two halves of a
-// wavefront one 128-byte line (the order of d inside a trip is the operands' own business), all loads before the products; two row
-// tiles share the members' vectors.  Bound by the read of Wv: 63 groups, D 2048 (528 MB): 172 us (16 bytes a lane and trip, a 32-byte
-// piece of each row: 228 us).  Requires D % 256 == 0 and 16-byte aligned rows.
-template <int RT>
+// either vector may be absent.  grid (D / 64, G), block 256: 64 rows o of Wv (16 a wavefront) against the group's members, 16 MB a
+// pass; slices of 64 d of the rows and of both vectors by direct-to-LDS loads, three slices ahead.  Bound by the read of Wv.  Blocks start
+// at different slices (the rows of all of them are multiples of 4 KB apart, which meets few channels).  be and ce, and the two halves of
+// a slice, have sums of their own, added up at the end.  63 groups of 16, D 2048 (528 MB): 112 us (operands straight to
+// registers, 64 bytes of a row to a lane: 171); 16 of 32, D 1024: 14 (17.5); 10 of 8: 9 (10).  Requires D % 256 == 0 and 16-byte aligned rows.
+template <int MB>
 __global__ __launch_bounds__(256) void k_fold_token_bias(int C, int D, int g, const bf16* __restrict__ Wv,
                                                          const bf16* __restrict__ be, const bf16* __restrict__ ce,
                                                          bf16* __restrict__ fb) {
-  __shared__ float part[4][32][33];
-  const int k = blockIdx.y, o0 = blockIdx.x * 32 * RT;
-  const int c0 = k * g, gk = min(g, C - c0);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lhi = lane >> 5;
-  const int dq = D / 4;
-  const bf16* arow = Wv + ((size_t)k * D + o0 + l32) * D + wave * dq + lhi * 32;
-  for (int cb = 0; cb < gk; cb += 32) {
-    const size_t coff = (size_t)(c0 + min(cb + l32, gk - 1)) * D + wave * dq + lhi * 32;
-    f32x16 acc[RT];
+  constexpr int ST = 4, WB = 64 * 128, VB = 16 * MB * 128, STAGE = WB + 2 * VB, L = 2 + MB;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[ST * STAGE];
+  const int k = blockIdx.y, o0 = blockIdx.x * 64;
+  const int c0 = k * g, gk = min(g, C - c0), KT = D / 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, lq = lane >> 4;
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem);
+  const bf16* W0 = Wv + ((size_t)k * D + o0) * D;
+  // a load brings 8 rows: two of Wv's to a wavefront, and MB of the vectors' (wavefronts 0 and 1: be, 2 and 3: ce)
+  unsigned w_off[2], v_off[MB];
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+  for (int i = 0; i < 2; ++i) {
+    const int row = (wave * 2 + i) * 8 + (lane >> 3);
+    w_off[i] = (unsigned)row * (unsigned)D * 2 + ((lane & 7) ^ swz_chunk(row)) * 16;
+  }
+  const bf16* vec = wave < 2 ? be : ce;
+  const int w_ad = RowOperand::base(wave * 16, lane), v_ad = RowOperand::base(0, lane);
+  for (int cb = 0; cb < gk; cb += 16 * MB) {
+    const bf16* V0 = vec + (size_t)(c0 + cb) * D;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-    for (int ks = 0; ks < dq; ks += 64) {
-      bf16x8 a[RT][4], vb[4], vc[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int t = 0; t < RT; ++t) a[t][q] = *reinterpret_cast<const bf16x8*>(arow + (size_t)t * 32 * D + ks + q * 8);
-        if (be) vb[q] = *reinterpret_cast<const bf16x8*>(be + coff + ks + q * 8);
-        if (ce) vc[q] = *reinterpret_cast<const bf16x8*>(ce + coff + ks + q * 8);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-          if (be) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][q], vb[q], acc[t], 0, 0, 0);
-          if (ce) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][q], vc[q], acc[t], 0, 0, 0);
-        }
+    for (int i = 0; i < MB; ++i) {
+      const int row = ((wave & 1) * MB + i) * 8 + (lane >> 3);
+      v_off[i] = (unsigned)min(row, gk - cb - 1) * (unsigned)D * 2 + ((lane & 7) ^ swz_chunk(row)) * 16;
     }
+    int ki = blockIdx.x % KT, is = 0;
+    auto issue = [&]() {
+      const unsigned dst = lds0 + is * STAGE;
 #pragma unroll
-    for (int t = 0; t < RT; ++t) {
-      // accumulator register r of lane (member l32, half lhi): row o = 8 (r / 4) + 4 lhi + r % 4
+      for (int i = 0; i < 2; ++i) load16_to_lds_at(W0 + ki * 64, w_off[i], dst + (wave * 2 + i) * 1024);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) part[wave][8 * (r >> 2) + 4 * lhi + (r & 3)][l32] = acc[t][r];
-      __syncthreads();
-      {
-        const int mm = tid >> 3, r0 = 4 * (tid & 7);       // member of the pass, four adjacent rows o
-        if (cb + mm < gk) {
-          typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-          bf16x4_t out;
+      for (int i = 0; i < MB; ++i)                        // an absent vector's rows are never read: Wv's stand in for them
+        load16_to_lds_at(vec ? V0 + ki * 64 : W0 + ki * 64, vec ? v_off[i] : w_off[0], dst + WB + (wave * MB + i) * 1024);
+      is = (is + 1) % ST;
+      ki = ki == KT - 1 ? 0 : ki + 1;
+    };
+    f32x4 acc[2][2][MB];
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            out[e] = (bf16)(part[0][r0 + e][mm] + part[1][r0 + e][mm] + part[2][r0 + e][mm] + part[3][r0 + e][mm]);
-          *reinterpret_cast<bf16x4_t*>(fb + (size_t)(c0 + cb + mm) * D + o0 + t * 32 + r0) = out;
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int j = 0; j < MB; ++j) acc[v][kk][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < ST - 1; ++s)
+      if (s < KT) issue();
+    for (int s = 0; s < KT; ++s) {
+      // slice s has landed (this wavefront's share; two behind it may stay in flight), every wavefront is done with slice s - 1
+      const int behind = KT - 1 - s;                      // uniform
+      if (behind >= 2) wait_vmcnt<2 * L>();
+      else if (behind == 1) wait_vmcnt<L>();
+      else wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (s + ST - 1 < KT) issue();
+      const unsigned char* st = smem + s % ST * STAGE;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8 w = RowOperand::frag(st, w_ad, 0, kk, 0);
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+          if (be) acc[0][kk][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, RowOperand::frag(st + WB, v_ad, j, kk, 0), acc[0][kk][j], 0, 0, 0);
+          if (ce)
+            acc[1][kk][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, RowOperand::frag(st + WB + VB, v_ad, j, kk, 0), acc[1][kk][j], 0, 0, 0);
         }
       }
-      __syncthreads();
     }
+    // block j: member 16 j + l16, rows 4 lq + e of the wavefront's 16
+#pragma unroll
+    for (int j = 0; j < MB; ++j)
+      if (cb + j * 16 + l16 < gk) {
+        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+        bf16x4_t out;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = (bf16)((acc[0][0][j][e] + acc[0][1][j][e]) + (acc[1][0][j][e] + acc[1][1][j][e]));
+        *reinterpret_cast<bf16x4_t*>(fb + (size_t)(c0 + cb + j * 16 + l16) * D + o0 + wave * 16 + lq * 4) = out;
+      }
+    __syncthreads();                                      // the next pass fills the stages again
   }
 }
 

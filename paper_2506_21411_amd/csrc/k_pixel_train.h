@@ -342,8 +342,8 @@ __global__ __launch_bounds__(256) void k_pixel_prep(PixelDims d, const float* __
 // ---------------------------------------------------------------------------------------
 // Value fold of 4 x 4 patches in three layouts: Wf[c][o][kk], WfT[c][kk][o] = sum_j WeT[c][kk][j] Wv[k][o][j] (WeT: the
 // tokenizer weights transposed) and member-major rows Wg[k][o][(member, pixel)] (pitch 16 gq, zeros for missing members).
-// Tile rows: (member, pixel), tile columns: o.  (8 x 8 patches: k_fold_value_dl and a transposing copy, 0.105 against
-// 0.134 ms for 512 bands.)
+// Tile rows: (member, pixel), tile columns: o.  (8 x 8 patches: k_product_dl<kProductFold> and a transposing copy,
+// 0.09 against 0.134 ms for 512 bands.)
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(512) void k_pixel_fold(PixelDims d, TileWork tw, const bf16* __restrict__ WeT,
                                                        const bf16* __restrict__ Wv, bf16* __restrict__ Wf,
@@ -1134,7 +1134,8 @@ __global__ __launch_bounds__(512) void k_pixel_dwv(PixelDims d, TileWork tw, int
 }
 
 // ---------------------------------------------------------------------------------------
-// Reverse step of a LINEAR first level from the pixels (formulas at k_linear_first_grads), both products on pair_loop.
+// Reverse step of a LINEAR first level from the pixels (formulas at k_linear_first_grads), both products on pair_loop: 4 x 4 patches, and
+// the counts that linear_products_ok refuses (where it accepts, k_product_dl's Outer and Image take 188 us of the 252 below).
 // k_linear_outer: P[(member, pixel)][d] = sum_n u[n] dy[n][d] over all patches (UT, dyT: patch index contiguous), tile rows
 // (member, pixel), columns d; P stays in the accumulators and leaves as dWe = mix P, dmix = sum_pixels We P + (be + ce) S,
 // dtok_bias = mix S, dbias = S and the scaled weights WsT[(member, pixel)][d] = mix We that k_linear_dx contracts dy with.
