@@ -30,7 +30,7 @@ PEAK = {"mfma_bf16_tflops": 2500.0, "hbm_gbs": 8000.0, "fp32_tflops": 157.3}
 
 # Stage names of the library's timing records -> kernel name prefixes in the rocprofv3 summaries under profiles/.
 STAGE_KERNEL = {"fused_vagg": "k_vagg_mfma", "tokenize": "k_tokenize_ws", "tokenize_mix": "k_tokenize_reduce_ring",
-                "tokenize_attend": "k_tokenize_reduce_ring", "oproj": "k_linear_dl"}
+                "tokenize_attend": "k_tokenize_reduce_ring", "oproj": "k_product_dl<Linear>"}
 
 
 def measured_traffic(workload, stage, level):
