@@ -709,6 +709,10 @@ int fast_scores(int B, int Cin, int N, int D, int heads, const dchag_level* lv, 
   return DCHAG_OK;
 }
 
+// The value GEMM's 32-bit lane offsets reach channel 7 of a chunk, head NHS - 1 of its slice, while they stay below 2^32 bytes (2.4 million
+// patches at 64 heads).
+inline bool vagg_wide(int heads, int NHS, int Np) { return (7L * heads + NHS) * Np * 4 > (1L << 32); }
+
 // One aggregation level on the bf16 MFMA path: weight-only prep, scores (MFMA on the tokens, or
 // from the pixels at the first level of a forward call), softmax over the group, value projection
 // fused with the weighted sum over the group, output projection.
@@ -742,12 +746,13 @@ int run_level_fast(int B, int Cin, int N, int D, int heads, const dchag_level* l
     const int dh = D / heads;
     const int NHS = dh >= kGemmBN ? 1 : kGemmBN / dh;
     const int lds = kGemmRingBytes + 3 * 8 * NHS * 32 * 4;
-    if (ensure_dynamic_lds(reinterpret_cast<const void*>(k_vagg_mfma), lds)) return DCHAG_ERR_LAUNCH;
+    auto vagg = vagg_wide(heads, NHS, Np) ? k_vagg_mfma<true> : k_vagg_mfma<false>;
+    if (ensure_dynamic_lds(reinterpret_cast<const void*>(vagg), lds)) return DCHAG_ERR_LAUNCH;
     // persistent workgroups: one per compute unit (the LDS ring allows no more), `slots` per XCD
     const int slots = per < compute_units() / kXcds ? per : compute_units() / kXcds;
-    k_vagg_mfma<<<dim3(slots * kXcds), dim3(512), lds, st>>>(Cin, N, D, heads, g, gpad, G, Np, tw, slots, zin,
-                                                            static_cast<const bf16*>(lv->Wv),
-                                                            static_cast<const bf16*>(lv->bv), alpha, O, S, Opart);
+    vagg<<<dim3(slots * kXcds), dim3(512), lds, st>>>(Cin, N, D, heads, g, gpad, G, Np, tw, slots, zin,
+                                                     static_cast<const bf16*>(lv->Wv), static_cast<const bf16*>(lv->bv), alpha, O,
+                                                     S, Opart);
     if ((rc = launch_status())) return rc;
     if (S > 1) {
       const long per_split = (long)B * G * N * D, quads = per_split / 4;

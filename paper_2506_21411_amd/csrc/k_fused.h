@@ -679,12 +679,15 @@ __device__ __forceinline__ void core_prologue(CoreFrags& f, const unsigned char*
 // Bound by the card's power limit: at 512 channels, D 1024, B 4, N 256 the matrix units are busy 64 % of the cycles at
 // 1.95 GHz (a library product of the same operands' size: 87 % at 1.57 GHz, 8 % more work a second), 835 us against 865 with
 // 32x32x16 instructions and whole stages (68 % at 1.79 GHz).
+// WIDE: 64-bit addresses for the softmax weights, whose eight channels of a chunk lie heads Np floats apart (host: vagg_wide).  It spills a
+// register, which the narrow one does not: level of 4 x 1000 channels, 300 patches, D 256 451 us instead of 441.
 // Dynamic LDS: ring (128 KiB) + 3 alpha tiles of 8 * NHS * 32 floats, used round-robin by chunk.
 // ---------------------------------------------------------------------------------------------
 struct VaggItem {
   int k, b, n0, o0, c0, gk, nch, h0, ch0, split;
 };
 
+template <bool WIDE>
 __global__ __launch_bounds__(512) void k_vagg_mfma(int Cin, int N, int D, int heads, int g, int gpad, int G, int Np,
                                                    TileWork tw, int slots, const bf16* __restrict__ z,
                                                    const bf16* __restrict__ Wv, const bf16* __restrict__ bv,
@@ -758,8 +761,9 @@ __global__ __launch_bounds__(512) void k_vagg_mfma(int Cin, int N, int D, int he
     const int kind = sl & ~2;
     if (sl == kSlotA0 && ki == 0 && L.wave < NHS) {      // entering a chunk (its slices are even in number): its softmax weights
       const int l = lane_id(), sgm = L.wave * 8 + (l >> 3);   // segment = (channel of the chunk, head of the slice)
-      load16_to_lds_at(run.al, ((unsigned)((sgm >> nhs_log) * heads + (sgm & (NHS - 1))) * Np + (l & 7) * 4) * 4,
-                       smem_off + kGemmRingBytes + (gci % 3) * atile + L.wave * 1024);
+      const unsigned row = (unsigned)((sgm >> nhs_log) * heads + (sgm & (NHS - 1)));
+      if constexpr (WIDE) load16_to_lds(run.al + (size_t)row * Np + (l & 7) * 4, alds + (gci % 3) * atile + L.wave * 1024);
+      else load16_to_lds_at(run.al, (row * Np + (l & 7) * 4) * 4, smem_off + kGemmRingBytes + (gci % 3) * atile + L.wave * 1024);
     }
     const bf16*& p = kind == kSlotA0 ? run.a0 : kind == kSlotA1 ? run.a1 : kind == kSlotB0 ? run.b0 : run.b1;
 #pragma unroll
