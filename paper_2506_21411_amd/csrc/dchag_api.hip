@@ -137,17 +137,27 @@ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 // Generic path: s holds scores [B,Cin,N,heads], v the projected values [B,Cin,N,D].
 struct LevelWs {
   size_t qp, mf, mb, alpha, s, v, o, vpart, total;
+  int splits;                      // fast path: items a group's chunks are dealt to (vagg_splits)
 };
 
 int compute_units();
 
 // Items the value GEMM of a level deals a group's chunks of 8 channels to, so that a level of few groups (the flat
-// baseline, the top of a hierarchy) still fills the chip: at most what leaves two items per compute unit, the chunks of the
-// smallest group and 8, and of those the count that takes least.  DCHAG_VAGG_SPLIT overrides (still clamped).
-int vagg_splits(int B, int Cin, int N, int D, int g) {
+// baseline, the top of a hierarchy) still fills the chip: 1, 2, 4 or 8, at most what leaves two items per compute unit and the chunks of
+// the smallest group, and of those the count that takes least by the model below, in us.  A workgroup's items all have the same
+// share of their groups' chunks (their distance in the launch's order is a multiple of the count), so the longest share times the
+// rounds of items is what the launch waits for; 18 us is a chunk's time at D 1024 on a chip that it does not fill, and a split costs the partial
+// sums' way through memory and a launch that adds them up.  Level calls, us, whole / in 2 / 4 / 8: 256 items of 4 chunks, D 1024 158 / 164 / 169;
+// 80 of 16, D 1024 433 / 288 / 299 / 263; 192 of 5, D 2048 290 / 344 / 352; 160 of 16, D 2048 812 / 888 / 741; 16 of 8, D 256
+// 101 / 80 / 69 / 65.  Over 61 levels of D 256 to 4096 and 1 to 16 chunks the model's count takes 0.4 % more than the best of the four (the worst
+// 13 %, where two items per compute unit bar it); as many as that bound allows, 2.6 % (24 %).
+// before: the workspace's bytes ahead of the partial sums; eight items a group where that is more than two per compute unit (65 to 96 items) are taken
+// only while the level still fits the static scratch (dchag_aggregate_level_static).
+// DCHAG_VAGG_SPLIT overrides (still clamped).
+int vagg_splits(int B, int Cin, int N, int D, int g, size_t before) {
   const int G = groups_of(Cin, g);
   const int last = Cin - (G - 1) * g;
-  const int nch_min = (std::min(g, last) + 7) / 8;
+  const int nch = (std::min(g, Cin) + 7) / 8, nch_min = (std::min(g, last) + 7) / 8;
   const long items = (long)(D / 256) * ((N + 31) / 32) * B * G;
   int S = 1;
   if (const char* e = dbg(SW_VAGG_SPLIT)) S = std::max(1, atoi(e));
@@ -155,15 +165,16 @@ int vagg_splits(int B, int Cin, int N, int D, int g) {
   while (S > nch_min) S >>= 1;
   S = std::max(S, 1);
   if (dbg(SW_VAGG_SPLIT)) return S;
-  // Of the counts up to that one (which the workspace has room for), the one whose rounds of items take least: 1 / S of an item each, and
-  // the partial sums and their merge, a fortieth of an item per split (256 items of 4 chunks: 169 us whole, 176 in two, 186 in four).
+  const size_t part = (size_t)B * G * N * D * 4;
   int best = 1;
   double least = 0;
   for (int t = 1; t <= S; t *= 2) {
-    const double cost = (double)((items * t + compute_units() - 1) / compute_units()) / t + (t > 1 ? t / 40. : 0);
-    if (t == 1 || cost < least) {
+    if (t == 8 && items * t > 2L * compute_units() && before + align_up(t * part) > DCHAG_STATIC_SCRATCH_BYTES) break;
+    const long per = (items * t + kXcds - 1) / kXcds, slots = std::min<long>(per, compute_units() / kXcds), rounds = (per + slots - 1) / slots;
+    const double us = rounds * ((nch + t - 1) / t * 18. * D / 1024 + 0.5) + (t > 1 ? 1.5 + 0.01 * items * t : 0);
+    if (t == 1 || us < least) {
       best = t;
-      least = cost;
+      least = us;
     }
   }
   return best;
@@ -186,9 +197,9 @@ LevelWs level_ws(dchag_dtype dt, int B, int Cin, int N, int D, int heads, int g)
   }
   w.o = off;  off += align_up((size_t)B * G * N * D * es);
   if (fast) {
-    const int S = vagg_splits(B, Cin, N, D, g);
+    w.splits = vagg_splits(B, Cin, N, D, g, off);
     w.vpart = off;
-    if (S > 1) off += align_up((size_t)S * B * G * N * D * 4);
+    if (w.splits > 1) off += align_up((size_t)w.splits * B * G * N * D * 4);
   }
   w.total = off;
   return w;
@@ -739,7 +750,7 @@ int run_level_fast(int B, int Cin, int N, int D, int heads, const dchag_level* l
     tw.n_tiles = D / kGemmBN;
     tw.m_tiles = (N + 31) / 32;
     tw.nb = B;
-    const int S = vagg_splits(B, Cin, N, D, g);
+    const int S = w.splits;
     float* Opart = reinterpret_cast<float*>(ws + w.vpart);
     tw.total = tw.n_tiles * tw.m_tiles * B * G * S;
     const int per = (tw.total + kXcds - 1) / kXcds;
