@@ -497,9 +497,19 @@ int generic_query_keys(int G, int D, int heads, const dchag_level* lv, const Pre
 
 // Scores, softmax and weighted sums in one kernel: while the partial scores of a patch fit 64 KiB of LDS.  Two patches a block, one
 // where two would leave compute units without a block or do not fit.
+// In single precision the separate kernels score by a product that shares a group's keys among 64 token rows, where here every patch or two
+// read all of them and a block of 16 rows of products holds only the group's members.  So one kernel wins by the members to a block of 16 heads
+// (more than three each) or by the launches it saves (few patches).  fp32, one kernel / separate, us, values: 64 channels x 512 patches,
+// D 512, 8 heads, groups of 1 508 / 435, 2 348 / 330, 4 266 / 274, 8 229 / 251; 32 heads, 4 293 / 271, 8 243 / 247; 64 heads, 8 277 / 248; D 128,
+// 32 heads, 1 159 / 81, 4 65 / 55, and over 128 patches 4 32 / 35.  Sums (4 x 1024 patches, one group, D 512): 32 heads, 4 215 / 217,
+// 16 334 / 337; 64 heads, 4 389 / 383, 16 584 / 545; 256 patches 69 / 97 and 83 / 109.  bf16 has no such product (a wavefront a token): 1.0 to 3.8
+// times as fast in one kernel at 8 to 64 heads and groups of 1 to 32.
 inline long level_generic_lds(int heads, int g, int patches) { return 16L * patches * g * round_up(heads, 8); }
-inline bool level_generic_ok(int heads, int g) {
-  return level_generic_lds(heads, g, 1) <= 65536 && !dbg(SW_GENERIC_LEVEL) && !dbg(SW_LEVEL_UNFUSED);
+template <typename T>
+bool level_generic_ok(bool values, int heads, int g, long patches) {      // patches: of all groups and batch elements
+  if (level_generic_lds(heads, g, 1) > 65536 || dbg(SW_GENERIC_LEVEL) || dbg(SW_LEVEL_UNFUSED)) return false;
+  const int blocks = (heads + 15) / 16;
+  return sizeof(T) == 2 || patches * blocks <= 4096 || (values ? g > 3 * blocks : blocks <= 2);
 }
 template <typename T, bool VALUES>
 int launch_level_generic(int B, int Cin, int N, int D, int heads, int g0, const T* z, const float* Mf, const T* V, float* alpha,
@@ -528,7 +538,7 @@ int run_level(dchag_dtype dt, int B, int Cin, int N, int D, int heads, const dch
   const PrepBufs& pb = ready ? *ready : own;
   int rc;
   if (!ready && (rc = generic_query_keys<T>(G, D, heads, lv, pb, st))) return rc;
-  const bool fused = level_generic_ok(heads, std::min(g, Cin));
+  const bool fused = level_generic_ok<T>(true, heads, std::min(g, Cin), (long)B * N * G);
   if (!fused) {
     StageTimer tm(DCHAG_STAGE_SCORES, st);
     if ((rc = token_scores(B, Cin, N, D, heads, g, zin, pb.Mf, S, st))) return rc;

@@ -480,7 +480,7 @@ int generic_alpha(int B, int Cin, int N, int D, int heads, const dchag_level* lv
   const int g = lv->group_size, G = groups_of(Cin, g);
   int rc;
   if (!prepared && (rc = generic_query_keys<T>(G, D, heads, lv, PrepBufs{lb.Qp, lb.Mf, lb.Mb}, st))) return rc;
-  *summed = level_generic_ok(heads, std::min(g, Cin));
+  *summed = level_generic_ok<T>(false, heads, std::min(g, Cin), (long)B * N * G);
   if (*summed) {
     StageTimer tm(DCHAG_STAGE_HEAD_SUMS, st);
     return launch_level_generic<T, false>(B, Cin, N, D, heads, g, zin, lb.Mf, nullptr, lb.alpha, lb.u, st);
