@@ -1,7 +1,11 @@
 """GPU parity of the products on 256 x 256 tiles (output projections, their input and weight gradients) where their tiles, segments
 and ragged rows end, against the oracle."""
+import re
+
 import numpy as np
 import pytest
+import torch
+from torch.profiler import ProfilerActivity, profile
 
 import oracle
 import paper_2506_21411_amd as dchag
@@ -12,11 +16,22 @@ from .test_gpu_train import TOL, dev, dev_level, host, rel_err
 
 pytestmark = pytest.mark.gpu
 
+LINEAR, BACK, WEIGHTS, FOLD, IMAGE, OUTER = range(6)       # kinds of k_product_dl
+
+
+def product_kinds(call):
+    """Kinds of k_product_dl that a call launched."""
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return {int(k) for e in prof.events() for k in re.findall(r"k_product_dl(?:<|ILi)(\d)", e.name)}
+
+
 TRAIN = [
     # two segments of the contraction of six slices each; rows of one and a half tiles; 33 groups, the last of one member
     dict(B=2, C=65, H=64, W=96, p=4, D=512, heads=8, group_sizes=(2, 33)),
-    # one segment of four slices (the shortest), three tiles of columns, a workgroup of no or of two tiles
-    dict(B=1, C=30, H=64, W=64, p=4, D=768, heads=12, group_sizes=(2, 15)),
+    # one segment of four slices (the shortest), three tiles of columns; 387 tiles of weights, two to some workgroups, and 129 of inputs
+    dict(B=1, C=86, H=64, W=64, p=4, D=768, heads=12, group_sizes=(2, 43)),
 ]
 
 
@@ -24,7 +39,9 @@ TRAIN = [
 def test_output_projection_gradients(kw, biases, monkeypatch):
     say(f"large products, training {kw}")
     monkeypatch.setenv("DCHAG_TRAIN_ROUTE", "tokens")
-    check_training_step(ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=61, **kw), biases=biases)
+    cfg = ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=61, **kw)
+    kinds = product_kinds(lambda: check_training_step(cfg, biases=biases))
+    assert kinds >= {LINEAR, BACK, WEIGHTS}, kinds
 
 
 @pytest.mark.parametrize("biases", [True, False])
@@ -38,6 +55,8 @@ def test_projection_of_ragged_rows(biases):
     say(f"large products, forward {cfg}")
     got = host(dchag.dchag_forward(*args))
     folded = host(dchag.dchag_forward_folded(*args))
+    assert product_kinds(lambda: dchag.dchag_forward(*args)) == {LINEAR}
+    assert product_kinds(lambda: dchag.dchag_forward_folded(*args)) == {LINEAR, FOLD}
     rows = np.r_[0:8, 120:136, 252:260]                   # patches at the edges of the tiles
     xs = pr.x.reshape(1, cfg.C, 10, 8, 26, 8).transpose(0, 2, 4, 1, 3, 5).reshape(cfg.N, cfg.C, 64)[rows]
     xs = xs.reshape(1, len(rows), cfg.C, 8, 8).transpose(0, 2, 3, 1, 4).reshape(1, cfg.C, 8, 8 * len(rows))
@@ -56,4 +75,5 @@ def test_linear_first_level_on_large_tiles(biases, monkeypatch):
     cfg = ShapeCfg(name="t", dtype="bf16", x_kind="gauss_mu_sigma", seed=68, B=2, C=163, H=192, W=128, p=8, D=512, heads=8,
                    group_sizes=(5, 33), level_kinds=("linear", "attention"))
     say(f"large products, linear first level {cfg}")
-    check_training_step(cfg, biases=biases)
+    kinds = product_kinds(lambda: check_training_step(cfg, biases=biases))
+    assert kinds >= {IMAGE, OUTER}, kinds
