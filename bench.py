@@ -250,9 +250,9 @@ def main() -> int:
         del src, dst, sink
         torch.cuda.empty_cache()
         return {"mfma_bf16_tflops": round(best, 1), "copy_gbs": round(copy, 1), "read_gbs": round(read, 1),
-                "how": "dchag_yardstick_mfma (16 wavefronts per compute unit, 8 independent 32x32x16 bf16 MFMAs per "
-                       "round, registers only), dchag_yardstick_copy (1 GiB read + 1 GiB written; bytes moved = 2 GiB) "
-                       "and dchag_yardstick_read (1 GiB read), best of 5 each"}
+                "how": "dchag_yardstick_mfma (8 wavefronts per compute unit, 32 independent 16x16x32 bf16 MFMAs per "
+                       "round on about normally distributed operands, registers only), dchag_yardstick_copy (1 GiB read + "
+                       "1 GiB written; bytes moved = 2 GiB) and dchag_yardstick_read (1 GiB read), best of 5 each"}
 
     if args.peaks:
         print(json.dumps({"achievable": measure_peaks(), "nominal": PEAK}))

@@ -363,8 +363,8 @@ int dchag_profile_end(dchag_stage_time *records, int cap);
  * Yardsticks for benchmarks (not part of the paper's method): what this GPU reaches on a loop of nothing but bf16
  * MFMAs and on a plain stream copy, so that a kernel's rate can be quoted against the achievable rate as well as
  * against the nominal peak.  Both are asynchronous on `stream`; the caller times them (HIP events).
- *   dchag_yardstick_mfma: every wavefront of 4 x (compute units) workgroups of 256 threads runs `iters` rounds of
- *     eight independent 32x32x16 bf16 MFMAs on registers; *flops (HOST) receives the number of flops launched.
+ *   dchag_yardstick_mfma: every wavefront of 2 x (compute units) workgroups of 256 threads runs `iters` rounds of
+ *     32 independent 16x16x32 bf16 MFMAs on registers; *flops (HOST) receives the number of flops launched.
  *     sink: device scratch of sink_floats >= 1024 x (compute units) floats (one value per thread is written).
  *   dchag_yardstick_copy: dst[0 .. bytes) = src[0 .. bytes) in 16-byte pieces (bytes % 16 == 0): reads `bytes`,
  *     writes `bytes`.

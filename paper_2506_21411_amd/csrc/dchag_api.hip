@@ -999,10 +999,10 @@ int dchag_yardstick_mfma(int iters, float* sink, size_t sink_floats, double* flo
   if (!sink || !flops) return DCHAG_ERR_NULL;
   if (iters < 1) return DCHAG_ERR_SHAPE;
   if (misaligned(sink)) return DCHAG_ERR_ALIGN;
-  const int blocks = 4 * compute_units();                 // 16 wavefronts per compute unit, four per SIMD
-  if (sink_floats < (size_t)blocks * 256) return DCHAG_ERR_WORKSPACE;
+  const int blocks = 2 * compute_units();                 // 8 wavefronts per compute unit, two per SIMD
+  if (sink_floats < (size_t)compute_units() * 1024) return DCHAG_ERR_WORKSPACE;
   k_yardstick_mfma<<<dim3(blocks), 256, 0, static_cast<hipStream_t>(stream)>>>(iters, sink);
-  *flops = (double)blocks * 4.0 * (double)iters * 8.0 * 32768.0;
+  *flops = (double)blocks * 4.0 * (double)iters * 32.0 * 16384.0;
   return launch_status();
 }
 

@@ -497,8 +497,8 @@ __global__ __launch_bounds__(256) void k_softmax_alpha(int Cin, int N, int heads
 // The 256 x 256 x 64 core of the large products (k_vagg_mfma, k_product_dl).
 //
 // Instruction: v_mfma_f32_16x16x32.  These kernels run into the card's power limit, so what counts is the work done per joule:
-// a loop of nothing but products on normally distributed operands reaches 1.95 PFLOP/s with 16x16x32 and 1.34 with
-// 32x32x16 (2.45 and 1.67 on constant operands; 256 x 8 wavefronts, a 128 x 64 tile each).
+// a loop of nothing but products on normally distributed operands reaches 1.93 PFLOP/s with 16x16x32 and 1.35 with
+// 32x32x16 (2.45 and 1.65 on constant operands; 256 x 8 wavefronts, a 128 x 64 tile each).
 //
 // Eight wavefronts (2 x 4).  A stage of the ring holds one slice of 64 contraction elements as four slots of 16 KiB (128
 // rows x 128 bytes, swizzled): A0, A1 (tile rows 0..127, 128..255) and B0, B1; two stages.  Wavefront (wm, wn) owns rows
@@ -679,9 +679,9 @@ __device__ __forceinline__ void core_prologue(CoreFrags& f, const unsigned char*
 // The kernel is persistent: workgroup L takes items L/8, L/8 + slots, ... of its XCD's contiguous
 // range, and the ring keeps prefetching across chunk and item boundaries.
 // Requires D % 256 == 0, dh = D / heads a multiple of 32, and 256 % dh == 0 or dh % 256 == 0.
-// Bound by the card's power limit: at 512 channels, D 1024, B 4, N 256 the matrix units are busy 64 % of the cycles at
-// 1.95 GHz (a library product of the same operands' size: 87 % at 1.57 GHz, 8 % more work a second), 835 us against 865 with
-// 32x32x16 instructions and whole stages (68 % at 1.79 GHz).
+// Held down by the card's power limit where the chip is full: at 512 channels, D 1024, B 4, N 256 790 us with the matrix units busy 73 % of the
+// cycles at 1.88 GHz (a library product of as many flops: 674 us, 88 % at 1.76 GHz; 32x32x16 instructions and whole stages before:
+// 865 us, 68 % at 1.79 GHz).  Its loads alone take 519 us, its products and LDS reads without loads 683.
 // WIDE: 64-bit addresses for the softmax weights, whose eight channels of a chunk lie heads Np floats apart (host: vagg_wide).  It spills a
 // register, which the narrow one does not: level of 4 x 1000 channels, 300 patches, D 256 451 us instead of 441.
 // Dynamic LDS: ring (128 KiB) + 3 alpha tiles of 8 * NHS * 32 floats, used round-robin by chunk.
