@@ -18,8 +18,8 @@ HIPCC_FLAGS = [
 
 
 def build(verbose: bool = True, out: str = LIB, defines=()) -> str:
-    """Compiles the library to `out` (default: the in-tree libdchag.so); `defines` are extra -D macros (the timing
-    probes of the GEMM core, which must never be built into the in-tree library)."""
+    """Compiles the library to `out` (default: the in-tree libdchag.so); `defines` are extra -D macros, for builds
+    that must never become the in-tree library."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if defines and os.path.abspath(out) == os.path.abspath(LIB):
         raise ValueError("a build with extra defines needs its own --out file")
@@ -39,7 +39,7 @@ if __name__ == "__main__":
     import argparse
     ap = argparse.ArgumentParser()
     ap.add_argument("--out", default=LIB)
-    ap.add_argument("--define", action="append", default=[], help="extra macro, e.g. DCHAG_RING_PROBE=1 (needs --out)")
+    ap.add_argument("--define", action="append", default=[], help="extra macro, NAME=VALUE (needs --out)")
     a = ap.parse_args()
     build(out=a.out, defines=a.define)
     sys.exit(0)

@@ -304,7 +304,9 @@ int launch_gemm_mfma_form(const GemmDesc& d, const bf16* A, const bf16* Bm, cons
   return launch_status();
 }
 
-// bf16 results in whole 16-byte pieces, 32-bit offsets inside a tile, 16-byte aligned operands: the ring.
+// bf16 results in whole 16-byte pieces, 32-bit offsets inside a tile, 16-byte aligned operands: the ring.  What it leaves to k_gemm_mfma of
+// bf16 results are products of one head at a time whose columns are no multiple of 8 (o_a = Wv_a u_a of heads of 4 or 12 columns: neither
+// operand transposed) and rows of 8 million elements; the debugging switches take every form there.
 inline bool gemm_ring_ok(const GemmDesc& d, const bf16* A, const bf16* Bm, const bf16* bias) {
   const bool at = d.A.s1 != 1, bt = d.Bm.s0 != 1;
   const long reach = (1L << 30) / 128;
@@ -352,7 +354,9 @@ int launch_gemm_bf16(const GemmDesc& d0, const bf16* A, const bf16* Bm, const bf
             mult8(d.C.s0) && !(reinterpret_cast<uintptr_t>(C) & 15) && !dbg(SW_GEMM_SCALAR_STORES);
   if (d.N <= 64) return launch_gemm_mfma_tile<128, 64, 4, 1, TC>(d, A, Bm, bias, C, rowsum, st);
   if (d.M <= 64) return launch_gemm_mfma_tile<64, 128, 1, 4, TC>(d, A, Bm, bias, C, rowsum, st);
-  // a product of few 128 x 128 tiles (the one-group top level) takes 64 x 64 tiles: four times the blocks
+  // a product whose 128 x 128 tiles keep at most half of the compute units busy (the one-group top level) takes 64 x 64 tiles: four
+  // times the blocks.  At exactly half (128 tiles of 16 slices, D 1024) the level calls take 95.5 us so and 98.9 with the large tiles, of 32 slices
+  // (D 2048) 158 and 165, of 8 (D 512) 66.5 and 68.1.
   const long batch = (long)(d.reduce_b ? 1 : d.nb) * d.nk * d.na;
   if ((long)((d.N + 127) / 128) * ((d.M + 127) / 128) * batch * 2 <= compute_units())
     return launch_gemm_mfma_tile<64, 64, 2, 2, TC>(d, A, Bm, bias, C, rowsum, st);

@@ -909,7 +909,8 @@ namespace dchag {
 // four wavefronts (WM x WN), operands staged through XOR-swizzled LDS rows of 64 contraction elements.
 // Same contract as k_gemm_generic (GemmDesc), restricted to:
 //   no ragged K, every operand has one unit stride, 16-byte aligned rows (so K % 8 == 0 where an operand's unit stride
-//   is the contraction index).  k_gemm_ring takes what has whole 16-byte pieces throughout; here are the fp32 results and the rest.
+//   is the contraction index).  k_gemm_ring takes what has whole 16-byte pieces throughout; here are the fp32 results and, of the bf16
+//   ones, heads whose columns are no multiple of 8.
 //   A last slice of fewer than 64 steps is filled up with zeros: the contraction over 135
 //   patches of a 384-wide model (a weight gradient, 8 groups) takes 8 us here against 75 us on the fp32-FMA kernel that
 //   used to take every K that is no multiple of 64.  Only EXTRA instances carry that code and the row addend (with both in

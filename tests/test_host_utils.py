@@ -130,4 +130,4 @@ def test_stage_model_of_a_training_step_without_first_level_tokens():
 def test_probe_builds_need_their_own_output_file():
     from paper_2506_21411_amd.build import LIB, build
     with pytest.raises(ValueError):
-        build(verbose=False, out=LIB, defines=["DCHAG_RING_PROBE=1"])
+        build(verbose=False, out=LIB, defines=["SOME_MACRO=1"])
