@@ -146,11 +146,11 @@ int compute_units();
 // baseline, the top of a hierarchy) still fills the chip: 1, 2, 4 or 8, at most what leaves two items per compute unit and the chunks of
 // the smallest group, and of those the count that takes least by the model below, in us.  A workgroup's items all have the same
 // share of their groups' chunks (their distance in the launch's order is a multiple of the count), so the longest share times the
-// rounds of items is what the launch waits for; 18 us is a chunk's time at D 1024 on a chip that it does not fill, and a split costs the partial
-// sums' way through memory and a launch that adds them up.  Level calls, us, whole / in 2 / 4 / 8: 256 items of 4 chunks, D 1024 158 / 164 / 169;
-// 80 of 16, D 1024 433 / 288 / 299 / 263; 192 of 5, D 2048 290 / 344 / 352; 160 of 16, D 2048 812 / 888 / 741; 16 of 8, D 256
-// 101 / 80 / 69 / 65.  Over 61 levels of D 256 to 4096 and 1 to 16 chunks the model's count takes 0.4 % more than the best of the four (the worst
-// 13 %, where two items per compute unit bar it); as many as that bound allows, 2.6 % (24 %).
+// rounds of items is what the launch waits for; 16 us is a chunk's time at D 1024 on a chip that it does not fill, and a split costs the partial
+// sums' way through memory and a launch that adds them up.  Level calls, us, whole / in 2 / 4 / 8: 256 items of 4 chunks, D 1024 154 / 160 /
+// 164; 80 of 16, D 1024 402 / 275 / 287 / 255; 192 of 5, D 2048 281 / 326 / 336; 160 of 16, D 2048 797 / 851 / 722; 16 of 8, D 256
+// 95 / 78 / 68 / 64.  Over 61 levels of D 256 to 4096 and 1 to 16 chunks the model's count takes 0.3 % more than the best of the four (the worst
+// 12 %, where two items per compute unit bar it); as many as that bound allows, 2.5 % (20 %).
 // before: the workspace's bytes ahead of the partial sums; eight items a group where that is more than two per compute unit (65 to 96 items) are taken
 // only while the level still fits the static scratch (dchag_aggregate_level_static).
 // DCHAG_VAGG_SPLIT overrides (still clamped).
@@ -171,7 +171,7 @@ int vagg_splits(int B, int Cin, int N, int D, int g, size_t before) {
   for (int t = 1; t <= S; t *= 2) {
     if (t == 8 && items * t > 2L * compute_units() && before + align_up(t * part) > DCHAG_STATIC_SCRATCH_BYTES) break;
     const long per = (items * t + kXcds - 1) / kXcds, slots = std::min<long>(per, compute_units() / kXcds), rounds = (per + slots - 1) / slots;
-    const double us = rounds * ((nch + t - 1) / t * 18. * D / 1024 + 0.5) + (t > 1 ? 1.5 + 0.01 * items * t : 0);
+    const double us = rounds * ((nch + t - 1) / t * 16. * D / 1024 + 0.5) + (t > 1 ? 1.5 + 0.01 * items * t : 0);
     if (t == 1 || us < least) {
       best = t;
       least = us;

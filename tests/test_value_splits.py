@@ -18,13 +18,14 @@ def splits(monkeypatch, B, C, N, D, heads, g):
 
 
 @pytest.mark.parametrize("shape,count", [
-    ((4, 64, 256, 1024, 16, 32), 1),      # 256 items of 4 chunks: 158 / 164 / 169
-    ((2, 96, 200, 1024, 16, 24), 1),      # 224 of 3: 119 / 145
-    ((3, 80, 128, 2048, 16, 40), 1),      # 192 of 5 (two would take three chunks, and six in all): 290 / 344 / 352
-    ((1, 256, 300, 1024, 16, 128), 8),    # 80 of 16: 433 / 288 / 299 / 263
-    ((1, 256, 300, 2048, 16, 128), 4),    # 160 of 16: 812 / 888 / 741
-    ((2, 64, 256, 256, 8, 64), 8),        # 16 of 8, the shortest chunks: 101 / 80 / 69 / 65
-    ((1, 512, 256, 256, 8, 64), 4),       # 64 of 8: 112 / 92 / 84 / 87
+    ((4, 64, 256, 1024, 16, 32), 1),      # 256 items of 4 chunks: 154 / 160 / 164
+    ((2, 96, 200, 1024, 16, 24), 1),      # 224 of 3: 115 / 137
+    ((3, 80, 128, 2048, 16, 40), 1),      # 192 of 5 (two would take three chunks, and six in all): 281 / 326 / 336
+    ((1, 256, 300, 1024, 16, 128), 8),    # 80 of 16: 402 / 275 / 287 / 255
+    ((1, 256, 300, 2048, 16, 128), 4),    # 160 of 16: 797 / 851 / 722
+    ((2, 64, 256, 256, 8, 64), 8),        # 16 of 8, the shortest chunks: 95 / 78 / 68 / 64
+    ((1, 512, 256, 256, 8, 64), 4),       # 64 of 8: 106 / 91 / 83 / 86
+    ((1, 256, 256, 256, 8, 16), 1),       # 128 of 2: 42.4 / 43.6
     ((1, 9, 32, 256, 8, 9), 2),           # fewer chunks than counts
 ])
 def test_count_by_measured_cost(shape, count, monkeypatch):
