@@ -1422,7 +1422,7 @@ int raise_pair_lds(K kern) { return ensure_dynamic_lds(reinterpret_cast<const vo
 
 // 8 x 8 patches whose count is whole slices (an even number of them a batch element, at least four), 32-bit offsets inside a group's
 // images, and tiles of either product for half of the compute units.  512 bands, 4 x 256 patches, D 1024, k_linear_outer, k_linear_dx and the
-// copies they read / these: 252 / 188 us; with fewer tiles (256 x 256 here, 128 x 256 there) half the chip would stand idle.
+// copies they read / these: 252 / 176 us; with fewer tiles (256 x 256 here, 128 x 256 there) half the chip would stand idle.
 inline bool linear_products_ok(int B, int G, int N, int g, int H, int W, int D) {
   const long tiles = (long)((g + 3) / 4) * G;
   return N % 128 == 0 && N >= 256 && W >= 16 && (long)g * H * W < (1L << 30) && (long)N * (W / 8) < (1L << 31) &&

@@ -911,8 +911,8 @@ __global__ __launch_bounds__(256) void k_vagg_merge(long quads, int S, int G, in
 //   kProductImage    image[b][c][pixel kk of patch n] = sum_d A[c][d][kk] B[b,k,n][d]        pixel gradients of a linear first level
 //   kProductOuter    P[c, kk][d] = sum_{b,n} u[b,c,n,kk] B[b,k,n][d], u: the 8 x 8 patches of the image A, which leaves as the linear
 //                    first level's gradients (see k_linear_outer)
-// us, 512 bands, 4 x 256 patches, D 1024, 128 x 256 tiles of pair_loop before: Outer 129 and 37 for the copies it read / 125 (70 without
-// its epilogue, which moves 200 MB), Image 88 / 63.
+// us, 512 bands, 4 x 256 patches, D 1024, 128 x 256 tiles of pair_loop before: Outer 129 and 37 for the copies it read / 116 (of it
+// about 55 for its epilogue, which moves 200 MB), Image 88 / 60.
 // The last two have tile rows (member, pixel), a member to a wavefront and slot, and multiply in plain order: a lane holds one column
 // and four adjacent pixels a block.  Outer reads its patches straight from the image, 16 bytes a lane (the eight pixel rows of two
 // members are the 16 chunks of a slot's row).
@@ -921,9 +921,9 @@ __global__ __launch_bounds__(256) void k_vagg_merge(long quads, int S, int G, in
 // contraction index is its row index is read by the transposing LDS reads (ColOperand): no transposed copy, no 2-byte reads.
 // Bound by the card's power limit where there are many tiles (the clock falls to 1.7 to 1.9 GHz) and by the last round of tiles.
 // One workgroup a tile, 2-byte stores and 32x32x16 instructions before, this after: 640 tiles of 16 slices (10 groups x 4096
-// rows, D 1024) 117 -> 95 us, 256 tiles 46 -> 38, 1008 tiles of 32 slices (63 x 512 rows, D 2048) 294 -> 255; against the general
-// 128 x 128 product kernel: Back 640 tiles 142 -> 90, 256 tiles 62 -> 36; Weights 160 tiles of 64 slices 214 -> 108, 256 of
-// 16 slices 70 -> 40.  Fold, eight 2-byte LDS reads a fragment before: 512 channels, D 1024 81 -> 65, 1000 channels, D 2048 550 -> 446.
+// rows, D 1024) 117 -> 91 us, 256 tiles 46 -> 37, 1008 tiles of 32 slices (63 x 512 rows, D 2048) 294 -> 236; against the general
+// 128 x 128 product kernel: Back 640 tiles 142 -> 86, 256 tiles 62 -> 34; Weights 160 tiles of 64 slices 214 -> 103, 256 of
+// 16 slices 70 -> 38.  Fold, eight 2-byte LDS reads a fragment before: 512 channels, D 1024 81 -> 61, 1000 channels, D 2048 550 -> 413.
 // Dynamic LDS: the ring (128 KiB).
 // ---------------------------------------------------------------------------------------------
 enum ProductKind { kProductLinear, kProductBack, kProductWeights, kProductFold, kProductImage, kProductOuter };

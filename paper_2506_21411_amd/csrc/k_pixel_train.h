@@ -1135,7 +1135,7 @@ __global__ __launch_bounds__(512) void k_pixel_dwv(PixelDims d, TileWork tw, int
 
 // ---------------------------------------------------------------------------------------
 // Reverse step of a LINEAR first level from the pixels (formulas at k_linear_first_grads), both products on pair_loop: 4 x 4 patches, and
-// the counts that linear_products_ok refuses (where it accepts, k_product_dl's Outer and Image take 188 us of the 252 below).
+// the counts that linear_products_ok refuses (where it accepts, k_product_dl's Outer and Image take 176 us instead of the 252 below).
 // k_linear_outer: P[(member, pixel)][d] = sum_n u[n] dy[n][d] over all patches (UT, dyT: patch index contiguous), tile rows
 // (member, pixel), columns d; P stays in the accumulators and leaves as dWe = mix P, dmix = sum_pixels We P + (be + ce) S,
 // dtok_bias = mix S, dbias = S and the scaled weights WsT[(member, pixel)][d] = mix We that k_linear_dx contracts dy with.
